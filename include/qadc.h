@@ -318,8 +318,8 @@ enum {
     PQ_OPT_PILOT_BLOCKS = 3,       /* most blocks per query that share that sample: 1..128 (128) */
     PQ_OPT_IVF_THREADS = 4,        /* threads per (query, list) block of the inverted-list scan:
                                       64, 128 or 256 (128) */
-    PQ_OPT_SHARED_PASSES = 5,      /* 1: four queries of a batch share each pass over the codes;
-                                      0: one pass per query (1) */
+    PQ_OPT_SHARED_PASSES = 5,      /* 1: the queries of a batch share passes over the codes (four, or
+                                      32 and more on the matrix cores); 0: one pass per query (1) */
     PQ_OPT_COARSE_FILTER = 6,      /* 1: the coarse search keeps only scores within a sampled bound;
                                       0: it always writes the full score matrix (1) */
     PQ_OPT_IVF_SHARED_LISTS = 7,   /* inverted-list search, 16 x 4-bit codes with 8-bit tables: one pass

@@ -85,6 +85,103 @@ static void plan_groups(DevLayout &L, int gmax) {
     }
 }
 
+// Steps of the batched matrix-core scan: 4-bit fields in pairs, 5-bit fields alone and halves of
+// 6-bit fields, 32 table entries each; a step's two halves (lower and upper 32 lanes) are of one
+// kind.  Any other width: no steps.  (Wider fields would need as many products as table entries;
+// the look-ups of the other scan kernels are cheaper there.)
+static void plan_mx(DevLayout &L) {
+    L.mx_steps = 0;
+    const bool nib = L.kind == SCAN_NIB8 || L.kind == SCAN_NIB16;
+    if (!nib && L.kind != SCAN_C5 && L.kind != SCAN_W64 && L.kind != SCAN_W128) return;
+    auto clear = [&]() {
+        for (int s = 0; s < MX_MAX_STEPS; ++s) {
+            L.mx_type[s] = MX_NIBBLES;
+            for (int h = 0; h < 2; ++h) L.mx_off[s][h] = L.mx_off2[s][h] = 0, L.mx_seg[2 * s + h][0] = L.mx_seg[2 * s + h][1] = -1;
+        }
+    };
+    clear();
+    if (nib) {  // half h has the h-th half of the code, step s its byte s
+        const int S = L.m / 4;
+        for (int s = 0; s < S; ++s)
+            for (int h = 0; h < 2; ++h) {
+                const int j = 2 * (h * S + s);
+                L.mx_seg[2 * s + h][0] = L.toff[j];
+                L.mx_seg[2 * s + h][1] = L.toff[j + 1];
+            }
+        L.mx_steps = S;
+        return;
+    }
+    const int words = L.kind == SCAN_W128 ? 2 : 1;
+    for (int j = 0; j < L.m; ++j)
+        if (L.nbits[j] < 4 || L.nbits[j] > 6) return;
+    // One step after another, 6-bit fields before 5-bit ones before nibbles, at least `least` steps
+    // per word (what a layout does not need stays empty: nibble steps of zeros).
+    int per_word = 0, cnt[2][3];
+    auto fill = [&](int least) {
+        clear();
+        per_word = least;
+        for (int pass = 0; pass < 2; ++pass)  // first the number of steps, then the steps
+            for (int w = 0; w < words; ++w) {
+                int s = 0;
+                for (int type = MX_SIX; type >= MX_NIBBLES; --type) {
+                    int h = 0, pending = -1;
+                    const int s0 = s;
+                    auto item = [&](int a, int b) {  // one half-step: sub-quantizer a (and b)
+                        const int at = w * per_word + s;
+                        if (pass == 1 && at < MX_MAX_STEPS) {
+                            L.mx_type[at] = type;
+                            L.mx_off[at][h] = L.bitoff[a] - 64 * w;
+                            L.mx_off2[at][h] = b >= 0 ? L.bitoff[b] - 64 * w : 0;
+                            const int t0 = L.toff[a] + (type == MX_SIX ? 32 * h : 0);
+                            L.mx_seg[2 * at + h][0] = t0;
+                            L.mx_seg[2 * at + h][1] = type != MX_NIBBLES ? t0 + 16 : (b >= 0 ? L.toff[b] : -1);
+                        }
+                        if (++h == 2) h = 0, ++s;
+                    };
+                    for (int j = 0; j < L.m; ++j) {
+                        if (words == 2 && L.bitoff[j] / 64 != w) continue;
+                        if (L.nbits[j] != 4 + type) continue;
+                        if (type == MX_SIX) item(j, -1), item(j, -1);
+                        else if (type == MX_FIVE) item(j, -1);
+                        else if (pending < 0) pending = j;
+                        else item(pending, j), pending = -1;
+                    }
+                    if (pending >= 0) item(pending, -1);
+                    if (h == 1) h = 0, ++s;
+                    cnt[w][type] = s - s0;
+                }
+                if (pass == 0 && s > per_word) per_word = s;
+            }
+    };
+    // The layouts whose steps the kernels know at compile time: {6,5,5,6,5,5,4,4} (40-bit codes),
+    // {6,6,4} x 4 and {6,5,5} x 4 per 64 bits, and any other with as many steps of each kind whose
+    // 6- and 5-bit fields lie as theirs do: within one dword, the first half of a kind's steps in the
+    // lower and the rest in the upper dword (40-bit codes: all in the lower).
+    fill(L.kind == SCAN_C5 ? 5 : 8);
+    L.mx_pat = 100 * cnt[0][MX_SIX] + 10 * cnt[0][MX_FIVE] + cnt[0][MX_NIBBLES];
+    bool known = L.kind == SCAN_C5 ? L.mx_pat == 221 : (L.mx_pat == 801 || L.mx_pat == 440);
+    for (int w = 0; w < words; ++w) {
+        known = known && 100 * cnt[w][MX_SIX] + 10 * cnt[w][MX_FIVE] + cnt[w][MX_NIBBLES] == L.mx_pat;
+        for (int s = 0, k = 0; known && s < per_word; ++s) {
+            const int at = w * per_word + s, type = L.mx_type[at];
+            if (type == MX_NIBBLES) break;
+            if (s > 0 && L.mx_type[at - 1] != type) k = 0;
+            const int upper = L.kind != SCAN_C5 && 2 * k >= cnt[w][type] ? 1 : 0;
+            ++k;
+            for (int h = 0; h < 2; ++h)
+                known = known && L.mx_seg[2 * at + h][0] >= 0 && L.mx_off[at][h] / 32 == upper &&
+                        (L.mx_off[at][h] + 3 + type) / 32 == upper;
+        }
+    }
+    if (!known) {
+        L.mx_pat = 0;
+        if (L.kind != SCAN_C5) fill(10);
+    }
+    // step counts the kernels exist for
+    if (per_word > (L.kind == SCAN_C5 ? 6 : 10)) return;
+    L.mx_steps = per_word * words;
+}
+
 extern "C" int pq_index_create(pq_index_t **out, int d, int m, const int32_t *nbits,
                                const int32_t *dsub, const float *codebooks, int acc_bits) {
     if (!out || !nbits || !dsub || !codebooks) {
@@ -167,6 +264,8 @@ extern "C" int pq_index_create(pq_index_t **out, int d, int m, const int32_t *nb
             same = same && L.goff[g + L.ng / 2] == L.goff[g] + 64 && L.gw[g + L.ng / 2] == L.gw[g];
         if (same) L.kind = SCAN_W128;
     }
+
+    plan_mx(L);
 
     pq_index *idx = new pq_index;
     idx->h = L;

@@ -6,6 +6,10 @@
 #include "qadc.h"
 #include "qadc_bench.h"
 
+#define MX_MAX_STEPS 20
+// what a half-step of the batched scan holds: two 4-bit fields; one 5-bit field; half of a 6-bit field
+enum { MX_NIBBLES = 0, MX_FIVE = 1, MX_SIX = 2 };
+
 // Layout of a product quantizer as the kernels see it.  A copy lives in device
 // memory; kernels read it through uniform (scalar) loads.
 //
@@ -35,6 +39,14 @@ struct DevLayout {
     int32_t gfirst[PQ_MAX_M];  // first sub-quantizer of group g
     int32_t gcount[PQ_MAX_M];  // sub-quantizers in group g
     int32_t gbase[PQ_MAX_M];   // first group-table entry of group g
+    // The batched scan on the matrix cores (scan_mx.hip): 64 table entries per product step, 32 per
+    // half of the wave.  mx_steps == 0: the layout has fields of other than 4, 5 or 6 bits.
+    int32_t mx_steps;
+    int32_t mx_pat;                    // 100 n6 + 10 n5 + n4 steps of each kind where the kernels know them, else 0
+    int32_t mx_type[MX_MAX_STEPS];     // MX_* below
+    int32_t mx_off[MX_MAX_STEPS][2];   // first bit of the half's field (within its 64-bit word of the code)
+    int32_t mx_off2[MX_MAX_STEPS][2];  // ... of its second nibble
+    int32_t mx_seg[2 * MX_MAX_STEPS][2];  // half 2 s + h: table entries of its values 0..15 and 16..31; -1 = none
 };
 
 // Scan specialisations by code shape:
@@ -95,6 +107,22 @@ int qadc_pilot_blocks_max(int nq);
 size_t qadc_pilot_scratch_bytes(int nq);
 PilotPlan qadc_pilot_plan(int nq, int64_t n, int t_eff, int R, bool have_scratch, bool cheap_lookups);
 
+// The batched scan on the matrix cores (scan_mx.hip), if the call takes it.
+struct MxPlan {
+    bool use;
+    int groups, ncol;   // blocks of 32 * ncol queries
+    int gpc, nb;        // groups of 64 nb codes, gpc per chunk and lane half; a chunk = gpc * nb * 128 codes
+    int nchunks, nmin;  // whole chunks, and group minima per query
+    size_t btab_off, min_off;  // operand tables and group minima within a query's part of the workspace
+};
+MxPlan qadc_mx_plan(const pq_index *idx, int nq, int64_t n, int R, const ScanPlan &sp);
+// scan and selection; the queries' group and operand tables are in the workspace already
+int qadc_scan_mx(const pq_index *idx, const pq_qparams_t *qparams, int nq, const uint8_t *codes, int64_t n, int R,
+                 int32_t *out_ids, uint16_t *out_keys, float *out_dist, char *ws, const ScanPlan &sp, const MxPlan &p,
+                 hipStream_t s);
+
+// btab_rel: if not 0, the operand tables of the batched matrix-core scan are written btab_rel bytes
+// behind the group tables, and no pilot is counted (that scan needs no bound).
 // gtab_out: if non-null, query q's group tables are also written to gtab_out + q*gtab_stride bytes.
 // hdr_out: if non-null, the scan header at hdr_out + q*gtab_stride is cleared (an empty candidate list).
 // scratch: null, or qadc_pilot_scratch_bytes(nq) bytes (256-byte aligned, any contents) that let
@@ -102,7 +130,7 @@ PilotPlan qadc_pilot_plan(int nq, int64_t n, int t_eff, int R, bool have_scratch
 int qadc_quantize_launch(const pq_index *idx, const float *queries, const float *tables_in,
                          float *tables_out, int nq, const uint8_t *codes, int64_t n, int t, int R,
                          void *qtables, pq_qparams_t *qparams, char *gtab_out, size_t gtab_stride,
-                         char *hdr_out, char *scratch, PilotPlan *plan_used, hipStream_t s);
+                         size_t btab_rel, char *hdr_out, char *scratch, PilotPlan *plan_used, hipStream_t s);
 
 
 #define QADC_HIP_TRY(expr)                                                        \

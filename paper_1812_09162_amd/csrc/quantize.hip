@@ -43,7 +43,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
            const float *__restrict__ queries, const float *__restrict__ tables_in,
            float *__restrict__ tables_out, const uint8_t *__restrict__ codes, int t_eff, int k,
            int pilot, int slice, int P, void *__restrict__ qtables,
-           pq_qparams_t *__restrict__ qparams, char *__restrict__ gtab_out, size_t gtab_stride,
+           pq_qparams_t *__restrict__ qparams, char *__restrict__ gtab_out, size_t gtab_stride, size_t btab_rel,
            char *__restrict__ hdr_out, uint16_t *__restrict__ bound_rec) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int T = shape.T, m = shape.m, cs = shape.cs, qmax = shape.qmax, d = shape.d;
@@ -250,6 +250,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
         if (gtab_out && first) {  // hand the prepared group tables to the scan kernel
             QT *dst = (QT *)(gtab_out + q * gtab_stride);
             for (int e = threadIdx.x; e < L->gtab_len; e += blockDim.x) dst[e] = gtab[e];
+            if (btab_rel) build_btab(L, qt, sizeof(QT) == 1 ? 0 : 8, (uint32_t *)(gtab_out + q * gtab_stride + btab_rel));
         }
     }
     if (hdr_out && first) scan_hdr_clear((ScanHdr *)(hdr_out + q * gtab_stride));  // empty candidate lists
@@ -431,7 +432,7 @@ template <int KIND, typename QT>
 static int launch_quantize(const pq_index *idx, const float *queries, const float *tables_in,
                            float *tables_out, int nq, const uint8_t *codes, int t_eff, int k,
                            const PilotPlan &pp, void *qtables, pq_qparams_t *qparams, char *gtab_out,
-                           size_t gtab_stride, char *hdr_out, uint16_t *bound_rec, hipStream_t s) {
+                           size_t gtab_stride, size_t btab_rel, char *hdr_out, uint16_t *bound_rec, hipStream_t s) {
     const size_t lds = quantize_lds(idx->h, t_eff, sizeof(QT));
     if (lds > 48 * 1024)
         QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_quantize<KIND, QT>,
@@ -444,7 +445,7 @@ static int launch_quantize(const pq_index *idx, const float *queries, const floa
     hipLaunchKernelGGL((k_quantize<KIND, QT>), dim3((unsigned)nq * (unsigned)pp.P), dim3(QUANT_THREADS), lds, s,
                        idx->dev, QuantShape{idx->h.T, idx->h.m, idx->h.cs, idx->h.qmax, idx->h.d, ubits, uds}, idx->edesc,
                        idx->codebooks, queries, tables_in, tables_out, codes, t_eff, k,
-                       pp.pilot, pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, hdr_out, bound_rec);
+                       pp.pilot, pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, btab_rel, hdr_out, bound_rec);
     QADC_LAUNCH_CHECK("k_quantize");
     return PQ_OK;
 }
@@ -455,18 +456,22 @@ static int launch_quantize(const pq_index *idx, const float *queries, const floa
 int qadc_quantize_launch(const pq_index *idx, const float *queries, const float *tables_in,
                          float *tables_out, int nq, const uint8_t *codes, int64_t n, int t, int R,
                          void *qtables, pq_qparams_t *qparams, char *gtab_out, size_t gtab_stride,
-                         char *hdr_out, char *scratch, PilotPlan *plan_used, hipStream_t s) {
+                         size_t btab_rel, char *hdr_out, char *scratch, PilotPlan *plan_used, hipStream_t s) {
     const int64_t want = t > 4 * (int64_t)R ? t : 4 * (int64_t)R;
     const int t_eff = (int)(n < want ? n : want);
     const int k = R < t_eff ? R : t_eff;
-    const PilotPlan pp = qadc_pilot_plan(nq, n, t_eff, R, scratch != nullptr,
-                                         idx->h.kind == SCAN_NIB8 || idx->h.kind == SCAN_NIB16);
+    PilotPlan pp = qadc_pilot_plan(nq, n, t_eff, R, scratch != nullptr,
+                                   idx->h.kind == SCAN_NIB8 || idx->h.kind == SCAN_NIB16);
+    if (btab_rel) {
+        pp.pilot = 0;
+        pp.P = 1;
+    }
     if (plan_used) *plan_used = pp;
     uint16_t *bound_rec = (uint16_t *)scratch;
     const bool u8 = idx->h.acc_bits == 8;
 #define QADC_GO(KIND, QT)                                                                       \
     return launch_quantize<KIND, QT>(idx, queries, tables_in, tables_out, nq, codes, t_eff, k, \
-                                     pp, qtables, qparams, gtab_out, gtab_stride, hdr_out, bound_rec, s)
+                                     pp, qtables, qparams, gtab_out, gtab_stride, btab_rel, hdr_out, bound_rec, s)
     switch (idx->h.kind) {
         case SCAN_NIB8:
             if (u8) QADC_GO(SCAN_NIB8, uint8_t); else QADC_GO(SCAN_NIB8, uint16_t);
@@ -510,5 +515,5 @@ extern "C" int pq_quantize_tables(const pq_index_t *idx, const float *tables, in
         return PQ_EINVAL;
     }
     return qadc_quantize_launch(idx, nullptr, tables, nullptr, nq, codes, n, t, R, qtables, qparams,
-                                nullptr, 0, nullptr, nullptr, nullptr, (hipStream_t)stream);
+                                nullptr, 0, 0, nullptr, nullptr, nullptr, (hipStream_t)stream);
 }

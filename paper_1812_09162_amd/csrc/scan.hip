@@ -36,7 +36,7 @@ constexpr int U5 = QADC_U5;  // 20-byte chunks per thread and tile, 5-byte codes
 template <int KIND, typename QT>
 __global__ void __launch_bounds__(256)
 k_prepare(const DevLayout *__restrict__ L, const void *__restrict__ qtables, char *__restrict__ ws,
-          size_t per_query, size_t gtab_off) {
+          size_t per_query, size_t gtab_off, size_t btab_rel) {
     extern __shared__ __align__(16) unsigned char smem[];
     QT *gtab = (QT *)smem;
     uint16_t *qs = (uint16_t *)(smem + (((size_t)L->gtab_len * sizeof(QT) + 15) & ~(size_t)15));
@@ -45,156 +45,8 @@ k_prepare(const DevLayout *__restrict__ L, const void *__restrict__ qtables, cha
     build_gtab<KIND, QT>(L, qs, gtab);
     QT *dst = (QT *)(ws + q * per_query + gtab_off);
     for (int e = threadIdx.x; e < L->gtab_len; e += blockDim.x) dst[e] = gtab[e];
+    if (btab_rel) build_btab(L, qs, sizeof(QT) == 1 ? 0 : 8, (uint32_t *)((char *)dst + btab_rel));
     scan_hdr_clear((ScanHdr *)(ws + q * per_query));  // empty candidate lists for the scan that follows
-}
-
-// Copy prepared group tables (a multiple of 16 bytes is allocated for them) into LDS.
-template <typename QT>
-__device__ __forceinline__ void load_gtab(const char *__restrict__ src, int gtab_len, QT *gtab) {
-    const int n16 = (gtab_len * (int)sizeof(QT) + 15) >> 4;
-    for (int i = threadIdx.x; i < n16; i += blockDim.x) ((uint4 *)gtab)[i] = ((const uint4 *)src)[i];
-    __syncthreads();
-}
-
-// -------------------------------------------------------------- selection ---
-struct FinalOut {
-    int32_t *ids;
-    uint16_t *keys;
-    float *dist;
-};
-
-// Rank the na candidates of S.A by (key, id) and write the first R, padding the rest.  The
-// candidates are first grouped by key bin (key >> shift, at most 256 bins) with a counting
-// sort of their indices; a candidate's rank is the number of candidates in lower bins plus
-// the number of smaller ones within its bin.  Block of NT threads.
-template <int NT, int ACAP>
-__device__ inline void rank_and_write(SelectLds<NT, ACAP> &S, int na, int R, const pq_qparams_t &prm,
-                                      uint32_t qmax, const FinalOut &o, int shift) {
-    const float fdelta = (float)prm.delta, fdmin = (float)prm.d_min;
-    const uint64_t *A = S.A;
-    if (na <= 2 * NT) {
-        // few candidates (the usual case): every candidate counts the smaller ones; all lanes
-        // read the same entry at a time
-        for (int i = threadIdx.x; i < na; i += NT) {
-            const uint64_t mine = A[i];
-            int r = 0;
-            for (int j = 0; j < na; ++j) r += (A[j] < mine) ? 1 : 0;
-            if (r < R) {
-                const uint32_t key = (uint32_t)(mine >> 32);
-                o.ids[r] = (int32_t)(uint32_t)mine;
-                o.keys[r] = (uint16_t)key;
-                o.dist[r] = fmaf((float)key, fdelta, fdmin);
-            }
-        }
-    } else {
-        uint32_t *cnt = &S.whist[0][0], *start = cnt + 256, *fill = cnt + 512;  // (NT >= 256: 1024 words there)
-        for (int i = threadIdx.x; i < 768; i += NT) cnt[i] = 0;
-        __syncthreads();
-        for (int i = threadIdx.x; i < na; i += NT) atomicAdd(&cnt[((uint32_t)(A[i] >> 32) >> shift) & 255u], 1u);
-        __syncthreads();
-        if (threadIdx.x < QADC_WAVE) {  // exclusive prefix of the 256 counts, four bins per lane
-            const int lane = threadIdx.x;
-            uint32_t c[4], sum = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                c[k] = cnt[4 * lane + k];
-                sum += c[k];
-            }
-            uint32_t run = qadc_wave_incl_scan(sum) - sum;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                start[4 * lane + k] = run;
-                run += c[k];
-            }
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < na; i += NT) {
-            const uint32_t b = ((uint32_t)(A[i] >> 32) >> shift) & 255u;
-            S.order[start[b] + atomicAdd(&fill[b], 1u)] = (uint16_t)i;
-        }
-        __syncthreads();
-        for (int p = threadIdx.x; p < na; p += NT) {
-            const uint64_t mine = A[S.order[p]];
-            const uint32_t b = ((uint32_t)(mine >> 32) >> shift) & 255u;
-            const int gs = (int)start[b], ge = gs + (int)cnt[b];
-            int r = gs;
-            if (gs < R) {  // (a whole bin at or beyond rank R cannot hold a result)
-                for (int j = gs; j < ge; ++j) r += (A[S.order[j]] < mine) ? 1 : 0;
-                if (r < R) {
-                    const uint32_t key = (uint32_t)(mine >> 32);
-                    o.ids[r] = (int32_t)(uint32_t)mine;
-                    o.keys[r] = (uint16_t)key;
-                    o.dist[r] = fmaf((float)key, fdelta, fdmin);
-                }
-            }
-        }
-    }
-    for (int r = (na < R ? na : R) + threadIdx.x; r < R; r += NT) {
-        o.ids[r] = -1;
-        o.keys[r] = (uint16_t)qmax;
-        o.dist[r] = INFINITY;
-    }
-}
-
-// Exact selection over all n codes by one block: histogram of key bins (two
-// levels for 16-bit keys) gives the R-th key k*; a second pass in id order keeps
-// every code below k* and the first (R - count_below) codes equal to k*.  A receives
-// min(R, n) entries; their number is left in sh[2].
-template <int KIND, typename QT>
-__device__ inline void exact_select(const DevLayout *L, const QT *gtab,
-                                    const uint8_t *__restrict__ codes, int64_t n, int R,
-                                    uint64_t *A, uint32_t *hist, uint32_t *sh) {
-    const int Rn = (int64_t)R < n ? R : (int)n;
-    const bool wide = L->acc_bits != 8;
-    uint32_t kstar = 0, below = 0;
-    for (int level = 0; level < (wide ? 2 : 1); ++level) {
-        for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
-        __syncthreads();
-        for (int64_t id = threadIdx.x; id < n; id += blockDim.x) {
-            uint32_t key = key_at<KIND, QT>(L, gtab, codes, id);
-            if (!wide)
-                atomicAdd(&hist[key], 1u);
-            else if (level == 0)
-                atomicAdd(&hist[key >> 8], 1u);
-            else if ((key >> 8) == kstar)
-                atomicAdd(&hist[key & 255u], 1u);
-        }
-        __syncthreads();
-        if (threadIdx.x < QADC_WAVE) qadc_wave_select_bin(hist, (uint32_t)Rn, below, sh);
-        __syncthreads();
-        kstar = (level == 0) ? sh[0] : ((kstar << 8) | sh[0]);
-        below = sh[1];
-        __syncthreads();
-    }
-    const uint32_t need = (uint32_t)Rn - below;  // ties to keep, lowest ids first
-    if (threadIdx.x == 0) sh[2] = 0;             // entries written to A
-    uint32_t tie_base = 0;
-    const int wave = threadIdx.x / QADC_WAVE, lane = threadIdx.x % QADC_WAVE;
-    const int nwaves = blockDim.x / QADC_WAVE;
-    uint32_t *wtot = sh + 8;  // nwaves words
-    __syncthreads();
-    for (int64_t base = 0; base < n; base += blockDim.x) {
-        const int64_t id = base + threadIdx.x;
-        const bool valid = id < n;
-        const uint32_t key = valid ? key_at<KIND, QT>(L, gtab, codes, id) : 0xffffffffu;
-        const bool lt = valid && key < kstar, eq = valid && key == kstar;
-        const uint64_t m = __ballot(eq);
-        if (lane == 0) wtot[wave] = (uint32_t)__popcll(m);
-        __syncthreads();
-        uint32_t woff = 0, tot = 0;
-        for (int w = 0; w < nwaves; ++w) {
-            uint32_t c = wtot[w];
-            woff += (w < wave) ? c : 0;
-            tot += c;
-        }
-        const uint32_t tie_rank = tie_base + woff + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-        if (lt || (eq && tie_rank < need)) {
-            uint32_t pos = atomicAdd(&sh[2], 1u);
-            A[pos] = ((uint64_t)key << 32) | (uint64_t)(uint32_t)id;
-        }
-        tie_base += tot;
-        __syncthreads();
-    }
 }
 
 // The selection of one query by a block of NT threads: from the candidate list, or from the
@@ -837,11 +689,16 @@ static int launch_scan(const pq_index *idx, const void *qtables, const pq_qparam
                        const uint16_t *bound_rec, int recP, uint32_t reck) {
     const DevLayout &h = idx->h;
     const size_t gtab_bytes = ((size_t)h.gtab_len * sizeof(QT) + 15) & ~(size_t)15;
+    // scan and selection of a batch asked for together: the matrix-core scan, where it applies
+    MxPlan mp;
+    mp.use = false;
+    if ((what & 3) == 3) mp = qadc_mx_plan(idx, nq, n, R, p);
     if (what & 4) {
         hipLaunchKernelGGL((k_prepare<KIND, QT>), dim3(nq), dim3(256), gtab_bytes + (size_t)h.T * 2, s,
-                           idx->dev, qtables, ws, p.per_query, p.gtab_off);
+                           idx->dev, qtables, ws, p.per_query, p.gtab_off, mp.use ? mp.btab_off - p.gtab_off : (size_t)0);
         QADC_LAUNCH_CHECK("k_prepare");
     }
+    if (mp.use) return qadc_scan_mx(idx, qparams, nq, codes, n, R, out_ids, out_keys, out_dist, ws, p, mp, s);
     const bool no_mq = qadc_option(PQ_OPT_SHARED_PASSES) == 0;
     bool fused = false;  // the scan kernel's last block does the selection
     if ((what & 1) && sizeof(QT) == 1 && nq >= 2 && (KIND == SCAN_NIB8 || KIND == SCAN_NIB16) && !no_mq) {
@@ -869,16 +726,7 @@ static int launch_scan(const pq_index *idx, const void *qtables, const pq_qparam
                                p.cap, (uint32_t)h.qmax, bound_rec, recP, reck);
         QADC_LAUNCH_CHECK("k_scan_mq");
     } else if (what & 1) {
-        GroupDesc gd;
-        memset(&gd, 0, sizeof(gd));
-        gd.ng = h.ng;
-        for (int g = 0; g < QADC_MAXG_FAST && g < h.ng; ++g) {
-            gd.off[g] = h.goff[g];
-            gd.w[g] = h.gw[g];
-            gd.base[g] = h.gbase[g];
-        }
-        if (KIND == SCAN_W128)  // NG = groups per 64-bit half
-            for (int g = 0; g < h.ng / 2; ++g) gd.base2[g] = h.gbase[g + h.ng / 2];
+        GroupDesc gd = group_desc_args(h);  // (W128: NG = groups per 64-bit half)
         constexpr bool desc_kind = KIND == SCAN_W64 || KIND == SCAN_C5 || KIND == SCAN_W128;
         const bool fast = (KIND == SCAN_W64 || KIND == SCAN_C5) && h.g32ok != 0 && h.ng >= 1 &&
                           h.ng <= QADC_MAXG_FAST;
@@ -1165,8 +1013,9 @@ extern "C" int pq_search_topk(const pq_index_t *idx, const float *queries, int n
     const ScanPlan p = qadc_scan_plan(idx, nq, n, R);
     char *scratch = ws + up256(p.total);
     PilotPlan pp;
-    rc = qadc_quantize_launch(idx, queries, nullptr, nullptr, nq, codes, n, t, R, qtables, qparams,
-                              ws + p.gtab_off, p.per_query, ws, scratch, &pp, s);
+    const MxPlan mp = qadc_mx_plan(idx, nq, n, R, p);
+    rc = qadc_quantize_launch(idx, queries, nullptr, nullptr, nq, codes, n, t, R, qtables, qparams, ws + p.gtab_off,
+                              p.per_query, mp.use ? mp.btab_off - p.gtab_off : (size_t)0, ws, scratch, &pp, s);
     if (rc != PQ_OK) return rc;
     // several pilot blocks per query: the scan adds their records up; one: the bound is in qparams
     const uint16_t *rec = pp.P > 1 ? (const uint16_t *)scratch : nullptr;

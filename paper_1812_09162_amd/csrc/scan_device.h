@@ -71,6 +71,29 @@ __device__ inline void build_gtab(const DevLayout *L, const uint16_t *qs, QT *gt
     __syncthreads();
 }
 
+// The nearest value not above x of the 6-bit format e2m3 in units of 1/8: 0..15 exactly, then steps
+// of 2 and of 4 up to 60.
+__device__ __forceinline__ uint32_t mx_floor_code(uint32_t x) {
+    return x < 16u ? x : (x < 32u ? 16u + ((x - 16u) >> 1) : (x < 60u ? 24u + ((x - 32u) >> 2) : 31u));
+}
+// The query's operand of the batched matrix-core scan: half-step i holds 32 codes of 6 bits in six
+// dwords, the quantized entries (qs, shifted right by `shift`) rounded down.  Block-wide, no barrier.
+__device__ inline void build_btab(const DevLayout *L, const uint16_t *qs, int shift, uint32_t *__restrict__ dst) {
+    const int total = L->mx_steps * 12;
+    for (int i = threadIdx.x; i < total; i += blockDim.x) {
+        const int item = i / 6, b0 = 32 * (i - item * 6);
+        const int seg0 = L->mx_seg[item][0], seg1 = L->mx_seg[item][1];
+        uint32_t w = 0;
+        for (int v = b0 / 6; 6 * v < b0 + 32; ++v) {
+            const int seg = v < 16 ? seg0 : seg1;
+            const uint32_t code = seg < 0 ? 0u : mx_floor_code((uint32_t)qs[seg + (v & 15)] >> shift);
+            const int pos = 6 * v - b0;
+            w |= pos >= 0 ? code << pos : code >> -pos;
+        }
+        dst[i] = w;
+    }
+}
+
 // Copy one query's quantized table from global memory into LDS as 16-bit words.
 // Ends with a block barrier.
 template <typename QT>
@@ -155,6 +178,32 @@ __device__ __forceinline__ uint32_t sum_groups_rt(const GroupDesc &d, const QT *
             s += gtab[d.base[g] + __builtin_amdgcn_ubfe(x, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])];
         }
     return s;
+}
+// ... of the upper half of a 128-bit code
+template <typename QT>
+__device__ __forceinline__ uint32_t sum_groups_rt_upper(const GroupDesc &d, const QT *gtab, uint32_t lo,
+                                                        uint32_t hi) {
+    uint32_t s = 0;
+#pragma unroll
+    for (int g = 0; g < QADC_MAXG_FAST; ++g)
+        if (g < d.ng) {
+            const uint32_t x = d.off[g] >= 32 ? hi : lo;
+            s += gtab[d.base2[g] + __builtin_amdgcn_ubfe(x, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])];
+        }
+    return s;
+}
+// the descriptors as a kernel argument (host); 128-bit codes: of the groups of one half
+static inline GroupDesc group_desc_args(const DevLayout &h) {
+    GroupDesc gd = {};
+    gd.ng = h.ng;
+    for (int g = 0; g < QADC_MAXG_FAST && g < h.ng; ++g) {
+        gd.off[g] = h.goff[g];
+        gd.w[g] = h.gw[g];
+        gd.base[g] = h.gbase[g];
+    }
+    if (h.kind == SCAN_W128)
+        for (int g = 0; g < h.ng / 2; ++g) gd.base2[g] = h.gbase[g + h.ng / 2];
+    return gd;
 }
 // code of at most 64 bits as two dwords, no group crossing the dword boundary; NG = number
 // of groups, fixed at compile time so that all lookups of a code are issued together
@@ -774,7 +823,9 @@ __device__ inline bool gather_select(const uint32_t *__restrict__ counts,
         __syncthreads();
     }
     return slow;
-}// Block-wide (1024 threads), for many short slot lists (the exhaustive scan leaves one list
+}
+
+// Block-wide (1024 threads), for many short slot lists (the exhaustive scan leaves one list
 // per scan block, a few entries each): same contract as gather_select.  W = 2^logw adjacent
 // threads (4 <= W <= 32) read the first W entries of a list, each thread serving NU lists
 // per batch, so that all loads of the common case, the list lengths included, are
@@ -891,4 +942,153 @@ __device__ inline bool gather_select_rows(const uint32_t *__restrict__ counts,
     na = slow ? 0 : (int)S.sh[0];
     __syncthreads();
     return slow;
+}
+
+// Copy prepared group tables (a multiple of 16 bytes is allocated for them) into LDS.
+template <typename QT>
+__device__ __forceinline__ void load_gtab(const char *__restrict__ src, int gtab_len, QT *gtab) {
+    const int n16 = (gtab_len * (int)sizeof(QT) + 15) >> 4;
+    for (int i = threadIdx.x; i < n16; i += blockDim.x) ((uint4 *)gtab)[i] = ((const uint4 *)src)[i];
+    __syncthreads();
+}
+
+// -------------------------------------------------------------- selection ---
+struct FinalOut {
+    int32_t *ids;
+    uint16_t *keys;
+    float *dist;
+};
+
+// Rank the na candidates of S.A by (key, id) and write the first R, padding the rest.  The
+// candidates are first grouped by key bin (key >> shift, at most 256 bins) with a counting
+// sort of their indices; a candidate's rank is the number of candidates in lower bins plus
+// the number of smaller ones within its bin.  Block of NT threads.
+template <int NT, int ACAP>
+__device__ inline void rank_and_write(SelectLds<NT, ACAP> &S, int na, int R, const pq_qparams_t &prm,
+                                      uint32_t qmax, const FinalOut &o, int shift) {
+    const float fdelta = (float)prm.delta, fdmin = (float)prm.d_min;
+    const uint64_t *A = S.A;
+    if (na <= 512) {
+        // few candidates (the usual case): every candidate counts the smaller ones; all lanes
+        // read the same entry at a time
+        for (int i = threadIdx.x; i < na; i += NT) {
+            const uint64_t mine = A[i];
+            int r = 0;
+            for (int j = 0; j < na; ++j) r += (A[j] < mine) ? 1 : 0;
+            if (r < R) {
+                const uint32_t key = (uint32_t)(mine >> 32);
+                o.ids[r] = (int32_t)(uint32_t)mine;
+                o.keys[r] = (uint16_t)key;
+                o.dist[r] = fmaf((float)key, fdelta, fdmin);
+            }
+        }
+    } else {
+        uint32_t *cnt = &S.whist[0][0], *start = cnt + 256, *fill = cnt + 512;  // (NT >= 256: 1024 words there)
+        for (int i = threadIdx.x; i < 768; i += NT) cnt[i] = 0;
+        __syncthreads();
+        for (int i = threadIdx.x; i < na; i += NT) atomicAdd(&cnt[((uint32_t)(A[i] >> 32) >> shift) & 255u], 1u);
+        __syncthreads();
+        if (threadIdx.x < QADC_WAVE) {  // exclusive prefix of the 256 counts, four bins per lane
+            const int lane = threadIdx.x;
+            uint32_t c[4], sum = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                c[k] = cnt[4 * lane + k];
+                sum += c[k];
+            }
+            uint32_t run = qadc_wave_incl_scan(sum) - sum;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                start[4 * lane + k] = run;
+                run += c[k];
+            }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < na; i += NT) {
+            const uint32_t b = ((uint32_t)(A[i] >> 32) >> shift) & 255u;
+            S.order[start[b] + atomicAdd(&fill[b], 1u)] = (uint16_t)i;
+        }
+        __syncthreads();
+        for (int p = threadIdx.x; p < na; p += NT) {
+            const uint64_t mine = A[S.order[p]];
+            const uint32_t b = ((uint32_t)(mine >> 32) >> shift) & 255u;
+            const int gs = (int)start[b], ge = gs + (int)cnt[b];
+            int r = gs;
+            if (gs < R) {  // (a whole bin at or beyond rank R cannot hold a result)
+                for (int j = gs; j < ge; ++j) r += (A[S.order[j]] < mine) ? 1 : 0;
+                if (r < R) {
+                    const uint32_t key = (uint32_t)(mine >> 32);
+                    o.ids[r] = (int32_t)(uint32_t)mine;
+                    o.keys[r] = (uint16_t)key;
+                    o.dist[r] = fmaf((float)key, fdelta, fdmin);
+                }
+            }
+        }
+    }
+    for (int r = (na < R ? na : R) + threadIdx.x; r < R; r += NT) {
+        o.ids[r] = -1;
+        o.keys[r] = (uint16_t)qmax;
+        o.dist[r] = INFINITY;
+    }
+}
+
+// Exact selection over all n codes by one block: histogram of key bins (two
+// levels for 16-bit keys) gives the R-th key k*; a second pass in id order keeps
+// every code below k* and the first (R - count_below) codes equal to k*.  A receives
+// min(R, n) entries; their number is left in sh[2].
+template <int KIND, typename QT>
+__device__ inline void exact_select(const DevLayout *L, const QT *gtab,
+                                    const uint8_t *__restrict__ codes, int64_t n, int R,
+                                    uint64_t *A, uint32_t *hist, uint32_t *sh) {
+    const int Rn = (int64_t)R < n ? R : (int)n;
+    const bool wide = L->acc_bits != 8;
+    uint32_t kstar = 0, below = 0;
+    for (int level = 0; level < (wide ? 2 : 1); ++level) {
+        for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
+        __syncthreads();
+        for (int64_t id = threadIdx.x; id < n; id += blockDim.x) {
+            uint32_t key = key_at<KIND, QT>(L, gtab, codes, id);
+            if (!wide)
+                atomicAdd(&hist[key], 1u);
+            else if (level == 0)
+                atomicAdd(&hist[key >> 8], 1u);
+            else if ((key >> 8) == kstar)
+                atomicAdd(&hist[key & 255u], 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x < QADC_WAVE) qadc_wave_select_bin(hist, (uint32_t)Rn, below, sh);
+        __syncthreads();
+        kstar = (level == 0) ? sh[0] : ((kstar << 8) | sh[0]);
+        below = sh[1];
+        __syncthreads();
+    }
+    const uint32_t need = (uint32_t)Rn - below;  // ties to keep, lowest ids first
+    if (threadIdx.x == 0) sh[2] = 0;             // entries written to A
+    uint32_t tie_base = 0;
+    const int wave = threadIdx.x / QADC_WAVE, lane = threadIdx.x % QADC_WAVE;
+    const int nwaves = blockDim.x / QADC_WAVE;
+    uint32_t *wtot = sh + 8;  // nwaves words
+    __syncthreads();
+    for (int64_t base = 0; base < n; base += blockDim.x) {
+        const int64_t id = base + threadIdx.x;
+        const bool valid = id < n;
+        const uint32_t key = valid ? key_at<KIND, QT>(L, gtab, codes, id) : 0xffffffffu;
+        const bool lt = valid && key < kstar, eq = valid && key == kstar;
+        const uint64_t m = __ballot(eq);
+        if (lane == 0) wtot[wave] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t woff = 0, tot = 0;
+        for (int w = 0; w < nwaves; ++w) {
+            uint32_t c = wtot[w];
+            woff += (w < wave) ? c : 0;
+            tot += c;
+        }
+        const uint32_t tie_rank = tie_base + woff + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (lt || (eq && tie_rank < need)) {
+            uint32_t pos = atomicAdd(&sh[2], 1u);
+            A[pos] = ((uint64_t)key << 32) | (uint64_t)(uint32_t)id;
+        }
+        tie_base += tot;
+        __syncthreads();
+    }
 }

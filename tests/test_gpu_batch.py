@@ -1,0 +1,123 @@
+"""GPU parity of the batched scan on the matrix cores: every query of a batch must give, byte for
+byte, what it gives alone (one query per call takes a different kernel), and a sample must match
+the CPU oracle.  Sizes sit at the edges of the 512- and 2048-code chunks, of the 32-query tiles and
+of the block that picks the results."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from harness import synth
+from paper_1812_09162_amd import binding as qb
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = {
+    "16x4": ([4] * 16, 8), "16x4u16": ([4] * 16, 16), "32x4": ([4] * 32, 8),
+    "c3": ([6, 5, 5, 6, 5, 5, 4, 4], 16), "c3u8": ([6, 5, 5, 6, 5, 5, 4, 4], 8), "5x8": ([5] * 8, 16),
+    "664": ([6, 6, 4] * 4, 16), "655": ([6, 5, 5] * 4, 16), "664u8": ([6, 6, 4] * 4, 8),
+    "6to4": ([6] * 8 + [4] * 4, 16),  # as many steps of each kind as {6,6,4} x 4, fields elsewhere
+    "odd64": ([4, 5, 6, 5, 4, 6, 6, 5, 5, 4, 6, 5], 16),
+    "664x2": ([6, 6, 4] * 8, 16), "655x2": ([6, 5, 5] * 8, 16), "mixed128": ([4, 6, 6, 5, 5, 6, 4, 6, 6, 5, 5, 6] * 2, 16),
+}
+
+
+def _make(name, n, nq, seed, data="aniso_gauss", d=96):
+    nbits, acc = LAYOUTS[name]
+    lay = synth.make_layout(d, nbits, acc)
+    g = torch.Generator().manual_seed(seed)
+    x = synth.GENERATORS[data](4096, d, seed)
+    cbs, o = [], 0
+    for k, s in zip(lay.ksub, lay.dsub):
+        cbs.append(x[torch.randperm(4096, generator=g)[:k], o:o + s].reshape(-1))
+        o += s
+    cb = torch.cat(cbs).contiguous()
+    sub = torch.stack([torch.randint(0, k, (n,), generator=g) for k in lay.ksub], 1).to(torch.uint8)
+    codes = synth.pack_codes(sub, lay)
+    queries = synth.GENERATORS[data](nq, d, seed + 1)
+    idx = qb.PqIndex(d, lay.nbits, lay.dsub, cb.cuda(), acc)
+    return lay, cb, codes, queries, idx
+
+
+def _check(lay, cb, codes, queries, idx, R, sample=2, t=400):
+    c, z = codes.cuda(), queries.cuda()
+    got = qb.pq_search_topk(idx, z, c, t, R)
+    for q in range(z.shape[0]):
+        one = qb.pq_search_topk(idx, z[q:q + 1], c, t, R)
+        for a, b in zip(got, one):
+            assert torch.equal(a[q].view(torch.uint8), b[0].view(torch.uint8)), q
+    for q in range(0, z.shape[0], max(1, z.shape[0] // sample))[:sample] if sample else []:
+        oi, ok, od = oracle.search(lay.d, lay.nbits, lay.dsub, lay.acc_bits, cb.numpy(), queries[q].numpy(),
+                                   codes.numpy(), t, R)
+        assert np.array_equal(got[0][q].cpu().numpy(), oi)
+        assert np.array_equal(got[1][q].cpu().numpy().astype(np.uint16), ok)
+        assert np.array_equal(got[2][q].cpu().numpy(), od)
+    return got
+
+
+@pytest.mark.parametrize("name", list(LAYOUTS))
+@pytest.mark.parametrize("n,nq,R", [(51_200, 33, 100), (51_711, 5, 10), (131_073, 65, 7)])
+def test_batch_equals_single(name, n, nq, R):
+    _check(*_make(name, n, nq, 3 + len(name)), R)
+
+
+@pytest.mark.parametrize("n", [4096, 4607, 4608, 4609, 2048 * 32 - 1, 2048 * 32 + 513])
+@pytest.mark.parametrize("nq", [5, 32, 97, 129])
+def test_chunk_and_tile_edges(n, nq):
+    _check(*_make("16x4", n, nq, n + nq), 10, sample=1)
+
+
+@pytest.mark.parametrize("name", ["16x4", "32x4", "c3", "664"])
+@pytest.mark.parametrize("R", [1, 128, 129, 256, 257, 1000])
+def test_result_lengths(name, R):
+    _check(*_make(name, 600_001, 6, R), R, sample=1)
+
+
+def test_small_blocks_and_large_chunks():
+    """more than 512 queries (small picking blocks); 16 groups per lane and chunk"""
+    _check(*_make("16x4", 300_007, 513, 8), 100, sample=1)
+    lay, cb, codes, queries, idx = _make("16x4", 4_200_003, 40, 9)
+    _check(lay, cb, codes, queries[:34], idx, 100, sample=0)
+    _check(lay, cb, codes, queries[:6], idx, 1, sample=0)  # (groups of more than 64 codes: little workspace)
+
+
+@pytest.mark.parametrize("name", ["16x4", "c3"])
+@pytest.mark.parametrize("distinct", [1, 7, 300])
+def test_equal_codes(name, distinct):
+    """crowds of equal keys: list overflow, segments, exact selection"""
+    lay, cb, codes, queries, idx = _make(name, 40_000, 6, 11)
+    g = torch.Generator().manual_seed(4)
+    codes = codes[torch.randint(0, distinct, (40_000,), generator=g)].contiguous()
+    _check(lay, cb, codes, queries, idx, 100, sample=1)
+
+
+def test_integer_data_and_calibration_at_the_end():
+    """integer tables (many ties); the first codes the best ones (everything else saturates) and the worst ones"""
+    lay, cb, codes, queries, idx = _make("16x4", 70_000, 8, 12, "gamma_ints", 128)
+    _check(lay, cb, codes, queries, idx, 100)
+    ids = qb.pq_search_topk(idx, queries[:1].cuda(), codes.cuda(), 400, 2000)[0][0].cpu().long()
+    rest = torch.ones(70_000, dtype=torch.bool)
+    rest[ids] = False
+    best_first = torch.cat([codes[ids], codes[rest]])
+    _check(lay, cb, best_first.contiguous(), queries, idx, 100, sample=1)
+    _check(lay, cb, best_first.flip(0).contiguous(), queries, idx, 100, sample=1)
+
+
+def test_stage_calls_and_bounds():
+    """the scan call with the quantizer's bound, an unknown one, and one below which few codes lie"""
+    lay, cb, codes, queries, idx = _make("16x4", 60_000, 40, 13)
+    c, z = codes.cuda(), queries.cuda()
+    tables = qb.pq_compute_tables(idx, z)
+    qt, qp = qb.pq_quantize_tables(idx, tables, c, 400, 50)
+    want = qb.pq_search_topk(idx, z, c, 400, 50)
+    for bound in (None, qb.PQ_KEY_BOUND_UNKNOWN, 40):
+        p = qp.clone()
+        if bound is not None:
+            p.view(torch.int32).view(40, 6)[:, 5] = bound if bound < 2 ** 31 else bound - 2 ** 32
+        got = qb.pq_adc_scan_topk(idx, qt, p, c, 50)
+        for q in range(40):
+            one = qb.pq_adc_scan_topk(idx, qt[q:q + 1].contiguous(), p[q:q + 1].contiguous(), c, 50)
+            for a, b, w in zip(got, one, want):
+                assert torch.equal(a[q], b[0])
+                if bound != 40:
+                    assert torch.equal(a[q], w[q])
