@@ -1,0 +1,43 @@
+// Shared by the two forms of the coarse search.
+#pragma once
+#include "scan_device.h"
+
+#define CS_MAX_NPROBE 1024
+
+__device__ inline void cs_rank_and_write(const uint64_t *A, int na, int k, int nprobe, int32_t *oid,
+                                         float *osc) {
+    for (int i = threadIdx.x; i < na; i += blockDim.x) {
+        const uint64_t mine = A[i];
+        int r = 0;
+        for (int j = 0; j < na; ++j) r += A[j] < mine ? 1 : 0;
+        if (r < k) {
+            oid[r] = (int32_t)(uint32_t)mine;
+            if (osc) osc[r] = qadc_ord2f((uint32_t)(mine >> 32));
+        }
+    }
+    for (int r = k + threadIdx.x; r < nprobe; r += blockDim.x) {
+        oid[r] = -1;
+        if (osc) osc[r] = INFINITY;
+    }
+}
+
+static inline size_t cs_up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// The half-precision form (coarse_half.hip) of a call, if it takes it.
+struct CoarseHalf {
+    bool use;
+    int S;       // product steps of 16 columns: d and three pieces of the norm
+    int P;       // cells of the pilot
+    int ntiles;  // tiles of 32 cells
+    int nslots;  // candidate lists per query
+};
+CoarseHalf qadc_coarse_half_plan(int nq, int K, int d, int nprobe);
+// workspace behind the norms and the score matrix, for passes of qc queries
+size_t qadc_coarse_half_bytes(int qc, int K);
+// norms (always) and, with hp.use, the cells' operand in `half`
+int qadc_coarse_cells(const float *centroids, int K, int d, const CoarseHalf &hp, float *cnorm, char *half, hipStream_t s);
+// one pass: results of nqc <= qc queries; *flag (cleared here) is raised when the exact form must take
+// the pass instead.  minima: nqc x P / 16 floats.
+int qadc_coarse_half_pass(const float *queries, int nqc, int qc, const float *centroids, int K, int d, int nprobe,
+                          const CoarseHalf &hp, const float *cnorm, char *half, float *minima, int32_t *probe_ids,
+                          float *probe_scores, int *flag, hipStream_t s);

@@ -11,7 +11,7 @@
 // each, i.e. exactly the chain above (verified bit for bit on gfx950), so the scores, and with
 // them the ranking, are reproducible by a scalar fmaf loop.
 //
-//   k_cnorm    ||c||^2 per centroid
+//   k_cstat    ||c||^2 per centroid (coarse_half.hip)
 //   k_scores   128 x 256 (queries x cells) score tiles per block of four waves, each wave a
 //              64 x 128 part as 2 x 4 MFMA tiles; operands staged through LDS in chunks of 32
 //              dimensions, the next chunk prefetched into registers while the current one is
@@ -28,7 +28,7 @@
 #include <math.h>
 #include <string.h>
 
-#include "scan_device.h"
+#include "coarse.h"
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -44,19 +44,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 #define CS_NW (CS_NT / 64)
 #define CS_WC (CS_NW / 2)            // waves side by side over the tile's cells
 #define CS_NJ (CS_TC / CS_WC / 32)   // 32 x 32 MFMA tiles side by side per wave
-#define CS_MAX_NPROBE 1024
 #define CS_SLOT 32    // candidate slots per (query, block of CS_TC cells) in the filtering form
-
-// --------------------------------------------------------------------- k_cnorm ---
-__global__ void __launch_bounds__(256)
-k_cnorm(const float *__restrict__ centroids, int K, int d, float *__restrict__ cnorm) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= K) return;
-    const float *p = centroids + (size_t)c * d;
-    float acc = 0.0f;
-    for (int l = 0; l < d; ++l) acc = __fmaf_rn(p[l], p[l], acc);
-    cnorm[c] = acc;
-}
 
 // -------------------------------------------------------------------- k_scores ---
 // scores[q][c] for q in [q0, q0 + nqc), c in [0, K); row stride ld (floats).
@@ -304,23 +292,6 @@ __device__ __forceinline__ void cs_hist_add(uint32_t *hist, uint32_t bin, bool a
         if (__lane_id() == leader) atomicAdd(&hist[b], (uint32_t)__popcll(act));
     } else if (active) {
         atomicAdd(&hist[bin], 1u);
-    }
-}
-
-__device__ inline void cs_rank_and_write(const uint64_t *A, int na, int k, int nprobe, int32_t *oid,
-                                         float *osc) {
-    for (int i = threadIdx.x; i < na; i += blockDim.x) {
-        const uint64_t mine = A[i];
-        int r = 0;
-        for (int j = 0; j < na; ++j) r += A[j] < mine ? 1 : 0;
-        if (r < k) {
-            oid[r] = (int32_t)(uint32_t)mine;
-            if (osc) osc[r] = qadc_ord2f((uint32_t)(mine >> 32));
-        }
-    }
-    for (int r = k + threadIdx.x; r < nprobe; r += blockDim.x) {
-        oid[r] = -1;
-        if (osc) osc[r] = INFINITY;
     }
 }
 
@@ -582,8 +553,6 @@ k_select_cand(const uint32_t *__restrict__ counts, const uint64_t *__restrict__ 
 }
 
 // ------------------------------------------------------------------------ host ---
-static size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
-
 // Queries per pass: as many as a 1 GiB score matrix (the fallback's) holds.  Larger passes give the
 // pilot, the selections and the guarded fallback launches more blocks each (10,000 queries over
 // 65,536 cells: 2.70 ms per call with 256 MiB, 2.42 with 512 MiB, 2.29 with 1 GiB).
@@ -612,16 +581,16 @@ static int coarse_pilot(int K, int nprobe) {
 }
 static size_t coarse_filter_bytes(int qc, int K, int nprobe) {
     const size_t ncb = ((size_t)K + CS_TC - 1) / CS_TC;
-    return up256((size_t)qc * ncb * CS_SLOT * sizeof(uint64_t)) + up256((size_t)qc * ncb * sizeof(uint32_t)) +
-           up256((size_t)qc * nprobe * sizeof(int32_t)) + up256((size_t)qc * nprobe * sizeof(float)) + 256;
+    return cs_up256((size_t)qc * ncb * CS_SLOT * sizeof(uint64_t)) + cs_up256((size_t)qc * ncb * sizeof(uint32_t)) +
+           cs_up256((size_t)qc * nprobe * sizeof(int32_t)) + cs_up256((size_t)qc * nprobe * sizeof(float)) + 256;
 }
 
 extern "C" size_t ivf_coarse_workspace_bytes(int nq, int K) {
     if (nq < 0 || K < 1) return 0;
     const size_t ld = ((size_t)K + 31) & ~(size_t)31;
     const int qc = coarse_chunk(nq, K);
-    return up256((size_t)K * sizeof(float)) + up256((size_t)qc * ld * sizeof(float)) +
-           coarse_filter_bytes(qc, K, CS_MAX_NPROBE);
+    const size_t f = coarse_filter_bytes(qc, K, CS_MAX_NPROBE), h = qadc_coarse_half_bytes(qc, K);
+    return cs_up256((size_t)K * sizeof(float)) + cs_up256((size_t)qc * ld * sizeof(float)) + (f > h ? f : h);
 }
 
 extern "C" int ivf_coarse_search(const float *queries, int nq, const float *centroids, int K, int d,
@@ -648,21 +617,23 @@ extern "C" int ivf_coarse_search(const float *queries, int nq, const float *cent
     }
     hipStream_t s = (hipStream_t)stream;
     float *cnorm = (float *)workspace;
-    float *scores = (float *)((char *)workspace + up256((size_t)K * sizeof(float)));
+    float *scores = (float *)((char *)workspace + cs_up256((size_t)K * sizeof(float)));
     const size_t ld = ((size_t)K + 31) & ~(size_t)31;
     const int qc = coarse_chunk(nq, K);
     // 16-byte loads need rows that start on 16-byte boundaries
     const int vec = (d % 4 == 0) && (((uintptr_t)queries | (uintptr_t)centroids) & 15u) == 0;
-    hipLaunchKernelGGL(k_cnorm, dim3((K + 255) / 256), dim3(256), 0, s, centroids, K, d, cnorm);
-    QADC_LAUNCH_CHECK("k_cnorm");
+    const CoarseHalf hp = qadc_coarse_half_plan(nq, K, d, nprobe);
     const int P = coarse_pilot(K, nprobe);
     const int ncb = (K + CS_TC - 1) / CS_TC;
-    char *fb = (char *)scores + up256((size_t)qc * ld * sizeof(float));
+    char *fb = (char *)scores + cs_up256((size_t)qc * ld * sizeof(float));
     uint64_t *slots = (uint64_t *)fb;
-    uint32_t *counts = (uint32_t *)(fb + up256((size_t)qc * ncb * CS_SLOT * sizeof(uint64_t)));
-    int32_t *pilot_ids = (int32_t *)((char *)counts + up256((size_t)qc * ncb * sizeof(uint32_t)));
-    float *pilot_sc = (float *)((char *)pilot_ids + up256((size_t)qc * nprobe * sizeof(int32_t)));
-    int *flag = (int *)((char *)pilot_sc + up256((size_t)qc * nprobe * sizeof(float)));
+    uint32_t *counts = (uint32_t *)(fb + cs_up256((size_t)qc * ncb * CS_SLOT * sizeof(uint64_t)));
+    int32_t *pilot_ids = (int32_t *)((char *)counts + cs_up256((size_t)qc * ncb * sizeof(uint32_t)));
+    float *pilot_sc = (float *)((char *)pilot_ids + cs_up256((size_t)qc * nprobe * sizeof(int32_t)));
+    int *flag = (int *)((char *)pilot_sc + cs_up256((size_t)qc * nprobe * sizeof(float)));
+    int rc = qadc_coarse_cells(centroids, K, d, hp, cnorm, fb, s);
+    if (rc != PQ_OK) return rc;
+    if (hp.use) flag = (int *)(fb + qadc_coarse_half_bytes(qc, K) - 256);
     // expected candidates per list: CS_TC nprobe / P <= 4
     const int logw = 3;
     for (int q0 = 0; q0 < nq; q0 += qc) {
@@ -672,7 +643,11 @@ extern "C" int ivf_coarse_search(const float *queries, int nq, const float *cent
         float *psc = probe_scores ? probe_scores + (size_t)q0 * nprobe : nullptr;
         const dim3 gq((K + CS_TC - 1) / CS_TC, (nqc + CS_TQ - 1) / CS_TQ);
         const int *guard = nullptr;
-        if (P > 0) {
+        if (hp.use) {
+            if ((rc = qadc_coarse_half_pass(qp, nqc, qc, centroids, K, d, nprobe, hp, cnorm, fb, scores, pid, psc, flag, s)) != PQ_OK)
+                return rc;
+            guard = flag;
+        } else if (P > 0) {
             // pilot: matrix form over the first P cells -> bound and best score per query
             hipLaunchKernelGGL(k_scores<false>, dim3(cs_grid(P / CS_TC, gq.y)), dim3(CS_NT), 0, s, qp, nqc,
                                centroids, P, d, cnorm, scores, (size_t)P, vec, (const float *)nullptr, 0, 0,

@@ -1,0 +1,62 @@
+"""The half-precision form of the coarse search (batches over many cells) must return, byte for byte,
+what the exact matrix form returns, on data of any scale, with ties, and where its bound fails and the
+exact form has to take over."""
+import pytest
+import torch
+
+from harness import synth
+from paper_1812_09162_amd import binding as qb
+
+pytestmark = pytest.mark.gpu
+
+
+def _data(kind, n, d, seed):
+    x = synth.GENERATORS["gamma_ints" if kind == "gamma" else "aniso_gauss"](n, d, seed)
+    if kind == "offset":      # all vectors close together, far from the origin
+        x = x + 30.0
+    elif kind == "tiny":
+        x = x * 1e-9
+    elif kind == "huge":
+        x = x * 1e9
+    elif kind == "ties":      # small integers: many equal scores
+        x = torch.round(x * 8.0)
+    elif kind == "spread":    # components of very different size
+        x = x * torch.logspace(-6, 3, d)
+    return x.cuda()
+
+
+def _check(z, c, nprobe):
+    got = qb.ivf_coarse_search(z, c, nprobe)
+    qb.pq_set_option(qb.PQ_OPT_COARSE_FILTER, 0)
+    try:
+        want = qb.ivf_coarse_search(z, c, nprobe)
+    finally:
+        qb.pq_set_option(qb.PQ_OPT_COARSE_FILTER, 1)
+    assert torch.equal(got[0], want[0])
+    assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
+
+
+@pytest.mark.parametrize("kind", ["gauss", "gamma", "offset", "tiny", "huge", "ties", "spread"])
+@pytest.mark.parametrize("nq,K,d,nprobe", [(64, 16384, 96, 64), (131, 20_011, 128, 33), (97, 33_001, 109, 1)])
+def test_kinds_of_data(kind, nq, K, d, nprobe):
+    _check(_data(kind, nq, d, 5), _data(kind, K, d, 6), nprobe)
+
+
+@pytest.mark.parametrize("d", [1, 13, 110, 125, 126, 142, 200, 256, 257])
+def test_dimensions(d):
+    _check(_data("gauss", 70, d, 7), _data("gauss", 17_000, d, 8), 40)
+
+
+@pytest.mark.parametrize("nq,K,nprobe", [(4100, 65_536, 64), (600, 65_543, 256), (64, 131_072, 200)])
+def test_sizes(nq, K, nprobe):
+    _check(_data("gauss", nq, 96, 9), _data("gauss", K, 96, 10), nprobe)
+
+
+def test_where_the_lists_or_the_range_do_not_suffice():
+    z, c = _data("gauss", 80, 96, 11), _data("gauss", 20_000, 96, 12)
+    order = (c - z[0]).square().sum(1).argsort()
+    _check(z, c[order].contiguous(), 64)                      # the nearest cells of a query side by side
+    _check(z, c[:50].repeat(400, 1).contiguous(), 64)         # every cell 400 times
+    _check(torch.cat([z[:70], z[70:] * 1e6]), c, 64)          # queries beyond the cells' range
+    _check(z * 0.0, c, 64)
+    _check(z, c * 0.0, 64)
