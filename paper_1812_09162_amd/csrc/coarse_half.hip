@@ -77,6 +77,67 @@ k_cstat(const float *__restrict__ centroids, int K, int d, float *__restrict__ c
     }
 }
 
+// ---------------------------------------------------------------- k_cdirect ---
+// A few queries: norms and scores of 64 cells per block of one wave, straight from the chains of the
+// definition (every thread those of one cell).  The cells are read once, in pieces of 32 dimensions
+// through LDS, the next piece requested before the current one is used; a call is bound by that read
+// and by its launches, of which this form has two instead of seven.
+template <int NQ>
+__global__ void __launch_bounds__(64)
+k_cdirect(const float *__restrict__ queries, int nq, const float *__restrict__ centroids, int K, int d,
+          float *__restrict__ scores, size_t ld, float *__restrict__ minima) {
+    __shared__ float t[64 * 33];
+    __shared__ __align__(16) float zs[32 * NQ];  // [dimension][query]
+    const int l = threadIdx.x;
+    const int64_t c0 = (int64_t)blockIdx.x * 64;
+    const int nc = K - c0 < 64 ? (int)(K - c0) : 64;
+    const float *base = centroids + c0 * d;
+    const int kl = l & 31, r0 = l >> 5;
+    float v[32], acc[NQ], norm = 0.0f;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[q] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = (r0 + 2 * i < nc && kl < d) ? base[(size_t)(r0 + 2 * i) * d + kl] : 0.0f;
+    for (int k0 = 0; k0 < d; k0 += 32) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 32; ++i) t[(r0 + 2 * i) * 33 + kl] = v[i];
+        for (int i = l; i < 32 * NQ; i += 64) {
+            const int q = i / 32, k = k0 + (i & 31);
+            zs[(i & 31) * NQ + q] = q < nq && k < d ? queries[(size_t)q * d + k] : 0.0f;
+        }
+        __syncthreads();
+        if (k0 + 32 < d)
+#pragma unroll
+            for (int i = 0; i < 32; ++i)
+                v[i] = (r0 + 2 * i < nc && k0 + 32 + kl < d) ? base[(size_t)(r0 + 2 * i) * d + k0 + 32 + kl] : 0.0f;
+        const int kn = d - k0 < 32 ? d - k0 : 32;
+        for (int k = 0; k < kn; ++k) {
+            const float x = t[l * 33 + k];
+            norm = __fmaf_rn(x, x, norm);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) acc[q] = __fmaf_rn(zs[k * NQ + q], x, acc[q]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (q >= nq) break;
+        const float sc = __fmaf_rn(-2.0f, acc[q], norm);
+        if (l < nc) scores[(size_t)q * ld + c0 + l] = sc;
+        const uint32_t m = qadc_wave_min(l < nc ? qadc_f2ord(sc) : 0xffffffffu);
+        if (l == 0) minima[(size_t)q * ld + blockIdx.x] = qadc_ord2f(m);  // the block's smallest, for the selection
+    }
+}
+
+int qadc_coarse_direct(const float *queries, int nq, const float *centroids, int K, int d, float *scores, size_t ld,
+                       float *minima, hipStream_t s) {
+#define CH_DIRECT(NQ) \
+    hipLaunchKernelGGL(k_cdirect<NQ>, dim3((K + 63) / 64), dim3(64), 0, s, queries, nq, centroids, K, d, scores, ld, minima)
+    if (nq == 1) CH_DIRECT(1); else if (nq <= 4) CH_DIRECT(4); else if (nq <= 8) CH_DIRECT(8); else CH_DIRECT(QADC_DIRECT_NQ);
+    QADC_LAUNCH_CHECK("k_cdirect");
+    return PQ_OK;
+}
+
 // the scale, a power of two, from the blocks' largest components (256 threads; LDS word s)
 __device__ __forceinline__ float ch_scale(const float *__restrict__ bmax, int nb, uint32_t *s) {
     uint32_t m = 0;

@@ -60,3 +60,19 @@ def test_where_the_lists_or_the_range_do_not_suffice():
     _check(torch.cat([z[:70], z[70:] * 1e6]), c, 64)          # queries beyond the cells' range
     _check(z * 0.0, c, 64)
     _check(z, c * 0.0, 64)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "gamma", "ties"])
+@pytest.mark.parametrize("nq,K,d,nprobe", [(1, 65_536, 96, 64), (2, 63, 20, 5), (4, 8192, 33, 64), (5, 8191, 32, 64),
+                                           (16, 70_001, 128, 1), (16, 300, 97, 300), (9, 300_000, 16, 1024), (3, 40_000, 1, 7)])
+def test_few_queries(kind, nq, K, d, nprobe):
+    """calls of up to 16 queries take the direct form: as rows of a larger batch in the matrix form"""
+    z, c = _data(kind, 20, d, 13), _data(kind, K, d, 14)
+    qb.pq_set_option(qb.PQ_OPT_COARSE_FILTER, 0)
+    try:
+        want = qb.ivf_coarse_search(z, c, nprobe)
+    finally:
+        qb.pq_set_option(qb.PQ_OPT_COARSE_FILTER, 1)
+    got = qb.ivf_coarse_search(z[:nq].contiguous(), c, nprobe)
+    assert torch.equal(got[0], want[0][:nq])
+    assert torch.equal(got[1].view(torch.int32), want[1][:nq].view(torch.int32))
