@@ -114,3 +114,35 @@ def test_encode_errors(qb):
     assert rc == qb.PQ_EINVAL
     assert qb.pq_encode(idx, x[:0]).shape == (0, 2)
     idx.close()
+
+
+@pytest.mark.parametrize("d,nbits", [(96, [4] * 16), (128, [4] * 32), (64, [8] * 16), (36, [2, 3, 4, 6] * 2), (132, [4] * 32)])
+@pytest.mark.parametrize("scale", [1.0, 1e-21, 1e-12, 1e18])
+def test_encode_near_ties(qb, d, nbits, scale):
+    """Vectors half way between two centroids of every sub-space, and a few units in the last place from
+    there; duplicate centroids; data of any scale (the terms' squares underflow, or their sums overflow)."""
+    lay = synth.make_layout(d, nbits, 16)
+    rng = np.random.default_rng(d)
+    parts, mids = [], []
+    for b, s in zip(lay.nbits, lay.dsub):
+        c = rng.normal(size=(1 << b, s)).astype(np.float32)
+        c[-1] = c[0]
+        parts.append(c)
+        a, o = rng.integers(0, 1 << b, 600), rng.integers(0, 1 << b, 600)
+        mids.append(((c[a].astype(np.float64) + c[o]) / 2).astype(np.float32))
+    x = np.concatenate(mids, axis=1)
+    x[200:] = np.nextafter(x[200:], np.float32(np.inf))
+    x[400:] = np.nextafter(x[400:], np.float32(np.inf))
+    cb = np.concatenate([p.reshape(-1) for p in parts]) * np.float32(scale)
+    x = (x * np.float32(scale)).astype(np.float32)
+    idx = qb.PqIndex(lay.d, lay.nbits, lay.dsub, torch.from_numpy(cb).to(dev()), 16)
+    want = oracle.encode(d, lay.nbits, lay.dsub, cb, x)
+    assert np.array_equal(qb.pq_encode(idx, torch.from_numpy(x).to(dev())).cpu().numpy(), want)
+    # vectors and codes at addresses that allow no wide access
+    flat = torch.empty(x.size + 1, device=dev())
+    flat[1:] = torch.from_numpy(x.reshape(-1)).to(dev())
+    room = torch.empty(want.size + 1, dtype=torch.uint8, device=dev())
+    got = room[1:].view(want.shape)
+    qb.pq_encode(idx, flat[1:].view(x.shape), codes=got)
+    assert np.array_equal(got.cpu().numpy(), want)
+    idx.close()
