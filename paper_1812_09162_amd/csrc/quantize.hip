@@ -60,6 +60,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     __shared__ uint32_t kmem[QADC_KTH_MEM];
     __shared__ double s_dmin, s_delta;
     __shared__ float s_dmax;
+    __shared__ uint32_t s_omin, s_scale;
     __shared__ uint32_t sdesc[PQ_MAX_M];  // table offset | bit offset << 12 | bits << 24 of each sub-quantizer
     __shared__ uint32_t pmin_ord[PQ_MAX_M];  // table minima as ordered words (qadc_f2ord), by LDS atomic min
     if ((int)threadIdx.x < m) {  // (read after the barriers of the table set-up)
@@ -218,13 +219,22 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
         if (threadIdx.x == 0) s_dmin = dm;
     }
     float dmax = INFINITY;
+    uint32_t omin = 0xffffffffu;
+    if (btab_rel) {  // the smallest calibration sum
+        for (int i = threadIdx.x; i < t_eff; i += blockDim.x) omin = min(omin, ord[i]);
+        omin = qadc_wave_min(omin);
+        if (threadIdx.x == 0) s_omin = 0xffffffffu;
+    }
     if (t_eff > 0) dmax = qadc_ord2f(qadc_block_kth_f32(ord, t_eff, k, hist, sel, kmem));
+    if (btab_rel && threadIdx.x % QADC_WAVE == 0) atomicMin(&s_omin, omin);
     __syncthreads();
     if (threadIdx.x == 0) {
         double delta = ((double)dmax - s_dmin) / (double)qmax;
         bool ok = (delta > 0.0) && isfinite(delta);
         s_delta = ok ? delta : 0.0;
         s_dmax = dmax;
+        if (btab_rel)
+            s_scale = mx_scale_of(ok && t_eff > 0 ? (float)(((double)qadc_ord2f(s_omin) - s_dmin) / delta) : (float)qmax, (uint32_t)qmax);
     }
     __syncthreads();
     const double delta = s_delta;
@@ -250,7 +260,10 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
         if (gtab_out && first) {  // hand the prepared group tables to the scan kernel
             QT *dst = (QT *)(gtab_out + q * gtab_stride);
             for (int e = threadIdx.x; e < L->gtab_len; e += blockDim.x) dst[e] = gtab[e];
-            if (btab_rel) build_btab(L, qt, sizeof(QT) == 1 ? 0 : 8, (uint32_t *)(gtab_out + q * gtab_stride + btab_rel));
+            if (btab_rel) {
+                build_btab(L, qt, s_scale, (uint32_t *)(gtab_out + q * gtab_stride + btab_rel));
+                if (threadIdx.x == 0) ((ScanHdr *)(hdr_out + q * gtab_stride))->scale = s_scale;
+            }
         }
     }
     if (hdr_out && first) scan_hdr_clear((ScanHdr *)(hdr_out + q * gtab_stride));  // empty candidate lists
@@ -445,7 +458,8 @@ static int launch_quantize(const pq_index *idx, const float *queries, const floa
     hipLaunchKernelGGL((k_quantize<KIND, QT>), dim3((unsigned)nq * (unsigned)pp.P), dim3(QUANT_THREADS), lds, s,
                        idx->dev, QuantShape{idx->h.T, idx->h.m, idx->h.cs, idx->h.qmax, idx->h.d, ubits, uds}, idx->edesc,
                        idx->codebooks, queries, tables_in, tables_out, codes, t_eff, k,
-                       pp.pilot, pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, btab_rel, hdr_out, bound_rec);
+                       pp.pilot, pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, btab_rel,
+                       hdr_out, bound_rec);
     QADC_LAUNCH_CHECK("k_quantize");
     return PQ_OK;
 }

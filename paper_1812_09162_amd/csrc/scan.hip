@@ -35,8 +35,8 @@ constexpr int U5 = QADC_U5;  // 20-byte chunks per thread and tile, 5-byte codes
 // One block per query: the query's group tables, written where k_scan blocks pick them up.
 template <int KIND, typename QT>
 __global__ void __launch_bounds__(256)
-k_prepare(const DevLayout *__restrict__ L, const void *__restrict__ qtables, char *__restrict__ ws,
-          size_t per_query, size_t gtab_off, size_t btab_rel) {
+k_prepare(const DevLayout *__restrict__ L, const void *__restrict__ qtables, const pq_qparams_t *__restrict__ qparams,
+          char *__restrict__ ws, size_t per_query, size_t gtab_off, size_t btab_rel) {
     extern __shared__ __align__(16) unsigned char smem[];
     QT *gtab = (QT *)smem;
     uint16_t *qs = (uint16_t *)(smem + (((size_t)L->gtab_len * sizeof(QT) + 15) & ~(size_t)15));
@@ -45,7 +45,12 @@ k_prepare(const DevLayout *__restrict__ L, const void *__restrict__ qtables, cha
     build_gtab<KIND, QT>(L, qs, gtab);
     QT *dst = (QT *)(ws + q * per_query + gtab_off);
     for (int e = threadIdx.x; e < L->gtab_len; e += blockDim.x) dst[e] = gtab[e];
-    if (btab_rel) build_btab(L, qs, sizeof(QT) == 1 ? 0 : 8, (uint32_t *)((char *)dst + btab_rel));
+    if (btab_rel) {  // (no bound: 5/8 of the range)
+        const uint32_t qmax = (uint32_t)L->qmax, kb = qparams[q].key_bound;
+        const uint32_t a = mx_scale_of(kb < qmax ? 1.2f * (float)kb : 0.625f * (float)qmax, qmax);
+        build_btab(L, qs, a, (uint32_t *)((char *)dst + btab_rel));
+        if (threadIdx.x == 0) ((ScanHdr *)(ws + q * per_query))->scale = a;
+    }
     scan_hdr_clear((ScanHdr *)(ws + q * per_query));  // empty candidate lists for the scan that follows
 }
 
@@ -695,7 +700,7 @@ static int launch_scan(const pq_index *idx, const void *qtables, const pq_qparam
     if ((what & 3) == 3) mp = qadc_mx_plan(idx, nq, n, R, p);
     if (what & 4) {
         hipLaunchKernelGGL((k_prepare<KIND, QT>), dim3(nq), dim3(256), gtab_bytes + (size_t)h.T * 2, s,
-                           idx->dev, qtables, ws, p.per_query, p.gtab_off, mp.use ? mp.btab_off - p.gtab_off : (size_t)0);
+                           idx->dev, qtables, qparams, ws, p.per_query, p.gtab_off, mp.use ? mp.btab_off - p.gtab_off : (size_t)0);
         QADC_LAUNCH_CHECK("k_prepare");
     }
     if (mp.use) return qadc_scan_mx(idx, qparams, nq, codes, n, R, out_ids, out_keys, out_dist, ws, p, mp, s);

@@ -76,9 +76,20 @@ __device__ inline void build_gtab(const DevLayout *L, const uint16_t *qs, QT *gt
 __device__ __forceinline__ uint32_t mx_floor_code(uint32_t x) {
     return x < 16u ? x : (x < 32u ? 16u + ((x - 16u) >> 1) : (x < 60u ? 24u + ((x - 32u) >> 2) : 31u));
 }
+// Levels of the batched matrix-core scan: entries and keys times a / 2^16, rounded down, so that a
+// code's sum of levels never exceeds the level of its key.  Sums are told apart up to 254, entries up to
+// 60.  The range of the keys is 255 levels (8-bit tables stay as they are, small entries exact) unless
+// `key`, which the R-th will hardly exceed, is near the top of it, as with R = 1, where the best
+// calibration code is the range: it is then brought to 160 levels, so that the entries of codes near the
+// R-th stay within 60.  (Only how many codes are scored again depends on the choice.)
+__device__ __forceinline__ uint32_t mx_level(uint32_t x, uint32_t a) { return (x * a) >> 16; }  // x < 2^16, a <= 2^16
+__device__ __forceinline__ uint32_t mx_scale_of(float key, uint32_t qmax) {
+    if (key <= 0.78f * (float)qmax) return qmax == 255u ? 65536u : 256u;
+    return (uint32_t)(160.0f * 65536.0f / fminf(key, (float)qmax));
+}
 // The query's operand of the batched matrix-core scan: half-step i holds 32 codes of 6 bits in six
-// dwords, the quantized entries (qs, shifted right by `shift`) rounded down.  Block-wide, no barrier.
-__device__ inline void build_btab(const DevLayout *L, const uint16_t *qs, int shift, uint32_t *__restrict__ dst) {
+// dwords, the quantized entries' levels rounded down.  Block-wide, no barrier.
+__device__ inline void build_btab(const DevLayout *L, const uint16_t *qs, uint32_t a, uint32_t *__restrict__ dst) {
     const int total = L->mx_steps * 12;
     for (int i = threadIdx.x; i < total; i += blockDim.x) {
         const int item = i / 6, b0 = 32 * (i - item * 6);
@@ -86,7 +97,7 @@ __device__ inline void build_btab(const DevLayout *L, const uint16_t *qs, int sh
         uint32_t w = 0;
         for (int v = b0 / 6; 6 * v < b0 + 32; ++v) {
             const int seg = v < 16 ? seg0 : seg1;
-            const uint32_t code = seg < 0 ? 0u : mx_floor_code((uint32_t)qs[seg + (v & 15)] >> shift);
+            const uint32_t code = seg < 0 ? 0u : mx_floor_code(mx_level((uint32_t)qs[seg + (v & 15)], a));
             const int pos = 6 * v - b0;
             w |= pos >= 0 ? code << pos : code >> -pos;
         }
@@ -425,7 +436,8 @@ __device__ __forceinline__ void slot_append_multi(const bool *pass, const uint32
 #define QADC_NSUB 64
 struct ScanHdr {                      // first bytes of a query's workspace
     uint32_t arrive;                  // lists whose blocks have all finished (fused selection only)
-    uint32_t pad[31];
+    uint32_t scale;                   // batched matrix-core scan: levels per key, times 2^16 (mx_level)
+    uint32_t pad[30];
     uint32_t count[QADC_NSUB][32];    // count[l][0] = candidates appended to list l (may exceed the capacity)
                                       // count[l][1] = blocks of list l that have finished (fused selection only)
 };

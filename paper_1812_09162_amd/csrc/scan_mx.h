@@ -6,9 +6,9 @@
 // [codes x K] x [K x queries], K = the table length.  The one-hot rows cost a shift or two per
 // sub-code and the product runs at the full rate of the 4- and 6-bit formats.  The entries are held
 // in the 6-bit format e2m3 (32 values, 0..60 in units of 1/8), rounded DOWN, of the quantized
-// entry (8-bit tables) or of its high byte (16-bit tables): small entries, which is what codes near
-// the result have, are exact, the sum is exact, and it bounds the code's key from below:
-//     sum <= key        (8-bit tables)          sum <= key >> 8   (16-bit tables)
+// entry's level: entries and keys are scaled, per query, by a factor (mx_level) that brings the R-th key
+// to about 100 levels.  Small entries, which is what codes near the result have, lose little, the sum is
+// exact, and it bounds the level of the code's key from below.
 //
 //   k_scan_mx  writes, per query, the smallest such sum of every group of 64 codes (one byte; sums
 //              above 255 as 255) and nothing else: no bound, no compare, no atomic.
@@ -362,8 +362,11 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
     constexpr int SEG = LIST / 16 < ULIST ? LIST / 16 : ULIST;  // units whose groups the lists surely hold
     const size_t q = blockIdx.x;
     const char *wq = ws + q * per_query;
-    constexpr int shift = sizeof(QT) == 1 ? 0 : 8;
+    constexpr int shift = sizeof(QT) == 1 ? 0 : 8;  // (key bins of the ranking)
     const uint32_t qmax = sizeof(QT) == 1 ? 255u : 65535u;
+    const uint32_t scale = ((const ScanHdr *)wq)->scale;
+    // the largest key of a level (level 255 stands for all above as well)
+    auto last_key = [scale, qmax](uint32_t level) { return level >= 255u ? qmax : min((((level + 1) << 16) - 1u) / scale, qmax); };
     const uint4 *row = (const uint4 *)(wq + min_off);
     const int units = (nmin + 15) >> 4;
     constexpr int UB = 10;
@@ -395,10 +398,11 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
     for (int i = threadIdx.x; i < 256; i += NT) S.hist[i] = 0;
     if (threadIdx.x < 4) S.sh[threadIdx.x] = 0;  // 0: entries in A, 1: overflow of A, 2: groups listed, 3: units listed
     __syncthreads();
-    // the bin of the R-th smallest counted value (255 if fewer were counted)
-    auto select_bin = [&]() {
+    // the bin of the kk-th smallest counted value (255 if fewer were counted), and in S.sh[5] how many
+    // values lie in the bins below it
+    auto select_bin = [&](uint32_t kk) {
         __syncthreads();
-        if (threadIdx.x < QADC_WAVE) qadc_wave_select_bin(S.hist, (uint32_t)R, 0u, S.sh + 4);
+        if (threadIdx.x < QADC_WAVE) qadc_wave_select_bin(S.hist, kk, 0u, S.sh + 4);
         __syncthreads();
         return S.sh[4];
     };
@@ -415,7 +419,7 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
                 if (um[k] <= 255u) atomicAdd(&S.hist[um[k]], 1u);
         }
     }
-    const uint32_t b0 = select_bin();
+    const uint32_t b0 = select_bin((uint32_t)R);
     const int64_t tail0 = (int64_t)(nmin / 2) << (7 + lnb);  // codes behind the last whole chunk
     // f(id, key) for every code of the groups with a minimum within thr, and of the tail
     auto each_code = [&](uint32_t thr, auto f) {
@@ -481,10 +485,10 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
         const uint32_t pos = atomicAdd(&S.sh[0], 1u);
         if (pos < (uint32_t)ACAP) S.A[pos] = ((uint64_t)key << 32) | id; else S.sh[1] = 1u;
     };
-    // 2. the codes within a margin above that minimum.  Every code whose key (its high byte) is within
-    //    `top` is in a group whose minimum is, so if there are R of them the result is among them.
-    const uint32_t top = min(b0 + (b0 >> 5) + (uint32_t)margin, 255u);
-    uint32_t bound = min(((top + 1) << shift) - 1u, prm.key_bound);
+    // 2. the codes within a margin above that minimum.  Every code whose key's level is within `top` is in
+    //    a group whose minimum is, so if there are R of them the result is among them.
+    const uint32_t top = min(b0 + (b0 >> 5) + (uint32_t)(scale == 65536u ? 1 : margin), 255u);
+    uint32_t bound = min(last_key(top), prm.key_bound);
     each_code(top, [&](uint32_t id, uint32_t key) { if (key <= bound) keep(id, key); });
     __syncthreads();
     int na = (int)S.sh[0];
@@ -494,10 +498,22 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
         __syncthreads();
         for (int i = threadIdx.x; i < 256; i += NT) S.hist[i] = 0;
         if (threadIdx.x < 2) S.sh[threadIdx.x] = 0;
-        each_code(b0, [&](uint32_t, uint32_t key) { atomicAdd(&S.hist[key >> shift], 1u); });
-        const uint32_t bin = select_bin();
-        bound = min(((bin + 1) << shift) - 1u, prm.key_bound);
-        each_code(bound >> shift, [&](uint32_t id, uint32_t key) { if (key <= bound) keep(id, key); });
+        each_code(b0, [&](uint32_t, uint32_t key) { atomicAdd(&S.hist[min(mx_level(key, scale), 255u)], 1u); });
+        const uint32_t bin = select_bin((uint32_t)R);
+        bound = last_key(bin);
+        const uint32_t lo = bin > 0 ? last_key(bin - 1) + 1u : 0u, width = bound - lo + 1u;
+        if (width > 1) {  // a level is many keys, and where keys are close together many codes: 256 parts of it
+            const uint32_t kk = (uint32_t)R - S.sh[5];
+            __syncthreads();
+            for (int i = threadIdx.x; i < 256; i += NT) S.hist[i] = 0;
+            each_code(b0, [&](uint32_t, uint32_t key) {
+                if (key >= lo && key <= bound) atomicAdd(&S.hist[((key - lo) << 8) / width], 1u);
+            });
+            const uint32_t part = select_bin(kk);
+            bound = lo + (uint32_t)(((uint64_t)(part + 1) * width - 1u) >> 8);
+        }
+        bound = min(bound, prm.key_bound);
+        each_code(bin, [&](uint32_t id, uint32_t key) { if (key <= bound) keep(id, key); });
         __syncthreads();
         na = (int)S.sh[0];
         over = S.sh[1] != 0;
@@ -579,8 +595,8 @@ int mx_launch(const pq_index *idx, const pq_qparams_t *qparams, int nq, const ui
     GroupDesc gd = group_desc_args(h);
     if ((KIND == SCAN_W64 || KIND == SCAN_C5) && (h.g32ok == 0 || h.ng > QADC_MAXG_FAST)) gd.ng = 0;
     if (KIND == SCAN_W128) gd.ng = h.ng / 2;
-    // levels the lower bounds fall short by: 16-bit tables lose half a level per sub-quantizer
-    const int margin = sizeof(QT) == 1 ? 1 : 1 + 3 * h.m / 8;
+    // levels the sums fall short by: about half a level per sub-quantizer where entries are scaled
+    const int margin = 1 + 3 * h.m / 8;
     const int lgpc = p.gpc == 16 ? 4 : 2, lnb = __builtin_ctz((unsigned)p.nb);
 #define QADC_PICK_GO(NT, CAP)                                                                                   \
     do {                                                                                                        \
