@@ -121,16 +121,13 @@ __device__ inline bool ivf_setup(const DevLayout *L, const EntryDesc *__restrict
 // d = 16 DS) by a block of 256 threads: thread e holds table entry e = centroid e % 16 of
 // sub-quantizer e / 16 at codebook offset e * DS, so nothing is looked up, the minima come
 // from lane exchanges, and the codebook values travel while the residual settles in LDS.
+// cv: the thread's codebook values; ze, ce: dimension e of the query and of the centroid (e < d).
 template <int DS>
-__device__ inline bool ivf_setup_fix(const float *__restrict__ cb, const float *__restrict__ z,
-                                     const float *__restrict__ cen, float dmax, bool quantize,
+__device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, float dmax, bool quantize,
                                      uint32_t qmax, const IvfLds &l) {
     constexpr int d = 16 * DS;
     const int e = threadIdx.x;
-    float cv[DS];
-#pragma unroll
-    for (int t = 0; t < DS; ++t) cv[t] = cb[e * DS + t];
-    if (e < d) l.zres[e] = __fsub_rn(z[e], cen[e]);
+    if (e < d) l.zres[e] = __fsub_rn(ze, ce);
     __syncthreads();
     const float *zz = l.zres + (e >> 4) * DS;
     float acc = 0.0f;
@@ -174,6 +171,18 @@ __device__ inline bool ivf_setup_fix(const float *__restrict__ cb, const float *
     l.qt[e] = (uint16_t)qv;
     __syncthreads();
     return true;
+}
+
+// the same with everything loaded here
+template <int DS>
+__device__ inline bool ivf_setup_fix(const float *__restrict__ cb, const float *__restrict__ z,
+                                     const float *__restrict__ cen, float dmax, bool quantize,
+                                     uint32_t qmax, const IvfLds &l) {
+    const int e = threadIdx.x;
+    float cv[DS];
+#pragma unroll
+    for (int t = 0; t < DS; ++t) cv[t] = cb[e * DS + t];
+    return ivf_setup_fix<DS>(cv, e < 16 * DS ? z[e] : 0.0f, e < 16 * DS ? cen[e] : 0.0f, dmax, quantize, qmax, l);
 }
 
 __device__ __forceinline__ uint32_t dist_bin(float dist, float lo, float scale) {
@@ -1387,6 +1396,15 @@ k_ivf_tight(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
     // cells and list bounds of TIGHT_PC probes are fetched at once, and (64-bit codes of
     // nibbles) a list's first codes are requested before its set-up and every further batch
     // before the previous one is looked up.
+    // Fixed shape: the codebook values and the query stay in registers, and the centroid of the next
+    // list is requested while the current one is scanned (517 -> 490 us per 1000 queries over 10^8 codes).
+    constexpr int CVN = DS > 0 ? DS : 1;
+    float cv[CVN], ze = 0.0f, ce = 0.0f;
+    if constexpr (DS > 0) {
+#pragma unroll
+        for (int t = 0; t < DS; ++t) cv[t] = cb[threadIdx.x * DS + t];
+        if ((int)threadIdx.x < 16 * DS) ze = queries[q * (16 * DS) + threadIdx.x];
+    }
     for (int a0 = 0; a0 < nprobe; a0 += TIGHT_PC) {
         __syncthreads();  // the previous chunk's entries have been used
         if (threadIdx.x < TIGHT_PC) {
@@ -1400,8 +1418,18 @@ k_ivf_tight(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
         }
         __syncthreads();
         const int a1 = nprobe - a0 < TIGHT_PC ? nprobe - a0 : TIGHT_PC;
-        for (int ai = 0; ai < a1; ++ai) {
-            if (s_plen[ai] <= 0) continue;
+        auto next_list = [&](int a) {  // the first list with codes from a on, or a1
+            while (a < a1 && s_plen[a] <= 0) ++a;
+            return a;
+        };
+        auto request_centroid = [&](int a) {
+            if (DS > 0 && a < a1 && (int)threadIdx.x < 16 * DS) ce = coarse[(size_t)s_pcell[a] * (16 * DS) + threadIdx.x];
+        };
+        int an = next_list(0);
+        request_centroid(an);
+        for (int ai = an; ai < a1; ai = an) {
+            const float ce_now = ce;
+            an = next_list(ai + 1);
             const int c = s_pcell[ai];
             const int64_t lo = s_plo[ai], hi = lo + s_plen[ai];
             uint2 wnext[TIGHT_U];
@@ -1416,7 +1444,8 @@ k_ivf_tight(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
             if constexpr (KIND == SCAN_NIB8) request(lo);
             bool ok;
             if constexpr (DS > 0) {
-                ok = ivf_setup_fix<DS>(cb, queries + q * (16 * DS), coarse + (size_t)c * (16 * DS), cur, true, qmax, l);
+                ok = ivf_setup_fix<DS>(cv, ze, ce_now, cur, true, qmax, l);
+                request_centroid(an);
                 if (ok) build_gtab<KIND, QT>(L, l.qt, (QT *)l.gtab);
             } else {
                 ok = ivf_setup<KIND, QT>(L, edesc, cb, queries + q * L->d, coarse + (size_t)c * L->d, cur, true, true, l);
