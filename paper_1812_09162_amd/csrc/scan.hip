@@ -47,7 +47,7 @@ k_prepare(const DevLayout *__restrict__ L, const void *__restrict__ qtables, con
     for (int e = threadIdx.x; e < L->gtab_len; e += blockDim.x) dst[e] = gtab[e];
     if (btab_rel) {  // (no bound: 5/8 of the range)
         const uint32_t qmax = (uint32_t)L->qmax, kb = qparams[q].key_bound;
-        const uint32_t a = mx_scale_of(kb < qmax ? 1.2f * (float)kb : 0.625f * (float)qmax, qmax);
+        const uint32_t a = mx_scale_of(kb < qmax ? (float)kb : 0.625f * (float)qmax, qmax);
         build_btab(L, qs, a, (uint32_t *)((char *)dst + btab_rel));
         if (threadIdx.x == 0) ((ScanHdr *)(ws + q * per_query))->scale = a;
     }
