@@ -42,8 +42,9 @@ int qadc_coarse_half_pass(const float *queries, int nqc, int qc, const float *ce
                           const CoarseHalf &hp, const float *cnorm, char *half, float *minima, int32_t *probe_ids,
                           float *probe_scores, int *flag, hipStream_t s);
 // Exact scores [nq][ld] of at most QADC_DIRECT_NQ queries, and the smallest of every 64 cells
-// [nq][ld].  (Calls of up to 16 queries: 65,536 cells, d = 96: 1 query 75 -> 25 us, 16 queries 78 -> 35;
-// 32 queries would take 77 of 80, their chains being what bounds a block then.)
+// [nq][ld].  (Calls of up to 16 queries: 65,536 cells, d = 96: 1 query 75 -> 14 us, 16 queries 78 -> 25.
+// 32 queries, with the selection over whole rows, against the batched form: 1024 cells 44 / 36 us,
+// 65,536 cells 76 / 68; their chains are what bounds a block then.)
 #define QADC_DIRECT_NQ 16
 int qadc_coarse_direct(const float *queries, int nq, const float *centroids, int K, int d, float *scores, size_t ld,
                        float *minima, hipStream_t s);
