@@ -485,10 +485,14 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
         const uint32_t pos = atomicAdd(&S.sh[0], 1u);
         if (pos < (uint32_t)ACAP) S.A[pos] = ((uint64_t)key << 32) | id; else S.sh[1] = 1u;
     };
-    // 2. the codes within a margin above that minimum.  Every code whose key's level is within `top` is in
-    //    a group whose minimum is, so if there are R of them the result is among them.
+    // 2. the codes within a margin above that minimum.  Every code whose unsaturated sum's level is within
+    //    `top` is in a group whose minimum is.  A key below q_max is that sum; a saturated code's sum of
+    //    levels can lie above the level of q_max where entries are scaled (sums of up to 255 are told apart, and
+    //    q_max has a level below that), so these are left out here, and if R codes are found without them the
+    //    result is among those.
+    const uint32_t most = mx_level(qmax, scale) < 255u ? qmax - 1u : qmax;  // the largest key that a minimum bounds
     const uint32_t top = min(b0 + (b0 >> 5) + (uint32_t)(scale == 65536u ? 1 : margin), 255u);
-    uint32_t bound = min(last_key(top), prm.key_bound);
+    uint32_t bound = min(min(last_key(top), most), prm.key_bound);
     each_code(top, [&](uint32_t id, uint32_t key) { if (key <= bound) keep(id, key); });
     __syncthreads();
     int na = (int)S.sh[0];
@@ -513,11 +517,14 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
             bound = lo + (uint32_t)(((uint64_t)(part + 1) * width - 1u) >> 8);
         }
         bound = min(bound, prm.key_bound);
-        each_code(bin, [&](uint32_t id, uint32_t key) { if (key <= bound) keep(id, key); });
-        __syncthreads();
-        na = (int)S.sh[0];
-        over = S.sh[1] != 0;
-        if (over) {  // more equal keys than the block can rank
+        over = bound > most;  // the R-th key may be a saturated one: the lowest ids of any group belong to it
+        if (!over) {
+            each_code(bin, [&](uint32_t id, uint32_t key) { if (key <= bound) keep(id, key); });
+            __syncthreads();
+            na = (int)S.sh[0];
+            over = S.sh[1] != 0;
+        }
+        if (over) {  // ... or more equal keys than the block can rank
             __syncthreads();
             exact_select<KIND, QT>(L, gtab, codes, n, R, S.A, S.hist, S.sh);
             __syncthreads();

@@ -105,6 +105,43 @@ def test_integer_data_and_calibration_at_the_end():
     _check(lay, cb, best_first.flip(0).contiguous(), queries, idx, 100, sample=1)
 
 
+@pytest.mark.parametrize("R", [1, 2, 3])
+@pytest.mark.parametrize("nq,n", [(5, 1_000_003), (64, 200_001)])
+def test_saturated_result(nq, n, R):
+    """The result is saturated, and so is every other code: of all of them the lowest ids are the answer,
+    also where these have larger sums than the best code's group (levels of entries are not clamped)."""
+    lay = synth.make_layout(16, [4] * 16, 8)
+    cb = torch.arange(16, dtype=torch.float32).repeat(16)
+    sub = torch.zeros((n, 16), dtype=torch.uint8)
+    sub[:, :3] = 2
+    sub[300] = 0
+    sub[300, 0] = 1
+    codes, queries = synth.pack_codes(sub, lay), torch.zeros(nq, 16)
+    idx = qb.PqIndex(16, lay.nbits, lay.dsub, cb.cuda(), 8)
+    got = _check(lay, cb, codes, queries, idx, R, sample=1)
+    if R == 1:
+        assert got[0].eq(0).all() and got[1].cpu().numpy().min() == 255
+
+
+@pytest.mark.parametrize("name", ["c3", "664", "16x4u16"])
+def test_saturated_best_code(name):
+    """Queries far from all centroids, the best code of each among the calibration codes: fp32 sums against
+    the fp64 sum of the entries leave it, for some of them, just above the top of the range, with all others."""
+    lay, cb, codes, queries, _ = _make(name, 262_144, 97, 21)
+    queries = queries + 150.0
+    o = dims = 0
+    best = torch.zeros(97, codes.shape[0])
+    sub = oracle.unpack(lay.nbits, codes.numpy())
+    for j, (k, s) in enumerate(zip(lay.ksub, lay.dsub)):
+        c = cb[o:o + k * s].reshape(k, s).double()
+        t = (queries[:, None, dims:dims + s].double() - c[None]).square().sum(2)
+        best += t[:, torch.from_numpy(sub[:, j].astype(np.int64))].float()
+        o, dims = o + k * s, dims + s
+    codes[300:397] = codes[best.argmin(1)].clone()
+    idx = qb.PqIndex(lay.d, lay.nbits, lay.dsub, cb.cuda(), lay.acc_bits)
+    _check(lay, cb, codes, queries, idx, 1)
+
+
 def test_stage_calls_and_bounds():
     """the scan call with the quantizer's bound, an unknown one, and one below which few codes lie"""
     lay, cb, codes, queries, idx = _make("16x4", 90_000, 40, 13)
