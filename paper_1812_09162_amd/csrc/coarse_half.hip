@@ -22,7 +22,10 @@
 // E, in units of v, bounds |v - exact / 2|: u = 2^-11 is the rounding of fp16, so the products are off
 // by at most (2 u + u^2) |z||c|; values below the fp16 normals by 2^-14 each (should the products take
 // them as zero); the sums here and the chains of the definition by less than 2^-14 (|z||c| + |c|^2) for
-// d <= 256.
+// d <= 256.  The chains also round where they underflow, each sum by 2^-150 or d 2^-150 in all, and end
+// at infinity where they overflow.  With the cells' largest component in [2^-50, 2^51) the first is
+// nothing beside the terms above (2^-34 in units of v against 2^-6), and the second cannot be (|z||c| of
+// a query within the fp16 range is below 2^111); other cells take the exact form.
 #include "coarse.h"
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
@@ -138,7 +141,7 @@ int qadc_coarse_direct(const float *queries, int nq, const float *centroids, int
     return PQ_OK;
 }
 
-// the scale, a power of two, from the blocks' largest components (256 threads; LDS word s)
+// the scale, a power of two, from the blocks' largest components (256 threads; LDS word s: the largest of all)
 __device__ __forceinline__ float ch_scale(const float *__restrict__ bmax, int nb, uint32_t *s) {
     uint32_t m = 0;
     for (int i = threadIdx.x; i < nb; i += 256) m = max(m, __float_as_uint(bmax[i]));
@@ -200,6 +203,8 @@ k_qprep(const float *__restrict__ queries, int nqc, int d, int S, const float *_
     if (threadIdx.x % QADC_WAVE == 0) atomicMax(&s2, m);
     __syncthreads();
     const float cmax2 = (g * __uint_as_float(s2)) * g * 1.0001f, cmax = sqrtf(cmax2);
+    const float mx = __uint_as_float(s);  // the cells' largest component (ch_scale)
+    const bool in_range = mx == 0.0f || (mx >= 0x1p-50f && mx < 0x1p51f);
     const int q0 = blockIdx.x * 32;
     __shared__ float s_off[32];
     // eight lanes per query: norm and largest component
@@ -224,8 +229,9 @@ k_qprep(const float *__restrict__ queries, int nqc, int d, int S, const float *_
         const float off = (1.01f * zn * cmax + 2.0f * e) * 0.125f;  // (the cells' column holds 8)
         if (part == 0) {
             s_off[threadIdx.x >> 3] = off;
-            // (components or sums beyond the fp16 range, or nothing comparable: the exact form takes the pass)
-            if (q < nqc) err[q] = zm < 16384.0f && off < 60000.0f ? e : INFINITY;
+            // (components or sums beyond the fp16 range, cells outside the bound's, or nothing comparable: the
+            // exact form takes the pass)
+            if (q < nqc) err[q] = in_range && zm < 16384.0f && off < 60000.0f ? e : INFINITY;
         }
     }
     __syncthreads();

@@ -1,9 +1,11 @@
 """The half-precision form of the coarse search (batches over many cells) must return, byte for byte,
 what the exact matrix form returns, on data of any scale, with ties, and where its bound fails and the
 exact form has to take over."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 from harness import synth
 from paper_1812_09162_amd import binding as qb
 
@@ -40,6 +42,19 @@ def _check(z, c, nprobe):
 @pytest.mark.parametrize("nq,K,d,nprobe", [(64, 16384, 96, 64), (131, 20_011, 128, 33), (97, 33_001, 109, 1)])
 def test_kinds_of_data(kind, nq, K, d, nprobe):
     _check(_data(kind, nq, d, 5), _data(kind, K, d, 6), nprobe)
+
+
+@pytest.mark.parametrize("zs,cs", [(1e-21, 1e-21), (3e-22, 3e-22), (1e-22, 1e-22), (1e-20, 1e-22), (3e-18, 3e-18),
+                                   (3e20, 3e18), (1e20, 1e17), (1e15, 1e15)])
+def test_products_outside_the_normal_range(zs, cs):
+    """Products that underflow leave the definition's chain with few distinct scores (ties: the lowest ids);
+    products that overflow leave scores of -inf."""
+    z, c = _data("gauss", 70, 96, 21) * zs, _data("gauss", 20_000, 96, 22) * cs
+    _check(z, c, 20)
+    ids, scores = qb.ivf_coarse_search(z, c, 20)
+    for q in (0, 69):
+        oi, osc = oracle.coarse_search(c.cpu().numpy(), z[q].cpu().numpy(), 20)
+        assert np.array_equal(ids[q].cpu().numpy(), oi) and np.array_equal(scores[q].cpu().numpy(), osc)
 
 
 @pytest.mark.parametrize("d", [1, 13, 110, 125, 126, 142, 200, 256, 257])
