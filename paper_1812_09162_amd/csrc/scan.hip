@@ -687,17 +687,15 @@ k_final(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparam
 
 // ------------------------------------------------------------------ host ---
 // what: 4 = prepare the group tables, 1 = scan kernel, 2 = selection kernel
+// mp: the matrix-core scan, if the call takes it (scan and selection asked for together).  The plan is
+// made once per call: tables are prepared for the scan that then runs, whatever other threads do to the options.
 template <int KIND, typename QT>
 static int launch_scan(const pq_index *idx, const void *qtables, const pq_qparams_t *qparams, int nq,
                        const uint8_t *codes, int64_t n, int R, int32_t *out_ids, uint16_t *out_keys,
-                       float *out_dist, char *ws, const ScanPlan &p, hipStream_t s, int what,
+                       float *out_dist, char *ws, const ScanPlan &p, const MxPlan &mp, hipStream_t s, int what,
                        const uint16_t *bound_rec, int recP, uint32_t reck) {
     const DevLayout &h = idx->h;
     const size_t gtab_bytes = ((size_t)h.gtab_len * sizeof(QT) + 15) & ~(size_t)15;
-    // scan and selection of a batch asked for together: the matrix-core scan, where it applies
-    MxPlan mp;
-    mp.use = false;
-    if ((what & 3) == 3) mp = qadc_mx_plan(idx, nq, n, R, p);
     if (what & 4) {
         hipLaunchKernelGGL((k_prepare<KIND, QT>), dim3(nq), dim3(256), gtab_bytes + (size_t)h.T * 2, s,
                            idx->dev, qtables, qparams, ws, p.per_query, p.gtab_off, mp.use ? mp.btab_off - p.gtab_off : (size_t)0);
@@ -823,12 +821,12 @@ static int launch_scan(const pq_index *idx, const void *qtables, const pq_qparam
 
 static int scan_dispatch(const pq_index *idx, const void *qtables, const pq_qparams_t *qparams,
                          int nq, const uint8_t *codes, int64_t n, int R, int32_t *out_ids,
-                         uint16_t *out_keys, float *out_dist, char *ws, const ScanPlan &p,
+                         uint16_t *out_keys, float *out_dist, char *ws, const ScanPlan &p, const MxPlan &mp,
                          hipStream_t s, int what, const uint16_t *bound_rec = nullptr, int recP = 0,
                          uint32_t reck = 0) {
     const bool u8 = idx->h.acc_bits == 8;
 #define QADC_GO(KIND, QT) \
-    return launch_scan<KIND, QT>(idx, qtables, qparams, nq, codes, n, R, out_ids, out_keys, out_dist, ws, p, s, what, \
+    return launch_scan<KIND, QT>(idx, qtables, qparams, nq, codes, n, R, out_ids, out_keys, out_dist, ws, p, mp, s, what, \
                                  bound_rec, recP, reck)
     switch (idx->h.kind) {
         case SCAN_NIB8:
@@ -884,8 +882,9 @@ static int scan_entry(const char *who, int what, const pq_index_t *idx, const vo
         qadc_set_error("%s: workspace of %zu bytes, need %zu", who, workspace_bytes, p.total);
         return PQ_ENOMEM;
     }
+    const MxPlan mp = (what & 3) == 3 ? qadc_mx_plan(idx, nq, n, R, p) : MxPlan{};
     return scan_dispatch(idx, qtables, qparams, nq, codes, n, R, out_ids, out_keys, out_dist,
-                         (char *)workspace, p, (hipStream_t)stream, what);
+                         (char *)workspace, p, mp, (hipStream_t)stream, what);
 }
 
 extern "C" int pq_adc_scan_topk(const pq_index_t *idx, const void *qtables,
@@ -1025,6 +1024,6 @@ extern "C" int pq_search_topk(const pq_index_t *idx, const float *queries, int n
     // several pilot blocks per query: the scan adds their records up; one: the bound is in qparams
     const uint16_t *rec = pp.P > 1 ? (const uint16_t *)scratch : nullptr;
     const uint32_t reck = (uint32_t)(R < pp.pilot ? R : pp.pilot);
-    return scan_dispatch(idx, qtables, qparams, nq, codes, n, R, out_ids, out_keys, out_dist, ws, p, s, 3, rec,
+    return scan_dispatch(idx, qtables, qparams, nq, codes, n, R, out_ids, out_keys, out_dist, ws, p, mp, s, 3, rec,
                          pp.P, reck);
 }

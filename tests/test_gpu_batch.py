@@ -2,6 +2,8 @@
 byte, what it gives alone (one query per call takes a different kernel), and a sample must match
 the CPU oracle.  Sizes sit at the edges of the 512- and 2048-code chunks, of the 32-query tiles and
 of the block that picks the results."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -160,3 +162,28 @@ def test_stage_calls_and_bounds():
                 assert torch.equal(a[q], b[0])
                 if bound != 40:
                     assert torch.equal(a[q], w[q])
+
+
+def test_option_set_by_another_thread():
+    """PQ_OPT_SHARED_PASSES changes no result, whenever it is set: a call prepares its tables for the scan
+    that it then runs"""
+    lay, cb, codes, queries, idx = _make("16x4", 400_000, 9, 14)
+    c, z = codes.cuda(), queries.cuda()
+    want = qb.pq_search_topk(idx, z, c, 400, 20)
+    done = threading.Event()
+
+    def toggle():
+        while not done.is_set():
+            qb.pq_set_option(qb.PQ_OPT_SHARED_PASSES, 0)
+            qb.pq_set_option(qb.PQ_OPT_SHARED_PASSES, 1)
+
+    thread = threading.Thread(target=toggle)
+    thread.start()
+    try:
+        for _ in range(300):
+            got = qb.pq_search_topk(idx, z, c, 400, 20)
+            assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, want))
+    finally:
+        done.set()
+        thread.join()
+        qb.pq_set_option(qb.PQ_OPT_SHARED_PASSES, 1)
