@@ -292,7 +292,7 @@ int pq_encode(const pq_index_t *idx, const float *vectors, int64_t n, const floa
  *   probe_ids    [dev][nq][nprobe] int32
  *   probe_scores [dev][nq][nprobe] float32, or NULL
  *   workspace    >= ivf_coarse_workspace_bytes(nq, K), 256-byte aligned, any content
- * Queries are processed in passes whose score matrix stays within 256 MB.
+ * Queries are processed in passes whose score matrix stays within 1 GB (or 128 queries, if more).
  * Errors: PQ_EINVAL (shape, null, alignment), PQ_ENOMEM (workspace), PQ_EHIP.
  */
 size_t ivf_coarse_workspace_bytes(int nq, int K);

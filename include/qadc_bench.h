@@ -44,6 +44,14 @@ enum { PQ_LDS_UNIFORM = 0, PQ_LDS_LINEAR = 1, PQ_LDS_RANDOM_2K = 2, PQ_LDS_RANDO
 #define PQ_LDS_PROBE_BLOCKS 2048
 int pq_lds_read_probe(int pattern, int iters, void *sink, void *stream);
 
+/*
+ * Which form ivf_coarse_search takes for a call of these sizes with a workspace of that many bytes
+ * (host arithmetic only; PQ_EINVAL or PQ_ENOMEM where the call is refused).  Every form returns the
+ * same bytes; tests ask so that the form they are written for is the one that runs.
+ */
+enum { PQ_COARSE_MATRIX = 0, PQ_COARSE_FILTER = 1, PQ_COARSE_HALF = 2, PQ_COARSE_DIRECT = 3 };
+int ivf_coarse_form(int nq, int K, int d, int nprobe, size_t workspace_bytes);
+
 #ifdef __cplusplus
 }
 #endif

@@ -28,10 +28,12 @@ EXPORTS = [
     "pq_adc_scan_candidates", "pq_adc_rescan_candidates", "pq_select_topk", "pq_copy_bytes", "pq_last_error",
     "ivf_coarse_workspace_bytes", "ivf_coarse_search", "pq_encode", "pq_adc_scan_topk_static",
     "pq_set_option", "pq_get_option", "ivf_adc_scan_topk_tightening", "pq_lds_read_probe",
+    "ivf_coarse_form",
 ]
 PQ_KEY_BOUND_UNKNOWN = 0xFFFFFFFF
 (PQ_OPT_SCAN_BLOCKS, PQ_OPT_PILOT_CODES, PQ_OPT_PILOT_CODES_SINGLE, PQ_OPT_PILOT_BLOCKS, PQ_OPT_IVF_THREADS,
  PQ_OPT_SHARED_PASSES, PQ_OPT_COARSE_FILTER, PQ_OPT_IVF_SHARED_LISTS) = range(8)
+PQ_COARSE_MATRIX, PQ_COARSE_FILTER, PQ_COARSE_HALF, PQ_COARSE_DIRECT = range(4)
 
 
 class QadcError(RuntimeError):
@@ -103,6 +105,8 @@ def load() -> ctypes.CDLL:
     lib.ivf_coarse_workspace_bytes.restype = sz
     lib.ivf_coarse_search.argtypes = [vp, i32, vp, i32, i32, i32, vp, vp, vp, sz, vp]
     lib.ivf_coarse_search.restype = i32
+    lib.ivf_coarse_form.argtypes = [i32, i32, i32, i32, sz]
+    lib.ivf_coarse_form.restype = i32
     _lib = lib
     return lib
 
@@ -375,6 +379,16 @@ def unpack_qparams(qparams: torch.Tensor):
 
 def ivf_coarse_workspace_bytes(nq: int, K: int) -> int:
     return int(load().ivf_coarse_workspace_bytes(nq, K))
+
+
+def ivf_coarse_form(nq: int, K: int, d: int, nprobe: int, workspace_bytes: Optional[int] = None) -> int:
+    """PQ_COARSE_*: the form such a call takes (with the workspace that ivf_coarse_workspace_bytes names)."""
+    if workspace_bytes is None:
+        workspace_bytes = ivf_coarse_workspace_bytes(nq, K)
+    form = load().ivf_coarse_form(nq, K, d, nprobe, workspace_bytes)
+    if form < 0:
+        _check(form)
+    return form
 
 
 def ivf_coarse_search(queries: torch.Tensor, centroids: torch.Tensor, nprobe: int,

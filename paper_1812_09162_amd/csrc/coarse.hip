@@ -689,22 +689,64 @@ static size_t coarse_filter_bytes(int qc, int K, int nprobe) {
            cs_up256((size_t)qc * nprobe * sizeof(int32_t)) + cs_up256((size_t)qc * nprobe * sizeof(float)) + 256;
 }
 
-extern "C" size_t ivf_coarse_workspace_bytes(int nq, int K) {
-    if (nq < 0 || K < 1) return 0;
-    const size_t ld = ((size_t)K + 31) & ~(size_t)31;
+// Bytes of the norms and of the score matrix, and the least a call needs: these and the filtering form's lists.
+static size_t coarse_matrix_bytes(int qc, int K) {
+    return cs_up256((size_t)qc * (((size_t)K + 31) & ~(size_t)31) * sizeof(float));
+}
+static size_t coarse_least_bytes(int nq, int K) {
     const int qc = coarse_chunk(nq, K);
-    const size_t f = coarse_filter_bytes(qc, K, CS_MAX_NPROBE), h = qadc_coarse_half_bytes(qc, K);
-    return cs_up256((size_t)K * sizeof(float)) + cs_up256((size_t)qc * ld * sizeof(float)) + (f > h ? f : h);
+    return cs_up256((size_t)K * sizeof(float)) + coarse_matrix_bytes(qc, K) + coarse_filter_bytes(qc, K, CS_MAX_NPROBE);
 }
 
-extern "C" int ivf_coarse_search(const float *queries, int nq, const float *centroids, int K, int d,
-                                 int nprobe, int32_t *probe_ids, float *probe_scores,
-                                 void *workspace, size_t workspace_bytes, void *stream) {
+extern "C" size_t ivf_coarse_workspace_bytes(int nq, int K) {
+    if (nq < 0 || K < 1) return 0;
+    const int qc = coarse_chunk(nq, K);
+    const size_t least = coarse_least_bytes(nq, K);
+    const size_t half = cs_up256((size_t)K * sizeof(float)) + qadc_coarse_half_bytes(nq, qc, K, coarse_matrix_bytes(qc, K));
+    return least > half ? least : half;
+}
+
+// What a call of these sizes does, made once.
+struct CoarsePlan {
+    int form, qc, P;  // PQ_COARSE_*; queries per pass; cells of the filtering form's pilot
+    CoarseHalf hp;
+};
+static int coarse_plan(int nq, int K, int d, int nprobe, size_t workspace_bytes, CoarsePlan &p) {
     if (nq < 0 || K < 1 || d < 1 || d > PQ_MAX_DIM || nprobe < 1 || nprobe > CS_MAX_NPROBE) {
         qadc_set_error("ivf_coarse_search: need nq>=0, K>=1, 1<=d<=%d, 1<=nprobe<=%d (got nq=%d K=%d d=%d nprobe=%d)",
                        PQ_MAX_DIM, CS_MAX_NPROBE, nq, K, d, nprobe);
         return PQ_EINVAL;
     }
+    p = {};
+    if (nq == 0) return PQ_OK;
+    // (with less than ivf_coarse_workspace_bytes says, some calls do without the half-precision form)
+    const size_t need = coarse_least_bytes(nq, K);
+    if (workspace_bytes < need) {
+        qadc_set_error("ivf_coarse_search: workspace of %zu bytes, need %zu", workspace_bytes, need);
+        return PQ_ENOMEM;
+    }
+    p.qc = coarse_chunk(nq, K);
+    p.form = PQ_COARSE_DIRECT;
+    if (nq <= QADC_DIRECT_NQ) return PQ_OK;
+    p.hp = qadc_coarse_half_plan(nq, p.qc, K, d, nprobe, coarse_matrix_bytes(p.qc, K),
+                                 workspace_bytes - cs_up256((size_t)K * sizeof(float)));
+    p.P = p.hp.use ? 0 : coarse_pilot(K, nprobe);
+    p.form = p.hp.use ? PQ_COARSE_HALF : (p.P > 0 ? PQ_COARSE_FILTER : PQ_COARSE_MATRIX);
+    return PQ_OK;
+}
+
+extern "C" int ivf_coarse_form(int nq, int K, int d, int nprobe, size_t workspace_bytes) {
+    CoarsePlan p;
+    const int rc = coarse_plan(nq, K, d, nprobe, workspace_bytes, p);
+    return rc != PQ_OK ? rc : p.form;
+}
+
+extern "C" int ivf_coarse_search(const float *queries, int nq, const float *centroids, int K, int d,
+                                 int nprobe, int32_t *probe_ids, float *probe_scores,
+                                 void *workspace, size_t workspace_bytes, void *stream) {
+    CoarsePlan cp;
+    int rc = coarse_plan(nq, K, d, nprobe, workspace_bytes, cp);
+    if (rc == PQ_EINVAL) return rc;
     if (nq == 0) return PQ_OK;
     if (!queries || !centroids || !probe_ids || !workspace) {
         qadc_set_error("ivf_coarse_search: null pointer");
@@ -714,24 +756,19 @@ extern "C" int ivf_coarse_search(const float *queries, int nq, const float *cent
         qadc_set_error("ivf_coarse_search: workspace must be 256-byte aligned");
         return PQ_EINVAL;
     }
-    const size_t need = ivf_coarse_workspace_bytes(nq, K);
-    if (workspace_bytes < need) {
-        qadc_set_error("ivf_coarse_search: workspace of %zu bytes, need %zu", workspace_bytes, need);
-        return PQ_ENOMEM;
-    }
+    if (rc != PQ_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
     float *cnorm = (float *)workspace;
     float *scores = (float *)((char *)workspace + cs_up256((size_t)K * sizeof(float)));
     const size_t ld = ((size_t)K + 31) & ~(size_t)31;
-    const int qc = coarse_chunk(nq, K);
+    const int qc = cp.qc;
     // 16-byte loads need rows that start on 16-byte boundaries
     const int vec = (d % 4 == 0) && (((uintptr_t)queries | (uintptr_t)centroids) & 15u) == 0;
-    if (nq <= QADC_DIRECT_NQ) {
+    if (cp.form == PQ_COARSE_DIRECT) {
         // (the score matrix has room for 128 queries at least: the minima take rows behind the scores)
         static_assert(2 * QADC_DIRECT_NQ <= CS_TQ, "rows for scores and minima");
         float *minima = scores + QADC_DIRECT_NQ * ld;
-        const int rc = qadc_coarse_direct(queries, nq, centroids, K, d, scores, ld, minima, s);
-        if (rc != PQ_OK) return rc;
+        if ((rc = qadc_coarse_direct(queries, nq, centroids, K, d, scores, ld, minima, s)) != PQ_OK) return rc;
         // (fewer than two pieces of 64 cells per result: most would have to be read anyway)
         if ((K + 63) / 64 >= 2 * nprobe && K <= CS_MIN_PIECES * 64)
             hipLaunchKernelGGL(k_select_min, dim3(nq), dim3(1024), 0, s, (const float *)scores, (const float *)minima, ld,
@@ -742,18 +779,18 @@ extern "C" int ivf_coarse_search(const float *queries, int nq, const float *cent
         QADC_LAUNCH_CHECK("k_select");
         return PQ_OK;
     }
-    const CoarseHalf hp = qadc_coarse_half_plan(nq, K, d, nprobe);
-    const int P = coarse_pilot(K, nprobe);
+    const CoarseHalf &hp = cp.hp;
+    const int P = cp.P;
     const int ncb = (K + CS_TC - 1) / CS_TC;
-    char *fb = (char *)scores + cs_up256((size_t)qc * ld * sizeof(float));
+    char *fb = (char *)scores + coarse_matrix_bytes(qc, K);
     uint64_t *slots = (uint64_t *)fb;
     uint32_t *counts = (uint32_t *)(fb + cs_up256((size_t)qc * ncb * CS_SLOT * sizeof(uint64_t)));
     int32_t *pilot_ids = (int32_t *)((char *)counts + cs_up256((size_t)qc * ncb * sizeof(uint32_t)));
     float *pilot_sc = (float *)((char *)pilot_ids + cs_up256((size_t)qc * nprobe * sizeof(int32_t)));
     int *flag = (int *)((char *)pilot_sc + cs_up256((size_t)qc * nprobe * sizeof(float)));
-    int rc = qadc_coarse_cells(centroids, K, d, hp, cnorm, fb, s);
+    rc = qadc_coarse_cells(centroids, K, d, hp, cnorm, (char *)scores, s);
     if (rc != PQ_OK) return rc;
-    if (hp.use) flag = (int *)(fb + qadc_coarse_half_bytes(qc, K) - 256);
+    if (hp.use) flag = (int *)((char *)scores + hp.flag);
     // expected candidates per list: CS_TC nprobe / P <= 4
     const int logw = 3;
     for (int q0 = 0; q0 < nq; q0 += qc) {
@@ -764,7 +801,7 @@ extern "C" int ivf_coarse_search(const float *queries, int nq, const float *cent
         const dim3 gq((K + CS_TC - 1) / CS_TC, (nqc + CS_TQ - 1) / CS_TQ);
         const int *guard = nullptr;
         if (hp.use) {
-            if ((rc = qadc_coarse_half_pass(qp, nqc, qc, centroids, K, d, nprobe, hp, cnorm, fb, scores, pid, psc, flag, s)) != PQ_OK)
+            if ((rc = qadc_coarse_half_pass(qp, nqc, centroids, K, d, nprobe, hp, cnorm, (char *)scores, pid, psc, s)) != PQ_OK)
                 return rc;
             guard = flag;
         } else if (P > 0) {

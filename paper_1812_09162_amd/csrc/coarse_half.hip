@@ -524,80 +524,94 @@ k_cpick(const float *__restrict__ queries, const float *__restrict__ centroids, 
 
 static int ch_steps(int d) { return d + 4 <= 7 * 16 ? 7 : (d + 4 <= 9 * 16 ? 9 : CH_MAX_S); }
 
-CoarseHalf qadc_coarse_half_plan(int nq, int K, int d, int nprobe) {
-    CoarseHalf p = {};
-    if (qadc_option(PQ_OPT_COARSE_FILTER) == 0 || nq < CH_MIN_NQ || d > CH_MAX_D || K < 16384 || K > (1 << 20)) return p;
-    // The pilot: 256 cells per result, at most a quarter of all.  Fewer than 192 per result and the lists
-    // (16 entries, about 512 nprobe / P of them used on average) overflow now and then, which costs the
-    // pass the exact form: 16,384 cells, nprobe 64 (P = 4096), 4000 queries: 459 us, exact form at once 260.
-    int64_t P = 256 * (int64_t)nprobe > 16384 ? 256 * (int64_t)nprobe : 16384;
-    if (P > 65536) P = 65536;
-    if (P > K / 4) P = K / 4;
-    P &= ~(int64_t)2047;
-    if (P < 192 * (int64_t)nprobe) return p;
-    p.use = true;
-    p.S = ch_steps(d);
-    p.P = (int)P;
-    p.ntiles = (K + 31) / 32;
-    p.nslots = 2 * ((p.ntiles + CH_TILES - 1) / CH_TILES);
-    return p;
-}
+static int64_t ch_pilot_most(int K) { return (K / 4 < 65536 ? K / 4 : 65536) & ~2047; }
 
-struct ChLayout {
-    size_t cells, qs, err, bmax, bnorm, bounds, ent, ids, counts, total;
-};
-static ChLayout ch_layout(int qc, int K) {
-    ChLayout o;
-    const size_t ntiles = ((size_t)K + 31) / 32, nslots = 2 * ((ntiles + CH_TILES - 1) / CH_TILES), q = (size_t)qc;
+// The score matrix is idle until the exact form has to take a pass over, so what only one pass needs lies
+// in it (about half of it: a list's entries are 2 bytes per query and cell, the matrix 4).  The cells'
+// operand outlives a pass; it follows the lists where there is a single one, and else the matrix.
+// 65,536 cells, d = 96, 4096 queries: 14 MB behind the matrix of 1 GiB (0.6 GB with all of it there).
+static void ch_layout(CoarseHalf &p, int nq, int qc, int K, size_t matrix_bytes) {
+    const size_t q = (size_t)qc;
     size_t at = 0;
     auto take = [&](size_t bytes) {
         const size_t r = at;
         at += cs_up256(bytes);
         return r;
     };
-    o.bmax = take(((size_t)K / 256 + 1) * 4);  // (these three lie at places that do not depend on qc)
-    o.bnorm = take(((size_t)K / 256 + 1) * 4);
-    o.cells = take(ntiles * CH_MAX_S * 1024);
-    o.qs = take((q + 31) / 32 * CH_MAX_S * 1024);
-    o.err = take(q * 4);
-    o.bounds = take(q * 8);
-    o.ent = take(q * nslots * CH_CAP * 64);
-    o.ids = take(q * nslots * CH_CAP * 4);
-    o.counts = take(q * nslots * 4);
-    o.total = at + 256;  // (the flag)
-    return o;
-}
-size_t qadc_coarse_half_bytes(int qc, int K) {
-    if (K < 16384 || K > (1 << 20)) return 0;
-    return ch_layout(qc, K).total;
+    p.minima = take(q * (size_t)(p.P / 16) * 4);
+    p.qs = take((q + 31) / 32 * (size_t)p.S * 1024);
+    p.err = take(q * 4);
+    p.bounds = take(q * 8);
+    p.ent = take(q * (size_t)p.nslots * CH_CAP * 64);
+    p.ids = take(q * (size_t)p.nslots * CH_CAP * 4);
+    p.counts = take(q * (size_t)p.nslots * 4);
+    if (nq > qc && at < matrix_bytes) at = matrix_bytes;
+    p.cells = take((size_t)p.ntiles * (size_t)p.S * 1024);
+    if (at < matrix_bytes) at = matrix_bytes;  // (read by the exact form's kernels, or by the next pass)
+    p.bmax = take(((size_t)K / 256 + 1) * 4);
+    p.bnorm = take(((size_t)K / 256 + 1) * 4);
+    p.flag = take(4);
+    p.total = at;
 }
 
-int qadc_coarse_cells(const float *centroids, int K, int d, const CoarseHalf &hp, float *cnorm, char *half, hipStream_t s) {
+static bool ch_sizes(int nq, int K) { return nq >= CH_MIN_NQ && K >= 16384 && K <= (1 << 20); }
+
+CoarseHalf qadc_coarse_half_plan(int nq, int qc, int K, int d, int nprobe, size_t matrix_bytes, size_t room) {
+    CoarseHalf p = {};
+    if (qadc_option(PQ_OPT_COARSE_FILTER) == 0 || !ch_sizes(nq, K) || d > CH_MAX_D) return p;
+    // The pilot: 256 cells per result, at most a quarter of all.  Fewer than 192 per result and the lists
+    // (16 entries, about 512 nprobe / P of them used on average) overflow now and then, which costs the
+    // pass the exact form: 16,384 cells, nprobe 64 (P = 4096), 4000 queries: 459 us, exact form at once 260.
+    int64_t P = 256 * (int64_t)nprobe > 16384 ? 256 * (int64_t)nprobe : 16384;
+    if (P > ch_pilot_most(K)) P = ch_pilot_most(K);
+    P &= ~(int64_t)2047;
+    if (P < 192 * (int64_t)nprobe) return p;
+    p.S = ch_steps(d);
+    p.P = (int)P;
+    p.ntiles = (K + 31) / 32;
+    p.nslots = 2 * ((p.ntiles + CH_TILES - 1) / CH_TILES);
+    ch_layout(p, nq, qc, K, matrix_bytes);
+    p.use = p.total <= room;
+    return p;
+}
+
+size_t qadc_coarse_half_bytes(int nq, int qc, int K, size_t matrix_bytes) {
+    if (!ch_sizes(nq, K)) return 0;
+    CoarseHalf p = {};
+    p.S = CH_MAX_S;
+    p.P = (int)ch_pilot_most(K);
+    p.ntiles = (K + 31) / 32;
+    p.nslots = 2 * ((p.ntiles + CH_TILES - 1) / CH_TILES);
+    ch_layout(p, nq, qc, K, matrix_bytes);
+    return p.total;
+}
+
+int qadc_coarse_cells(const float *centroids, int K, int d, const CoarseHalf &hp, float *cnorm, char *base, hipStream_t s) {
     const int nb = (K + 255) / 256;
-    const ChLayout o = ch_layout(0, K);
-    float *bmax = hp.use ? (float *)(half + o.bmax) : nullptr, *bnorm = hp.use ? (float *)(half + o.bnorm) : nullptr;
+    float *bmax = hp.use ? (float *)(base + hp.bmax) : nullptr, *bnorm = hp.use ? (float *)(base + hp.bnorm) : nullptr;
     hipLaunchKernelGGL(k_cstat, dim3(nb), dim3(256), 0, s, centroids, K, d, cnorm, bmax, bnorm);
     QADC_LAUNCH_CHECK("k_cstat");
     if (!hp.use) return PQ_OK;
     hipLaunchKernelGGL(k_cprep, dim3(hp.ntiles < 2048 ? hp.ntiles : 2048), dim3(256), 0, s, centroids, K, d, hp.S, (const float *)cnorm,
-                       (const float *)bmax, nb, (uint4 *)(half + o.cells), hp.ntiles);
+                       (const float *)bmax, nb, (uint4 *)(base + hp.cells), hp.ntiles);
     QADC_LAUNCH_CHECK("k_cprep");
     return PQ_OK;
 }
 
-int qadc_coarse_half_pass(const float *queries, int nqc, int qc, const float *centroids, int K, int d, int nprobe,
-                          const CoarseHalf &hp, const float *cnorm, char *half, float *minima, int32_t *probe_ids,
-                          float *probe_scores, int *flag, hipStream_t s) {
-    const ChLayout o = ch_layout(qc, K);
+int qadc_coarse_half_pass(const float *queries, int nqc, const float *centroids, int K, int d, int nprobe,
+                          const CoarseHalf &hp, const float *cnorm, char *base, int32_t *probe_ids,
+                          float *probe_scores, hipStream_t s) {
     const int nb = (K + 255) / 256, nqt = (nqc + 31) / 32;
-    const u32x4 *cells = (const u32x4 *)(half + o.cells);
-    uint4 *qs = (uint4 *)(half + o.qs);
-    float *err = (float *)(half + o.err);
-    float2 *bounds = (float2 *)(half + o.bounds);
-    uint4 *ent = (uint4 *)(half + o.ent);
-    uint32_t *ids = (uint32_t *)(half + o.ids), *counts = (uint32_t *)(half + o.counts);
-    hipLaunchKernelGGL(k_qprep, dim3(nqt), dim3(256), 0, s, queries, nqc, d, hp.S, (const float *)(half + o.bmax),
-                       (const float *)(half + o.bnorm), nb, qs, err);
+    float *minima = (float *)(base + hp.minima);
+    int *flag = (int *)(base + hp.flag);
+    const u32x4 *cells = (const u32x4 *)(base + hp.cells);
+    uint4 *qs = (uint4 *)(base + hp.qs);
+    float *err = (float *)(base + hp.err);
+    float2 *bounds = (float2 *)(base + hp.bounds);
+    uint4 *ent = (uint4 *)(base + hp.ent);
+    uint32_t *ids = (uint32_t *)(base + hp.ids), *counts = (uint32_t *)(base + hp.counts);
+    hipLaunchKernelGGL(k_qprep, dim3(nqt), dim3(256), 0, s, queries, nqc, d, hp.S, (const float *)(base + hp.bmax),
+                       (const float *)(base + hp.bnorm), nb, qs, err);
     QADC_LAUNCH_CHECK("k_qprep");
 #define CH_SCAN(SV, NCOLV, PILOTV, NT, TILES)                                                                            \
     hipLaunchKernelGGL((k_cscan<SV, NCOLV, PILOTV>), dim3(((NT) + (TILES) - 1) / (TILES), (nqt + 4 * NCOLV - 1) / (4 * NCOLV)), \

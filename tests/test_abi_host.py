@@ -83,3 +83,32 @@ def test_calls_reject_null_handle():
     assert lib.pq_code_size(None) == 0 and lib.pq_table_len(None) == 0
     assert lib.pq_workspace_bytes(None, 1, 10, 10) == 0
     lib.pq_index_destroy(None)
+
+
+def _coarse_bytes_without_half_form(nq, K):
+    """norms, score matrix, and the candidate lists of the filtering form (32 entries per 256 cells)"""
+    def up(x):
+        return (x + 255) // 256 * 256
+    ld, ncb = (K + 31) // 32 * 32, (K + 255) // 256
+    qc = min(max((1 << 30) // (4 * ld) // 128 * 128, 128), (nq + 127) // 128 * 128)
+    return up(4 * K) + up(qc * ld * 4) + up(qc * ncb * 256) + up(qc * ncb * 4) + 2 * up(qc * 1024 * 4) + 256
+
+
+@pytest.mark.parametrize("nq,K", [(1, 100), (16, 65_536), (63, 65_536), (64, 16_384), (100, 20_011), (128, 65_536),
+                                  (1000, 65_536), (4097, 65_536), (10_000, 65_536), (256, 1 << 20), (1000, 1_000_000)])
+def test_coarse_workspace_keeps_within_what_the_matrix_form_needs(nq, K):
+    """A workspace of the matrix form's size is accepted, whichever form would run with more; the size asked
+    for is hardly larger (the matrix has room for the half-precision form's lists)."""
+    least, asked = _coarse_bytes_without_half_form(nq, K), qb.ivf_coarse_workspace_bytes(nq, K)
+    assert least <= asked <= 1.4 * least
+    for d, nprobe in ((96, 64), (256, 1), (257, 1024)):
+        assert qb.ivf_coarse_form(nq, K, d, nprobe, least) in (qb.PQ_COARSE_MATRIX, qb.PQ_COARSE_FILTER,
+                                                               qb.PQ_COARSE_HALF, qb.PQ_COARSE_DIRECT)
+        with pytest.raises(qb.QadcError) as e:
+            qb.ivf_coarse_form(nq, K, d, nprobe, least - 1)
+        assert e.value.code == qb.PQ_ENOMEM
+    # 96 and 128 dimensions over 65,536 cells, long batches: also with the smaller workspace
+    if nq >= 1000 and K == 65_536:
+        assert least == asked
+    for nq2 in (64, 1000, 10_000):
+        assert qb.ivf_coarse_form(nq2, 65_536, 96, 64, _coarse_bytes_without_half_form(nq2, 65_536)) == qb.PQ_COARSE_HALF

@@ -27,15 +27,21 @@ def _data(kind, n, d, seed):
     return x.cuda()
 
 
-def _check(z, c, nprobe):
-    got = qb.ivf_coarse_search(z, c, nprobe)
+def _matrix(z, c, nprobe):
     qb.pq_set_option(qb.PQ_OPT_COARSE_FILTER, 0)
     try:
-        want = qb.ivf_coarse_search(z, c, nprobe)
+        return qb.ivf_coarse_search(z, c, nprobe)
     finally:
         qb.pq_set_option(qb.PQ_OPT_COARSE_FILTER, 1)
+
+
+def _same(got, want):
     assert torch.equal(got[0], want[0])
     assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
+
+
+def _check(z, c, nprobe):
+    _same(qb.ivf_coarse_search(z, c, nprobe), _matrix(z, c, nprobe))
 
 
 @pytest.mark.parametrize("kind", ["gauss", "gamma", "offset", "tiny", "huge", "ties", "spread"])
@@ -75,6 +81,24 @@ def test_where_the_lists_or_the_range_do_not_suffice():
     _check(torch.cat([z[:70], z[70:] * 1e6]), c, 64)          # queries beyond the cells' range
     _check(z * 0.0, c, 64)
     _check(z, c * 0.0, 64)
+
+
+@pytest.mark.parametrize("nq,K,d", [(64, 65_536, 250), (300, 16_384, 96), (5000, 65_600, 40)])
+def test_smallest_workspace(nq, K, d):
+    """with no more workspace than the matrix form needs: the half-precision form where it fits, else another;
+    several passes, one of which the exact form takes over"""
+    z, c = _data("gauss", nq, d, 23), _data("gauss", K, d, 24)
+    z[nq // 2] *= 1e7
+    least = qb.ivf_coarse_workspace_bytes(nq, K)
+    while True:
+        try:
+            qb.ivf_coarse_form(nq, K, d, 20, least - 256)
+        except qb.QadcError:
+            break
+        least -= 256
+    got = qb.ivf_coarse_search(z, c, 20, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    _same(got, _matrix(z, c, 20))
+    _check(z, c, 20)
 
 
 @pytest.mark.parametrize("kind", ["gauss", "gamma", "ties"])
