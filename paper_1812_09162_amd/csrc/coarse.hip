@@ -301,7 +301,7 @@ struct SelectRowLds {
 };
 // The selection over one row s of K scores, by a block of BD threads.
 template <int BD>
-__device__ inline void cs_select_row(const float *__restrict__ s, int K, int nprobe, int32_t *__restrict__ oid,
+__device__ __forceinline__ void cs_select_row(const float *__restrict__ s, int K, int nprobe, int32_t *__restrict__ oid,
                                      float *__restrict__ osc, SelectRowLds &S) {
     uint32_t *hist = S.hist, *sel = S.sel, *wcnt = S.wcnt, *s_lo = S.lo, *s_hi = S.hi;
     uint64_t *A = S.A;
