@@ -45,9 +45,17 @@ enum { PQ_LDS_UNIFORM = 0, PQ_LDS_LINEAR = 1, PQ_LDS_RANDOM_2K = 2, PQ_LDS_RANDO
 int pq_lds_read_probe(int pattern, int iters, void *sink, void *stream);
 
 /*
+ * Which form pq_search_topk and pq_adc_scan_topk take for a call of these sizes: look-ups in LDS or the
+ * matrix cores (PQ_EINVAL for bad sizes).  Both return the same bytes; tests ask so that the form they
+ * are written for is the one that runs.
+ */
+enum { PQ_SCAN_LOOKUP = 0, PQ_SCAN_MATRIX = 1 };
+int pq_search_form(const pq_index_t *idx, int nq, int64_t n, int R);
+
+/*
  * Which form ivf_coarse_search takes for a call of these sizes with a workspace of that many bytes
  * (host arithmetic only; PQ_EINVAL or PQ_ENOMEM where the call is refused).  Every form returns the
- * same bytes; tests ask so that the form they are written for is the one that runs.
+ * same bytes.
  */
 enum { PQ_COARSE_MATRIX = 0, PQ_COARSE_FILTER = 1, PQ_COARSE_HALF = 2, PQ_COARSE_DIRECT = 3 };
 int ivf_coarse_form(int nq, int K, int d, int nprobe, size_t workspace_bytes);

@@ -28,11 +28,12 @@ EXPORTS = [
     "pq_adc_scan_candidates", "pq_adc_rescan_candidates", "pq_select_topk", "pq_copy_bytes", "pq_last_error",
     "ivf_coarse_workspace_bytes", "ivf_coarse_search", "pq_encode", "pq_adc_scan_topk_static",
     "pq_set_option", "pq_get_option", "ivf_adc_scan_topk_tightening", "pq_lds_read_probe",
-    "ivf_coarse_form",
+    "ivf_coarse_form", "pq_search_form",
 ]
 PQ_KEY_BOUND_UNKNOWN = 0xFFFFFFFF
 (PQ_OPT_SCAN_BLOCKS, PQ_OPT_PILOT_CODES, PQ_OPT_PILOT_CODES_SINGLE, PQ_OPT_PILOT_BLOCKS, PQ_OPT_IVF_THREADS,
  PQ_OPT_SHARED_PASSES, PQ_OPT_COARSE_FILTER, PQ_OPT_IVF_SHARED_LISTS) = range(8)
+PQ_SCAN_LOOKUP, PQ_SCAN_MATRIX = range(2)
 PQ_COARSE_MATRIX, PQ_COARSE_FILTER, PQ_COARSE_HALF, PQ_COARSE_DIRECT = range(4)
 
 
@@ -105,6 +106,8 @@ def load() -> ctypes.CDLL:
     lib.ivf_coarse_workspace_bytes.restype = sz
     lib.ivf_coarse_search.argtypes = [vp, i32, vp, i32, i32, i32, vp, vp, vp, sz, vp]
     lib.ivf_coarse_search.restype = i32
+    lib.pq_search_form.argtypes = [vp, i32, i64, i32]
+    lib.pq_search_form.restype = i32
     lib.ivf_coarse_form.argtypes = [i32, i32, i32, i32, sz]
     lib.ivf_coarse_form.restype = i32
     _lib = lib
@@ -240,6 +243,14 @@ def pq_adc_scan_topk_static(idx: PqIndex, qtables: torch.Tensor, qparams: torch.
 
 def pq_search_workspace_bytes(idx: PqIndex, nq: int, n: int, R: int) -> int:
     return int(load().pq_search_workspace_bytes(idx.handle, nq, n, R))
+
+
+def pq_search_form(idx: PqIndex, nq: int, n: int, R: int) -> int:
+    """PQ_SCAN_*: the form that pq_search_topk and pq_adc_scan_topk take for such a call."""
+    form = load().pq_search_form(idx.handle, nq, n, R)
+    if form < 0:
+        _check(form)
+    return form
 
 
 def pq_search_topk(idx: PqIndex, queries: torch.Tensor, codes: torch.Tensor, t: int, R: int,

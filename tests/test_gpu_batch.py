@@ -41,6 +41,12 @@ def _make(name, n, nq, seed, data="aniso_gauss", d=96):
     return lay, cb, codes, queries, idx
 
 
+def _matrix(idx, nq, n, R):
+    """the call is one of the matrix cores' (whose sizes pq_search_form knows)"""
+    assert qb.pq_search_form(idx, nq, n, R) == qb.PQ_SCAN_MATRIX
+    return True
+
+
 def _check(lay, cb, codes, queries, idx, R, sample=2, t=400):
     c, z = codes.cuda(), queries.cuda()
     got = qb.pq_search_topk(idx, z, c, t, R)
@@ -57,12 +63,62 @@ def _check(lay, cb, codes, queries, idx, R, sample=2, t=400):
     return got
 
 
-# (the matrix cores take a batch from some 800,000 codes times passes of four queries on, irregular
-# layouts from 6,000,000 on, and from 1,000 / 8,000 codes per result on)
+# (The matrix cores take a batch from some 800,000 codes times passes of four queries on, irregular
+# layouts from 6,000,000 on, and from 1,000 / 8,000 codes per result on, and more where that does not
+# pay: _matrix() asks.  Smaller calls are look-ups, which also have to agree with the single query.)
 @pytest.mark.parametrize("name", list(LAYOUTS))
 @pytest.mark.parametrize("n,nq,R", [(262_144, 97, 32), (131_583, 225, 1), (300_033, 84, 33)])
 def test_batch_equals_single(name, n, nq, R):
     _check(*_make(name, n, nq, 3 + len(name)), R, sample=1)
+
+
+# per layout: codes, queries, results at which it is the matrix cores' turn (40-bit codes and 128-bit ones of
+# other fields have the narrowest range)
+MATRIX_SIZES = {
+    "16x4": (262_144, 97, 32), "16x4u16": (262_144, 97, 32), "32x4": (131_583, 225, 1), "c3": (1_600_001, 17, 100),
+    "c3u8": (1_607_680, 16, 100), "5x8": (1_600_513, 18, 100), "664": (300_033, 84, 33), "655": (262_144, 97, 32),
+    "664u8": (300_033, 84, 33), "6to4": (262_144, 97, 32), "odd64": (400_000, 61, 50), "664x2": (131_583, 225, 1),
+    "655x2": (300_033, 84, 33), "mixed128": (300_033, 84, 33),
+}
+
+
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_matrix_form_equals_single(name):
+    n, nq, R = MATRIX_SIZES[name]
+    lay, cb, codes, queries, idx = _make(name, n, nq, 30 + len(name))
+    assert _matrix(idx, nq, n, R)
+    _check(lay, cb, codes, queries, idx, R, sample=1)
+
+
+@pytest.mark.parametrize("name", ["c3", "664", "16x4u16"])
+def test_matrix_form_single_best(name):
+    lay, cb, codes, queries, idx = _make(name, 1_600_003, 17, 40)
+    assert _matrix(idx, 17, 1_600_003, 1)
+    _check(lay, cb, codes, queries, idx, 1, sample=1)
+
+
+@pytest.mark.parametrize("n", [200_704, 200_703, 200_705, 2048 * 100 - 1, 2048 * 100, 2048 * 100 + 513])
+@pytest.mark.parametrize("nq", [40, 65, 97])
+def test_matrix_form_chunk_and_tile_edges(n, nq):
+    lay, cb, codes, queries, idx = _make("16x4", n, nq, n + nq)
+    assert _matrix(idx, nq, n, 10)
+    _check(lay, cb, codes, queries, idx, 10, sample=1)
+
+
+def test_which_form():
+    """the lines the rule draws: what is taken, and what stays with the look-ups (or went back to them)"""
+    idx = {name: _make(name, 64, 1, 1)[4] for name in LAYOUTS}
+    yes = [("16x4", 5, 10_000_000, 100), ("16x4", 9, 10_000_000, 1000), ("16x4", 256, 100_000, 10), ("32x4", 100, 50_000, 1),
+           ("c3", 32, 10_000_000, 100), ("664", 5, 4_000_000, 100), ("664", 32, 10_000_000, 100), ("664x2", 9, 4_000_000, 100),
+           ("odd64", 13, 4_000_000, 100), ("mixed128", 64, 1_000_000, 100), ("32x4", 8, 10_000_000, 500)]
+    no = [("16x4", 4, 10_000_000, 100), ("16x4", 8, 10_000_000, 1000), ("16x4", 32, 100_000, 10), ("32x4", 8, 10_000_000, 1000),
+          ("c3", 64, 2_000_000, 64), ("c3", 32, 800_000, 1), ("c3", 64, 8_000_000, 1000), ("664", 5, 4_000_000, 1),
+          ("664", 8, 10_000_000, 500), ("664x2", 8, 4_000_000, 100), ("odd64", 8, 4_000_000, 100), ("5x8", 64, 4_000_000, 1),
+          ("mixed128", 100, 4_000_000, 100), ("mixed128", 16, 1_000_000, 100), ("16x4u16", 8, 4_000_000, 500)]
+    for name, nq, n, R in yes:
+        assert qb.pq_search_form(idx[name], nq, n, R) == qb.PQ_SCAN_MATRIX, (name, nq, n, R)
+    for name, nq, n, R in no:
+        assert qb.pq_search_form(idx[name], nq, n, R) == qb.PQ_SCAN_LOOKUP, (name, nq, n, R)
 
 
 @pytest.mark.parametrize("n", [16_384, 16_895, 16_896, 16_897, 2048 * 32 - 1, 2048 * 32 + 513])
@@ -85,22 +141,26 @@ def test_small_blocks_and_large_chunks():
     _check(lay, cb, codes, queries[:6], idx, 1, sample=0)  # (groups of more than 64 codes: little workspace)
 
 
-@pytest.mark.parametrize("name,n,R", [("16x4", 100_000, 100), ("c3", 262_144, 32)])
+@pytest.mark.parametrize("name,n,nq,R", [("16x4", 100_000, 130, 100), ("c3", 262_144, 130, 32), ("16x4", 200_001, 40, 100),
+                                         ("664", 262_144, 100, 32), ("c3", 1_600_001, 16, 100)])
 @pytest.mark.parametrize("distinct", [1, 7, 300])
-def test_equal_codes(name, n, R, distinct):
+def test_equal_codes(name, n, nq, R, distinct):
     """crowds of equal keys: list overflow, segments, exact selection"""
-    lay, cb, codes, queries, idx = _make(name, n, 130, 11)
+    lay, cb, codes, queries, idx = _make(name, n, nq, 11)
+    assert nq == 130 or _matrix(idx, nq, n, R)
     g = torch.Generator().manual_seed(4)
     codes = codes[torch.randint(0, distinct, (n,), generator=g)].contiguous()
     _check(lay, cb, codes, queries, idx, R, sample=1)
 
 
-def test_integer_data_and_calibration_at_the_end():
+@pytest.mark.parametrize("n", [110_000, 220_000])
+def test_integer_data_and_calibration_at_the_end(n):
     """integer tables (many ties); the first codes the best ones (everything else saturates) and the worst ones"""
-    lay, cb, codes, queries, idx = _make("16x4", 110_000, 40, 12, "gamma_ints", 128)
+    lay, cb, codes, queries, idx = _make("16x4", n, 40, 12, "gamma_ints", 128)
+    assert n == 110_000 or _matrix(idx, 40, n, 100)
     _check(lay, cb, codes, queries, idx, 100)
     ids = qb.pq_search_topk(idx, queries[:1].cuda(), codes.cuda(), 400, 2000)[0][0].cpu().long()
-    rest = torch.ones(110_000, dtype=torch.bool)
+    rest = torch.ones(n, dtype=torch.bool)
     rest[ids] = False
     best_first = torch.cat([codes[ids], codes[rest]])
     _check(lay, cb, best_first.contiguous(), queries, idx, 100, sample=1)
@@ -120,33 +180,37 @@ def test_saturated_result(nq, n, R):
     sub[300, 0] = 1
     codes, queries = synth.pack_codes(sub, lay), torch.zeros(nq, 16)
     idx = qb.PqIndex(16, lay.nbits, lay.dsub, cb.cuda(), 8)
+    assert _matrix(idx, nq, n, R)
     got = _check(lay, cb, codes, queries, idx, R, sample=1)
     if R == 1:
         assert got[0].eq(0).all() and got[1].cpu().numpy().min() == 255
 
 
-@pytest.mark.parametrize("name", ["c3", "664", "16x4u16"])
-def test_saturated_best_code(name):
+@pytest.mark.parametrize("name,n,nq", [("c3", 262_144, 97), ("664", 262_144, 97), ("16x4u16", 262_144, 97), ("c3", 1_600_003, 18)])
+def test_saturated_best_code(name, n, nq):
     """Queries far from all centroids, the best code of each among the calibration codes: fp32 sums against
     the fp64 sum of the entries leave it, for some of them, just above the top of the range, with all others."""
-    lay, cb, codes, queries, _ = _make(name, 262_144, 97, 21)
+    lay, cb, codes, queries, _ = _make(name, n, nq, 21)
     queries = queries + 150.0
     o = dims = 0
-    best = torch.zeros(97, codes.shape[0])
+    best = torch.zeros(nq, codes.shape[0])
     sub = oracle.unpack(lay.nbits, codes.numpy())
     for j, (k, s) in enumerate(zip(lay.ksub, lay.dsub)):
         c = cb[o:o + k * s].reshape(k, s).double()
         t = (queries[:, None, dims:dims + s].double() - c[None]).square().sum(2)
         best += t[:, torch.from_numpy(sub[:, j].astype(np.int64))].float()
         o, dims = o + k * s, dims + s
-    codes[300:397] = codes[best.argmin(1)].clone()
+    codes[300:300 + nq] = codes[best.argmin(1)].clone()
     idx = qb.PqIndex(lay.d, lay.nbits, lay.dsub, cb.cuda(), lay.acc_bits)
+    assert (name == "c3" and n == 262_144) or _matrix(idx, nq, n, 1)
     _check(lay, cb, codes, queries, idx, 1)
 
 
-def test_stage_calls_and_bounds():
+@pytest.mark.parametrize("n", [90_000, 210_000])
+def test_stage_calls_and_bounds(n):
     """the scan call with the quantizer's bound, an unknown one, and one below which few codes lie"""
-    lay, cb, codes, queries, idx = _make("16x4", 90_000, 40, 13)
+    lay, cb, codes, queries, idx = _make("16x4", n, 40, 13)
+    assert n == 90_000 or _matrix(idx, 40, n, 50)
     c, z = codes.cuda(), queries.cuda()
     tables = qb.pq_compute_tables(idx, z)
     qt, qp = qb.pq_quantize_tables(idx, tables, c, 400, 50)
@@ -169,6 +233,7 @@ def test_option_set_by_another_thread():
     that it then runs"""
     lay, cb, codes, queries, idx = _make("16x4", 400_000, 9, 14)
     c, z = codes.cuda(), queries.cuda()
+    assert _matrix(idx, 9, 400_000, 20)
     want = qb.pq_search_topk(idx, z, c, 400, 20)
     done = threading.Event()
 
