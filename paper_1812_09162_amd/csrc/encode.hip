@@ -11,13 +11,15 @@
 // codebooks of up to 16 KB are read from memory with scalar loads (they stay in the scalar cache), larger
 // ones are staged in LDS when they fit (one word broadcast to 64 lanes).  A second step packs.
 //
-// Bound by the vector units: eq. (1) term by term is three operations per dimension and centroid.  In
-// sub-spaces of up to 8 dimensions the nearest centroid is found from ||x||^2 + ||c||^2 - 2 x.c, one fused
+// Bound by the vector units: eq. (1) term by term is three operations per dimension and centroid.  Where
+// it pays (enc_form) the nearest centroid of a sub-space of up to 8 dimensions is found from ||x||^2 + ||c||^2 - 2 x.c, one fused
 // multiply-add per dimension; the distances of eq. (1) themselves are computed only in waves that hold a
 // vector whose two smallest values are closer than the rounding of both forms can account for, and then
 // decide.  The norms are taken once per block, which runs over many tiles; tiles are staged with 16-byte
 // loads and without a division per value.  10^7 vectors, d = 96, 16 x 4 bits: 1.23 ms (2.12 term by
 // term; 1.37 without the next tile requested ahead).
+#include <type_traits>
+
 #include "qadc_device.h"
 
 #define ENC_VB 64  // vectors per tile
@@ -93,6 +95,7 @@ __device__ __forceinline__ int enc_nearest_fast(const float *xv, const float *c,
     return besti;
 }
 
+template <bool FAST, bool AHEAD>
 __global__ void __launch_bounds__(256)
 k_encode(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc, const float *__restrict__ cb,
          const float *__restrict__ x, int64_t n, const float *__restrict__ shift_rows,
@@ -101,45 +104,46 @@ k_encode(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc, c
     extern __shared__ __align__(16) unsigned char smem[];
     const int d = L->d, m = L->m, cs = L->cs, T = L->T;
     const int ldx = d | 1;  // odd row stride: lanes of a wave (consecutive vectors) hit distinct banks
-    // squared norms [T], and the largest norm per sub-quantizer (bits) [m];
-    // nothing where there is no room for them (nrm_words == 0)
+    // FAST: squared norms [T], and the largest norm per sub-quantizer (bits) [m]
     float *nrm = (float *)smem;
     uint32_t *nmax = (uint32_t *)nrm + ((T + 3) & ~3);
     float *xs = nrm + nrm_words;                           // [ENC_VB][ldx]
     float *cbs = xs + (size_t)ENC_VB * ldx;                // [cb_floats] (0 if they do not fit)
     uint8_t *sub = (uint8_t *)(cbs + cb_floats);           // [ENC_VB][m]
-    if (nrm_words)
+    if constexpr (FAST)
         for (int i = threadIdx.x; i < m; i += 256) nmax[i] = 0;
     for (int e = threadIdx.x; e < cb_floats; e += 256) cbs[e] = cb[e];
-    __syncthreads();
-    for (int e = threadIdx.x; nrm_words && e < T; e += 256) {
-        const EntryDesc ed = edesc[e];
-        const float *c = cb + ed.cb_off;
-        float s = 0.0f;
-        for (int l = 0; l < ed.ds; ++l) s = __fmaf_rn(c[l], c[l], s);
-        atomicMax(&nmax[ed.j], __float_as_uint(s));
-        nrm[e] = s;
+    if constexpr (FAST) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < T; e += 256) {
+            const EntryDesc ed = edesc[e];
+            const float *c = cb + ed.cb_off;
+            float s = 0.0f;
+            for (int l = 0; l < ed.ds; ++l) s = __fmaf_rn(c[l], c[l], s);
+            atomicMax(&nmax[ed.j], __float_as_uint(s));
+            nrm[e] = s;
+        }
     }
     // this thread's first 16-byte piece of a tile: vector sv, piece sl of its d4; the next is 256 further on
     const int d4 = vec ? d >> 2 : 1, dv = 256 / d4, dl = 256 - dv * d4;
     const int sv = (int)threadIdx.x / d4, sl = (int)threadIdx.x - sv * d4;
-    enc_f4 nx[ENC_PF];
+    enc_f4 nx[AHEAD ? ENC_PF : 1];
     auto request = [&](int64_t t) {  // (pieces past the end: the last one again)
         const int64_t left = n - t * ENC_VB;
         const int last = (int)(left < ENC_VB ? left : ENC_VB) * d4 - 1;
         const enc_f4 *src = (const enc_f4 *)(x + (size_t)t * ENC_VB * d);
 #pragma unroll
-        for (int i = 0; i < ENC_PF; ++i) {
+        for (int i = 0; i < (AHEAD ? ENC_PF : 1); ++i) {
             const int e = i * 256 + (int)threadIdx.x;
             nx[i] = __builtin_nontemporal_load(src + (e < last ? e : last));
         }
     };
-    if (vec && d <= 4 * 4 * ENC_PF) request(blockIdx.x);
+    if constexpr (AHEAD) request(blockIdx.x);
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int64_t v0 = tile * ENC_VB;
         const int nv = n - v0 < ENC_VB ? (int)(n - v0) : ENC_VB;
         __syncthreads();  // the previous tile has been packed
-        if (vec && d <= 4 * 4 * ENC_PF) {
+        if constexpr (AHEAD) {
             // the tile is in registers already; the next one is requested before this one is encoded
             int v = sv, l4 = sl;
 #pragma unroll
@@ -206,20 +210,28 @@ k_encode(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc, c
                 const float *c = c0 + L->cboff[j];
                 const float *xv = xs + (v < nv ? v : 0) * ldx + L->dimoff[j];
                 const float *nj = nrm + L->toff[j];
-                const float mx = nrm_words ? __uint_as_float(__builtin_amdgcn_readfirstlane(nmax[j])) : 0.0f;
+                const float mx = FAST ? __uint_as_float(__builtin_amdgcn_readfirstlane(nmax[j])) : 0.0f;
                 float best = INFINITY;
                 int besti = 0;
                 // (four centroids at a time: tables that begin on a multiple of four entries)
-                const bool fast = nrm_words != 0 && (L->toff[j] & 3) == 0 && nb >= 2;
-                switch (fast ? ds : 0) {  // uniform over the wave; widths up to 8 are unrolled without predicates
-                    case 1: besti = enc_nearest_fast<1>(xv, c, nj, mx, nb); break;
-                    case 2: besti = enc_nearest_fast<2>(xv, c, nj, mx, nb); break;
-                    case 3: besti = enc_nearest_fast<3>(xv, c, nj, mx, nb); break;
-                    case 4: besti = enc_nearest_fast<4>(xv, c, nj, mx, nb); break;
-                    case 5: besti = enc_nearest_fast<5>(xv, c, nj, mx, nb); break;
-                    case 6: besti = enc_nearest_fast<6>(xv, c, nj, mx, nb); break;
-                    case 7: besti = enc_nearest_fast<7>(xv, c, nj, mx, nb); break;
-                    case 8: besti = enc_nearest_fast<8>(xv, c, nj, mx, nb); break;
+                const bool fast = FAST && (L->toff[j] & 3) == 0 && nb >= 2;
+                auto nearest = [&](auto width) {
+                    constexpr int DS = decltype(width)::value;
+                    if constexpr (FAST) {
+                        besti = enc_nearest_fast<DS>(xv, c, nj, mx, nb);
+                    } else {
+                        enc_nearest<DS>(xv, c, 1 << nb, best, besti);
+                    }
+                };
+                switch (!FAST || fast ? ds : 0) {  // uniform over the wave; widths up to 8 are unrolled without predicates
+                    case 1: nearest(std::integral_constant<int, 1>()); break;
+                    case 2: nearest(std::integral_constant<int, 2>()); break;
+                    case 3: nearest(std::integral_constant<int, 3>()); break;
+                    case 4: nearest(std::integral_constant<int, 4>()); break;
+                    case 5: nearest(std::integral_constant<int, 5>()); break;
+                    case 6: nearest(std::integral_constant<int, 6>()); break;
+                    case 7: nearest(std::integral_constant<int, 7>()); break;
+                    case 8: nearest(std::integral_constant<int, 8>()); break;
                     default:
                         for (int i = 0; i < (1 << nb); ++i) {
                             float acc = 0.0f;
@@ -267,6 +279,44 @@ k_encode(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc, c
     }
 }
 
+// Which form a call takes: FAST = the expanded form (its norms are taken once per block, of up to 4096 that
+// run over the tiles); AHEAD = a tile requested while the one before is encoded (32 registers, which halve the
+// wavefronts of a SIMD to four).  Without both every tile has a block of its own.  Times in us, of 10^6
+// vectors unless said, FAST + AHEAD / AHEAD / neither:
+//   16 x 4 bits, d = 96: 129 / 132 / 140 (232 with loads of one value each); d = 128: 148 / 159 / 209
+//   {6,6,4} x 8, d = 128: 915 / 1009 / 1130; 2 * 10^5 vectors: 238 / 241 / 241
+//   16 x 8 bits, d = 128: 2000 / 2177 / 3190; d = 96: 1759 / 1742 / 1464
+//   8 x 8 bits (sub-spaces of 12 and 16 dimensions), d = 96: 5041 / 5230 / 4099; d = 128: 8273 / 6818 / 6441
+//   {6,5,5,6,5,5,4,4}, d = 96: 1016 / 1057 / 778; d = 128: 2640 / 1915 / 1955
+//   64 x 4 bits, d = 96: 1268 / 1230 / 1055
+struct EncForm {
+    bool fast, ahead;
+};
+static EncForm enc_form(const DevLayout &h, int64_t tiles, size_t lds, size_t norms, bool vec) {
+    EncForm f;
+    int64_t cb = 0;
+    bool narrow = true;  // all sub-spaces within what the expanded form is unrolled for
+    for (int j = 0; j < h.m; ++j) {
+        cb += ((int64_t)1 << h.nbits[j]) * h.dsub[j];
+        narrow = narrow && h.dsub[j] <= 8;
+    }
+    const int64_t most = 160 * 1024, per_cu = most / (int64_t)lds, with_norms = most / (int64_t)(lds + norms);
+    // The expanded form: wide sub-spaces (it saves one operation in three per dimension and adds some per
+    // centroid) of 16 centroids and more; enough tiles per block to pay for the norms, or so few that the
+    // latency of a block counts; and norms that do not cost a CU too many of its blocks.
+    if (!narrow || h.T < 16 * h.m || with_norms < 1)
+        f.fast = false;
+    else if (tiles <= 256)
+        f.fast = cb >= 5 * (int64_t)h.T;
+    else
+        f.fast = tiles >= 3 * (int64_t)h.T &&
+                 (with_norms == per_cu ? cb >= 4 * (int64_t)h.T : 4 * with_norms >= 3 * per_cu && cb >= 6 * (int64_t)h.T);
+    // The tile ahead: its registers cost nothing where LDS allows no more than four blocks of a CU.  (Sub-spaces
+    // of two dimensions have too little to do per tile: 64 x 4 bits, d = 128, 1000 vectors 73 us, 69 without.)
+    f.ahead = vec && h.d <= 4 * 4 * ENC_PF && (f.fast || (per_cu <= 4 && cb >= 3 * (int64_t)h.T));
+    return f;
+}
+
 extern "C" int pq_encode(const pq_index_t *idx, const float *vectors, int64_t n,
                          const float *shift_rows, const int32_t *shift_ids, uint8_t *codes,
                          void *stream) {
@@ -287,29 +337,36 @@ extern "C" int pq_encode(const pq_index_t *idx, const float *vectors, int64_t n,
     // small codebooks are read through the scalar cache instead (faster than LDS reads)
     if (cbf * sizeof(float) <= 16 * 1024) cbf = 0;
     size_t lds = base_lds + cbf * sizeof(float);
-    // norms, where they leave at least two blocks per CU (or fit at all, for dimensions that do not)
-    size_t nrm_words = (size_t)((h.T + 3) & ~3) + (size_t)((h.m + 3) & ~3);
-    if (lds + nrm_words * sizeof(float) > (lds > 80 * 1024 ? 160 : 80) * 1024) nrm_words = 0;
-    lds += nrm_words * sizeof(float);
-    if (lds > 160 * 1024) {
-        qadc_set_error("pq_encode: d=%d needs %zu bytes of LDS per block, more than 163840", h.d, lds);
-        return PQ_EINVAL;
-    }
-    if (lds > 48 * 1024)
-        QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_encode, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)lds));
     const int64_t blocks = (n + ENC_VB - 1) / ENC_VB;
     if (blocks > 0x7fffffffLL) {
         qadc_set_error("pq_encode: n=%lld too large for one call", (long long)n);
         return PQ_EINVAL;
     }
-    // several tiles per block (the norms are taken once), as many blocks as keep every CU full
-    const int64_t most = 256 * 16;
     const int vec = h.d % 4 == 0 && (((uintptr_t)vectors | (uintptr_t)shift_rows) & 15u) == 0;
+    size_t nrm_words = (size_t)((h.T + 3) & ~3) + (size_t)((h.m + 3) & ~3);
+    const EncForm f = enc_form(h, blocks, lds, nrm_words * sizeof(float), vec != 0);
+    if (!f.fast) nrm_words = 0;
+    lds += nrm_words * sizeof(float);
+    if (lds > 160 * 1024) {
+        qadc_set_error("pq_encode: d=%d needs %zu bytes of LDS per block, more than 163840", h.d, lds);
+        return PQ_EINVAL;
+    }
     const int nib = (h.kind == SCAN_NIB8 || h.kind == SCAN_NIB16) && ((uintptr_t)codes & 3u) == 0;
-    hipLaunchKernelGGL(k_encode, dim3((unsigned)(blocks < most ? blocks : most)), dim3(256), lds, (hipStream_t)stream,
-                       idx->dev, idx->edesc, idx->codebooks, vectors, n, shift_rows, shift_ids, codes, (int)cbf,
-                       (int)nrm_words, blocks, vec, nib);
+    const int64_t grid = f.fast || f.ahead ? (blocks < 256 * 16 ? blocks : 256 * 16) : blocks;
+#define ENC_GO(FAST, AHEAD)                                                                                       \
+    do {                                                                                                          \
+        if (lds > 48 * 1024)                                                                                      \
+            QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_encode<FAST, AHEAD>,                                 \
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));              \
+        hipLaunchKernelGGL((k_encode<FAST, AHEAD>), dim3((unsigned)grid), dim3(256), lds, (hipStream_t)stream,    \
+                           idx->dev, idx->edesc, idx->codebooks, vectors, n, shift_rows, shift_ids, codes, (int)cbf, \
+                           (int)nrm_words, blocks, vec, nib);                                                     \
+    } while (0)
+    if (f.fast && f.ahead) ENC_GO(true, true);
+    else if (f.fast) ENC_GO(true, false);
+    else if (f.ahead) ENC_GO(false, true);
+    else ENC_GO(false, false);
+#undef ENC_GO
     QADC_LAUNCH_CHECK("k_encode");
     return PQ_OK;
 }

@@ -146,3 +146,46 @@ def test_encode_near_ties(qb, d, nbits, scale):
     qb.pq_encode(idx, flat[1:].view(x.shape), codes=got)
     assert np.array_equal(got.cpu().numpy(), want)
     idx.close()
+
+
+@pytest.mark.parametrize("d,nbits,n", [
+    # the expanded form, which long lists take (256 vectors per table entry) ...
+    (96, [4] * 16, 65_536 + 1), (96, [4] * 16, 262_144 + 129), (128, [4] * 16, 262_144 + 65), (128, [6, 6, 4] * 8, 300_001),
+    (36, [4] * 6, 30_000), (20, [4] * 4, 20_001), (28, [5] * 4, 40_000), (132, [4] * 32, 262_144 + 65),
+    # ... and short ones with eight dimensions
+    (128, [4] * 16, 600), (16, [5] * 2, 63),
+    # term by term, tiles requested ahead (d = 128) and not
+    (128, [8] * 8, 262_144 + 65), (96, [8] * 8, 262_144 + 65), (128, [4] * 32, 262_144 + 1),
+])
+@pytest.mark.parametrize("shift", [False, True])
+def test_encode_forms_and_second_tiles(qb, d, nbits, n, shift):
+    """Near ties as above in every form of the kernel, in lists long enough that a block encodes a second
+    and a third tile (4096 blocks of 64 vectors), the last one partly filled."""
+    lay = synth.make_layout(d, nbits, 16)
+    rng = np.random.default_rng(n)
+    parts, mids = [], []
+    for b, s in zip(lay.nbits, lay.dsub):
+        c = rng.normal(size=(1 << b, s)).astype(np.float32)
+        c[-1] = c[0]
+        parts.append(c)
+        a, o = rng.integers(0, 1 << b, 601), rng.integers(0, 1 << b, 601)
+        mids.append(((c[a].astype(np.float64) + c[o]) / 2).astype(np.float32))
+    x = np.concatenate(mids, axis=1)
+    x[300:] = np.nextafter(x[300:], np.float32(np.inf))
+    x[450:] = rng.normal(size=x[450:].shape)
+    cb = np.concatenate([p.reshape(-1) for p in parts])
+    rows = rng.integers(-4, 5, size=(7, d)).astype(np.float32)
+    ids = rng.integers(0, 7, size=601).astype(np.int32)
+    if shift:
+        x = x + rows[ids]
+    want = oracle.encode(d, lay.nbits, lay.dsub, cb, x, rows[ids] if shift else None)
+    pick = torch.arange(n, device=dev()) % 601
+    idx = qb.PqIndex(lay.d, lay.nbits, lay.dsub, torch.from_numpy(cb).to(dev()), 16)
+    xs = torch.from_numpy(x).to(dev())[pick].contiguous()
+    sh = (torch.from_numpy(rows).to(dev()), torch.from_numpy(ids).to(dev())[pick].contiguous()) if shift else (None, None)
+    want = torch.from_numpy(want).to(dev())[pick]
+    assert torch.equal(qb.pq_encode(idx, xs, *sh), want)
+    flat = torch.empty(xs.numel() + 1, device=dev())  # an address that allows no wide loads
+    flat[1:] = xs.view(-1)
+    assert torch.equal(qb.pq_encode(idx, flat[1:].view(n, d), *sh), want)
+    idx.close()
