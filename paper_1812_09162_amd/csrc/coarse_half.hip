@@ -517,11 +517,6 @@ k_cpick(const float *__restrict__ queries, const float *__restrict__ centroids, 
 #define CH_TILES 32   // tiles of 32 cells per k_cscan block and candidate list
 #define CH_CAP 16     // entries (16 cells each) per list
 #define CH_MAX_S 18   // steps of 16 columns: d <= CH_MAX_D and four more
-// Queries from which it wins, 65,536 cells, d = 96 / 128: 64 queries 73 us against 83 (85 against 92),
-// 1000 queries 97 against 206, 4000 queries 213 against 635; below, the conversion of the cells is what
-// a call costs.
-#define CH_MIN_NQ 64
-
 static int ch_steps(int d) { return d + 4 <= 7 * 16 ? 7 : (d + 4 <= 9 * 16 ? 9 : CH_MAX_S); }
 
 static int64_t ch_pilot_most(int K) { return (K / 4 < 65536 ? K / 4 : 65536) & ~2047; }
@@ -554,18 +549,42 @@ static void ch_layout(CoarseHalf &p, int nq, int qc, int K, size_t matrix_bytes)
     p.total = at;
 }
 
-static bool ch_sizes(int nq, int K) { return nq >= CH_MIN_NQ && K >= 16384 && K <= (1 << 20); }
+// When it wins over the fp32 forms; figures in us, those / this one.  It costs the conversion of all cells,
+// which a batch has to pay for, and its steps are made for 108, 140 and 252 dimensions, whatever d is:
+// `fill` of 100 columns are used.  The fp32 products take tiles of 128 queries, one or many.
+//   up to 128 queries     d = 96, nprobe 20: 16,384 cells 63 / 54, 32,768: 64 / 58; nprobe 64: 65,536 cells 72 / 76,
+//                         262,144: 137 / 156
+//   129 .. 256            65,536 cells, nprobe 64, 160 queries: d = 96 84 / 76, d = 64 69 / 71, d = 144 117 / 114
+//   from 257 on           65,536 cells, 512 queries: d = 64 101 / 74, d = 144 175 / 119, d = 32 77 / 66, but with 32,768
+//                         cells and d = 32 no gain (1.01); 1000 queries 117 / 78
+// Few dimensions over many cells: the error bound takes in so many cells that the lists overflow and the
+// exact form follows (byte-range data, d = 16, 10^6 cells: 12 times the time of the fp32 form).
+static bool ch_sizes(int nq, int K) {
+    return nq >= 64 && K >= 16384 && K <= (nq <= 128 ? 32768 : (1 << 20));
+}
+static bool ch_pays(int nq, int K, int d) {
+    const int fill = 100 * d / (16 * ch_steps(d));
+    if (!ch_sizes(nq, K)) return false;
+    if (nq <= 256) return fill >= 65;
+    return fill >= 40 || (d >= 16 && nq >= 1000 && K <= 131072);
+}
 
 CoarseHalf qadc_coarse_half_plan(int nq, int qc, int K, int d, int nprobe, size_t matrix_bytes, size_t room) {
     CoarseHalf p = {};
-    if (qadc_option(PQ_OPT_COARSE_FILTER) == 0 || !ch_sizes(nq, K) || d > CH_MAX_D) return p;
+    if (qadc_option(PQ_OPT_COARSE_FILTER) == 0 || d > CH_MAX_D || !ch_pays(nq, K, d)) return p;
     // The pilot: 256 cells per result, at most a quarter of all.  Fewer than 192 per result and the lists
     // (16 entries, about 512 nprobe / P of them used on average) overflow now and then, which costs the
     // pass the exact form: 16,384 cells, nprobe 64 (P = 4096), 4000 queries: 459 us, exact form at once 260.
+    // Over all cells about nprobe K / P lie within its bound; k_cpick holds 2048, so the pilot grows with K,
+    // for a quarter of that, or five eighths where it cannot (262,144 cells, nprobe 300, 1000 queries: 301 us, fp32
+    // 704; 10^6 cells, nprobe 64, 1000 queries: P = 16,384 left
+    // 3900, and every pass went to the exact form as well: 5970 us, fp32 2620, with P = 65,536 1140).
     int64_t P = 256 * (int64_t)nprobe > 16384 ? 256 * (int64_t)nprobe : 16384;
+    const int64_t near = nprobe * (int64_t)K;
+    if (P * (CH_PICK / 4) < near) P = (near / (CH_PICK / 4) + 2047) & ~(int64_t)2047;
     if (P > ch_pilot_most(K)) P = ch_pilot_most(K);
     P &= ~(int64_t)2047;
-    if (P < 192 * (int64_t)nprobe) return p;
+    if (P < 192 * (int64_t)nprobe || P * (CH_PICK / 8 * 5) < near) return p;
     p.S = ch_steps(d);
     p.P = (int)P;
     p.ntiles = (K + 31) / 32;

@@ -110,5 +110,17 @@ def test_coarse_workspace_keeps_within_what_the_matrix_form_needs(nq, K):
     # 96 and 128 dimensions over 65,536 cells, long batches: also with the smaller workspace
     if nq >= 1000 and K == 65_536:
         assert least == asked
-    for nq2 in (64, 1000, 10_000):
+    for nq2 in (129, 1000, 10_000):
         assert qb.ivf_coarse_form(nq2, 65_536, 96, 64, _coarse_bytes_without_half_form(nq2, 65_536)) == qb.PQ_COARSE_HALF
+
+
+def test_which_coarse_form():
+    """The lines between the forms: nq, K, d, nprobe."""
+    H, F, M, D = qb.PQ_COARSE_HALF, qb.PQ_COARSE_FILTER, qb.PQ_COARSE_MATRIX, qb.PQ_COARSE_DIRECT
+    for call, form in (((1, 65_536, 96, 64), D), ((16, 300, 97, 300), D), ((17, 65_536, 96, 64), F), ((63, 16_384, 96, 20), F),
+                       ((64, 16_384, 96, 20), H), ((64, 16_384, 96, 22), F), ((128, 32_768, 96, 32), H), ((128, 32_769, 96, 32), F),
+                       ((129, 65_536, 96, 64), H), ((200, 65_536, 64, 64), F), ((256, 65_536, 144, 64), F), ((257, 65_536, 144, 64), H),
+                       ((257, 65_536, 64, 64), H), ((999, 65_536, 32, 64), F), ((1000, 65_536, 32, 64), H), ((1000, 200_000, 32, 64), F),
+                       ((1000, 65_536, 15, 64), F), ((1000, 1_000_000, 96, 64), H), ((1000, 1_000_000, 96, 84), F), ((1000, 262_144, 96, 300), H),
+                       ((1000, 16_384, 96, 64), F), ((1000, 16_000, 96, 1), M), ((1000, 65_536, 257, 64), F), ((1000, 300, 96, 64), M)):
+        assert qb.ivf_coarse_form(*call) == form, call

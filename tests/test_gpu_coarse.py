@@ -104,6 +104,7 @@ def test_coarse_search_full_k_sampled(qb):
 @pytest.mark.parametrize("K,d,nq,nprobe,seed", [
     (20_000, 96, 70, 64, 31), (16_511, 40, 130, 1, 32), (30_001, 128, 9, 20, 33), (17_000, 17, 257, 64, 34),
     (70_001, 24, 33, 64, 35), (60_000, 16, 20, 200, 36),   # the 1024-thread candidate selection
+    (30_001, 128, 19, 20, 37),
 ])
 def test_coarse_search_filtering_form_bit_exact(qb, K, d, nq, nprobe, seed):
     """K large enough for the form that never writes the score matrix (pilot bound, candidate
@@ -111,6 +112,7 @@ def test_coarse_search_filtering_form_bit_exact(qb, K, d, nq, nprobe, seed):
     rng = np.random.default_rng(seed)
     cen = rng.normal(size=(K, d)).astype(np.float32)
     qs = rng.normal(size=(nq, d)).astype(np.float32)
+    assert qb.ivf_coarse_form(nq, K, d, nprobe) == (qb.PQ_COARSE_DIRECT if nq <= 16 else qb.PQ_COARSE_FILTER)
     check(qb, cen, qs, nprobe, nq_oracle=min(nq, 24))
 
 
@@ -126,8 +128,15 @@ def test_coarse_search_filtering_form_overflow_falls_back(qb):
     ids = check(qb, cen, qs, 64)
     assert set(range(12_800, 12_840)) <= set(ids[0].tolist())
     same = np.ones((18_000, 8), np.float32)
+    for nq, form in ((3, qb.PQ_COARSE_DIRECT), (40, qb.PQ_COARSE_FILTER)):
+        assert qb.ivf_coarse_form(nq, 18_000, 8, 60) == form
+        ids = check(qb, same, np.zeros((nq, 8), np.float32), 60)
+        assert ids[2].tolist() == list(range(60))
     ids = check(qb, same, np.zeros((3, 8), np.float32), 100)
     assert ids[2].tolist() == list(range(100))
+    assert qb.ivf_coarse_form(70, 18_000, 96, 20) == qb.PQ_COARSE_HALF
+    ids = check(qb, np.ones((18_000, 96), np.float32), np.ones((70, 96), np.float32), 20)
+    assert ids[69].tolist() == list(range(20))
 
 
 @pytest.mark.parametrize("K,d,nq,nprobe,seed,unit", [

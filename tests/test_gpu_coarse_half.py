@@ -40,7 +40,9 @@ def _same(got, want):
     assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
 
 
-def _check(z, c, nprobe):
+def _check(z, c, nprobe, half=False):
+    if half:
+        assert qb.ivf_coarse_form(z.shape[0], c.shape[0], c.shape[1], nprobe) == qb.PQ_COARSE_HALF
     _same(qb.ivf_coarse_search(z, c, nprobe), _matrix(z, c, nprobe))
 
 
@@ -56,7 +58,7 @@ def test_products_outside_the_normal_range(zs, cs):
     """Products that underflow leave the definition's chain with few distinct scores (ties: the lowest ids);
     products that overflow leave scores of -inf."""
     z, c = _data("gauss", 70, 96, 21) * zs, _data("gauss", 20_000, 96, 22) * cs
-    _check(z, c, 20)
+    _check(z, c, 20, half=True)
     ids, scores = qb.ivf_coarse_search(z, c, 20)
     for q in (0, 69):
         oi, osc = oracle.coarse_search(c.cpu().numpy(), z[q].cpu().numpy(), 20)
@@ -71,6 +73,40 @@ def test_dimensions(d):
 @pytest.mark.parametrize("nq,K,nprobe", [(4100, 65_536, 64), (600, 65_543, 256), (64, 131_072, 200)])
 def test_sizes(nq, K, nprobe):
     _check(_data("gauss", nq, 96, 9), _data("gauss", K, 96, 10), nprobe)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "gamma", "offset", "tiny", "huge", "ties", "spread"])
+@pytest.mark.parametrize("nq,K,d,nprobe", [(64, 16_384, 96, 20), (128, 20_011, 128, 21), (97, 32_768, 109, 1), (300, 70_001, 100, 80)])
+def test_kinds_of_data_in_half_precision(kind, nq, K, d, nprobe):
+    _check(_data(kind, nq, d, 5), _data(kind, K, d, 6), nprobe, half=True)
+
+
+@pytest.mark.parametrize("d,nq", [(16, 1000), (33, 1000), (48, 257), (96, 300), (108, 70), (109, 300), (110, 70), (125, 300),
+                                  (126, 70), (140, 300), (141, 300), (142, 300), (200, 70), (252, 300), (253, 70), (256, 300)])
+def test_dimensions_in_half_precision(d, nq):
+    """edges of the 7, 9 and 18 steps of 16 columns"""
+    _check(_data("gauss", nq, d, 7), _data("gauss", 17_000, d, 8), 20, half=True)
+
+
+@pytest.mark.parametrize("nq,K,nprobe", [(600, 65_543, 80), (300, 262_144, 300), (129, 131_072, 160), (200, 1_000_003, 60), (4097, 65_600, 1), (257, 16_384, 1)])
+def test_sizes_in_half_precision(nq, K, nprobe):
+    _check(_data("gauss", nq, 96, 9), _data("gauss", K, 96, 10), nprobe, half=True)
+
+
+def test_where_the_lists_or_the_range_do_not_suffice_in_half_precision():
+    """calls that the exact form has to take over, in whole or for one of several passes"""
+    z, c = _data("gauss", 80, 96, 11), _data("gauss", 20_000, 96, 12)
+    order = (c - z[0]).square().sum(1).argsort()
+    _check(z, c[order].contiguous(), 20, half=True)                      # the nearest cells of a query side by side
+    _check(z, c[order.flip(0)].contiguous(), 20, half=True)
+    _check(z, c[:50].repeat(400, 1).contiguous(), 20, half=True)         # every cell 400 times: more than a block picks from
+    _check(torch.cat([z[:70], z[70:] * 1e6]), c, 20, half=True)          # queries beyond the cells' range
+    _check(z * 0.0, c, 20, half=True)
+    _check(z, c * 0.0, 20, half=True)
+    few = c.clone()
+    few[1000:] = c[1000:1001]                                            # one cell 19,000 times, far from or near to a query
+    _check(z, few, 20, half=True)
+    _check(torch.cat([z[:70], few[1000:1001].repeat(10, 1)]), few, 20, half=True)
 
 
 def test_where_the_lists_or_the_range_do_not_suffice():
