@@ -486,10 +486,9 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
         if (pos < (uint32_t)ACAP) S.A[pos] = ((uint64_t)key << 32) | id; else S.sh[1] = 1u;
     };
     // 2. the codes within a margin above that minimum.  Every code whose unsaturated sum's level is within
-    //    `top` is in a group whose minimum is.  A key below q_max is that sum; a saturated code's sum of
-    //    levels can lie above the level of q_max where entries are scaled (sums of up to 255 are told apart, and
-    //    q_max has a level below that), so these are left out here, and if R codes are found without them the
-    //    result is among those.
+    //    `top` is in a group whose minimum is.  A key below q_max is that sum.  A saturated code's sum can be
+    //    larger than its key, and where entries are scaled so that q_max has a level below 255, its sum of levels
+    //    too: such codes are left out here, and if R are found without them the result is among those.
     const uint32_t most = mx_level(qmax, scale) < 255u ? qmax - 1u : qmax;  // the largest key that a minimum bounds
     const uint32_t top = min(b0 + (b0 >> 5) + (uint32_t)(scale == 65536u ? 1 : margin), 255u);
     uint32_t bound = min(min(last_key(top), most), prm.key_bound);

@@ -11,76 +11,80 @@ extern template int mx_launch<SCAN_W128, uint16_t>(MX_ARGS);
 
 // When the matrix cores win.  Look-ups take a time in proportion to codes times passes (of four queries);
 // here 32 queries are one product, but some 28 us go to launches and picking whatever the size, and the
-// picking of a query, by one block, grows with the results and with what a code costs to score again.  The
-// lines below are where, in 29,088 pairs of timings of both forms (16 layouts, 20,000 to 8 * 10^6 codes, 5
-// to 256 queries, R = 1 to 2000, two kinds of data), this form stops being the slower one.  Figures in us,
-// look-ups / here.
+// picking of a query, by one block, grows with the results and with what a code costs to score again; where
+// its keys leave many codes as near as the R-th, that block has most of the list to score again.  The lines
+// are where, in 29,088 pairs of timings of both forms (16 layouts, 20,000 to 8 * 10^6 codes, 5 to 256
+// queries, R = 1 to 2000, two kinds of data), this form stops being the slower one: of the 6560 that it takes
+// 74 are slower by 4 % or more.  Figures in us, look-ups / here; k = 1000 codes, M = 10^6.
 //
-// Up to one pass (four queries) the look-ups: 16 x 4 bits, 10^7 codes, 4 queries: 61 / 58, 5: 87 / 58.
-#define MX_MIN_NQ 5
-// m x 4 bits.  Codes times passes from 800,000 on (400,000 codes, 8 queries, R = 100: 39 / 34; 200,000: 30
-// and 34) and 1000 codes per result (400,000 codes, R = 500, 48 queries: 97 / 130).  Short lists with long
-// batches: 100,000 codes, 32 queries, R = 10: 33 / 47, and 256 queries 87 / 67; 32 x 4 bits, twice the
-// look-ups per code, from 50,000 codes on (100 queries, R = 1: 76 / 45).
+// Codes times passes, and codes per result.  m x 4 bits, R = 100, 8 queries: 400k 39 / 34, 200k 30 / 34; R = 500,
+// 48 queries, 400k: 97 / 130.  Irregular layouts, where a code is dearer to score again: {6,6,4} x 4, 64 queries,
+// R = 100: 400k 153 / 148, 800k 177 / 85; R = 250, 800k: 202 / 240.
 #define MX_MIN_CODES_NIB 800000
 #define MX_MIN_RATIO_NIB 1000
+#define MX_MIN_CODES 6000000
+#define MX_MIN_RATIO 8000
+// Short lists, m x 4 bits: 16 x 4, R = 10, 100k: 32 queries 33 / 47, 256 queries 87 / 67; 32 x 4 (twice the
+// look-ups), R = 1, 50k, 100 queries: 76 / 45.
 #define MX_MIN_LIST_8 200000
 #define MX_MIN_LIST_16 50000
 #define MX_LONG_NIB 6000000
-// Irregular layouts, where a code is dearer to score again: 6 * 10^6 ({6,6,4} x 4, R = 100, 64 queries:
-// 400,000 codes 153 / 148, 800,000 177 / 85) and 8000 codes per result ({6,6,4} x 4, 800,000 codes, R = 250, 64 queries: 202
-// and 240).
-#define MX_MIN_CODES 6000000
-#define MX_MIN_RATIO 8000
-// The single best code: the look-ups have no bound below the top of the range (40-bit codes, 3.2 * 10^6, 256
-// queries: 28 ms / 0.25) but in a short list one query in some dozens has most of it near its best code,
-// and its block all of it to score again ({6,5,5,6,5,5,4,4}, 800,000 codes, 32 queries: 0.10 ms / 2.5 ms).
-#define MX_MIN_LIST_ONE 1600000
-
-// 128-bit codes of other field patterns, R up to 100: 64 queries, 1.6 * 10^6 codes 475 / 324, 3.2 * 10^6 605 / 563;
-// 100 queries 599 / 545 and 802 / 896
+// Of 40-bit codes more are equal, and of many queries one has a crowd of them near its R-th: {6,5,5,6,5,5,4,4},
+// R = 500, 3.2M: 32 queries 187 / 127, 64 queries 231 / 709; R = 100, 800k: 110 / 57 and 136 / 191.
+#define MX_MANY_40 40
+// 128-bit codes of other field patterns (twice the products, one tile of queries per wave): R = 64, 64 queries,
+// 1.6M 475 / 324, 3.2M 605 / 563; 100 queries 599 / 545 and 802 / 896.
 #define MX_MOST_128 2000000
 
-// Passes that the look-ups must take at least.
-static int mx_min_passes(const DevLayout &h, int R) {
-    const bool wide = h.acc_bits != 8, w128 = h.kind == SCAN_NIB16 || h.kind == SCAN_W128;
-    // m x 4 bits: R = 1000, 8 * 10^6 codes, 8 queries 124 / 126, 12 queries 170 / 126; with 16-bit tables
-    // (32 x 4) 3.2 * 10^6 codes, R = 250, 8 queries 124 / 197, 16 queries 220 / 200
-    if (h.kind == SCAN_NIB8) return 2 + R / (wide ? 200 : 1000);
-    if (h.kind == SCAN_NIB16) return wide ? (R < 32 ? 2 : 3 + R / 100) : 2 + R / 1000;
-    // field patterns known at compile time: {6,6,4} x 4, 3.2 * 10^6 codes, 5 queries, R = 100: 100 / 78, R = 500
-    // 130 / 164; {6,5,5} x 8, R = 250: 200 / 314, 16 queries 397 / 319
-    if (h.mx_pat != 0) {
-        const int need = (w128 ? 3 : 2) + R / 200;
-        return R < 100 && need < 3 ? 3 : need;
+// Queries that it takes at least, with which the picking is worth the passes.
+static int mx_min_queries(const DevLayout &h, int R) {
+    const bool wide = h.acc_bits != 8, known = h.mx_pat != 0;
+    switch (h.kind) {
+        // m x 4 bits: 16 x 4, 10M, R = 100, 4 queries 61 / 58, 5: 87 / 58; R = 1000, 8M: 8 queries 124 / 126, 12: 170 / 126.
+        // 16-bit tables, 3.2M: 16 x 4, R = 500, 8 queries 79 / 93, 12: 104 / 94; 32 x 4, R = 250, 12: 173 / 199, 16: 220 / 200
+        case SCAN_NIB8: return wide ? (R < 32 ? 5 : 5 + R / 60) : 5 + 4 * (R / 1000);
+        case SCAN_NIB16: return wide ? (R < 32 ? 5 : 5 + R / 30) : 5 + 4 * (R / 1000);
+        // {6,6,4} x 4 (a known pattern), 3.2M: R = 500, 8 queries 143 / 165, 12: 203 / 168; R = 1, 8M, 8 queries 117 / 136.  Other
+        // patterns, one tile of queries per wave: 3.2M, R = 100, 8 queries 91 / 116, 12: 123 / 117
+        case SCAN_W64:
+            if (known) return R == 1 ? 9 : (R <= 100 ? 5 : 5 + R / 70);
+            return R == 1 ? 16 : 12 + R / 100;
+        // {6,5,5} x 8, 3.2M, R = 250: 8 queries 216 / 315, 12: 316 / 317; other patterns, 1.6M, R = 64, 16 queries 282 / 208
+        case SCAN_W128: return known ? (R <= 100 ? 5 : 6 + R / 50) : 16 + R / 12;
+        // {5} x 8, 1.6M, R = 100: 5 queries 60 / 68, 8: 75 / 68
+        default: return known ? 5 + R / 150 : 8 + R / 250;
     }
-    // others, one tile of queries per wave: 3.2 * 10^6 codes, R = 100, 5 queries 69 / 115, 8: 91 / 116, 16: 160 / 117
-    // (128-bit codes, twice the products: see MX_MOST_128)
-    return (w128 ? 8 : 4) + R / 400;
+}
+
+// Codes of an irregular layout that a few results need.  The single best code: the look-ups have no bound
+// below the top of the range (40-bit codes, 3.2M, 256 queries: 28 ms / 0.25) but in a short list one query in
+// some dozens has most of it near its best code ({6,5,5,6,5,5,4,4}, 800k, 32 queries: 104 / 2500; {5} x 7, 1.6M:
+// 167 / 5100; {6,6,4} x 4 with 8-bit tables, 800k, 100 queries 207 / 2190).  Up to 99: R = 64, 1.6M codes of 40 bits: 32
+// queries 122 / 51, 64 queries 150 / 395; other patterns, 400k, R = 32, 60 queries: 143 / 167.
+static int64_t mx_min_list(const DevLayout &h, int nq, int R) {
+    const bool c5 = h.kind == SCAN_C5, known = h.mx_pat != 0;
+    if (R == 1) return c5 ? (known ? 1600000 : 3200000) : (h.acc_bits == 8 ? 1600000 : (known ? 0 : 800000));
+    if (R < 100 && c5 && known) return nq > MX_MANY_40 ? 6400000 : 1600000;
+    return R < 100 && !known ? 800000 : 0;
 }
 
 MxPlan qadc_mx_plan(const pq_index *idx, int nq, int64_t n, int R, const ScanPlan &sp) {
     MxPlan p;
     memset(&p, 0, sizeof(p));
     const DevLayout &h = idx->h;
-    if (h.mx_steps == 0 || nq < MX_MIN_NQ || qadc_option(PQ_OPT_SHARED_PASSES) == 0) return p;
-    const bool nib = h.kind == SCAN_NIB8 || h.kind == SCAN_NIB16;
+    if (h.mx_steps == 0 || nq < mx_min_queries(h, R) || qadc_option(PQ_OPT_SHARED_PASSES) == 0) return p;
     const int passes = (nq + 3) / 4;
-    if (passes < mx_min_passes(h, R)) return p;
-    if (nib) {
+    if (h.kind == SCAN_NIB8 || h.kind == SCAN_NIB16) {
         if (n * passes < MX_MIN_CODES_NIB || n < (int64_t)MX_MIN_RATIO_NIB * R) return p;
         if (n < (h.kind == SCAN_NIB8 ? MX_MIN_LIST_8 : MX_MIN_LIST_16) && n * passes < MX_LONG_NIB) return p;
     } else {
+        const bool many = h.kind == SCAN_C5 && nq > MX_MANY_40;
+        if (n * passes < MX_MIN_CODES || n < (int64_t)(many ? 2 * MX_MIN_RATIO : MX_MIN_RATIO) * R) return p;
         // A few results: the calibration ends the range of the keys close to the R-th, the levels are coarse
-        // there, and where distances are alike most groups hold a code within them (40-bit codes, 2.5 * 10^6,
-        // R = 10, 64 queries: 151 / 432, R = 100 165 / 78).  40-bit codes, of which more are equal, from R = 100
-        // on (1.6 * 10^6 codes, R = 64, 64 queries: 150 / 395) and with twice the codes per result (3.2 * 10^6,
-        // R = 500, 64 queries: 231 / 709).
-        const bool c5 = h.kind == SCAN_C5, plain = h.mx_pat != 0 && h.acc_bits == 16 && !c5;
-        if (n * passes < MX_MIN_CODES || n < (int64_t)(c5 ? 2 * MX_MIN_RATIO : MX_MIN_RATIO) * R) return p;
+        // there, and where distances are alike most groups hold a code within them (40-bit codes, 2.5M, R = 10,
+        // 64 queries: 151 / 432).
+        if ((R > 1 && R < 32) || n < mx_min_list(h, nq, R)) return p;
         if (h.kind == SCAN_W128 && h.mx_pat == 0 && (n > MX_MOST_128 || R > 100)) return p;
-        if (R > 1 && R < (c5 ? 100 : 32)) return p;
-        if (R == 1 && ((!plain && n < MX_MIN_LIST_ONE) || (c5 && h.mx_pat == 0))) return p;
     }
     const int tiles = (nq + 31) / 32;  // of 32 queries
     const int most = mx_most(h.kind, h.mx_pat != 0);

@@ -77,8 +77,8 @@ def test_batch_equals_single(name, n, nq, R):
 MATRIX_SIZES = {
     "16x4": (262_144, 97, 32), "16x4u16": (262_144, 97, 32), "32x4": (131_583, 225, 1), "c3": (1_600_001, 17, 100),
     "c3u8": (1_607_680, 16, 100), "5x8": (1_600_513, 18, 100), "664": (300_033, 84, 33), "655": (262_144, 97, 32),
-    "664u8": (300_033, 84, 33), "6to4": (262_144, 97, 32), "odd64": (400_000, 61, 50), "664x2": (131_583, 225, 1),
-    "655x2": (300_033, 84, 33), "mixed128": (300_033, 84, 33),
+    "664u8": (300_033, 84, 33), "6to4": (800_001, 33, 33), "odd64": (800_513, 61, 50), "664x2": (131_583, 225, 1),
+    "655x2": (300_033, 84, 33), "mixed128": (800_100, 40, 33),
 }
 
 
@@ -109,12 +109,14 @@ def test_which_form():
     """the lines the rule draws: what is taken, and what stays with the look-ups (or went back to them)"""
     idx = {name: _make(name, 64, 1, 1)[4] for name in LAYOUTS}
     yes = [("16x4", 5, 10_000_000, 100), ("16x4", 9, 10_000_000, 1000), ("16x4", 256, 100_000, 10), ("32x4", 100, 50_000, 1),
-           ("c3", 32, 10_000_000, 100), ("664", 5, 4_000_000, 100), ("664", 32, 10_000_000, 100), ("664x2", 9, 4_000_000, 100),
-           ("odd64", 13, 4_000_000, 100), ("mixed128", 64, 1_000_000, 100), ("32x4", 8, 10_000_000, 500)]
+           ("c3", 32, 10_000_000, 100), ("c3", 32, 1_000_000, 100), ("c3", 32, 1_600_000, 64), ("664", 5, 4_000_000, 100),
+           ("664", 32, 10_000_000, 100), ("664x2", 5, 4_000_000, 100), ("odd64", 13, 4_000_000, 100), ("5x8", 8, 4_000_000, 100),
+           ("mixed128", 24, 1_000_000, 100), ("32x4", 8, 10_000_000, 500), ("16x4u16", 13, 4_000_000, 500)]
     no = [("16x4", 4, 10_000_000, 100), ("16x4", 8, 10_000_000, 1000), ("16x4", 32, 100_000, 10), ("32x4", 8, 10_000_000, 1000),
-          ("c3", 64, 2_000_000, 64), ("c3", 32, 800_000, 1), ("c3", 64, 8_000_000, 1000), ("664", 5, 4_000_000, 1),
-          ("664", 8, 10_000_000, 500), ("664x2", 8, 4_000_000, 100), ("odd64", 8, 4_000_000, 100), ("5x8", 64, 4_000_000, 1),
-          ("mixed128", 100, 4_000_000, 100), ("mixed128", 16, 1_000_000, 100), ("16x4u16", 8, 4_000_000, 500)]
+          ("c3", 64, 2_000_000, 64), ("c3", 32, 800_000, 1), ("c3", 64, 8_000_000, 1000), ("c3", 64, 1_000_000, 100),
+          ("664", 5, 4_000_000, 1), ("664", 8, 10_000_000, 500), ("664u8", 100, 800_000, 1), ("655x2", 8, 4_000_000, 250),
+          ("odd64", 12, 4_000_000, 100), ("odd64", 60, 400_000, 32), ("5x8", 64, 1_600_000, 1), ("5x8", 7, 4_000_000, 100),
+          ("mixed128", 100, 4_000_000, 100), ("mixed128", 16, 1_000_000, 100), ("16x4u16", 8, 4_000_000, 500), ("664", 64, 4_000_000, 10)]
     for name, nq, n, R in yes:
         assert qb.pq_search_form(idx[name], nq, n, R) == qb.PQ_SCAN_MATRIX, (name, nq, n, R)
     for name, nq, n, R in no:
