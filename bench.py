@@ -27,6 +27,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
+MX_PEAK_TFLOPS = 10000.0  # published dense rate of its 4- and 6-bit matrix formats
 LLC_BYTES = 256 << 20   # last-level (Infinity) cache
 
 
@@ -247,6 +248,23 @@ def scan_kernel_time(qb, idx, queries, codes, batch, R, nsamples=8, reps=200, t=
     return total_ms / launches, launches
 
 
+def scan_call_time(qb, idx, queries, codes, batch, R, reps=20, t=400):
+    """Average duration (ms) of one pq_adc_scan_topk call, back to back on one stream."""
+    import torch
+    q = queries[:batch].contiguous()
+    qt, qp = qb.pq_quantize_tables(idx, qb.pq_compute_tables(idx, q), codes, t, R)
+    ws = torch.empty(qb.pq_workspace_bytes(idx, batch, codes.shape[0], R), dtype=torch.uint8, device=codes.device)
+    out = qb.pq_adc_scan_topk(idx, qt, qp, codes, R, workspace=ws)
+    torch.cuda.synchronize()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    for _ in range(reps):
+        qb.pq_adc_scan_topk(idx, qt, qp, codes, R, workspace=ws, out=out)
+    e1.record()
+    e1.synchronize()
+    return e0.elapsed_time(e1) / reps
+
+
 def isolated_latency(run, nsteps=200):
     """One query at a time on one stream with a device synchronisation after each: the wall
     time a lone request sees.  Returns (median_ms, min_ms)."""
@@ -465,8 +483,9 @@ def main():
         extras["isolated_latency_ms"]["graph_replay"] = {
             "median": gmed, "min": gmn, "replays_equal_to_eager": gchk,
             "note": "the same step recorded once per query into a HIP graph and replayed"}
-        # query-batched passes: bound by LDS reads, not HBM.  Ceiling: one 8-byte table entry per
-        # lane, 16 lanes per CU and clock without bank conflicts (128 B/clk) = 256 CUs x 16 x 2.4 GHz
+        # passes of the look-up kernels shared by four queries: bound by LDS reads, not HBM.  Ceiling:
+        # one 8-byte table entry per lane, 16 lanes per CU and clock without bank conflicts
+        # (128 B/clk) = 256 CUs x 16 x 2.4 GHz
         lds_ceiling = 256 * 16 * 2.4e9
         # the same read measured on this GPU for the kernel's own address pattern (every lane an
         # independent entry of a 2 KB table: bank conflicts included) and for a conflict-free one
@@ -487,23 +506,31 @@ def main():
             r2 = Runner(qb, idx, pr.queries, pr.codes, bs, a.R, streams=min(a.streams, 2),
                         fused=not a.unfused)
             d2 = sorted(r2.run(st, 2, 5))[2]
+            leg = extras[f"batch{bs}"] = {
+                "ms_per_step": d2 / st * 1e3,
+                "gcodes_per_s": bs * n * st / d2 / 1e9,
+                "glookups_per_s": bs * n * lay.m * st / d2 / 1e9,
+            }
+            if qb.pq_search_form(idx, bs, n, a.R) == qb.PQ_SCAN_MATRIX:
+                # the scan as a product [codes x T] . [T x queries] of 4- and 6-bit operands, with the
+                # preparation of its tables and the picking of the results (no entry point runs it alone)
+                cms, ops = scan_call_time(qb, idx, pr.queries, pr.codes, bs, a.R), 2.0 * n * idx.table_len * bs
+                leg["scan_call_ms"] = cms
+                leg["roofline"] = {
+                    "bound": "mfma", "kernel": "k_prepare + k_scan_mx + k_pick (pq_adc_scan_topk)", "unit": "TFLOP/s",
+                    "achieved": ops / (cms * 1e-3) / 1e12, "peak": MX_PEAK_TFLOPS,
+                    "frac": ops / (cms * 1e-3) / 1e12 / MX_PEAK_TFLOPS, "flops_per_call": ops}
+                continue
             kms, _ = scan_kernel_time(qb, idx, pr.queries, pr.codes, bs, a.R, nsamples=2, reps=5)
             # one LDS read of an 8-byte entry serves four queries' lookups of one group
             # (m x 4 layouts: a group is a code byte; irregular layouts: ng groups per code)
             groups = lay.m // 2 if set(lay.nbits) == {4} else None
             reads = ((bs + 3) // 4) * groups * float(n) if groups else None
-            extras[f"batch{bs}"] = {
-                "ms_per_step": d2 / st * 1e3,
-                "gcodes_per_s": bs * n * st / d2 / 1e9,
-                "glookups_per_s": bs * n * lay.m * st / d2 / 1e9,
-                "scan_kernel_ms": kms,
-                "scan_kernel_glookups_per_s": bs * n * lay.m / (kms * 1e-3) / 1e9,
-            }
+            leg["scan_kernel_ms"] = kms
+            leg["scan_kernel_glookups_per_s"] = bs * n * lay.m / (kms * 1e-3) / 1e9
             if reads:
-                extras[f"batch{bs}"]["roofline"] = {
+                leg["roofline"] = {
                     "bound": "lds", "kernel": "k_scan_mq", "unit": "G 8-byte LDS reads/s",
-                    "note": "the look-up kernel alone (small batches); a step of this size takes k_scan_mx, "
-                            "whose time is in ms_per_step",
                     "achieved": reads / (kms * 1e-3) / 1e9, "peak": lds_ceiling / 1e9,
                     "frac": reads / (kms * 1e-3) / lds_ceiling, "lds_reads_per_launch": reads,
                     "peak_measured_conflict_free": lds_measured["conflict_free"] / 1e9,

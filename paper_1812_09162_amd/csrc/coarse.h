@@ -50,7 +50,7 @@ int qadc_coarse_half_pass(const float *queries, int nqc, const float *centroids,
 // Exact scores [nq][ld] of at most QADC_DIRECT_NQ queries, and the smallest of every 64 cells
 // [nq][ld].  (Calls of up to 16 queries: 65,536 cells, d = 96: 1 query 75 -> 14 us, 16 queries 78 -> 25.
 // 32 queries, with the selection over whole rows, against the batched form: 1024 cells 44 / 36 us,
-// 65,536 cells 76 / 68; their chains are what bounds a block then.)
+// 65,536 cells 76 / 68, but 16,384 cells 49 / 65; their chains are what bounds a block then.)
 #define QADC_DIRECT_NQ 16
 int qadc_coarse_direct(const float *queries, int nq, const float *centroids, int K, int d, float *scores, size_t ld,
                        float *minima, hipStream_t s);

@@ -77,7 +77,7 @@ __device__ __forceinline__ uint32_t mx_floor_code(uint32_t x) {
     return x < 16u ? x : (x < 32u ? 16u + ((x - 16u) >> 1) : (x < 60u ? 24u + ((x - 32u) >> 2) : 31u));
 }
 // Levels of the batched matrix-core scan: entries and keys times a / 2^16, rounded down, so that a
-// code's sum of levels never exceeds the level of its key.  Sums are told apart up to 254, entries up to
+// code's sum of levels never exceeds the level of its unsaturated sum.  Sums are told apart up to 254, entries up to
 // 60.  The range of the keys is 255 levels (8-bit tables stay as they are, small entries exact) unless
 // `key`, which the R-th will hardly exceed, is near the top of it, as with R = 1, where the best
 // calibration code is the range: it is then brought to 160 levels, so that the entries of codes near the

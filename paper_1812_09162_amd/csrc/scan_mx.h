@@ -6,9 +6,10 @@
 // [codes x K] x [K x queries], K = the table length.  The one-hot rows cost a shift or two per
 // sub-code and the product runs at the full rate of the 4- and 6-bit formats.  The entries are held
 // in the 6-bit format e2m3 (32 values, 0..60 in units of 1/8), rounded DOWN, of the quantized
-// entry's level: entries and keys are scaled, per query, by a factor (mx_level) that brings the R-th key
-// to about 100 levels.  Small entries, which is what codes near the result have, lose little, the sum is
-// exact, and it bounds the level of the code's key from below.
+// entry's level: entries and keys are scaled, per query, by a factor (mx_level) that leaves the range of the
+// keys 255 levels or, where the R-th key is expected near its top, brings that key to 160.  Small entries, which
+// is what codes near the result have, lose little, the sum is exact, and it bounds the level of the code's
+// unsaturated sum, its key unless that is q_max, from below.
 //
 //   k_scan_mx  writes, per query, the smallest such sum of every group of 64 codes (one byte; sums
 //              above 255 as 255) and nothing else: no bound, no compare, no atomic.
@@ -19,7 +20,7 @@
 //
 // What bounds it: the matrix cores, and beside them the vector units (minima, row addresses), whose
 // time adds to theirs on this chip (2 + 2 waves per SIMD of products and of minima: 1.05 and 1.10 ms
-// alone, 1.83 together).  16 x 4 bits, K = 256: four products of 64 (36 clocks each) and eight
+// alone, 1.83 together).  16 x 4 bits, K = 256: four products of 64 (32 clocks each) and eight
 // three-operand minima per 32 x 32 results.  10^7 codes, 256 queries: 237 us = 10.8 T (code, query)
 // pairs/s, 940 us as look-ups in LDS (k_scan_mq); 32 queries: 39 and 165 us; {6,6,4} x 4, 32 queries:
 // 80 and 230 us (110 with the one-hot rows shifted together on the vector units).  k_pick: 16 us for
@@ -355,7 +356,7 @@ k_pick(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams
     typedef SelectLds<NT, ACAP> Lds;
     Lds &S = *(Lds *)smem;
     QT *gtab = (QT *)(smem + sizeof(Lds));
-    // until the ranking, the room of its histograms lists groups (group << 8 | minimum), and that of
+    // until the ranking, the room of its histograms lists groups, and that of
     // its order the 16-byte units of minima they come from
     constexpr int LIST = NT / 64 * 256, ULIST = ACAP / 2;
     uint32_t *list = &S.whist[0][0], *ulist = (uint32_t *)S.order;
