@@ -511,7 +511,7 @@ def main():
                 "gcodes_per_s": bs * n * st / d2 / 1e9,
                 "glookups_per_s": bs * n * lay.m * st / d2 / 1e9,
             }
-            if qb.pq_search_form(idx, bs, n, a.R) == qb.PQ_SCAN_MATRIX:
+            if qb.pq_search_form(idx, bs, n, a.R) == qb.pq_scan_form(idx, bs, n, a.R) == qb.PQ_SCAN_MATRIX:
                 # the scan as a product [codes x T] . [T x queries] of 4- and 6-bit operands, with the
                 # preparation of its tables and the picking of the results (no entry point runs it alone)
                 cms, ops = scan_call_time(qb, idx, pr.queries, pr.codes, bs, a.R), 2.0 * n * idx.table_len * bs

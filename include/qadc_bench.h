@@ -45,12 +45,13 @@ enum { PQ_LDS_UNIFORM = 0, PQ_LDS_LINEAR = 1, PQ_LDS_RANDOM_2K = 2, PQ_LDS_RANDO
 int pq_lds_read_probe(int pattern, int iters, void *sink, void *stream);
 
 /*
- * Which form pq_search_topk and pq_adc_scan_topk take for a call of these sizes: look-ups in LDS or the
- * matrix cores (PQ_EINVAL for bad sizes).  Both return the same bytes; tests ask so that the form they
- * are written for is the one that runs.
+ * Which form pq_search_topk (pq_search_form) and pq_adc_scan_topk (pq_scan_form) take for a call of these
+ * sizes: look-ups in LDS or the matrix cores (PQ_EINVAL for bad sizes).  Both return the same bytes;
+ * tests ask so that the form they are written for is the one that runs.
  */
 enum { PQ_SCAN_LOOKUP = 0, PQ_SCAN_MATRIX = 1 };
 int pq_search_form(const pq_index_t *idx, int nq, int64_t n, int R);
+int pq_scan_form(const pq_index_t *idx, int nq, int64_t n, int R);
 
 /*
  * Which form ivf_coarse_search takes for a call of these sizes with a workspace of that many bytes

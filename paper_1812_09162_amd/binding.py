@@ -28,7 +28,7 @@ EXPORTS = [
     "pq_adc_scan_candidates", "pq_adc_rescan_candidates", "pq_select_topk", "pq_copy_bytes", "pq_last_error",
     "ivf_coarse_workspace_bytes", "ivf_coarse_search", "pq_encode", "pq_adc_scan_topk_static",
     "pq_set_option", "pq_get_option", "ivf_adc_scan_topk_tightening", "pq_lds_read_probe",
-    "ivf_coarse_form", "pq_search_form",
+    "ivf_coarse_form", "pq_search_form", "pq_scan_form",
 ]
 PQ_KEY_BOUND_UNKNOWN = 0xFFFFFFFF
 (PQ_OPT_SCAN_BLOCKS, PQ_OPT_PILOT_CODES, PQ_OPT_PILOT_CODES_SINGLE, PQ_OPT_PILOT_BLOCKS, PQ_OPT_IVF_THREADS,
@@ -108,6 +108,8 @@ def load() -> ctypes.CDLL:
     lib.ivf_coarse_search.restype = i32
     lib.pq_search_form.argtypes = [vp, i32, i64, i32]
     lib.pq_search_form.restype = i32
+    lib.pq_scan_form.argtypes = lib.pq_search_form.argtypes
+    lib.pq_scan_form.restype = i32
     lib.ivf_coarse_form.argtypes = [i32, i32, i32, i32, sz]
     lib.ivf_coarse_form.restype = i32
     _lib = lib
@@ -246,8 +248,16 @@ def pq_search_workspace_bytes(idx: PqIndex, nq: int, n: int, R: int) -> int:
 
 
 def pq_search_form(idx: PqIndex, nq: int, n: int, R: int) -> int:
-    """PQ_SCAN_*: the form that pq_search_topk and pq_adc_scan_topk take for such a call."""
+    """PQ_SCAN_*: the form that pq_search_topk takes for such a call."""
     form = load().pq_search_form(idx.handle, nq, n, R)
+    if form < 0:
+        _check(form)
+    return form
+
+
+def pq_scan_form(idx: PqIndex, nq: int, n: int, R: int) -> int:
+    """PQ_SCAN_*: the form that pq_adc_scan_topk takes for such a call."""
+    form = load().pq_scan_form(idx.handle, nq, n, R)
     if form < 0:
         _check(form)
     return form

@@ -115,7 +115,8 @@ struct MxPlan {
     int nchunks, nmin;  // whole chunks, and group minima per query
     size_t btab_off, min_off;  // operand tables and group minima within a query's part of the workspace
 };
-MxPlan qadc_mx_plan(const pq_index *idx, int nq, int64_t n, int R, const ScanPlan &sp);
+// bounded: the call has its tables and a bound already (no pilot is saved)
+MxPlan qadc_mx_plan(const pq_index *idx, int nq, int64_t n, int R, const ScanPlan &sp, bool bounded);
 // scan and selection; the queries' group and operand tables are in the workspace already
 int qadc_scan_mx(const pq_index *idx, const pq_qparams_t *qparams, int nq, const uint8_t *codes, int64_t n, int R,
                  int32_t *out_ids, uint16_t *out_keys, float *out_dist, char *ws, const ScanPlan &sp, const MxPlan &p,

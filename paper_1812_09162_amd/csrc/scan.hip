@@ -882,7 +882,7 @@ static int scan_entry(const char *who, int what, const pq_index_t *idx, const vo
         qadc_set_error("%s: workspace of %zu bytes, need %zu", who, workspace_bytes, p.total);
         return PQ_ENOMEM;
     }
-    const MxPlan mp = (what & 3) == 3 ? qadc_mx_plan(idx, nq, n, R, p) : MxPlan{};
+    const MxPlan mp = (what & 3) == 3 ? qadc_mx_plan(idx, nq, n, R, p, true) : MxPlan{};
     return scan_dispatch(idx, qtables, qparams, nq, codes, n, R, out_ids, out_keys, out_dist,
                          (char *)workspace, p, mp, (hipStream_t)stream, what);
 }
@@ -1017,7 +1017,7 @@ extern "C" int pq_search_topk(const pq_index_t *idx, const float *queries, int n
     const ScanPlan p = qadc_scan_plan(idx, nq, n, R);
     char *scratch = ws + up256(p.total);
     PilotPlan pp;
-    const MxPlan mp = qadc_mx_plan(idx, nq, n, R, p);
+    const MxPlan mp = qadc_mx_plan(idx, nq, n, R, p, false);
     rc = qadc_quantize_launch(idx, queries, nullptr, nullptr, nq, codes, n, t, R, qtables, qparams, ws + p.gtab_off,
                               p.per_query, mp.use ? mp.btab_off - p.gtab_off : (size_t)0, ws, scratch, &pp, s);
     if (rc != PQ_OK) return rc;

@@ -68,7 +68,37 @@ static int64_t mx_min_list(const DevLayout &h, int nq, int R) {
     return R < 100 && !known ? 800000 : 0;
 }
 
-MxPlan qadc_mx_plan(const pq_index *idx, int nq, int64_t n, int R, const ScanPlan &sp) {
+// The same for a call that is given a bound with its tables (pq_adc_scan_topk): the pilot, which the batched scan
+// does without and which is most of what a short list costs the look-ups, is paid for already.  Lines from
+// 26,240 pairs of timings of that call; of the 3974 that it takes 28 are slower by 4 % or more.  16 x 4 bits,
+// R = 100, 8 queries: 400k 18 / 29, 1.6M 28 / 30, 5 queries 3.2M 36 / 34; R = 10, 800k: 12 queries 19 / 24, 32: 31 / 24;
+// R = 500, 3.2M: 8 queries 56 / 60, 16: 80 / 61; R = 1, 3.2M, 64 queries: 92 / 160 on one kind of data, 101 / 54 on the other.
+#define MX_MIN_CODES_BOUNDED 6400000
+static bool mx_pays_bounded(const DevLayout &h, int nq, int64_t n, int R) {
+    const bool wide = h.acc_bits != 8, known = h.mx_pat != 0;
+    const int64_t work = n * ((nq + 3) / 4);
+    // (32 x 4 bits with 16-bit tables, 3.2M, R = 250: 16 queries 168 / 191, 32: 290 / 195)
+    const int step = wide && h.kind == SCAN_NIB16 ? 125 : 250;
+    if (work < (int64_t)MX_MIN_CODES_BOUNDED * (R < step ? 1 : R / step)) return false;
+    switch (h.kind) {
+        case SCAN_NIB8:
+        case SCAN_NIB16:
+            if (R < 32) return n >= 800000 && nq >= 12 && !(R == 1 && h.kind == SCAN_NIB8 && !wide);
+            return n >= 400000 && nq >= (R >= 500 || (wide && h.kind == SCAN_NIB16 && R >= 100) ? 12 : 5);
+        // {6,6,4} x 8, 8M, R = 250: 12 queries 330 / 392, 24: 499 / 397; other patterns, 1.6M, R = 64, 64 queries: 320 / 308
+        case SCAN_W128: return known && R < 1000 && nq >= (R < 100 ? 5 : (R < 250 ? 12 : 24)) && (R > 1 || n >= 800000);
+        // {6,6,4} x 4, 3.2M, R = 100: 8 queries 61 / 66, 16: 97 / 70; other patterns, 1.6M: 16 queries 76 / 92, 32: 111 / 92
+        case SCAN_W64:
+            if (!known && (work < 2 * (int64_t)MX_MIN_CODES_BOUNDED || (R < 100 && n < 1600000))) return false;
+            return R > 1 && n >= 800000 && nq >= (R < 1000 ? 12 : 24) && (R < 500 || work >= 25000000);
+        // 40 bits: {6,5,5,6,5,5,4,4}, 3.2M, R = 100: 8 queries 45 / 51, 16: 66 / 53
+        default:
+            if (known) return R > 1 && R < 500 && nq >= 12 && n >= (R < 100 ? 6400000 : (R < 250 ? 1600000 : 3200000));
+            return R > 1 && nq >= 8 && n >= (R < 100 ? 3200000 : 800000) && (R < 500 || work >= 25000000);
+    }
+}
+
+MxPlan qadc_mx_plan(const pq_index *idx, int nq, int64_t n, int R, const ScanPlan &sp, bool bounded) {
     MxPlan p;
     memset(&p, 0, sizeof(p));
     const DevLayout &h = idx->h;
@@ -86,6 +116,7 @@ MxPlan qadc_mx_plan(const pq_index *idx, int nq, int64_t n, int R, const ScanPla
         if ((R > 1 && R < 32) || n < mx_min_list(h, nq, R)) return p;
         if (h.kind == SCAN_W128 && h.mx_pat == 0 && (n > MX_MOST_128 || R > 100)) return p;
     }
+    if (bounded && !mx_pays_bounded(h, nq, n, R)) return p;
     const int tiles = (nq + 31) / 32;  // of 32 queries
     const int most = mx_most(h.kind, h.mx_pat != 0);
     p.groups = (tiles + most - 1) / most;
@@ -126,10 +157,16 @@ int qadc_scan_mx(const pq_index *idx, const pq_qparams_t *qparams, int nq, const
 #undef QADC_GO
 }
 
-extern "C" int pq_search_form(const pq_index_t *idx, int nq, int64_t n, int R) {
+static int mx_form(const char *who, const pq_index_t *idx, int nq, int64_t n, int R, bool bounded) {
     if (!idx || nq < 0 || n < 0 || R < 1 || R > PQ_MAX_R) {
-        qadc_set_error("pq_search_form: bad handle, nq, n or R");
+        qadc_set_error("%s: bad handle, nq, n or R", who);
         return PQ_EINVAL;
     }
-    return qadc_mx_plan(idx, nq, n, R, qadc_scan_plan(idx, nq, n, R)).use ? PQ_SCAN_MATRIX : PQ_SCAN_LOOKUP;
+    return qadc_mx_plan(idx, nq, n, R, qadc_scan_plan(idx, nq, n, R), bounded).use ? PQ_SCAN_MATRIX : PQ_SCAN_LOOKUP;
+}
+extern "C" int pq_search_form(const pq_index_t *idx, int nq, int64_t n, int R) {
+    return mx_form("pq_search_form", idx, nq, n, R, false);
+}
+extern "C" int pq_scan_form(const pq_index_t *idx, int nq, int64_t n, int R) {
+    return mx_form("pq_scan_form", idx, nq, n, R, true);
 }

@@ -117,6 +117,14 @@ def test_which_form():
           ("664", 5, 4_000_000, 1), ("664", 8, 10_000_000, 500), ("664u8", 100, 800_000, 1), ("655x2", 8, 4_000_000, 250),
           ("odd64", 12, 4_000_000, 100), ("odd64", 60, 400_000, 32), ("5x8", 64, 1_600_000, 1), ("5x8", 7, 4_000_000, 100),
           ("mixed128", 100, 4_000_000, 100), ("mixed128", 16, 1_000_000, 100), ("16x4u16", 8, 4_000_000, 500), ("664", 64, 4_000_000, 10)]
+    stage_yes = [("16x4", 5, 4_000_000, 100), ("16x4", 1000, 1_000_003, 100), ("16x4", 32, 1_000_000, 10), ("32x4", 12, 4_000_000, 1),
+                 ("664", 16, 4_000_000, 100), ("664x2", 24, 8_000_000, 250), ("c3", 16, 4_000_000, 100), ("odd64", 32, 2_000_000, 100)]
+    stage_no = [("16x4", 8, 400_000, 100), ("16x4", 32, 400_000, 10), ("16x4", 256, 4_000_000, 1), ("664", 8, 4_000_000, 100),
+                ("664x2", 12, 8_000_000, 250), ("c3", 8, 4_000_000, 100), ("odd64", 16, 1_600_000, 100), ("mixed128", 64, 1_600_000, 64)]
+    for name, nq, n, R in stage_yes:
+        assert qb.pq_scan_form(idx[name], nq, n, R) == qb.PQ_SCAN_MATRIX, (name, nq, n, R)
+    for name, nq, n, R in stage_no:
+        assert qb.pq_scan_form(idx[name], nq, n, R) == qb.PQ_SCAN_LOOKUP, (name, nq, n, R)
     for name, nq, n, R in yes:
         assert qb.pq_search_form(idx[name], nq, n, R) == qb.PQ_SCAN_MATRIX, (name, nq, n, R)
     for name, nq, n, R in no:
@@ -208,11 +216,11 @@ def test_saturated_best_code(name, n, nq):
     _check(lay, cb, codes, queries, idx, 1)
 
 
-@pytest.mark.parametrize("n", [90_000, 210_000])
+@pytest.mark.parametrize("n", [90_000, 1_000_003])
 def test_stage_calls_and_bounds(n):
     """the scan call with the quantizer's bound, an unknown one, and one below which few codes lie"""
     lay, cb, codes, queries, idx = _make("16x4", n, 40, 13)
-    assert n == 90_000 or _matrix(idx, 40, n, 50)
+    assert n == 90_000 or qb.pq_scan_form(idx, 40, n, 50) == qb.PQ_SCAN_MATRIX
     c, z = codes.cuda(), queries.cuda()
     tables = qb.pq_compute_tables(idx, z)
     qt, qp = qb.pq_quantize_tables(idx, tables, c, 400, 50)
