@@ -14,8 +14,8 @@ extern template int mx_launch<SCAN_W128, uint16_t>(MX_ARGS);
 // picking of a query, by one block, grows with the results and with what a code costs to score again; where
 // its keys leave many codes as near as the R-th, that block has most of the list to score again.  The lines
 // are where, in 29,088 pairs of timings of both forms (16 layouts, 20,000 to 8 * 10^6 codes, 5 to 256
-// queries, R = 1 to 2000, two kinds of data), this form stops being the slower one: of the 6560 that it takes
-// 74 are slower by 4 % or more.  Figures in us, look-ups / here; k = 1000 codes, M = 10^6.
+// queries, R = 1 to 2000, two kinds of data), this form stops being the slower one: of the 6576 that it takes
+// 76 are slower by 4 % or more.  Figures in us, look-ups / here; k = 1000 codes, M = 10^6.
 //
 // Codes times passes, and codes per result.  m x 4 bits, R = 100, 8 queries: 400k 39 / 34, 200k 30 / 34; R = 500,
 // 48 queries, 400k: 97 / 130.  Irregular layouts, where a code is dearer to score again: {6,6,4} x 4, 64 queries,
@@ -24,9 +24,10 @@ extern template int mx_launch<SCAN_W128, uint16_t>(MX_ARGS);
 #define MX_MIN_RATIO_NIB 1000
 #define MX_MIN_CODES 6000000
 #define MX_MIN_RATIO 8000
-// Short lists, m x 4 bits: 16 x 4, R = 10, 100k: 32 queries 33 / 47, 256 queries 87 / 67; 32 x 4 (twice the
-// look-ups), R = 1, 50k, 100 queries: 76 / 45.
+// Short lists, m x 4 bits: 16 x 4, 100k: R = 10, 32 queries 33 / 47, 256 queries 87 / 67; R = 100, 64
+// queries 49 / 43; 32 x 4 (twice the look-ups), R = 1, 50k, 100 queries: 76 / 45.
 #define MX_MIN_LIST_8 200000
+#define MX_MIN_LIST_8_LONG 100000
 #define MX_MIN_LIST_16 50000
 #define MX_LONG_NIB 6000000
 // Of 40-bit codes more are equal, and of many queries one has a crowd of them near its R-th: {6,5,5,6,5,5,4,4},
@@ -106,7 +107,8 @@ MxPlan qadc_mx_plan(const pq_index *idx, int nq, int64_t n, int R, const ScanPla
     const int passes = (nq + 3) / 4;
     if (h.kind == SCAN_NIB8 || h.kind == SCAN_NIB16) {
         if (n * passes < MX_MIN_CODES_NIB || n < (int64_t)MX_MIN_RATIO_NIB * R) return p;
-        if (n < (h.kind == SCAN_NIB8 ? MX_MIN_LIST_8 : MX_MIN_LIST_16) && n * passes < MX_LONG_NIB) return p;
+        const int list = h.kind == SCAN_NIB16 ? MX_MIN_LIST_16 : (R < 100 ? MX_MIN_LIST_8 : MX_MIN_LIST_8_LONG);
+        if (n < list && n * passes < MX_LONG_NIB) return p;
     } else {
         const bool many = h.kind == SCAN_C5 && nq > MX_MANY_40;
         if (n * passes < MX_MIN_CODES || n < (int64_t)(many ? 2 * MX_MIN_RATIO : MX_MIN_RATIO) * R) return p;

@@ -108,7 +108,7 @@ def test_matrix_form_chunk_and_tile_edges(n, nq):
 def test_which_form():
     """the lines the rule draws: what is taken, and what stays with the look-ups (or went back to them)"""
     idx = {name: _make(name, 64, 1, 1)[4] for name in LAYOUTS}
-    yes = [("16x4", 5, 10_000_000, 100), ("16x4", 9, 10_000_000, 1000), ("16x4", 256, 100_000, 10), ("32x4", 100, 50_000, 1),
+    yes = [("16x4", 5, 10_000_000, 100), ("16x4", 9, 10_000_000, 1000), ("16x4", 256, 100_000, 10), ("16x4", 48, 110_000, 100), ("32x4", 100, 50_000, 1),
            ("c3", 32, 10_000_000, 100), ("c3", 32, 1_000_000, 100), ("c3", 32, 1_600_000, 64), ("664", 5, 4_000_000, 100),
            ("664", 32, 10_000_000, 100), ("664x2", 5, 4_000_000, 100), ("odd64", 13, 4_000_000, 100), ("5x8", 8, 4_000_000, 100),
            ("mixed128", 24, 1_000_000, 100), ("32x4", 8, 10_000_000, 500), ("16x4u16", 13, 4_000_000, 500)]
