@@ -15,7 +15,7 @@
 //   k_ivf_final  one block per query: gather the candidates, find the bin of the
 //                R-th, rank the few up to it; exact multi-pass selection over
 //                all probed codes if a slot list overflowed.
-#include "scan_device.h"
+#include "ivf_mx.h"
 
 struct IvfLds {
     float *zres;   // [d]
@@ -216,6 +216,8 @@ __device__ __forceinline__ void calib_list(int a, const int32_t *__restrict__ pr
 // sub-quantizers' table offset, bit offset and width from a small LDS array.
 // pair_cnt (or null): bucket counts of the pairs' sort by cell, pair_nb buckets and one more
 // for pairs without a list, zero on entry; the block adds its query's pairs.
+// bounds (or null): d_max and thr0 of every query once more, side by side (k_ivf_scan_mx reads those of many
+// queries per block, and in the workspace they are pages apart).
 template <bool NIB, int DS = 0>
 __global__ void __launch_bounds__(256)
 k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
@@ -223,7 +225,8 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
             const float *__restrict__ coarse, const int64_t *__restrict__ list_offsets,
             const uint8_t *__restrict__ list_codes, const float *__restrict__ queries,
             const int32_t *__restrict__ probe_ids, int nprobe, int K, int want, int pilot_want,
-            int R, char *__restrict__ ws, size_t per_query, uint32_t *__restrict__ pair_cnt, int pair_nb) {
+            int R, char *__restrict__ ws, size_t per_query, uint32_t *__restrict__ pair_cnt, int pair_nb,
+            float2 *__restrict__ bounds) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sel[8];
@@ -280,6 +283,7 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
             st->thr0 = INFINITY;
             st->lo = 0.f;
             st->scale = 0.f;
+            if (bounds) bounds[q] = make_float2(INFINITY, INFINITY);
         }
         return;
     }
@@ -429,6 +433,7 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
         st->dmax = dmax;
         st->thr0 = thr0;
         st->lo = lo;
+        if (bounds) bounds[q] = make_float2(dmax, thr0);
         st->scale = (span > 0.f && isfinite(span)) ? 256.0f / span : 0.f;
     }
 }
@@ -759,248 +764,14 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
     if (threadIdx.x == 0) counts[a] = s_count;  // uncapped: > cap_b tells k_ivf_final about the overflow
 }
 
-// --------------------------------------------------------- k_ivf_scan_mq ---
-// One pass over a list for up to four of the queries that probe it (Section 2.1.3: every
-// (query, cell) pair has its own tables, but the codes of the cell are the same for all).
-// For calls with several (query, probe) pairs per cell, 16 x 4-bit codes over equal sub-spaces
-// and 8-bit tables.  The pairs are sorted by cell exactly (one bucket per cell), the pairs of a
-// cell are cut into groups of at most four, and a block of four waves serves one group: wave w
-// builds the residual tables and the quantizer of the group's w-th pair exactly as k_ivf_scan
-// does, writes its byte-indexed group tables as field w of 8-byte entries {u16 q0..q3} in LDS,
-// and then all four waves scan the list once: one 8-byte read per code byte serves the four
-// pairs.  Every pair keeps its own slot list and count, so the selection is unchanged.
-#define IVF_MQ 4
-// A group: up to four (query, probe) pairs of one cell, in one 32-byte record so that a block's
-// loads depend on one another two deep (record; then queries, list bounds and so on).
-struct __align__(16) IvfGroup {
-    uint32_t pair[IVF_MQ];  // q * nprobe + a; entries beyond k repeat the first
-    int32_t cell;
-    int32_t k;
-    int32_t pad[2];
-};
-struct IvfMqLds {                      // behind the interleaved tables (which start at LDS address 0)
-    float zres[IVF_MQ][128];
-    float pmin[IVF_MQ][16];
-    uint16_t qt[IVF_MQ][256];
-    double sc[IVF_MQ][2];              // d_min, delta
-    unsigned long long slot[IVF_MQ];   // slot list of the pair
-    float thr[IVF_MQ];                 // pruning bound; -inf: nothing passes (no pair, or list skipped)
-    uint32_t count[IVF_MQ];
-    uint32_t *counts_out[IVF_MQ];
-    int flag[IVF_MQ];
-};
-#define IVF_MQ_TAB_BYTES (8 * 256 * 8)
-
-// the four packed sums of one 64-bit code: lo = {q0, q1}, hi = {q2, q3} (16 bits each; eight
-// addends of at most 510 cannot carry)
-__device__ __forceinline__ void ivf_mq_sums(uint32_t w0, uint32_t w1, uint32_t three, uint32_t &lo, uint32_t &hi) {
-    const uint2 e0 = mq_entry<0>(0, w0, three), e1 = mq_entry<1>(1, w0, three);
-    const uint2 e2 = mq_entry<2>(2, w0, three), e3 = mq_entry<3>(3, w0, three);
-    const uint2 e4 = mq_entry<0>(4, w1, three), e5 = mq_entry<1>(5, w1, three);
-    const uint2 e6 = mq_entry<2>(6, w1, three), e7 = mq_entry<3>(7, w1, three);
-    lo = e0.x + e1.x + e2.x + e3.x + e4.x + e5.x + e6.x + e7.x;
-    hi = e0.y + e1.y + e2.y + e3.y + e4.y + e5.y + e6.y + e7.y;
-}
-
-template <int DS>
-__global__ void __launch_bounds__(256)
-k_ivf_scan_mq(const float *__restrict__ cb, const float *__restrict__ coarse,
-              const int64_t *__restrict__ list_offsets, const uint8_t *__restrict__ list_codes,
-              const int32_t *__restrict__ list_ids, const float *__restrict__ queries, int nprobe,
-              char *__restrict__ ws, size_t per_query, size_t counts_off, size_t slots_off, int cap_b,
-              const IvfGroup *__restrict__ gdesc, const uint32_t *__restrict__ ngroups) {
-    extern __shared__ __align__(16) unsigned char smem[];  // tables at LDS address 0 (no static LDS here)
-    IvfMqLds &S = *(IvfMqLds *)(smem + IVF_MQ_TAB_BYTES);
-    if (blockIdx.x >= *ngroups) return;
-    constexpr int d = 16 * DS;
-    constexpr uint32_t qmax = 255;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const IvfGroup *gp = gdesc + blockIdx.x;
-    const int k = gp->k;  // 1..4 pairs, all of cell c, whose list is not empty
-    const int c = gp->cell;
-    const bool act = w < k;
-    const uint32_t pair = gp->pair[w];  // (idle waves mirror pair 0, store nothing)
-    const int64_t lo = list_offsets[c], hi = list_offsets[c + 1];
-    const size_t q = pair / (uint32_t)nprobe;
-    const int a = (int)(pair % (uint32_t)nprobe);
-    char *wq = ws + q * per_query;
-    const IvfState *st = (const IvfState *)wq;
-    const float dmax = st->dmax, thr0 = st->thr0;
-    // the first codes of the list, requested now and used after the set-up
-    constexpr int PF = 2;
-    const int64_t lo2 = (lo + 1) & ~(int64_t)1;
-    const int64_t npair = hi > lo2 ? (hi - lo2) >> 1 : 0;
-    const uint4 *__restrict__ pairs = (const uint4 *)(list_codes + lo2 * 8);
-    uint4 pp[PF];
-    if (npair > 0) {
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-            int64_t pi = (int64_t)u * 256 + threadIdx.x;
-            pi = pi < npair ? pi : npair - 1;
-            pp[u] = pairs[pi];
-        }
-    }
-    // codebook values of this lane's four table entries e = lane + 64 i
-    float cv[4][DS];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int t = 0; t < DS; ++t) cv[i][t] = cb[(lane + 64 * i) * DS + t];
-    for (int i = lane; i < d; i += 64) S.zres[w][i] = __fsub_rn(queries[q * d + i], coarse[(size_t)c * d + i]);
-    if (lane == 0) {
-        S.count[w] = 0;
-        S.slot[w] = (unsigned long long)((uint64_t *)(wq + slots_off) + (size_t)a * cap_b);
-        S.counts_out[w] = (uint32_t *)(wq + counts_off) + a;
-    }
-    __syncthreads();
-    // eq. (1), terms in ascending dimension order; 16 adjacent lanes hold one sub-quantizer
-    float tv[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int e = lane + 64 * i;
-        const float *zz = S.zres[w] + (e >> 4) * DS;
-        float acc = 0.0f;
-#pragma unroll
-        for (int t = 0; t < DS; ++t) {
-            const float diff = __fsub_rn(zz[t], cv[i][t]);
-            acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-        }
-        tv[i] = acc;
-        float mn = acc;
-#pragma unroll
-        for (int sft = 1; sft < 16; sft <<= 1) {
-            const float o = __shfl_xor(mn, sft, QADC_WAVE);
-            mn = o < mn ? o : mn;
-        }
-        if ((lane & 15) == 0) S.pmin[w][e >> 4] = mn;
-    }
-    __syncthreads();
-    if (lane == 0) {
-        double dm = 0.0;
-        for (int j = 0; j < 16; ++j) dm = dm + (double)S.pmin[w][j];
-        double delta = ((double)dmax - dm) / (double)qmax;
-        if (!((delta > 0.0) && isfinite(delta))) delta = 0.0;
-        const int skip = dm >= (double)dmax;  // Section 3.4: nothing in this list is closer than d_max
-        S.sc[w][0] = dm;
-        S.sc[w][1] = delta;
-        S.flag[w] = skip;
-        S.thr[w] = (act && !skip) ? thr0 : -INFINITY;
-    }
-    __syncthreads();
-    {
-        const double delta = S.sc[w][1];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = lane + 64 * i;
-            uint32_t qv = 0;
-            if (delta > 0.0) {
-                const double x = floor(((double)tv[i] - (double)S.pmin[w][e >> 4]) / delta);
-                qv = (x >= (double)qmax) ? qmax : (uint32_t)x;
-            }
-            S.qt[w][e] = (uint16_t)qv;
-        }
-    }
-    __syncthreads();
-    // the interleaved tables: entry (g, byte) holds, for each of the four pairs, low-nibble entry +
-    // high-nibble entry; a thread writes whole 8-byte entries
-    {
-        uint2 *tab = (uint2 *)smem;
-        for (int x = threadIdx.x; x < 8 * 256; x += 256) {
-            const int g = x >> 8, byte = x & 255;
-            const int il = 32 * g + (byte & 15), ih = 32 * g + 16 + (byte >> 4);
-            uint32_t v[IVF_MQ];
-#pragma unroll
-            for (int j = 0; j < IVF_MQ; ++j) v[j] = (uint32_t)S.qt[j][il] + (uint32_t)S.qt[j][ih];
-            tab[x] = make_uint2(v[0] | (v[1] << 16), v[2] | (v[3] << 16));
-        }
-    }
-    __syncthreads();
-    // ---- one pass over the list for the four pairs
-    float fdelta[IVF_MQ], fdmin[IVF_MQ], thr[IVF_MQ];
-#pragma unroll
-    for (int j = 0; j < IVF_MQ; ++j) {
-        fdelta[j] = (float)S.sc[j][1];
-        fdmin[j] = (float)S.sc[j][0];
-        thr[j] = S.thr[j];
-    }
-    const uint32_t three = 3;
-    for (int64_t pb = 0; pb < npair; pb += (int64_t)PF * 256) {
-        // the next round of codes is requested before this one is looked up
-        uint4 cur[PF];
-#pragma unroll
-        for (int u = 0; u < PF; ++u) cur[u] = pp[u];
-        if (pb + (int64_t)PF * 256 < npair) {
-#pragma unroll
-            for (int u = 0; u < PF; ++u) {
-                int64_t pi = pb + (int64_t)(PF + u) * 256 + threadIdx.x;
-                pi = pi < npair ? pi : npair - 1;
-                pp[u] = pairs[pi];
-            }
-        }
-        uint32_t slo[2 * PF], shi[2 * PF];
-        bool valid[PF];
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-            valid[u] = pb + (int64_t)u * 256 + threadIdx.x < npair;
-            ivf_mq_sums(cur[u].x, cur[u].y, three, slo[2 * u], shi[2 * u]);
-            ivf_mq_sums(cur[u].z, cur[u].w, three, slo[2 * u + 1], shi[2 * u + 1]);
-        }
-        uint32_t ord[IVF_MQ][2 * PF];
-        bool pass[IVF_MQ][2 * PF], any = false;
-#pragma unroll
-        for (int j = 0; j < IVF_MQ; ++j)
-#pragma unroll
-            for (int u = 0; u < 2 * PF; ++u) {
-                const uint32_t sum = j == 0 ? (slo[u] & 0xffffu) : (j == 1 ? (slo[u] >> 16) : (j == 2 ? (shi[u] & 0xffffu) : (shi[u] >> 16)));
-                const float dist = fmaf((float)(sum > qmax ? qmax : sum), fdelta[j], fdmin[j]);
-                ord[j][u] = qadc_f2ord(dist);
-                pass[j][u] = valid[u >> 1] && dist <= thr[j];
-                any = any || pass[j][u];
-            }
-        if (__ballot(any) != 0) {
-            uint32_t id[2 * PF];
-#pragma unroll
-            for (int u = 0; u < 2 * PF; ++u) {
-                const int64_t pos = lo2 + 2 * (pb + (int64_t)(u >> 1) * 256 + threadIdx.x) + (u & 1);
-                bool need = false;
-#pragma unroll
-                for (int j = 0; j < IVF_MQ; ++j) need = need || pass[j][u];
-                id[u] = need ? (uint32_t)list_ids[pos] : 0u;
-            }
-#pragma unroll
-            for (int j = 0; j < IVF_MQ; ++j)
-                slot_append_multi<2 * PF>(pass[j], ord[j], id, (uint64_t *)S.slot[j], (uint32_t)cap_b, &S.count[j]);
-        }
-    }
-    // the codes outside the 16-byte pairs: position lo if it is odd, position hi-1 if one is left over
-    if (threadIdx.x < QADC_WAVE) {
-        int64_t pos = -1;
-        if (threadIdx.x == 0 && lo2 != lo) pos = lo;
-        if (threadIdx.x == 1 && lo2 + 2 * npair < hi) pos = hi - 1;
-        uint32_t l2 = 0, h2 = 0, idv = 0;
-        if (pos >= 0) {
-            const uint2 cw = *(const uint2 *)(list_codes + pos * 8);
-            ivf_mq_sums(cw.x, cw.y, three, l2, h2);
-            idv = (uint32_t)list_ids[pos];
-        }
-#pragma unroll
-        for (int j = 0; j < IVF_MQ; ++j) {
-            const uint32_t sum = j == 0 ? (l2 & 0xffffu) : (j == 1 ? (l2 >> 16) : (j == 2 ? (h2 & 0xffffu) : (h2 >> 16)));
-            const float dist = fmaf((float)(sum > qmax ? qmax : sum), fdelta[j], fdmin[j]);
-            slot_append(pos >= 0 && dist <= thr[j], qadc_f2ord(dist), idv, (uint64_t *)S.slot[j], (uint32_t)cap_b, &S.count[j]);
-        }
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < k) *S.counts_out[threadIdx.x] = S.count[threadIdx.x];  // uncapped, as in k_ivf_scan
-}
-
-// Sorting the pairs by cell exactly, and cutting each cell's pairs into groups of IVF_MQ.
+// Sorting the pairs by cell exactly, and cutting each cell's pairs into groups of IVF_COLS
+// (k_ivf_scan_mx).
 // start[c] / gstart[c] = pairs / groups in cells before c (c = 0 .. nb, nb = K + 1 buckets: the
 // last holds the pairs without a list, which get no groups); cnt is cleared to serve as fill
 // cursors.  Two launches of nb / 1024 blocks: sums per block of 1024 buckets, then every block
 // adds up the sums before it and scans its own buckets.
 __device__ __forceinline__ uint32_t ivf_groups_of(uint32_t pairs, int bucket, int nb) {
-    return bucket < nb - 1 ? (pairs + IVF_MQ - 1) / IVF_MQ : 0u;
+    return bucket < nb - 1 ? (pairs + IVF_COLS - 1) / IVF_COLS : 0u;
 }
 // block-wide sums of two values (1024 threads); the result reaches every thread
 __device__ __forceinline__ void ivf_block_sum2(uint32_t &a, uint32_t &b, uint32_t (*wsum)[16]) {
@@ -1077,15 +848,8 @@ k_group_fill(const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ star
     if (c < K) {
         const uint32_t n = cnt[c], s0 = start[c];
         uint32_t g = gstart[c];
-        for (uint32_t i = 0; i < n; i += IVF_MQ, ++g) {
-            IvfGroup gr;
-            gr.k = (int32_t)(n - i < IVF_MQ ? n - i : (uint32_t)IVF_MQ);
-            gr.cell = c;
-            gr.pad[0] = gr.pad[1] = 0;
-#pragma unroll
-            for (int j = 0; j < IVF_MQ; ++j) gr.pair[j] = order[s0 + i + (j < gr.k ? (uint32_t)j : 0u)];
-            gdesc[g] = gr;
-        }
+        for (uint32_t i = 0; i < n; i += IVF_COLS, ++g)
+            gdesc[g] = IvfGroup{c, s0 + i, (int32_t)(n - i < IVF_COLS ? n - i : (uint32_t)IVF_COLS), 0};
     }
     const uint32_t nodd = cnt[K], sodd = start[K];
     for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < nodd; i += gridDim.x * 256) {
@@ -1538,7 +1302,7 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
     // blocks in the order of the probed cells (see ivf_pair_bucket):
     // sortws = cnt[NB+1] | start[NB+1] | order[pairs]
     const uint32_t *order = nullptr;
-    // fixed shape of k_ivf_scan's fast set-up and of k_ivf_scan_mq: 16 x 4 bits over equal
+    // fixed shape of k_ivf_scan's fast set-up and of k_ivf_scan_mx: 16 x 4 bits over equal
     // sub-spaces of 4, 6 or 8 dimensions, 8-bit tables
     const int dsf = (KIND == SCAN_NIB8 && sizeof(QT) == 1) ? ivf_fixed_shape(idx) : 0;
     const IvfGroup *gdesc = nullptr;
@@ -1548,12 +1312,17 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
     // the counters are cleared before it and the rest of the sort follows it.
     uint32_t *pair_cnt = nullptr;
     int pair_nb = 0;
+    float2 *bounds = nullptr;
     const int64_t npairs = (int64_t)nq * nprobe;
     const int sort_kind = tighten || !sortws ? 0 : (shared_lists && dsf != 0 ? 2 : 1);
     if (sort_kind == 2) {
-        // pairs sorted by cell exactly and cut into groups of four (see k_ivf_scan_mq):
-        // sortws = cnt[K+2] | start[K+2] | gstart[K+2] | bsum[2 * 1024] | order[pairs] | (16-byte aligned) gdesc[pairs/4 + K + 1]
+        // pairs sorted by cell exactly and cut into groups of IVF_COLS (see k_ivf_scan_mx):
+        // sortws = cnt[K+2] | start[K+2] | gstart[K+2] | bsum[2 * 1024] | order[pairs] | (16-byte aligned) gdesc[pairs/IVF_COLS + K + 1] | bounds[nq]
         const size_t nbw = (size_t)K + 2;
+        max_groups = (size_t)(npairs / IVF_COLS) + (size_t)K + 1;
+        IvfGroup *gd = (IvfGroup *)(((uintptr_t)(sortws + 3 * nbw + 2048 + npairs) + 15) & ~(uintptr_t)15);
+        gdesc = gd;
+        bounds = (float2 *)(gd + max_groups);
         hipLaunchKernelGGL(k_pair_zero, dim3((unsigned)((nbw + 255) / 256)), dim3(256), 0, s, sortws, (int)nbw);
         QADC_LAUNCH_CHECK("k_pair_zero");
         pair_cnt = sortws;
@@ -1600,7 +1369,7 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
         hipLaunchKernelGGL((k_ivf_calib<__VA_ARGS__>), dim3(nq), dim3(256), lds_calib, s, idx->dev,  \
                            idx->edesc, idx->codebooks, coarse, list_offsets, list_codes, queries,    \
                            probe_ids, nprobe, K, want, pilot_want, R, ws, p.per_query, pair_cnt,     \
-                           pair_nb);                                                                 \
+                           pair_nb, bounds);                                                                 \
     } while (0)
     // (the fixed 16 x 4-bit shape has a set-up of its own)
     if (dsf == 4) QADC_IVF_CALIB(true, 4);
@@ -1642,8 +1411,6 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
         const size_t nbw = (size_t)K + 2;
         uint32_t *cnt = sortws, *start = sortws + nbw, *gstart = sortws + 2 * nbw, *bsum = sortws + 3 * nbw;
         uint32_t *ord = bsum + 2048;
-        IvfGroup *gd = (IvfGroup *)(((uintptr_t)(ord + npairs) + 15) & ~(uintptr_t)15);
-        max_groups = (size_t)(npairs / IVF_MQ) + (size_t)K + 1;
         const unsigned scan_blocks = (unsigned)((K + 1 + 1023) / 1024);  // <= 1024: K < 2^20 is checked by the caller
         hipLaunchKernelGGL(k_pair_block_sums, dim3(scan_blocks), dim3(1024), 0, s, (const uint32_t *)cnt, K + 1, bsum);
         QADC_LAUNCH_CHECK("k_pair_block_sums");
@@ -1655,10 +1422,9 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
         QADC_LAUNCH_CHECK("k_pair_fill");
         hipLaunchKernelGGL(k_group_fill, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, s, (const uint32_t *)cnt,
                            (const uint32_t *)start, (const uint32_t *)gstart, (const uint32_t *)ord, K, nprobe,
-                           ws, p.per_query, p.counts_off, gd);
+                           ws, p.per_query, p.counts_off, (IvfGroup *)gdesc);
         QADC_LAUNCH_CHECK("k_group_fill");
         order = ord;
-        gdesc = gd;
         ngroups = gstart + (K + 1);
     } else if (sort_kind == 1) {
         const int NB = pair_nb;
@@ -1671,29 +1437,13 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
         order = ord;
     }
     if (gdesc) {
-        const size_t lds_mq = IVF_MQ_TAB_BYTES + sizeof(IvfMqLds);
-        static int mq_static_lds = -1;  // k_ivf_scan_mq addresses its tables from LDS address 0
-        if (mq_static_lds < 0) {
-            hipFuncAttributes a4, a6, a8;
-            if (hipFuncGetAttributes(&a4, (const void *)k_ivf_scan_mq<4>) != hipSuccess ||
-                hipFuncGetAttributes(&a6, (const void *)k_ivf_scan_mq<6>) != hipSuccess ||
-                hipFuncGetAttributes(&a8, (const void *)k_ivf_scan_mq<8>) != hipSuccess) {
-                qadc_set_error("k_ivf_scan_mq: hipFuncGetAttributes failed");
-                return PQ_EHIP;
-            }
-            mq_static_lds = (int)(a4.sharedSizeBytes + a6.sharedSizeBytes + a8.sharedSizeBytes);
-        }
-        if (mq_static_lds != 0) {
-            qadc_set_error("k_ivf_scan_mq: static LDS of %d bytes (its tables must start at LDS address 0)", mq_static_lds);
-            return PQ_EHIP;
-        }
-#define QADC_IVF_MQ(DSV)                                                                             \
-    hipLaunchKernelGGL((k_ivf_scan_mq<DSV>), dim3((unsigned)max_groups), dim3(256), lds_mq, s,       \
+#define QADC_IVF_MX(DSV)                                                                             \
+    hipLaunchKernelGGL((k_ivf_scan_mx<DSV>), dim3((unsigned)max_groups), dim3(256), 0, s,            \
                        idx->codebooks, coarse, list_offsets, list_codes, list_ids, queries, nprobe,  \
-                       ws, p.per_query, p.counts_off, p.slots_off, p.cap_b, gdesc, ngroups)
-        if (dsf == 4) QADC_IVF_MQ(4); else if (dsf == 6) QADC_IVF_MQ(6); else QADC_IVF_MQ(8);
-#undef QADC_IVF_MQ
-        QADC_LAUNCH_CHECK("k_ivf_scan_mq");
+                       ws, p.per_query, p.counts_off, p.slots_off, p.cap_b, gdesc, ngroups, order, bounds)
+        if (dsf == 4) QADC_IVF_MX(4); else if (dsf == 6) QADC_IVF_MX(6); else QADC_IVF_MX(8);
+#undef QADC_IVF_MX
+        QADC_LAUNCH_CHECK("k_ivf_scan_mx");
     } else {
     const int scan_threads = (int)qadc_option(PQ_OPT_IVF_THREADS);
     // table entries per thread: the low-latency set-up holds up to four in registers
@@ -1738,15 +1488,19 @@ static size_t ivf_sort_bytes(int nq, int nprobe, int K) {
     const size_t nb = K < IVF_SORT_BUCKETS ? (size_t)K : (size_t)IVF_SORT_BUCKETS;
     return ((2 * (nb + 1) + (size_t)nq * (size_t)nprobe) * sizeof(uint32_t) + 255) & ~(size_t)255;
 }
-// the sort by cell and the groups of k_ivf_scan_mq
+// the sort by cell and the groups of k_ivf_scan_mx
 static size_t ivf_group_bytes(int nq, int nprobe, int K) {
     const size_t pairs = (size_t)nq * (size_t)nprobe;
     return ((3 * ((size_t)K + 2) + 2048 + pairs) * sizeof(uint32_t) + 16 +
-            (pairs / IVF_MQ + (size_t)K + 1) * sizeof(IvfGroup) + 255) & ~(size_t)255;
+            (pairs / IVF_COLS + (size_t)K + 1) * sizeof(IvfGroup) + (size_t)nq * sizeof(float2) + 255) & ~(size_t)255;
 }
-// Half-pairs per cell from which one pass per list for four pairs beats a block per pair
-// (C4 shape, measured: 1 pair per cell -7 %, 2 pairs +9 %, 3.9 pairs +22 %, 9.8 pairs +32 %)
+// When one pass over a list for the pairs that probe it (k_ivf_scan_mx) beats a block per pair: from one and a half
+// pairs per cell on, and not below a thousand pairs, where the four extra launches of the exact sort show.  16 x 4 bits,
+// d = 96, R = 100, us a call, block per pair / shared: 2 * 10^7 codes in 16384 lists, 64 probes: 1 pair per cell 129 / 140,
+// 1.5 151 / 155, 2 173 / 163, 4 265 / 198; in 4096 lists: 0.25 (1024 pairs) 154 / 122, 1.5 171 / 144; 2 * 10^6 in 4096:
+// 2 85 / 89, 4 103 / 99; 500,000 codes in 100 lists, 20 probes: 4 (400 pairs) 73 / 85.
 #define IVF_SHARED_MIN_HALF_PAIRS_PER_CELL 3
+#define IVF_SHARED_MIN_PAIRS 1024
 
 extern "C" size_t ivf_sorted_workspace_bytes(const pq_index_t *idx, int nq, int nprobe, int R, int K) {
     if (!idx || nq < 0 || nprobe < 1 || R < 1 || K < 1) return 0;
@@ -1801,11 +1555,12 @@ static int ivf_search(const char *name, bool tighten, const pq_index_t *idx, con
     if (!tighten && (int64_t)nq * nprobe * 4 >= (int64_t)K &&
         workspace_bytes >= base_bytes + ivf_sort_bytes(nq, nprobe, K))
         sortws = (uint32_t *)(ws + base_bytes);
-    // many pairs per cell (or the option says always): one pass over a list serves four pairs
+    // many pairs per cell (or the option says always): one pass over a list serves up to sixteen pairs
     const int64_t shared_opt = qadc_option(PQ_OPT_IVF_SHARED_LISTS);
     const bool shared_lists = !tighten && shared_opt != 0 && ivf_fixed_shape(idx) != 0 && K < (1 << 20) &&
                               workspace_bytes >= base_bytes + ivf_group_bytes(nq, nprobe, K) &&
-                              (shared_opt == 2 || 2 * (int64_t)nq * nprobe >= (int64_t)IVF_SHARED_MIN_HALF_PAIRS_PER_CELL * K);
+                              (shared_opt == 2 || ((int64_t)nq * nprobe >= IVF_SHARED_MIN_PAIRS &&
+                                                   2 * (int64_t)nq * nprobe >= (int64_t)IVF_SHARED_MIN_HALF_PAIRS_PER_CELL * K));
     if (shared_lists) sortws = (uint32_t *)(ws + base_bytes);
     const bool u8 = idx->h.acc_bits == 8;
 #define QADC_GO(KIND, QT)                                                                          \

@@ -71,10 +71,11 @@ __device__ inline void build_gtab(const DevLayout *L, const uint16_t *qs, QT *gt
     __syncthreads();
 }
 
-// The nearest value not above x of the 6-bit format e2m3 in units of 1/8: 0..15 exactly, then steps
-// of 2 and of 4 up to 60.
+// The nearest value not above x (< 2^24) of the 6-bit format e2m3 in units of 1/8: 0..15 exactly, then steps
+// of 2 and of 4 up to 60.  From 8 on it is x's exponent and three upper fraction bits as a float.
 __device__ __forceinline__ uint32_t mx_floor_code(uint32_t x) {
-    return x < 16u ? x : (x < 32u ? 16u + ((x - 16u) >> 1) : (x < 60u ? 24u + ((x - 32u) >> 2) : 31u));
+    const int c = (int)(__float_as_uint((float)x) >> 20) - (129 << 3);
+    return (uint32_t)min(max(c, (int)min(x, 7u)), 31);
 }
 // Levels of the batched matrix-core scan: entries and keys times a / 2^16, rounded down, so that a
 // code's sum of levels never exceeds the level of its unsaturated sum.  Sums are told apart up to 254, entries up to
