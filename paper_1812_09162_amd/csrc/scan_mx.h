@@ -18,12 +18,13 @@
 //              be within it lies in a group whose minimum is within it.  Those codes' exact keys are
 //              computed from the group tables, and the R smallest (key, id) are written.
 //
-// What bounds it: the matrix cores, and beside them the vector units (minima, row addresses), whose
-// time adds to theirs on this chip (2 + 2 waves per SIMD of products and of minima: 1.05 and 1.10 ms
-// alone, 1.83 together).  16 x 4 bits, K = 256: four products of 64 (32 clocks each) and eight
-// three-operand minima per 32 x 32 results.  10^7 codes, 256 queries: 237 us = 10.8 T (code, query)
-// pairs/s, 940 us as look-ups in LDS (k_scan_mq); 32 queries: 39 and 165 us; {6,6,4} x 4, 32 queries:
-// 80 and 230 us (110 with the one-hot rows shifted together on the vector units).  k_pick: 16 us for
+// What bounds it: the matrix cores (busy 74 % of the time at 256 queries, at the 2.0 GHz the chip holds under
+// them), and beside them the vector units (minima, row addresses), which overlap them in part where both alternate
+// in a wave's stream.  16 x 4 bits, K = 256: four products of 64 (32 clocks each) and eight
+// three-operand minima per 32 x 32 results.  10^7 codes, 256 queries: 205 us = 12.5 T (code, query)
+// pairs/s, 940 us as look-ups in LDS (k_scan_mq); 32 queries: 40 and 165 us; {6,6,4} x 4, 32 queries:
+// 67 and 230 us (81 with the minima behind all products of a tile; 110 with the one-hot rows shifted together
+// on the vector units).  k_pick: 16 us for
 // 32 queries, 24 for 256 (it replaces the quantizer's pilot and k_final: 95 + 16 us at 256 queries).
 #include <string.h>
 
@@ -192,6 +193,49 @@ k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char 
             offs[s] = (uint32_t)((h ? md.off[s][1] : md.off[s][0]) + 28) & 31u;
         else
             offs[s] = h ? (uint32_t)(md.off[s][1] | md.off2[s][1] << 6) : (uint32_t)(md.off[s][0] | md.off2[s][0] << 6);
+    // A lane's row of product step s for tile t of a block of codes.
+    auto row_of = [&](const MxCodes<KIND> &cd, int t, int s) {
+        const uint32_t *w = cd.w[t];
+        if constexpr (NIB) {
+            const uint32_t x = w[s >> 2];
+            uint32_t at;
+            switch (s & 3) {
+                case 0: at = mx_byte_x16<0>(x, four); break;
+                case 1: at = mx_byte_x16<1>(x, four); break;
+                case 2: at = mx_byte_x16<2>(x, four); break;
+                default: at = mx_byte_x16<3>(x, four); break;
+            }
+            return *(const uint4 *)((const char *)lut + at);
+        } else {
+            // (128-bit codes: the steps of the upper word follow those of the lower)
+            constexpr int HS = KIND == SCAN_W128 ? S / 2 : S;
+            constexpr int W0 = MxCodes<KIND>::W - 2;
+            const uint32_t lo = s < HS ? w[0] : w[W0], hi = s < HS ? w[1] : w[W0 + 1];
+            constexpr int N6 = PAT / 100, N5 = PAT / 10 % 10;
+            const int sw = s % HS;
+            if (PAT != 0 && sw < N6 + N5) {
+                // the field, rotated to bit 4 of its dword: the steps of a kind are in the order of
+                // the code, half of them in each dword (40-bit codes: all in the lower)
+                const bool upper = KIND != SCAN_C5 && (sw < N6 ? 2 * sw >= N6 : 2 * (sw - N6) >= N5);
+                const uint32_t x = upper ? hi : lo;
+                const uint32_t r = __builtin_amdgcn_alignbit(x, x, offs[s]);
+                const uint32_t at = sw < N6 ? ((r & 0x3f0u) | hbase) : (r & 0x1f0u);
+                return *(const uint4 *)((const char *)lut + at);
+            } else {
+                const uint64_t v = ((uint64_t)hi << 32) | lo;
+                const int type = PAT == 0 ? md.type[s] : MX_NIBBLES;
+                const uint32_t x = (uint32_t)(v >> (offs[s] & 63u));
+                MxRow y;
+                if (type == MX_SIX)
+                    y = mx_row_five(x, ((x >> 4) & 2u) ^ hz);
+                else if (type == MX_FIVE)
+                    y = mx_row_five(x, 2);
+                else
+                    y = mx_row_nibbles(x << 2, (uint32_t)(v >> ((offs[s] >> 6) & 63u)) << 2);
+                return make_uint4((uint32_t)y.lo, (uint32_t)(y.lo >> 32), (uint32_t)y.hi, (uint32_t)(y.hi >> 32));
+            }
+        }
+    };
     for (int ch = blockIdx.x * 4 + wave; ch < nchunks; ch += gridDim.x * 4) {
         const int64_t first = (int64_t)ch * nblk * 128 + 4 * c;
         MxCodes<KIND> cur, nxt;
@@ -204,74 +248,43 @@ k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char 
             for (int i = 0; i < 4; ++i) pk[ct][i] = 0;
         }
         int inb = 0, gi = 0;
+        cur.arrange(h);
+        uint4 row[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) row[s] = row_of(cur, 0, s);
         for (int blk = 0; blk < nblk; ++blk) {
             nxt.request(codes, first + (int64_t)(blk + 1 < nblk ? blk + 1 : blk) * 128, h);
-            cur.arrange(h);
+            // Units (tile, query tile) in turn on two accumulators: between the products of one, the minima of the
+            // one before (sums are >= 0: their bit patterns order as integers) and, in a tile's last unit, the
+            // rows of the next tile.  Products and vector instructions overlap on this chip where they alternate in
+            // a wave's stream (four products 131 clocks, 32 minima 140, alternating 175, one after the other 271).
+            mx_v16f acc[2];
+            auto minima = [&](const mx_v16f &a, uint32_t &m, int p) {
+                m = min(m, min(__float_as_uint(a[2 * p]), __float_as_uint(a[2 * p + 1])));
+            };
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                mx_v16f acc[NCOL];
-                const uint32_t *w = cur.w[t];
+            for (int u = 0; u < 4 * NCOL; ++u) {
+                const int t = u / NCOL, ct = u % NCOL, before = (u + NCOL - 1) % NCOL;
+                if (t == 3 && ct == NCOL - 1) nxt.arrange(h);
 #pragma unroll
                 for (int s = 0; s < S; ++s) {
-                    uint4 row;
-                    if constexpr (NIB) {
-                        const uint32_t x = w[s >> 2];
-                        uint32_t at;
-                        switch (s & 3) {
-                            case 0: at = mx_byte_x16<0>(x, four); break;
-                            case 1: at = mx_byte_x16<1>(x, four); break;
-                            case 2: at = mx_byte_x16<2>(x, four); break;
-                            default: at = mx_byte_x16<3>(x, four); break;
-                        }
-                        row = *(const uint4 *)((const char *)lut + at);
-                    } else {
-                        // (128-bit codes: the steps of the upper word follow those of the lower)
-                        constexpr int HS = KIND == SCAN_W128 ? S / 2 : S;
-                        constexpr int W0 = MxCodes<KIND>::W - 2;
-                        const uint32_t lo = s < HS ? w[0] : w[W0], hi = s < HS ? w[1] : w[W0 + 1];
-                        constexpr int N6 = PAT / 100, N5 = PAT / 10 % 10;
-                        const int sw = s % HS;
-                        if (PAT != 0 && sw < N6 + N5) {
-                            // the field, rotated to bit 4 of its dword: the steps of a kind are in the order of
-                            // the code, half of them in each dword (40-bit codes: all in the lower)
-                            const bool upper = KIND != SCAN_C5 && (sw < N6 ? 2 * sw >= N6 : 2 * (sw - N6) >= N5);
-                            const uint32_t x = upper ? hi : lo;
-                            const uint32_t r = __builtin_amdgcn_alignbit(x, x, offs[s]);
-                            const uint32_t at = sw < N6 ? ((r & 0x3f0u) | hbase) : (r & 0x1f0u);
-                            row = *(const uint4 *)((const char *)lut + at);
-                        } else {
-                            const uint64_t v = ((uint64_t)hi << 32) | lo;
-                            const int type = PAT == 0 ? md.type[s] : MX_NIBBLES;
-                            const uint32_t x = (uint32_t)(v >> (offs[s] & 63u));
-                            MxRow y;
-                            if (type == MX_SIX)
-                                y = mx_row_five(x, ((x >> 4) & 2u) ^ hz);
-                            else if (type == MX_FIVE)
-                                y = mx_row_five(x, 2);
-                            else
-                                y = mx_row_nibbles(x << 2, (uint32_t)(v >> ((offs[s] >> 6) & 63u)) << 2);
-                            row = make_uint4((uint32_t)y.lo, (uint32_t)(y.lo >> 32), (uint32_t)y.hi, (uint32_t)(y.hi >> 32));
-                        }
-                    }
-                    const mx_v8i a = {(int)row.x, (int)row.y, (int)row.z, (int)row.w, 0, 0, 0, 0};
+                    const mx_v8i a = {(int)row[s].x, (int)row[s].y, (int)row[s].z, (int)row[s].w, 0, 0, 0, 0};
+                    const uint32_t *bs = b[ct][s];
+                    const mx_v8i bv = {(int)bs[0], (int)bs[1], (int)bs[2], (int)bs[3], (int)bs[4], (int)bs[5], 0, 0};
+                    const mx_v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    // formats: 4 = 4 bits (one-hot rows), 2 = 6 bits e2m3 (tables)
+                    acc[u & 1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, bv, s == 0 ? zero : acc[u & 1], 4, 2, 0, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (ct == NCOL - 1) row[s] = t < 3 ? row_of(cur, t + 1, s) : row_of(nxt, 0, s);
+                    if (u > 0 && s > 0) {  // (the last product of the unit before needs a step or two to finish)
 #pragma unroll
-                    for (int ct = 0; ct < NCOL; ++ct) {
-                        const uint32_t *bs = b[ct][s];
-                        const mx_v8i bv = {(int)bs[0], (int)bs[1], (int)bs[2], (int)bs[3], (int)bs[4], (int)bs[5], 0, 0};
-                        const mx_v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                        // formats: 4 = 4 bits (one-hot rows), 2 = 6 bits e2m3 (tables)
-                        acc[ct] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, bv, s == 0 ? zero : acc[ct], 4, 2, 0, 0, 0, 0);
+                        for (int p = 8 * (s - 1) / (S - 1); p < 8 * s / (S - 1); ++p) minima(acc[(u + 1) & 1], mn[before], p);
                     }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                // sums are >= 0: their bit patterns order as integers
-#pragma unroll
-                for (int ct = 0; ct < NCOL; ++ct)
-#pragma unroll
-                    for (int r = 0; r < 16; r += 2) {
-                        const uint32_t u = __float_as_uint(acc[ct][r]), v = __float_as_uint(acc[ct][r + 1]);
-                        mn[ct] = min(mn[ct], min(u, v));
-                    }
             }
+#pragma unroll
+            for (int p = 0; p < 8; ++p) minima(acc[1], mn[NCOL - 1], p);
             if (++inb == nb) {
                 inb = 0;
 #pragma unroll
