@@ -204,35 +204,12 @@ __device__ inline uint32_t qadc_block_kth_u32(const uint32_t *vals, int cnt, int
 // each instead of the radix selection's four passes; a crowded bin (many equal values) or a
 // degenerate range falls back to qadc_block_kth_u32.  All threads of the block call it; `hist`
 // is 256 words of LDS, `sel` eight, `mem` QADC_KTH_MEM.  Returns the value to every thread.
+// mn, mx: the smallest and largest value; `hist` is clear, and a barrier lies behind both.
 #define QADC_KTH_MEM 256
 __device__ inline uint32_t qadc_block_kth_f32(const uint32_t *vals, int cnt, int k, uint32_t *hist,
-                                              uint32_t *sel, uint32_t *mem) {
-    uint32_t mn = 0xffffffffu, mx = 0u;
-    for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
-        const uint32_t v = vals[i];
-        mn = v < mn ? v : mn;
-        mx = v > mx ? v : mx;
-    }
-    mn = qadc_wave_min(mn);
-    mx = qadc_wave_max(mx);
-    if (threadIdx.x == 0) {
-        sel[0] = 0xffffffffu;
-        sel[1] = 0u;
-        sel[2] = 0u;  // members gathered
-    }
-    for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
-    __syncthreads();
-    if (threadIdx.x % QADC_WAVE == 0) {
-        atomicMin(&sel[0], mn);
-        atomicMax(&sel[1], mx);
-    }
-    __syncthreads();
-    mn = sel[0];
-    mx = sel[1];
-    if (mn == mx) {
-        __syncthreads();
-        return mn;
-    }
+                                              uint32_t *sel, uint32_t *mem, uint32_t mn, uint32_t mx) {
+    if (threadIdx.x == 0) sel[2] = 0u;  // members gathered
+    if (mn == mx) return mn;
     const float fmn = qadc_ord2f(mn);
     const float scale = 256.0f / (qadc_ord2f(mx) - fmn);
     const bool usable = scale > 0.0f && scale <= 3.0e38f;  // (block-uniform)
@@ -272,4 +249,32 @@ __device__ inline uint32_t qadc_block_kth_f32(const uint32_t *vals, int cnt, int
     const uint32_t res = sel[3];
     __syncthreads();
     return res;
+}
+
+// The same when the range has to be found first.
+__device__ inline uint32_t qadc_block_kth_f32(const uint32_t *vals, int cnt, int k, uint32_t *hist,
+                                              uint32_t *sel, uint32_t *mem) {
+    uint32_t mn = 0xffffffffu, mx = 0u;
+    for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
+        const uint32_t v = vals[i];
+        mn = v < mn ? v : mn;
+        mx = v > mx ? v : mx;
+    }
+    mn = qadc_wave_min(mn);
+    mx = qadc_wave_max(mx);
+    if (threadIdx.x == 0) {
+        sel[0] = 0xffffffffu;
+        sel[1] = 0u;
+    }
+    for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
+    __syncthreads();
+    if (threadIdx.x % QADC_WAVE == 0) {
+        atomicMin(&sel[0], mn);
+        atomicMax(&sel[1], mx);
+    }
+    __syncthreads();
+    mn = sel[0];
+    mx = sel[1];
+    __syncthreads();
+    return qadc_block_kth_f32(vals, cnt, k, hist, sel, mem, mn, mx);
 }

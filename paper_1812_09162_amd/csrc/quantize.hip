@@ -25,19 +25,48 @@
 // carry q_max as the bound.  Block 0 of a query stores the tables and the parameters.
 // `queries` non-null: tables are computed here (and stored to tables_out if
 // that is non-null); otherwise they are read from tables_in.
-#ifndef QUANT_THREADS
+// Threads of a block: QUANT_WIDE while the blocks of a call do not fill the chip (a block's time is then a chain of
+// dependent steps, each shorter with more threads), QUANT_THREADS when they do (quantize_wide).
 #define QUANT_THREADS 256
-#endif
+#define QUANT_WIDE 1024
 // The few layout numbers the kernel needs before anything else, as kernel arguments (reading
 // them through the layout pointer would be a memory round trip ahead of every other load).
 struct QuantShape {
     int T, m, cs, qmax, d;
     int ubits, uds;  // bits and dimensions of every sub-quantizer if they are all alike, else 0
 };
-// NIB8 pilot codes a thread holds in registers per batch
+// Pilot codes of a thread per batch (a wide block's batch is 4096 codes, the longest slice that is usual)
 #define PILOT_PER_THREAD 8
-template <int KIND, typename QT>
-__global__ void __launch_bounds__(QUANT_THREADS)
+#define PILOT_PER_THREAD_WIDE 4
+// An entry of eq. (1): DS dimensions in ascending order, the codebook values requested eight at a time.
+__device__ __forceinline__ float quant_entry(const float *z, const float *__restrict__ c, int ds) {
+    float acc = 0.0f;
+    int l = 0;
+    for (; l + 8 <= ds; l += 8) {
+        float cv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) cv[u] = c[l + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float diff = __fsub_rn(z[l + u], cv[u]);
+            acc = __fadd_rn(acc, __fmul_rn(diff, diff));
+        }
+    }
+    if (l < ds) {
+        float cv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) cv[u] = l + u < ds ? c[l + u] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (l + u < ds) {
+                const float diff = __fsub_rn(z[l + u], cv[u]);
+                acc = __fadd_rn(acc, __fmul_rn(diff, diff));
+            }
+    }
+    return acc;
+}
+template <int KIND, typename QT, int NT>
+__global__ void __launch_bounds__(NT)
 k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryDesc *__restrict__ edesc,
            const float *__restrict__ cb,
            const float *__restrict__ queries, const float *__restrict__ tables_in,
@@ -58,9 +87,8 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     __shared__ __align__(16) uint32_t hist[256];
     __shared__ uint32_t sel[8];
     __shared__ uint32_t kmem[QADC_KTH_MEM];
-    __shared__ double s_dmin, s_delta;
-    __shared__ float s_dmax;
-    __shared__ uint32_t s_omin, s_scale;
+    __shared__ double s_dmin;
+    __shared__ uint32_t s_range[2];  // smallest and largest calibration sum, as ordered words
     __shared__ uint32_t sdesc[PQ_MAX_M];  // table offset | bit offset << 12 | bits << 24 of each sub-quantizer
     __shared__ uint32_t pmin_ord[PQ_MAX_M];  // table minima as ordered words (qadc_f2ord), by LDS atomic min
     if ((int)threadIdx.x < m) {  // (read after the barriers of the table set-up)
@@ -69,20 +97,24 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
         pmin_ord[threadIdx.x] = 0xffffffffu;
     }
 
+    if (threadIdx.x == 0) {
+        s_range[0] = 0xffffffffu;
+        s_range[1] = 0u;
+    }
     const size_t q = blockIdx.x / (unsigned)P;
     const int p = (int)(blockIdx.x % (unsigned)P);
     const bool first = p == 0;
     const int lo = (int64_t)p * slice < pilot ? p * slice : pilot;
     const int hi = (int64_t)lo + slice < pilot ? lo + slice : pilot;
-    constexpr int PPT = KIND == SCAN_NIB8 ? PILOT_PER_THREAD : 8;  // pilot codes per thread and batch
-    const int step = PPT * (int)blockDim.x;
+    constexpr int PPT = NT > QUANT_THREADS ? PILOT_PER_THREAD_WIDE : PILOT_PER_THREAD;
+    const int step = PPT * NT;
 
     // The first batch of this block's pilot codes is requested now and used at the very end.
     uint2 pc[PPT];
     if (KIND == SCAN_NIB8 && hi > lo) {
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
-            int id = lo + u * (int)blockDim.x + (int)threadIdx.x;
+            int id = lo + u * NT + (int)threadIdx.x;
             id = id < hi ? id : hi - 1;
             pc[u] = *(const uint2 *)(codes + (size_t)id * 8);
         }
@@ -90,35 +122,47 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
 
     // The calibration code of this thread (at most one per thread in the common case) and the
     // descriptor of its table entry are requested now as well: they do not depend on anything.
-    const bool cal_pre = t_eff <= 2 * (int)blockDim.x && cs <= 16;  // up to two per thread
+    const bool cal_pre = t_eff <= 2 * NT && cs <= 16;  // up to two per thread
     uint32_t cw[2][4] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
     if (cal_pre) {
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            const int pp = r * (int)blockDim.x + (int)threadIdx.x;
+            const int pp = r * NT + (int)threadIdx.x;
             if (pp < t_eff) qadc_load_code16(codes + (size_t)pp * cs, cs, cw[r]);
         }
     }
     EntryDesc ed0 = {0, 0, 0, 0};
-    if ((int)threadIdx.x < T) ed0 = edesc[threadIdx.x];
+    const bool alike = queries && shape.ubits > 0 && shape.uds > 0;
+    if (!alike && (int)threadIdx.x < T) ed0 = edesc[threadIdx.x];
 
-    if (queries && shape.ubits > 0 && shape.uds > 0 && T > (int)blockDim.x) {
-        // long tables of sub-quantizers that are all alike (m x 8 bits): entry e is centroid
+    if (alike) {
+        // sub-quantizers that are all alike (m x 4 or m x 8 bits): entry e is centroid
         // e mod 2^bits of sub-quantizer e >> bits at codebook offset e * ds, so nothing has to
         // be looked up before the codebook values are requested, and the loop over the
         // dimensions has the same length in every lane
-        float *zs = (float *)ord;
-        for (int i = threadIdx.x; i < d; i += blockDim.x) zs[i] = queries[q * d + i];
-        __syncthreads();
+        float *zs = (float *)ord;  // the query lives where the ADC sums go later
         const int ub = shape.ubits, ds = shape.uds;
-        for (int e = threadIdx.x; e < T; e += blockDim.x) {
+        // the first eight codebook values of this thread's first entry travel while the query settles in LDS
+        float c0[8];
+        const float *cp = cb + ((int)threadIdx.x < T ? (size_t)threadIdx.x * ds : 0);
+#pragma unroll
+        for (int l = 0; l < 8; ++l) c0[l] = l < ds ? cp[l] : 0.0f;
+        for (int i = threadIdx.x; i < d; i += NT) zs[i] = queries[q * d + i];
+        __syncthreads();
+        for (int e = threadIdx.x; e < T; e += NT) {
             const int j = e >> ub;
             const float *c = cb + (size_t)e * ds;
             const float *z = zs + j * ds;
             float acc = 0.0f;
-            for (int l = 0; l < ds; ++l) {
-                float diff = __fsub_rn(z[l], c[l]);
-                acc = __fadd_rn(acc, __fmul_rn(diff, diff));
+            if (e == (int)threadIdx.x && ds <= 8) {
+#pragma unroll
+                for (int l = 0; l < 8; ++l)
+                    if (l < ds) {
+                        float diff = __fsub_rn(z[l], c0[l]);
+                        acc = __fadd_rn(acc, __fmul_rn(diff, diff));
+                    }
+            } else {
+                acc = quant_entry(z, c, ds);
             }
             tab[e] = acc;
             esub[e] = (uint8_t)j;
@@ -127,43 +171,21 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
         }
         __syncthreads();
     } else if (queries) {
-        float *zs = (float *)ord;  // the query lives where the ADC sums go later
-        for (int i = threadIdx.x; i < d; i += blockDim.x) zs[i] = queries[q * d + i];
-        for (int e = threadIdx.x; e < T; e += blockDim.x)
-            esub[e] = (uint8_t)(e == (int)threadIdx.x ? ed0.j : edesc[e].j);
-        // the first eight codebook values of this thread's own entry: requested before the
-        // barrier, so that they travel while the query settles in LDS
-        float c0[8];
-#pragma unroll
-        for (int l = 0; l < 8; ++l) c0[l] = ((int)threadIdx.x < T && l < ed0.ds) ? cb[ed0.cb_off + l] : 0.0f;
+        float *zs = (float *)ord;
+        for (int i = threadIdx.x; i < d; i += NT) zs[i] = queries[q * d + i];
         __syncthreads();
-        for (int e = threadIdx.x; e < T; e += blockDim.x) {
-            const bool own = e == (int)threadIdx.x;
-            const EntryDesc ed = own ? ed0 : edesc[e];
-            const int ds = ed.ds;
-            const float *c = cb + ed.cb_off;
-            const float *z = zs + ed.dim_off;
-            float acc = 0.0f;
-            if (own) {
-#pragma unroll
-                for (int l = 0; l < 8; ++l)
-                    if (l < ds) {
-                        float diff = __fsub_rn(z[l], c0[l]);
-                        acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-                    }
-            }
-            for (int l = own ? 8 : 0; l < ds; ++l) {
-                float diff = __fsub_rn(z[l], c[l]);
-                acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-            }
+        for (int e = threadIdx.x; e < T; e += NT) {
+            const EntryDesc ed = e == (int)threadIdx.x ? ed0 : edesc[e];
+            const float acc = quant_entry(zs + ed.dim_off, cb + ed.cb_off, ed.ds);
             tab[e] = acc;
+            esub[e] = (uint8_t)ed.j;
             atomicMin(&pmin_ord[ed.j], qadc_f2ord(acc));
             if (tables_out && first) tables_out[q * T + e] = acc;
         }
         __syncthreads();
     } else {
         __syncthreads();  // pmin_ord is set up
-        for (int e = threadIdx.x; e < T; e += blockDim.x) {
+        for (int e = threadIdx.x; e < T; e += NT) {
             const float v = tables_in[q * T + e];
             const int j = e == (int)threadIdx.x ? ed0.j : edesc[e].j;
             tab[e] = v;
@@ -173,8 +195,9 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
         __syncthreads();
     }
     if ((int)threadIdx.x < m) pmin[threadIdx.x] = qadc_ord2f(pmin_ord[threadIdx.x]);
-    // float ADC of the calibration codes
-    for (int pp = threadIdx.x, r = 0; pp < t_eff; pp += blockDim.x, ++r) {
+    // float ADC of the calibration codes, and on the way their smallest and largest
+    uint32_t omin = 0xffffffffu, omax = 0u;
+    for (int pp = threadIdx.x, r = 0; pp < t_eff; pp += NT, ++r) {
         const uint8_t *code = codes + (size_t)pp * cs;
         float s = 0.0f;
         const uint32_t *cwr = cw[r & 1];  // (r < 2 whenever cal_pre)
@@ -204,11 +227,22 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
             for (int j = 0; j < m; ++j)
                 s = __fadd_rn(s, tab[L->toff[j] + qadc_extract_sub(code, L->bitoff[j], L->nbits[j])]);
         }
-        ord[pp] = qadc_f2ord(s);
+        const uint32_t o = qadc_f2ord(s);
+        ord[pp] = o;
+        omin = o < omin ? o : omin;
+        omax = o > omax ? o : omax;
     }
+    omin = qadc_wave_min(omin);
+    omax = qadc_wave_max(omax);
+    if (threadIdx.x % QADC_WAVE == 0 && omin <= omax) {  // (s_range is set up before the table's barriers)
+        atomicMin(&s_range[0], omin);
+        atomicMax(&s_range[1], omax);
+    }
+    for (int i = threadIdx.x; i < 256; i += NT) hist[i] = 0;
     __syncthreads();
-    if (threadIdx.x < QADC_WAVE) {  // d_min = sum of the minima in fp64, ascending j (m <= 64: one per lane)
-        const double mine = (int)threadIdx.x < m ? (double)pmin[threadIdx.x] : 0.0;
+    if (threadIdx.x >= NT - QADC_WAVE) {  // d_min = sum of the minima in fp64, ascending j (m <= 64: one per lane)
+        const int lane = (int)(threadIdx.x % QADC_WAVE);
+        const double mine = lane < m ? (double)pmin[lane] : 0.0;
         const unsigned long long bits = (unsigned long long)__double_as_longlong(mine);
         double dm = 0.0;
         for (int j = 0; j < m; ++j) {  // (lane reads: no memory involved)
@@ -216,33 +250,29 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
             const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), j);
             dm = dm + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
         }
-        if (threadIdx.x == 0) s_dmin = dm;
+        if (lane == 0) s_dmin = dm;
     }
     float dmax = INFINITY;
-    uint32_t omin = 0xffffffffu;
-    if (btab_rel) {  // the smallest calibration sum
-        for (int i = threadIdx.x; i < t_eff; i += blockDim.x) omin = min(omin, ord[i]);
-        omin = qadc_wave_min(omin);
-        if (threadIdx.x == 0) s_omin = 0xffffffffu;
-    }
-    if (t_eff > 0) dmax = qadc_ord2f(qadc_block_kth_f32(ord, t_eff, k, hist, sel, kmem));
-    if (btab_rel && threadIdx.x % QADC_WAVE == 0) atomicMin(&s_omin, omin);
+    if (t_eff > 0) dmax = qadc_ord2f(qadc_block_kth_f32(ord, t_eff, k, hist, sel, kmem, s_range[0], s_range[1]));
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double delta = ((double)dmax - s_dmin) / (double)qmax;
-        bool ok = (delta > 0.0) && isfinite(delta);
-        s_delta = ok ? delta : 0.0;
-        s_dmax = dmax;
-        if (btab_rel)
-            s_scale = mx_scale_of(ok && t_eff > 0 ? (float)(((double)qadc_ord2f(s_omin) - s_dmin) / delta) : (float)qmax, (uint32_t)qmax);
-    }
-    __syncthreads();
-    const double delta = s_delta;
-    for (int e = threadIdx.x; e < T; e += blockDim.x) {
-        const int j = esub[e];
+    // (every thread divides: no barrier behind one that does)
+    const double dmin = s_dmin;
+    double delta = ((double)dmax - dmin) / (double)qmax;
+    const bool ok = (delta > 0.0) && isfinite(delta);
+    delta = ok ? delta : 0.0;
+    const uint32_t mx_scale = btab_rel ? mx_scale_of(ok && t_eff > 0 ? (float)(((double)qadc_ord2f(s_range[0]) - dmin) / delta) : (float)qmax, (uint32_t)qmax) : 0u;
+    // floor((p - p_min) / delta) in fp32 where that cannot differ: the fp32 value is off by at most 3 * 2^-24 of
+    // itself (difference, reciprocal and product are each rounded once); where a whole number is within twice
+    // that, or delta is not of ordinary size, the division is done in fp64.  (16-bit tables: too few bits are left.)
+    const float inv = sizeof(QT) == 1 && delta > 1e-30 && delta < 1e30 ? (float)(1.0 / delta) : 0.0f;
+    for (int e = threadIdx.x; e < T; e += NT) {
+        const float p = tab[e], pm = pmin[esub[e]];
         uint32_t qv = 0;
-        if (delta > 0.0) {
-            double x = floor(((double)tab[e] - (double)pmin[j]) / delta);
+        const float xf = (p - pm) * inv;
+        if (inv > 0.0f && (xf >= 255.5f || fmaf(xf, 3.6e-7f, fabsf(__builtin_amdgcn_fractf(xf) - 0.5f)) < 0.5f)) {
+            qv = (uint32_t)fminf(xf, 255.0f);
+        } else if (delta > 0.0) {
+            double x = floor(((double)p - (double)pm) / delta);
             qv = (x >= (double)qmax) ? (uint32_t)qmax : (uint32_t)x;
         }
         qt[e] = (uint16_t)qv;
@@ -259,17 +289,17 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
         build_gtab<KIND, QT>(L, qt, gtab);
         if (gtab_out && first) {  // hand the prepared group tables to the scan kernel
             QT *dst = (QT *)(gtab_out + q * gtab_stride);
-            for (int e = threadIdx.x; e < L->gtab_len; e += blockDim.x) dst[e] = gtab[e];
+            for (int e = threadIdx.x; e < L->gtab_len; e += NT) dst[e] = gtab[e];
             if (btab_rel) {
-                build_btab(L, qt, s_scale, (uint32_t *)(gtab_out + q * gtab_stride + btab_rel));
-                if (threadIdx.x == 0) ((ScanHdr *)(hdr_out + q * gtab_stride))->scale = s_scale;
+                build_btab(L, qt, mx_scale, (uint32_t *)(gtab_out + q * gtab_stride + btab_rel));
+                if (threadIdx.x == 0) ((ScanHdr *)(hdr_out + q * gtab_stride))->scale = mx_scale;
             }
         }
     }
     if (hdr_out && first) scan_hdr_clear((ScanHdr *)(hdr_out + q * gtab_stride));  // empty candidate lists
     if (pilot > 0) {
         const int shift = sizeof(QT) == 1 ? 0 : 8;
-        for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
+        for (int i = threadIdx.x; i < 256; i += NT) hist[i] = 0;
         __syncthreads();
         // count one key (0xffffffff = none); the top bin collects every saturated key and
         // is counted once per wave
@@ -284,14 +314,15 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
                 if (base != lo) {
 #pragma unroll
                     for (int u = 0; u < PPT; ++u) {
-                        int id = base + u * (int)blockDim.x + (int)threadIdx.x;
+                        int id = base + u * NT + (int)threadIdx.x;
                         id = id < hi ? id : hi - 1;
                         pc[u] = *(const uint2 *)(codes + (size_t)id * 8);
                     }
                 }
 #pragma unroll
                 for (int u = 0; u < PPT; ++u) {
-                    const int id = base + u * (int)blockDim.x + (int)threadIdx.x;
+                    if (base + u * NT >= hi) break;
+                    const int id = base + u * NT + (int)threadIdx.x;
                     const uint32_t sm = sum8(gtab, pc[u].x, pc[u].y);
                     count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu);
                 }
@@ -302,31 +333,32 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
             const GroupDesc gd = load_group_desc(L);
             for (int base = lo; base < hi; base += step) {
                 if (KIND == SCAN_W64) {
-                    uint2 w[8];
+                    uint2 w[PPT];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        int id = base + u * (int)blockDim.x + (int)threadIdx.x;
+                    for (int u = 0; u < PPT; ++u) {
+                        int id = base + u * NT + (int)threadIdx.x;
                         id = id < hi ? id : hi - 1;
                         w[u] = *(const uint2 *)(codes + (size_t)id * 8);
                     }
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int id = base + u * (int)blockDim.x + (int)threadIdx.x;
+                    for (int u = 0; u < PPT; ++u) {
+                        if (base + u * NT >= hi) break;
+                        const int id = base + u * NT + (int)threadIdx.x;
                         const uint32_t sm = sum_groups_rt(gd, gtab, w[u].x, w[u].y);
                         count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu);
                     }
                 } else {
-                    uint32_t c5[2][5];
+                    uint32_t c5[PPT / 4][5];
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int id = base + 4 * (u * (int)blockDim.x + (int)threadIdx.x);
+                    for (int u = 0; u < PPT / 4; ++u) {
+                        const int id = base + 4 * (u * NT + (int)threadIdx.x);
 #pragma unroll
                         for (int i = 0; i < 5; ++i)  // a chunk not wholly inside is handled code by code
                             c5[u][i] = id + 3 < hi ? ((const uint32_t *)(codes + (size_t)id * 5))[i] : 0u;
                     }
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int id = base + 4 * (u * (int)blockDim.x + (int)threadIdx.x);
+                    for (int u = 0; u < PPT / 4; ++u) {
+                        const int id = base + 4 * (u * NT + (int)threadIdx.x);
                         uint32_t k4[4];
                         if (id + 3 < hi) {
                             // code v = bits [40v, 40v+40) of the chunk, as (low dword, high byte)
@@ -353,11 +385,11 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
             }
         } else {
             for (int base = lo; base < hi; base += step) {
-                uint32_t key[8];
-                keys_batch<KIND, QT, 8>(L, gtab, codes, (int64_t)base + threadIdx.x, blockDim.x,
+                uint32_t key[PPT];
+                keys_batch<KIND, QT, PPT>(L, gtab, codes, (int64_t)base + threadIdx.x, NT,
                                         (int64_t)hi, key);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) count_key(key[u]);
+                for (int u = 0; u < PPT; ++u) count_key(key[u]);
             }
         }
         __syncthreads();
@@ -379,9 +411,9 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     if (!first) return;
     if (threadIdx.x == 0) {
         pq_qparams_t prm;
-        prm.d_min = s_dmin;
-        prm.delta = s_delta;
-        prm.d_max = s_dmax;
+        prm.d_min = dmin;
+        prm.delta = delta;
+        prm.d_max = dmax;
         prm.key_bound = bound;
         qparams[q] = prm;
     }
@@ -390,6 +422,9 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
 // Codes one pilot block counts per batch (eight per thread) and at most in total.
 #define PILOT_BATCH (8 * QUANT_THREADS)
 #define PILOT_BLOCK_MAX 65536
+// Pilot codes per result of long lists: 32 x 4 bits, 2 * 10^7 codes, R = 1000, whole call: 512 100.6 us, 1024 96.3, 2048 95.2, 4096 102.8
+// (fewer candidates to gather against more codes to count).
+#define PILOT_PER_RESULT 1024
 
 int qadc_pilot_blocks_max(int nq) {
     const int64_t cap = qadc_option(PQ_OPT_PILOT_BLOCKS);
@@ -418,7 +453,7 @@ PilotPlan qadc_pilot_plan(int nq, int64_t n, int t_eff, int R, bool have_scratch
     if (multi > 262144 && multi > per_block * pmax) multi = per_block * pmax > 262144 ? per_block * pmax : 262144;
     int64_t want = pmax > 1 ? multi : single;
     // the candidates the scan keeps grow with R / pilot: long result lists get a longer pilot
-    if (pmax > 1 && want < 512 * (int64_t)R) want = 512 * (int64_t)R;
+    if (pmax > 1 && want < PILOT_PER_RESULT * (int64_t)R) want = PILOT_PER_RESULT * (int64_t)R;
     if (want > (int64_t)pmax * PILOT_BLOCK_MAX) want = (int64_t)pmax * PILOT_BLOCK_MAX;
     if (want < 64 * (int64_t)R) want = 64 * (int64_t)R;
     if (want < t_eff) want = t_eff;
@@ -441,25 +476,34 @@ static size_t quantize_lds(const DevLayout &h, int t_eff, size_t esz) {
            (size_t)h.gtab_len * esz;
 }
 
+// Wide blocks while at most two of them share a CU.  k_quantize, 256 / 1024 threads: 16 x 4 bits, 10^7 codes, R = 100, 1 query
+// (128 blocks) 11.0 / 8.6 us; 32 x 4 bits, 2 * 10^7 codes, R = 1000 (4000 calibration codes) 29 / 18.8 us, with twice the
+// pilot; {6,5,5,6,5,5,4,4} 21 / 13.8 us; {6,6,4} x 4, 32 queries 22 / 15.2 us.  A thousand queries, one block each: 95 us with 256.
+static bool quantize_wide(int64_t blocks) { return blocks <= 512; }
+
 template <int KIND, typename QT>
 static int launch_quantize(const pq_index *idx, const float *queries, const float *tables_in,
                            float *tables_out, int nq, const uint8_t *codes, int t_eff, int k,
                            const PilotPlan &pp, void *qtables, pq_qparams_t *qparams, char *gtab_out,
                            size_t gtab_stride, size_t btab_rel, char *hdr_out, uint16_t *bound_rec, hipStream_t s) {
     const size_t lds = quantize_lds(idx->h, t_eff, sizeof(QT));
-    if (lds > 48 * 1024)
-        QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_quantize<KIND, QT>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     int ubits = idx->h.nbits[0], uds = idx->h.dsub[0];
     for (int j = 1; j < idx->h.m; ++j) {
         if (idx->h.nbits[j] != ubits) ubits = 0;
         if (idx->h.dsub[j] != uds) uds = 0;
     }
-    hipLaunchKernelGGL((k_quantize<KIND, QT>), dim3((unsigned)nq * (unsigned)pp.P), dim3(QUANT_THREADS), lds, s,
-                       idx->dev, QuantShape{idx->h.T, idx->h.m, idx->h.cs, idx->h.qmax, idx->h.d, ubits, uds}, idx->edesc,
-                       idx->codebooks, queries, tables_in, tables_out, codes, t_eff, k,
-                       pp.pilot, pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, btab_rel,
-                       hdr_out, bound_rec);
+#define QADC_QUANT_GO(NT)                                                                                         \
+    do {                                                                                                          \
+        if (lds > 48 * 1024)                                                                                      \
+            QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_quantize<KIND, QT, NT>,                              \
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));              \
+        hipLaunchKernelGGL((k_quantize<KIND, QT, NT>), dim3((unsigned)nq * (unsigned)pp.P), dim3(NT), lds, s,     \
+                           idx->dev, QuantShape{idx->h.T, idx->h.m, idx->h.cs, idx->h.qmax, idx->h.d, ubits, uds}, \
+                           idx->edesc, idx->codebooks, queries, tables_in, tables_out, codes, t_eff, k, pp.pilot, \
+                           pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, btab_rel, hdr_out, bound_rec); \
+    } while (0)
+    if (quantize_wide((int64_t)nq * pp.P)) QADC_QUANT_GO(QUANT_WIDE); else QADC_QUANT_GO(QUANT_THREADS);
+#undef QADC_QUANT_GO
     QADC_LAUNCH_CHECK("k_quantize");
     return PQ_OK;
 }

@@ -983,11 +983,17 @@ __device__ inline void rank_and_write(SelectLds<NT, ACAP> &S, int na, int R, con
     const uint64_t *A = S.A;
     if (na <= 512) {
         // few candidates (the usual case): every candidate counts the smaller ones; all lanes
-        // read the same entry at a time
+        // read the same four entries at a time (the list is filled up with largest ones)
+        if (threadIdx.x < 4) S.A[na + threadIdx.x] = ~0ull;
+        __syncthreads();
         for (int i = threadIdx.x; i < na; i += NT) {
             const uint64_t mine = A[i];
             int r = 0;
-            for (int j = 0; j < na; ++j) r += (A[j] < mine) ? 1 : 0;
+#pragma unroll 4
+            for (int j = 0; j < na; j += 4) {
+                const ulonglong2 a = *(const ulonglong2 *)&A[j], b = *(const ulonglong2 *)&A[j + 2];
+                r += (a.x < mine ? 1 : 0) + (a.y < mine ? 1 : 0) + (b.x < mine ? 1 : 0) + (b.y < mine ? 1 : 0);
+            }
             if (r < R) {
                 const uint32_t key = (uint32_t)(mine >> 32);
                 o.ids[r] = (int32_t)(uint32_t)mine;
@@ -1028,6 +1034,7 @@ __device__ inline void rank_and_write(SelectLds<NT, ACAP> &S, int na, int R, con
             const int gs = (int)start[b], ge = gs + (int)cnt[b];
             int r = gs;
             if (gs < R) {  // (a whole bin at or beyond rank R cannot hold a result)
+#pragma unroll 8
                 for (int j = gs; j < ge; ++j) r += (A[S.order[j]] < mine) ? 1 : 0;
                 if (r < R) {
                     const uint32_t key = (uint32_t)(mine >> 32);
