@@ -11,6 +11,9 @@
 // codebooks of up to 16 KB are read from memory with scalar loads (they stay in the scalar cache), larger
 // ones are staged in LDS when they fit (one word broadcast to 64 lanes).  A second step packs.
 //
+// 16 and 32 sub-quantizers of 4 bits over equal sub-spaces have a kernel of their own on the matrix cores
+// (k_encode_mx); what follows is about the rest.
+//
 // Bound by the vector units: eq. (1) term by term is three operations per dimension and centroid.  Where
 // it pays (enc_form) the nearest centroid of a sub-space of up to 8 dimensions is found from ||x||^2 + ||c||^2 - 2 x.c, one fused
 // multiply-add per dimension; the distances of eq. (1) themselves are computed only in waves that hold a
@@ -23,6 +26,7 @@
 #include "qadc_device.h"
 
 #define ENC_VB 64  // vectors per tile
+#define ENC_MX_BLOCKS 3  // of a CU, which run over the tiles (matrix form)
 #define ENC_PF 8   // 16-byte pieces of a tile a thread holds: d <= 128
 typedef float enc_f4 __attribute__((ext_vector_type(4)));
 
@@ -279,11 +283,188 @@ k_encode(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc, c
     }
 }
 
+// ------------------------------------------------------- on the matrix cores ---
+// M sub-quantizers of 4 bits over DS dimensions each.  The expanded form's products are a matrix product of a
+// sub-quantizer's 16 centroids and 16 vectors, which the fp32 matrix instruction takes four dimensions at a time (a
+// chain of fused multiply-adds in ascending order).  A wave encodes tiles of 16 vectors by itself, staged in rows of
+// its own in LDS and read as lane (vector l % 16, dimension l / 16 of four); the centroids stay in its registers
+// (times -2).  A lane gets the values of four centroids for one vector; with their index in the low four bits the two
+// smallest of the 16 take seven minima and maxima and, for four sub-quantizers together, fifteen operations across
+// lanes, which leave lane (v, g) with vector v and sub-quantizer {0, 2, 1, 3}[g] of the four.  Near ties are decided
+// by eq. (1) as in enc_nearest_fast; the offset that keeps values above zero is the whole vector's norm here.
+// What bounds it: memory, behind it minima and packing on the vector units (137 instructions a wave per 1024 values, 57 % of the
+// time) and the products (28 %), which three wavefronts per SIMD do not quite overlap (minima a sub-quantizer behind its
+// products did not either).  10^7 vectors, d = 96, 16 x 4 bits: 960 us (4.08 TB/s; a copy of this card's memory runs at 4.8),
+// 1185 with the expanded form on the vector units; two and four wavefronts per SIMD 1110 and 1066.
+typedef float enc_v4f __attribute__((ext_vector_type(4)));
+template <int M, int DS>
+struct EncMxLds {
+    static constexpr int D = M * DS, ROW = D + 4;  // a row is an odd multiple of four floats: no bank conflicts
+    float xs[4][16][ROW];
+    float cb[M * 16 * DS];
+    float nrm[M][16];
+    uint32_t nmax[M];
+};
+template <int M, int DS>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ENC_MX_BLOCKS)))
+k_encode_mx(const float *__restrict__ cb, const float *__restrict__ x, int64_t n, const float *__restrict__ shift_rows,
+            const int32_t *__restrict__ shift_ids, uint8_t *__restrict__ codes, int64_t ntiles) {
+    constexpr int KK = (DS + 3) / 4, D = M * DS, D4 = D / 4, PF = D4 * 16 / 64;
+    static_assert(D % 16 == 0 && M % 4 == 0 && M <= 32, "rows of whole 16-byte pieces, groups of four sub-quantizers");
+    typedef EncMxLds<M, DS> Lds;
+    __shared__ __align__(16) Lds S;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int v = lane & 15, g = lane >> 4;
+    for (int e = threadIdx.x; e < M * 16 * DS; e += 256) S.cb[e] = cb[e];
+    if (threadIdx.x < M) S.nmax[threadIdx.x] = 0;
+    S.xs[w][v][D + g] = 0.0f;  // (read as the missing dimensions of the last sub-quantizer)
+    __syncthreads();
+    for (int e = threadIdx.x; e < M * 16; e += 256) {
+        float s = 0.0f;
+#pragma unroll
+        for (int l = 0; l < DS; ++l) s = __fmaf_rn(S.cb[e * DS + l], S.cb[e * DS + l], s);
+        (&S.nrm[0][0])[e] = s;
+        atomicMax(&S.nmax[e >> 4], __float_as_uint(s));
+    }
+    float a[M][KK];
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) a[j][kk] = 4 * kk + g < DS ? -2.0f * S.cb[(j * 16 + v) * DS + 4 * kk + g] : 0.0f;
+    __syncthreads();
+    float (*xs)[Lds::ROW] = S.xs[w];
+    enc_f4 nx[PF];
+    auto request = [&](int64_t tile) {  // (rows past the end: the last one again)
+        const int64_t left = n - tile * 16;
+        const int rows = left < 16 ? (int)left : 16;
+        const enc_f4 *src = (const enc_f4 *)(x + (size_t)tile * 16 * D);
+#pragma unroll
+        for (int i = 0; i < PF; ++i) {
+            const int e = i * 64 + lane;
+            nx[i] = __builtin_nontemporal_load(src + (rows == 16 ? e : min(e / D4, rows - 1) * D4 + e % D4));
+        }
+    };
+    const int64_t stride = (int64_t)gridDim.x * 4;
+    int64_t tile = (int64_t)blockIdx.x * 4 + w;
+    if (tile < ntiles) request(tile);
+    const uint32_t idx0 = 4u * (uint32_t)g;
+    const int sub = g == 1 ? 2 : (g == 2 ? 1 : g);  // of a group of four: the one this lane ends up with
+    for (; tile < ntiles; tile += stride) {
+        const int64_t v0 = tile * 16;
+#pragma unroll
+        for (int i = 0; i < PF; ++i) {
+            const int e = i * 64 + lane, r = e / D4, l4 = e % D4;
+            enc_f4 val = nx[i];
+            if (shift_rows) {
+                const int64_t row = v0 + r < n ? v0 + r : n - 1;
+                const enc_f4 s = *(const enc_f4 *)(shift_rows + (size_t)shift_ids[row] * D + 4 * l4);
+                val.x = __fsub_rn(val.x, s.x);
+                val.y = __fsub_rn(val.y, s.y);
+                val.z = __fsub_rn(val.z, s.z);
+                val.w = __fsub_rn(val.w, s.w);
+            }
+            *(enc_f4 *)&xs[r][4 * l4] = val;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the rows are this wave's own)
+        if (tile + stride < ntiles) request(tile + stride);
+        float b[M][KK], xx = 0.0f;
+#pragma unroll
+        for (int j = 0; j < M; ++j)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                b[j][kk] = xs[v][j * DS + 4 * kk + g];
+                xx = __fmaf_rn(b[j][kk], b[j][kk], xx);  // (some dimensions count twice: a bound is all it has to be)
+            }
+        {
+            auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(xx), __float_as_uint(xx), false, false);
+            xx = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+            r = __builtin_amdgcn_permlane16_swap(__float_as_uint(xx), __float_as_uint(xx), false, false);
+            xx = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+        uint32_t word[M / 8];
+#pragma unroll
+        for (int i = 0; i < M / 8; ++i) word[i] = 0;
+#pragma unroll
+        for (int q = 0; q < M / 4; ++q) {
+            // S bounds |2 x.c| and half of any distance of these sub-quantizers (nmax: of the largest of them)
+            const uint4 nm4 = *(const uint4 *)&S.nmax[4 * q];
+            const float Sb = xx + __uint_as_float(max(max(nm4.x, nm4.y), max(nm4.z, nm4.w)));
+            const float off = __fmaf_rn(Sb, 1.0f / 65536.0f, xx);
+            uint32_t m1[4], m2[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int j = 4 * q + u;
+                const float4 n4 = *(const float4 *)&S.nrm[j][4 * g];
+                enc_v4f acc = {n4.x + off, n4.y + off, n4.z + off, n4.w + off};
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j][kk], b[j][kk], acc, 0, 0, 0);
+                uint32_t k[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) k[i] = (__float_as_uint(acc[i]) & ~15u) | (idx0 + (uint32_t)i);
+                const uint32_t lo0 = min(k[0], k[1]), hi0 = max(k[0], k[1]), lo1 = min(k[2], k[3]), hi1 = max(k[2], k[3]);
+                m1[u] = min(lo0, lo1);
+                m2[u] = min(min(hi0, hi1), max(lo0, lo1));
+            }
+            auto merge32 = [](uint32_t &p1, uint32_t &p2, uint32_t q1, uint32_t q2) {
+                const auto r1 = __builtin_amdgcn_permlane32_swap(p1, q1, false, false), r2 = __builtin_amdgcn_permlane32_swap(p2, q2, false, false);
+                p1 = min((uint32_t)r1[0], (uint32_t)r1[1]);
+                p2 = min(min((uint32_t)r2[0], (uint32_t)r2[1]), max((uint32_t)r1[0], (uint32_t)r1[1]));
+            };
+            merge32(m1[0], m2[0], m1[1], m2[1]);
+            merge32(m1[2], m2[2], m1[3], m2[3]);
+            const auto r1 = __builtin_amdgcn_permlane16_swap(m1[0], m1[2], false, false), r2 = __builtin_amdgcn_permlane16_swap(m2[0], m2[2], false, false);
+            const uint32_t k1 = min((uint32_t)r1[0], (uint32_t)r1[1]);
+            const uint32_t k2 = min(min((uint32_t)r2[0], (uint32_t)r2[1]), max((uint32_t)r1[0], (uint32_t)r1[1]));
+            // Roundings: at most DS + 3 of the expanded form and DS + 2 of eq. (1), each 2^-24 of at most 2 S (one more
+            // for the roundings of S itself), for two values; the dropped bits: 2^-19 of a value.  (Sums near the
+            // smallest normal numbers round otherwise: S > 1e-30.)
+            constexpr float ROUND = (2 * DS + 6) * 4 / 16777216.0f;
+            const float f1 = __uint_as_float(k1 & ~15u), f2 = __uint_as_float(k2 & ~15u);
+            const bool clear = Sb > 1e-30f && f2 - f1 > __fmaf_rn(f2, 1.0f / 262144.0f, Sb * ROUND);
+            int besti = (int)(k1 & 15u);
+            if (__ballot(!clear) != 0) {
+                if (!clear) {
+                    float best = INFINITY;
+                    enc_nearest<DS>(&xs[v][(4 * q + sub) * DS], &S.cb[(4 * q + sub) * 16 * DS], 16, best, besti);
+                }
+            }
+            word[q >> 1] |= (uint32_t)besti << (16 * (q & 1) + 4 * sub);
+        }
+        // a vector's words, from its four lanes; lane (v, g) stores word g (and g + 4)
+#pragma unroll
+        for (int i = 0; i < M / 8; ++i) {
+            auto r = __builtin_amdgcn_permlane32_swap(word[i], word[i], false, false);
+            word[i] = (uint32_t)r[0] | (uint32_t)r[1];
+            r = __builtin_amdgcn_permlane16_swap(word[i], word[i], false, false);
+            word[i] = (uint32_t)r[0] | (uint32_t)r[1];
+        }
+        if (v0 + v < n) {
+            uint32_t *dst = (uint32_t *)(codes + (size_t)(v0 + v) * (M / 2));
+#pragma unroll
+            for (int i = 0; i < M / 8; ++i)
+                if (i == g) dst[i] = word[i];
+        }
+    }
+}
+
+// The matrix form takes 16 or 32 sub-quantizers of 4 bits over equal sub-spaces; vectors and shifts are read in
+// 16-byte pieces.  At every size and on both kinds of data it was the
+// faster one, us, expanded form on the vector units / here: 16 x 4 bits, d = 96: 1000 vectors 10.8 / 9.5, 2 * 10^6 250 / 212; d = 128:
+// 287 / 233; 32 x 4 bits, d = 96: 365 / 297, integer-valued data 364 / 341 (near ties); d = 128: 368 / 318.
+static int enc_mx_width(const pq_index *idx, bool vec, bool nib) {
+    const DevLayout &h = idx->h;
+    if (!vec || !nib || h.ds_uniform == 0 || h.d != h.m * h.ds_uniform) return 0;
+    if (h.kind == SCAN_NIB8 && (h.ds_uniform == 4 || h.ds_uniform == 6 || h.ds_uniform == 8)) return h.ds_uniform;
+    if (h.kind == SCAN_NIB16 && (h.ds_uniform == 3 || h.ds_uniform == 4)) return h.ds_uniform;
+    return 0;
+}
+
 // Which form a call takes: FAST = the expanded form (its norms are taken once per block, of up to 4096 that
 // run over the tiles); AHEAD = a tile requested while the one before is encoded (32 registers, which halve the
 // wavefronts of a SIMD to four).  Without both every tile has a block of its own.  Times in us, of 10^6
 // vectors unless said, FAST + AHEAD / AHEAD / neither:
-//   16 x 4 bits, d = 96: 129 / 132 / 140 (232 with loads of one value each); d = 128: 148 / 159 / 209
+//   16 x 4 bits, d = 96 (where vectors or codes are not aligned for the matrix form): 129 / 132 / 140 (232 with loads of
+//   one value each); d = 128: 148 / 159 / 209
 //   {6,6,4} x 8, d = 128: 915 / 1009 / 1130; 2 * 10^5 vectors: 238 / 241 / 241
 //   16 x 8 bits, d = 128: 2000 / 2177 / 3190; d = 96: 1759 / 1742 / 1464
 //   8 x 8 bits (sub-spaces of 12 and 16 dimensions), d = 96: 5041 / 5230 / 4099; d = 128: 8273 / 6818 / 6441
@@ -330,6 +511,23 @@ extern "C" int pq_encode(const pq_index_t *idx, const float *vectors, int64_t n,
         return PQ_EINVAL;
     }
     const DevLayout &h = idx->h;
+    const int vec = h.d % 4 == 0 && (((uintptr_t)vectors | (uintptr_t)shift_rows) & 15u) == 0;
+    const int nib = (h.kind == SCAN_NIB8 || h.kind == SCAN_NIB16) && ((uintptr_t)codes & 3u) == 0;
+    if (const int ds = enc_mx_width(idx, vec != 0, nib != 0)) {
+        const int64_t tiles = (n + 15) / 16, most = 256 * ENC_MX_BLOCKS;
+        const unsigned grid = (unsigned)((tiles + 3) / 4 < most ? (tiles + 3) / 4 : most);
+#define ENC_MX_GO(M, DS)                                                                                         \
+    hipLaunchKernelGGL((k_encode_mx<M, DS>), dim3(grid), dim3(256), 0, (hipStream_t)stream, idx->codebooks,       \
+                       vectors, n, shift_rows, shift_ids, codes, tiles)
+        if (h.kind == SCAN_NIB8) {
+            if (ds == 4) ENC_MX_GO(16, 4); else if (ds == 6) ENC_MX_GO(16, 6); else ENC_MX_GO(16, 8);
+        } else {
+            if (ds == 3) ENC_MX_GO(32, 3); else ENC_MX_GO(32, 4);
+        }
+#undef ENC_MX_GO
+        QADC_LAUNCH_CHECK("k_encode_mx");
+        return PQ_OK;
+    }
     size_t cbf = 0;  // codebook floats
     for (int j = 0; j < h.m; ++j) cbf += ((size_t)1 << h.nbits[j]) * (size_t)h.dsub[j];
     const size_t base_lds = (size_t)ENC_VB * (size_t)(h.d | 1) * sizeof(float) + (size_t)ENC_VB * (size_t)h.m;
@@ -342,7 +540,6 @@ extern "C" int pq_encode(const pq_index_t *idx, const float *vectors, int64_t n,
         qadc_set_error("pq_encode: n=%lld too large for one call", (long long)n);
         return PQ_EINVAL;
     }
-    const int vec = h.d % 4 == 0 && (((uintptr_t)vectors | (uintptr_t)shift_rows) & 15u) == 0;
     size_t nrm_words = (size_t)((h.T + 3) & ~3) + (size_t)((h.m + 3) & ~3);
     const EncForm f = enc_form(h, blocks, lds, nrm_words * sizeof(float), vec != 0);
     if (!f.fast) nrm_words = 0;
@@ -351,7 +548,6 @@ extern "C" int pq_encode(const pq_index_t *idx, const float *vectors, int64_t n,
         qadc_set_error("pq_encode: d=%d needs %zu bytes of LDS per block, more than 163840", h.d, lds);
         return PQ_EINVAL;
     }
-    const int nib = (h.kind == SCAN_NIB8 || h.kind == SCAN_NIB16) && ((uintptr_t)codes & 3u) == 0;
     const int64_t grid = f.fast || f.ahead ? (blocks < 256 * 16 ? blocks : 256 * 16) : blocks;
 #define ENC_GO(FAST, AHEAD)                                                                                       \
     do {                                                                                                          \

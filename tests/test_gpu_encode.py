@@ -189,3 +189,33 @@ def test_encode_forms_and_second_tiles(qb, d, nbits, n, shift):
     flat[1:] = xs.view(-1)
     assert torch.equal(qb.pq_encode(idx, flat[1:].view(n, d), *sh), want)
     idx.close()
+
+
+@pytest.mark.parametrize("d,m", [(64, 16), (96, 16), (128, 16), (96, 32), (128, 32)])
+@pytest.mark.parametrize("kind", ["skewed", "integer", "unbounded"])
+def test_encode_matrix_form(qb, d, m, kind):
+    """The products on the matrix cores: counts around a wave's tile of 16 vectors and around its second tile
+    (3072 waves), sub-spaces of very different size (what decides is small beside the vector's norm), many equal
+    distances, and vectors with infinities and NaN in one sub-space, which must not touch the others."""
+    lay = synth.make_layout(d, [4] * m, 16)
+    rng = np.random.default_rng(d + m)
+    ds = d // m
+    cb = rng.normal(size=(m, 16, ds)).astype(np.float32)
+    x = rng.normal(size=(700, m, ds)).astype(np.float32)
+    if kind == "skewed":
+        s = np.float32(10.0) ** rng.integers(-9, 10, (m, 1))
+        cb, x = cb * s[:, None, :], x * s[None]
+    elif kind == "integer":
+        cb, x = np.round(2 * cb), np.round(2 * x)
+    else:
+        x[::3, 1, 0] = np.inf
+        x[1::3, m - 1, ds - 1] = -np.inf
+        cb[2, 5] = 3e38
+    cb, x = cb.astype(np.float32).reshape(-1), x.astype(np.float32).reshape(700, d)
+    with np.errstate(all="ignore"):
+        want = torch.from_numpy(oracle.encode(d, lay.nbits, lay.dsub, cb, x)).to(dev())
+    idx = qb.PqIndex(lay.d, lay.nbits, lay.dsub, torch.from_numpy(cb).to(dev()), 8)
+    for n in (1, 15, 16, 17, 63, 64, 65, 3072 * 16 + 1, 3 * 3072 * 16 - 5):
+        pick = torch.arange(n, device=dev()) % 700
+        assert torch.equal(qb.pq_encode(idx, torch.from_numpy(x).to(dev())[pick].contiguous()), want[pick]), n
+    idx.close()
