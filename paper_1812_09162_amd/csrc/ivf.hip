@@ -118,7 +118,7 @@ __device__ inline bool ivf_setup(const DevLayout *L, const EntryDesc *__restrict
 }
 
 // The same for the fixed shape 16 x 4 bits over sub-spaces of DS dimensions each (T = 256,
-// d = 16 DS) by a block of 256 threads: thread e holds table entry e = centroid e % 16 of
+// d = 16 DS) by a block of at least 256 threads: thread e < 256 holds table entry e = centroid e % 16 of
 // sub-quantizer e / 16 at codebook offset e * DS, so nothing is looked up, the minima come
 // from lane exchanges, and the codebook values travel while the residual settles in LDS.
 // cv: the thread's codebook values; ze, ce: dimension e of the query and of the centroid (e < d).
@@ -129,21 +129,23 @@ __device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, 
     const int e = threadIdx.x;
     if (e < d) l.zres[e] = __fsub_rn(ze, ce);
     __syncthreads();
-    const float *zz = l.zres + (e >> 4) * DS;
     float acc = 0.0f;
+    if (e < 256) {  // (whole waves)
+        const float *zz = l.zres + (e >> 4) * DS;
 #pragma unroll
-    for (int t = 0; t < DS; ++t) {
-        const float diff = __fsub_rn(zz[t], cv[t]);
-        acc = __fadd_rn(acc, __fmul_rn(diff, diff));
-    }
-    l.tab[e] = acc;
-    float mn = acc;
+        for (int t = 0; t < DS; ++t) {
+            const float diff = __fsub_rn(zz[t], cv[t]);
+            acc = __fadd_rn(acc, __fmul_rn(diff, diff));
+        }
+        l.tab[e] = acc;
+        float mn = acc;
 #pragma unroll
-    for (int sft = 1; sft < 16; sft <<= 1) {
-        const float o = __shfl_xor(mn, sft, QADC_WAVE);
-        mn = o < mn ? o : mn;
+        for (int sft = 1; sft < 16; sft <<= 1) {
+            const float o = __shfl_xor(mn, sft, QADC_WAVE);
+            mn = o < mn ? o : mn;
+        }
+        if ((e & 15) == 0) l.pmin[e >> 4] = mn;
     }
-    if ((e & 15) == 0) l.pmin[e >> 4] = mn;
     __syncthreads();
     if (e == 0) {
         double dm = 0.0;
@@ -163,12 +165,14 @@ __device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, 
     if (!quantize) return true;
     if (*l.flag) return false;
     const double delta = l.sc[1];
-    uint32_t qv = 0;
-    if (delta > 0.0) {
-        const double x = floor(((double)acc - (double)l.pmin[e >> 4]) / delta);
-        qv = (x >= (double)qmax) ? qmax : (uint32_t)x;
+    if (e < 256) {
+        uint32_t qv = 0;
+        if (delta > 0.0) {
+            const double x = floor(((double)acc - (double)l.pmin[e >> 4]) / delta);
+            qv = (x >= (double)qmax) ? qmax : (uint32_t)x;
+        }
+        l.qt[e] = (uint16_t)qv;
     }
-    l.qt[e] = (uint16_t)qv;
     __syncthreads();
     return true;
 }
@@ -181,7 +185,7 @@ __device__ inline bool ivf_setup_fix(const float *__restrict__ cb, const float *
     const int e = threadIdx.x;
     float cv[DS];
 #pragma unroll
-    for (int t = 0; t < DS; ++t) cv[t] = cb[e * DS + t];
+    for (int t = 0; t < DS; ++t) cv[t] = e < 256 ? cb[e * DS + t] : 0.0f;
     return ivf_setup_fix<DS>(cv, e < 16 * DS ? z[e] : 0.0f, e < 16 * DS ? cen[e] : 0.0f, dmax, quantize, qmax, l);
 }
 
@@ -192,6 +196,11 @@ __device__ __forceinline__ uint32_t dist_bin(float dist, float lo, float scale) 
 
 // ------------------------------------------------------------ k_ivf_calib ---
 #define CALIB_PC 64      // probes whose cell and list bounds the block keeps in LDS
+// Queries up to which the calibration runs blocks of 1024 threads (its time is then a block's chain of steps, in which
+// the pilot's look-ups and the selections take a third as long); a call's us, blocks of 256 / 1024, 32 probes: 16 x 4 bits,
+// 1 query 41.2 / 36.5, 256 98.6 / 93.3, 400 117.7 / 113.0, 1024 186 / 201; {6,5,5} x 4: 1 99 / 69, 400 295 / 292, 1024 607 / 620;
+// 8 x 8: 1 167 / 118, 400 591 / 590, 512 703 / 731.
+#define CALIB_WIDE_QUERIES 384
 #define CALIB_EARLY1 2   // codes per thread requested before the set-up, calibration pass
 #define CALIB_EARLY2 4   // the same, pilot pass
 
@@ -218,8 +227,8 @@ __device__ __forceinline__ void calib_list(int a, const int32_t *__restrict__ pr
 // for pairs without a list, zero on entry; the block adds its query's pairs.
 // bounds (or null): d_max and thr0 of every query once more, side by side (k_ivf_scan_mx reads those of many
 // queries per block, and in the workspace they are pages apart).
-template <bool NIB, int DS = 0>
-__global__ void __launch_bounds__(256)
+template <bool NIB, int DS, int NT>
+__global__ void __launch_bounds__(NT)
 k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
             const float *__restrict__ cb,
             const float *__restrict__ coarse, const int64_t *__restrict__ list_offsets,
@@ -227,6 +236,7 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
             const int32_t *__restrict__ probe_ids, int nprobe, int K, int want, int pilot_want,
             int R, char *__restrict__ ws, size_t per_query, uint32_t *__restrict__ pair_cnt, int pair_nb,
             float2 *__restrict__ bounds) {
+    constexpr int EARLY1 = NT > 256 ? 1 : CALIB_EARLY1, EARLY2 = NT > 256 ? 2 : CALIB_EARLY2;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sel[8];
@@ -255,7 +265,7 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
     __syncthreads();
     {
         long long np = 0;
-        for (int a = threadIdx.x; a < nprobe; a += blockDim.x) {
+        for (int a = threadIdx.x; a < nprobe; a += NT) {
             const int c = probes[a];
             const bool valid = c >= 0 && c < K;
             const int64_t lo = valid ? list_offsets[c] : 0, hi = valid ? list_offsets[c + 1] : 0;
@@ -296,11 +306,11 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
         if (hi == lo) continue;
         const int take = (int)((hi - lo) < (int64_t)(t_eff - seen) ? (hi - lo) : (int64_t)(t_eff - seen));
         // the first codes are requested before the set-up (their sub-codes index its tables)
-        uint2 early[CALIB_EARLY1];
+        uint2 early[EARLY1];
         if (NIB) {
 #pragma unroll
-            for (int u = 0; u < CALIB_EARLY1; ++u) {
-                const int p = (int)threadIdx.x + u * 256;
+            for (int u = 0; u < EARLY1; ++u) {
+                const int p = (int)threadIdx.x + u * NT;
                 early[u] = *(const uint2 *)(list_codes + (size_t)(lo + (p < take ? p : take - 1)) * 8);
             }
         }
@@ -332,10 +342,10 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
         int p = threadIdx.x;
         if (NIB) {
 #pragma unroll
-            for (int u = 0; u < CALIB_EARLY1; ++u, p += 256)
+            for (int u = 0; u < EARLY1; ++u, p += NT)
                 if (p < take) adc(p, true, early[u]);
         }
-        for (; p < take; p += blockDim.x) adc(p, false, make_uint2(0u, 0u));
+        for (; p < take; p += NT) adc(p, false, make_uint2(0u, 0u));
         seen += take;
         __syncthreads();
     }
@@ -348,11 +358,11 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
         calib_list(a, probes, list_offsets, K, s_pcell, s_plo, s_plen, c, lo, hi);
         if (hi == lo) continue;
         const int take = (int)((hi - lo) < (int64_t)(pilot - seen) ? (hi - lo) : (int64_t)(pilot - seen));
-        uint2 early[CALIB_EARLY2];
+        uint2 early[EARLY2];
         if (NIB) {
 #pragma unroll
-            for (int u = 0; u < CALIB_EARLY2; ++u) {
-                const int p = (int)threadIdx.x + u * 256;
+            for (int u = 0; u < EARLY2; ++u) {
+                const int p = (int)threadIdx.x + u * NT;
                 early[u] = *(const uint2 *)(list_codes + (size_t)(lo + (p < take ? p : take - 1)) * 8);
             }
         }
@@ -390,27 +400,27 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
         };
         int p = threadIdx.x;
         if (NIB) {
-            // rounds of CALIB_EARLY2 codes per thread; the next round is requested before the
+            // rounds of EARLY2 codes per thread; the next round is requested before the
             // current one is looked up
             while (p < take) {
-                uint2 cur[CALIB_EARLY2];
+                uint2 cur[EARLY2];
 #pragma unroll
-                for (int u = 0; u < CALIB_EARLY2; ++u) cur[u] = early[u];
-                const int pn = p + CALIB_EARLY2 * 256;
+                for (int u = 0; u < EARLY2; ++u) cur[u] = early[u];
+                const int pn = p + EARLY2 * NT;
                 if (pn < take) {
 #pragma unroll
-                    for (int u = 0; u < CALIB_EARLY2; ++u) {
-                        const int pp = pn + u * 256;
+                    for (int u = 0; u < EARLY2; ++u) {
+                        const int pp = pn + u * NT;
                         early[u] = *(const uint2 *)(list_codes + (size_t)(lo + (pp < take ? pp : take - 1)) * 8);
                     }
                 }
 #pragma unroll
-                for (int u = 0; u < CALIB_EARLY2; ++u)
-                    if (p + u * 256 < take) qadc_of(p + u * 256, true, cur[u]);
+                for (int u = 0; u < EARLY2; ++u)
+                    if (p + u * NT < take) qadc_of(p + u * NT, true, cur[u]);
                 p = pn;
             }
         }
-        for (; p < take; p += blockDim.x) qadc_of(p, false, make_uint2(0u, 0u));
+        for (; p < take; p += NT) qadc_of(p, false, make_uint2(0u, 0u));
         seen += take;
         __syncthreads();
     }
@@ -418,7 +428,7 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
     uint32_t t0 = qadc_block_kth_u32(ord, pilot, k, 4, hist, sel);
     // smallest pilot distance: block minimum
     uint32_t l0 = 0xffffffffu;
-    for (int p = threadIdx.x; p < pilot; p += blockDim.x) l0 = ord[p] < l0 ? ord[p] : l0;
+    for (int p = threadIdx.x; p < pilot; p += NT) l0 = ord[p] < l0 ? ord[p] : l0;
     l0 = qadc_wave_min(l0);
     __syncthreads();
     if (threadIdx.x == 0) sel[0] = 0xffffffffu;
@@ -1363,19 +1373,25 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
     } else {
         if ((rc = allow_lds(k_ivf_final<KIND, QT, false>, lds_final)) != PQ_OK) return rc;
     }
-#define QADC_IVF_CALIB(...)                                                                          \
+#define QADC_IVF_CALIB1(NIBV, DSV, NTV)                                                              \
     do {                                                                                             \
-        if ((rc = allow_lds(k_ivf_calib<__VA_ARGS__>, lds_calib)) != PQ_OK) return rc;               \
-        hipLaunchKernelGGL((k_ivf_calib<__VA_ARGS__>), dim3(nq), dim3(256), lds_calib, s, idx->dev,  \
+        if ((rc = allow_lds(k_ivf_calib<NIBV, DSV, NTV>, lds_calib)) != PQ_OK) return rc;            \
+        hipLaunchKernelGGL((k_ivf_calib<NIBV, DSV, NTV>), dim3(nq), dim3(NTV), lds_calib, s, idx->dev, \
                            idx->edesc, idx->codebooks, coarse, list_offsets, list_codes, queries,    \
                            probe_ids, nprobe, K, want, pilot_want, R, ws, p.per_query, pair_cnt,     \
-                           pair_nb, bounds);                                                                 \
+                           pair_nb, bounds);                                                         \
+    } while (0)
+#define QADC_IVF_CALIB(NIBV, DSV)                                                                    \
+    do {                                                                                             \
+        if (nq <= CALIB_WIDE_QUERIES) QADC_IVF_CALIB1(NIBV, DSV, 1024);                              \
+        else QADC_IVF_CALIB1(NIBV, DSV, 256);                                                        \
     } while (0)
     // (the fixed 16 x 4-bit shape has a set-up of its own)
     if (dsf == 4) QADC_IVF_CALIB(true, 4);
     else if (dsf == 6) QADC_IVF_CALIB(true, 6);
     else if (dsf == 8) QADC_IVF_CALIB(true, 8);
-    else QADC_IVF_CALIB(NIB);
+    else QADC_IVF_CALIB(NIB, 0);
+#undef QADC_IVF_CALIB1
 #undef QADC_IVF_CALIB
     QADC_LAUNCH_CHECK("k_ivf_calib");
     if (tighten) {
