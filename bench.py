@@ -801,7 +801,7 @@ def main_encode(a):
         "ms_per_step": dt / steps * 1e3, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"C1encode: n={n}, d={lay.d}, m={lay.m}, bits=4, entry=pq_encode", "seed": 18120922},
-        "roofline": {"bound": "hbm", "kernel": "k_encode", "achieved": nbytes / (ms * 1e-3) / 1e9,
+        "roofline": {"bound": "hbm", "kernel": "k_encode_mx", "achieved": nbytes / (ms * 1e-3) / 1e9,
                      "peak": 8000.0, "unit": "GB/s", "frac": nbytes / (ms * 1e-3) / 1e9 / 8000.0,
                      "traffic": None, "kernel_avg_ms": ms, "algorithmic_bytes_per_launch": nbytes},
     }))

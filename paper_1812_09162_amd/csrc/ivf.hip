@@ -122,7 +122,7 @@ __device__ inline bool ivf_setup(const DevLayout *L, const EntryDesc *__restrict
 // sub-quantizer e / 16 at codebook offset e * DS, so nothing is looked up, the minima come
 // from lane exchanges, and the codebook values travel while the residual settles in LDS.
 // cv: the thread's codebook values; ze, ce: dimension e of the query and of the centroid (e < d).
-template <int DS>
+template <int DS, int NT = 256>
 __device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, float dmax, bool quantize,
                                      uint32_t qmax, const IvfLds &l) {
     constexpr int d = 16 * DS;
@@ -130,7 +130,8 @@ __device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, 
     if (e < d) l.zres[e] = __fsub_rn(ze, ce);
     __syncthreads();
     float acc = 0.0f;
-    if (e < 256) {  // (whole waves)
+    uint32_t mb = 0;
+    if (NT == 256 || e < 256) {  // (whole waves)
         const float *zz = l.zres + (e >> 4) * DS;
 #pragma unroll
         for (int t = 0; t < DS; ++t) {
@@ -138,13 +139,12 @@ __device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, 
             acc = __fadd_rn(acc, __fmul_rn(diff, diff));
         }
         l.tab[e] = acc;
-        float mn = acc;
-#pragma unroll
-        for (int sft = 1; sft < 16; sft <<= 1) {
-            const float o = __shfl_xor(mn, sft, QADC_WAVE);
-            mn = o < mn ? o : mn;
-        }
-        if ((e & 15) == 0) l.pmin[e >> 4] = mn;
+        mb = __float_as_uint(acc);  // minimum over 16 lanes (squares: the bit patterns order as integers)
+        mb = min(mb, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mb, 0xB1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
+        mb = min(mb, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mb, 0x4E, 0xf, 0xf, true));   // quad_perm [2,3,0,1]
+        mb = min(mb, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mb, 0x141, 0xf, 0xf, true));  // row_half_mirror
+        mb = min(mb, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mb, 0x140, 0xf, 0xf, true));  // row_mirror
+        if ((e & 15) == 0) l.pmin[e >> 4] = __uint_as_float(mb);
     }
     __syncthreads();
     if (e == 0) {
@@ -165,10 +165,18 @@ __device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, 
     if (!quantize) return true;
     if (*l.flag) return false;
     const double delta = l.sc[1];
-    if (e < 256) {
+    if (NT == 256 || e < 256) {
+        // floor((p - p_min) / delta) in fp32 where that cannot differ (8-bit tables): the fp32 value is off by at most
+        // 2^-21 of itself (difference, delta and product are each rounded once, the reciprocal is within 2^-23); where a
+        // whole number is within that, or delta is not of ordinary size, the division is done in fp64
+        const float pm = __uint_as_float(mb), fd = (float)delta;
+        const float x32 = (acc - pm) * __builtin_amdgcn_rcpf(fd);
         uint32_t qv = 0;
-        if (delta > 0.0) {
-            const double x = floor(((double)acc - (double)l.pmin[e >> 4]) / delta);
+        if (qmax == 255u && fd > 1e-30f && fd < 1e30f &&
+            (x32 >= 255.5f || fmaf(x32, 4.8e-7f, fabsf(__builtin_amdgcn_fractf(x32) - 0.5f)) < 0.5f)) {
+            qv = (uint32_t)fminf(x32, 255.0f);
+        } else if (delta > 0.0) {
+            const double x = floor(((double)acc - (double)pm) / delta);
             qv = (x >= (double)qmax) ? qmax : (uint32_t)x;
         }
         l.qt[e] = (uint16_t)qv;
@@ -178,15 +186,15 @@ __device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, 
 }
 
 // the same with everything loaded here
-template <int DS>
+template <int DS, int NT = 256>
 __device__ inline bool ivf_setup_fix(const float *__restrict__ cb, const float *__restrict__ z,
                                      const float *__restrict__ cen, float dmax, bool quantize,
                                      uint32_t qmax, const IvfLds &l) {
     const int e = threadIdx.x;
     float cv[DS];
 #pragma unroll
-    for (int t = 0; t < DS; ++t) cv[t] = e < 256 ? cb[e * DS + t] : 0.0f;
-    return ivf_setup_fix<DS>(cv, e < 16 * DS ? z[e] : 0.0f, e < 16 * DS ? cen[e] : 0.0f, dmax, quantize, qmax, l);
+    for (int t = 0; t < DS; ++t) cv[t] = NT == 256 || e < 256 ? cb[e * DS + t] : 0.0f;
+    return ivf_setup_fix<DS, NT>(cv, e < 16 * DS ? z[e] : 0.0f, e < 16 * DS ? cen[e] : 0.0f, dmax, quantize, qmax, l);
 }
 
 __device__ __forceinline__ uint32_t dist_bin(float dist, float lo, float scale) {
@@ -315,7 +323,7 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
             }
         }
         if constexpr (DS > 0)
-            ivf_setup_fix<DS>(cb, z, coarse + (size_t)c * (16 * DS), 0.f, false, (uint32_t)qmax, l);
+            ivf_setup_fix<DS, NT>(cb, z, coarse + (size_t)c * (16 * DS), 0.f, false, (uint32_t)qmax, l);
         else
             ivf_setup<SCAN_GENERIC, uint16_t>(L, edesc, cb, z, coarse + (size_t)c * L->d, 0.f, false, false, l);
         auto adc = [&](int p, bool have, uint2 v) {  // have: v holds the code already (NIB)
@@ -368,7 +376,7 @@ k_ivf_calib(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
         }
         bool ok;
         if constexpr (DS > 0)
-            ok = ivf_setup_fix<DS>(cb, z, coarse + (size_t)c * (16 * DS), dmax, true, (uint32_t)qmax, l);
+            ok = ivf_setup_fix<DS, NT>(cb, z, coarse + (size_t)c * (16 * DS), dmax, true, (uint32_t)qmax, l);
         else
             ok = ivf_setup<SCAN_GENERIC, uint16_t>(L, edesc, cb, z, coarse + (size_t)c * L->d, dmax, true, false, l);
         const float fdelta = (float)l.sc[1], fdmin = (float)l.sc[0];
@@ -1282,6 +1290,13 @@ k_ivf_tight(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc
                 cur = worst < cur ? worst : cur;
             }
         }
+    }
+    if (nsorted == na) {  // in order already
+        for (int r = threadIdx.x; r < R; r += 256) {
+            out_ids[q * R + r] = r < na ? (int32_t)(uint32_t)A[r] : -1;
+            out_dist[q * R + r] = r < na ? qadc_ord2f((uint32_t)(A[r] >> 32)) : INFINITY;
+        }
+        return;
     }
     ivf_rank_and_write(A, na, R, out_ids + q * R, out_dist + q * R);
 }
