@@ -166,14 +166,12 @@ __device__ inline bool ivf_setup_fix(const float (&cv)[DS], float ze, float ce, 
     if (*l.flag) return false;
     const double delta = l.sc[1];
     if (NT == 256 || e < 256) {
-        // floor((p - p_min) / delta) in fp32 where that cannot differ (8-bit tables): the fp32 value is off by at most
-        // 2^-21 of itself (difference, delta and product are each rounded once, the reciprocal is within 2^-23); where a
-        // whole number is within that, or delta is not of ordinary size, the division is done in fp64
+        // floor((p - p_min) / delta) in fp32 where that cannot differ (8-bit tables), else (or with a delta not of
+        // ordinary size) in fp64
         const float pm = __uint_as_float(mb), fd = (float)delta;
         const float x32 = (acc - pm) * __builtin_amdgcn_rcpf(fd);
         uint32_t qv = 0;
-        if (qmax == 255u && fd > 1e-30f && fd < 1e30f &&
-            (x32 >= 255.5f || fmaf(x32, 4.8e-7f, fabsf(__builtin_amdgcn_fractf(x32) - 0.5f)) < 0.5f)) {
+        if (qmax == 255u && fd > 1e-30f && fd < 1e30f && quotient_sure(x32, QUOTIENT_SLACK_RCP)) {
             qv = (uint32_t)fminf(x32, 255.0f);
         } else if (delta > 0.0) {
             const double x = floor(((double)acc - (double)pm) / delta);

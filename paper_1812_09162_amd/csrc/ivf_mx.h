@@ -2,6 +2,7 @@
 // One pass over an inverted list for up to sixteen of the queries that probe it, on the matrix cores
 // (Section 2.1.3: every (query, cell) pair has its own tables, but the codes of the cell are the same
 // for all).  16 x 4-bit codes over equal sub-spaces, 8-bit tables.
+#include "quotient.h"
 #include "scan_device.h"
 
 typedef int ivf_v8i __attribute__((ext_vector_type(8)));
@@ -188,18 +189,17 @@ k_ivf_scan_mx(const float *__restrict__ cb, const float *__restrict__ coarse,
                 // (saturated codes have the largest key: if that is within the bound, all codes are)
                 S.top[col] = within > (int)qmax ? INFINITY : (float)(within - 1) * 0.125f;
             }
-            // floor((p - p_min) / delta) in fp32 where that cannot differ: the fp32 value is off by at most 3 * 2^-24 of
-            // itself (difference, reciprocal and product are each rounded once); where a whole number is within twice
-            // that, or delta is not of ordinary size (inv == 0), the division is done in fp64
+            // floor((p - p_min) / delta) in fp32 where that cannot differ, else (or with a delta not of ordinary size,
+            // inv == 0) in fp64, by the whole wave: the reads of a lane's delta want all lanes active
             uint32_t qv[4];
             bool sure = inv > 0.0f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float x = (tv[i][r] - S.pmin[col][g + 4 * r]) * inv;
                 qv[r] = (uint32_t)fminf(x, 255.0f);
-                sure = sure & ((x >= 255.5f) | (fmaf(x, 3.6e-7f, fabsf(__builtin_amdgcn_fractf(x) - 0.5f)) < 0.5f));
+                sure = sure & quotient_sure(x, QUOTIENT_SLACK);
             }
-            if (!sure) {
+            if (__ballot(!sure) != 0) {
                 const unsigned long long db = (unsigned long long)__double_as_longlong(dl);
                 const double delta = __longlong_as_double((long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(db >> 32), i) << 32) |
                                                                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)db, i)));

@@ -3,6 +3,7 @@
 #include <stdlib.h>
 
 
+#include "quotient.h"
 #include "scan_device.h"
 
 // P blocks per query (grid = nq * P, block q*P + p).  Every block of a query computes
@@ -261,15 +262,14 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     const bool ok = (delta > 0.0) && isfinite(delta);
     delta = ok ? delta : 0.0;
     const uint32_t mx_scale = btab_rel ? mx_scale_of(ok && t_eff > 0 ? (float)(((double)qadc_ord2f(s_range[0]) - dmin) / delta) : (float)qmax, (uint32_t)qmax) : 0u;
-    // floor((p - p_min) / delta) in fp32 where that cannot differ: the fp32 value is off by at most 3 * 2^-24 of
-    // itself (difference, reciprocal and product are each rounded once); where a whole number is within twice
-    // that, or delta is not of ordinary size, the division is done in fp64.  (16-bit tables: too few bits are left.)
+    // floor((p - p_min) / delta) in fp32 where that cannot differ, else (or with a delta not of ordinary size) in fp64.
+    // (16-bit tables: too few bits are left.)
     const float inv = sizeof(QT) == 1 && delta > 1e-30 && delta < 1e30 ? (float)(1.0 / delta) : 0.0f;
     for (int e = threadIdx.x; e < T; e += NT) {
         const float p = tab[e], pm = pmin[esub[e]];
         uint32_t qv = 0;
         const float xf = (p - pm) * inv;
-        if (inv > 0.0f && (xf >= 255.5f || fmaf(xf, 3.6e-7f, fabsf(__builtin_amdgcn_fractf(xf) - 0.5f)) < 0.5f)) {
+        if (inv > 0.0f && quotient_sure(xf, QUOTIENT_SLACK)) {
             qv = (uint32_t)fminf(xf, 255.0f);
         } else if (delta > 0.0) {
             double x = floor(((double)p - (double)pm) / delta);
