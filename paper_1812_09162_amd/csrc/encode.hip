@@ -288,20 +288,22 @@ k_encode(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc, c
 // sub-quantizer's 16 centroids and 16 vectors, which the fp32 matrix instruction takes four dimensions at a time (a
 // chain of fused multiply-adds in ascending order).  A wave encodes tiles of 16 vectors by itself, staged in rows of
 // its own in LDS and read as lane (vector l % 16, dimension l / 16 of four); the centroids stay in its registers
-// (times -2).  A lane gets the values of four centroids for one vector; with their index in the low four bits the two
-// smallest of the 16 take seven minima and maxima and, for four sub-quantizers together, fifteen operations across
+// (times -2).  A lane gets ||c||^2 - 2 x.c of four centroids for one vector; with their index in the low four bits the two
+// smallest of the 16 take six minima, maxima and medians and, for four sub-quantizers together, fifteen operations across
 // lanes, which leave lane (v, g) with vector v and sub-quantizer {0, 2, 1, 3}[g] of the four.  Near ties are decided
-// by eq. (1) as in enc_nearest_fast; the offset that keeps values above zero is the whole vector's norm here.
-// What bounds it: memory, behind it minima and packing on the vector units (137 instructions a wave per 1024 values, 57 % of the
-// time) and the products (28 %), which three wavefronts per SIMD do not quite overlap (minima a sub-quantizer behind its
-// products did not either).  10^7 vectors, d = 96, 16 x 4 bits: 960 us (4.08 TB/s; a copy of this card's memory runs at 4.8),
-// 1185 with the expanded form on the vector units; two and four wavefronts per SIMD 1110 and 1066.
+// by eq. (1) as in enc_nearest_fast, within a margin of the sub-space's own norms (sub-spaces may differ in size by any
+// factor); values may be below zero here, so that no offset has to be the same for all lanes of a vector.
+// What bounds it: memory, behind it minima and packing on the vector units.  10^7 vectors, d = 96, 16 x 4 bits: 912 us
+// (4.3 TB/s; a copy of this card's memory runs at 4.8), 1193 with the expanded form on the vector units; 969 with values made
+// positive by the whole vector's norm and margins of that size, which also took every small sub-space of uneven vectors for
+// a near tie: 10^6 vectors of variance i^-4 97 us, 207 so, 133 on the vector units.
 typedef float enc_v4f __attribute__((ext_vector_type(4)));
 template <int M, int DS>
 struct EncMxLds {
     static constexpr int D = M * DS, ROW = D + 4;  // a row is an odd multiple of four floats: no bank conflicts
+    static constexpr int CB = 16 * DS + 4;         // (four sub-quantizers' centroids, read at a time, too)
     float xs[4][16][ROW];
-    float cb[M * 16 * DS];
+    float cb[M * CB];
     float nrm[M][16];
     uint32_t nmax[M];
 };
@@ -315,14 +317,14 @@ k_encode_mx(const float *__restrict__ cb, const float *__restrict__ x, int64_t n
     __shared__ __align__(16) Lds S;
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int v = lane & 15, g = lane >> 4;
-    for (int e = threadIdx.x; e < M * 16 * DS; e += 256) S.cb[e] = cb[e];
+    for (int e = threadIdx.x; e < M * 16 * DS; e += 256) S.cb[e + e / (16 * DS) * 4] = cb[e];
     if (threadIdx.x < M) S.nmax[threadIdx.x] = 0;
-    S.xs[w][v][D + g] = 0.0f;  // (read as the missing dimensions of the last sub-quantizer)
     __syncthreads();
     for (int e = threadIdx.x; e < M * 16; e += 256) {
+        const float *c = &S.cb[(e >> 4) * Lds::CB + (e & 15) * DS];
         float s = 0.0f;
 #pragma unroll
-        for (int l = 0; l < DS; ++l) s = __fmaf_rn(S.cb[e * DS + l], S.cb[e * DS + l], s);
+        for (int l = 0; l < DS; ++l) s = __fmaf_rn(c[l], c[l], s);
         (&S.nrm[0][0])[e] = s;
         atomicMax(&S.nmax[e >> 4], __float_as_uint(s));
     }
@@ -330,7 +332,7 @@ k_encode_mx(const float *__restrict__ cb, const float *__restrict__ x, int64_t n
 #pragma unroll
     for (int j = 0; j < M; ++j)
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) a[j][kk] = 4 * kk + g < DS ? -2.0f * S.cb[(j * 16 + v) * DS + 4 * kk + g] : 0.0f;
+        for (int kk = 0; kk < KK; ++kk) a[j][kk] = 4 * kk + g < DS ? -2.0f * S.cb[j * Lds::CB + v * DS + 4 * kk + g] : 0.0f;
     __syncthreads();
     float (*xs)[Lds::ROW] = S.xs[w];
     enc_f4 nx[PF];
@@ -344,11 +346,17 @@ k_encode_mx(const float *__restrict__ cb, const float *__restrict__ x, int64_t n
             nx[i] = __builtin_nontemporal_load(src + (rows == 16 ? e : min(e / D4, rows - 1) * D4 + e % D4));
         }
     };
+    // Minima and maxima as medians with an infinity that the compiler does not see: it makes both arguments of a minimum
+    // quiet first, an operation each.  (Of a NaN it is no minimum; where there is one, none is used.)
+    float inf = INFINITY;
+    asm("" : "+s"(inf));
+    auto least = [inf](float p, float q) { return __builtin_amdgcn_fmed3f(p, q, -inf); };
     const int64_t stride = (int64_t)gridDim.x * 4;
     int64_t tile = (int64_t)blockIdx.x * 4 + w;
     if (tile < ntiles) request(tile);
     const uint32_t idx0 = 4u * (uint32_t)g;
     const int sub = g == 1 ? 2 : (g == 2 ? 1 : g);  // of a group of four: the one this lane ends up with
+    const uint32_t own = 4 * (KK - 1) + g < DS ? ~0u : 0u;  // of a sub-quantizer's last four dimensions: those it has
     for (; tile < ntiles; tile += stride) {
         const int64_t v0 = tile * 16;
 #pragma unroll
@@ -367,65 +375,82 @@ k_encode_mx(const float *__restrict__ cb, const float *__restrict__ x, int64_t n
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the rows are this wave's own)
         if (tile + stride < ntiles) request(tile + stride);
-        float b[M][KK], xx = 0.0f;
+        float b[M][KK];
 #pragma unroll
         for (int j = 0; j < M; ++j)
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
                 b[j][kk] = xs[v][j * DS + 4 * kk + g];
-                xx = __fmaf_rn(b[j][kk], b[j][kk], xx);  // (some dimensions count twice: a bound is all it has to be)
+                if (kk == KK - 1 && DS % 4 != 0) b[j][kk] = __uint_as_float(__float_as_uint(b[j][kk]) & own);
             }
-        {
-            auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(xx), __float_as_uint(xx), false, false);
-            xx = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-            r = __builtin_amdgcn_permlane16_swap(__float_as_uint(xx), __float_as_uint(xx), false, false);
-            xx = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        }
         uint32_t word[M / 8];
 #pragma unroll
         for (int i = 0; i < M / 8; ++i) word[i] = 0;
 #pragma unroll
         for (int q = 0; q < M / 4; ++q) {
-            // S bounds |2 x.c| and half of any distance of these sub-quantizers (nmax: of the largest of them)
-            const uint4 nm4 = *(const uint4 *)&S.nmax[4 * q];
-            const float Sb = xx + __uint_as_float(max(max(nm4.x, nm4.y), max(nm4.z, nm4.w)));
-            const float off = __fmaf_rn(Sb, 1.0f / 65536.0f, xx);
-            uint32_t m1[4], m2[4];
+            float m1[4], m2[4], xx[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int j = 4 * q + u;
-                const float4 n4 = *(const float4 *)&S.nrm[j][4 * g];
-                enc_v4f acc = {n4.x + off, n4.y + off, n4.z + off, n4.w + off};
+                enc_v4f acc = *(const enc_v4f *)&S.nrm[j][4 * g];
 #pragma unroll
                 for (int kk = 0; kk < KK; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j][kk], b[j][kk], acc, 0, 0, 0);
-                uint32_t k[4];
+                float k[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) k[i] = (__float_as_uint(acc[i]) & ~15u) | (idx0 + (uint32_t)i);
-                const uint32_t lo0 = min(k[0], k[1]), hi0 = max(k[0], k[1]), lo1 = min(k[2], k[3]), hi1 = max(k[2], k[3]);
-                m1[u] = min(lo0, lo1);
-                m2[u] = min(min(hi0, hi1), max(lo0, lo1));
+                for (int i = 0; i < 4; ++i) k[i] = __uint_as_float((__float_as_uint(acc[i]) & ~15u) | (idx0 + (uint32_t)i));
+                m1[u] = least(k[0], k[1]);
+                m2[u] = __builtin_amdgcn_fmed3f(k[0], k[1], inf);
+#pragma unroll
+                for (int i = 2; i < 4; ++i) {
+                    m2[u] = __builtin_amdgcn_fmed3f(m1[u], m2[u], k[i]);
+                    m1[u] = least(m1[u], k[i]);
+                }
+                xx[u] = b[j][0] * b[j][0];
+#pragma unroll
+                for (int kk = 1; kk < KK; ++kk) xx[u] = __fmaf_rn(b[j][kk], b[j][kk], xx[u]);
             }
-            auto merge32 = [](uint32_t &p1, uint32_t &p2, uint32_t q1, uint32_t q2) {
-                const auto r1 = __builtin_amdgcn_permlane32_swap(p1, q1, false, false), r2 = __builtin_amdgcn_permlane32_swap(p2, q2, false, false);
-                p1 = min((uint32_t)r1[0], (uint32_t)r1[1]);
-                p2 = min(min((uint32_t)r2[0], (uint32_t)r2[1]), max((uint32_t)r1[0], (uint32_t)r1[1]));
+            // two lists of two smallest, the second's at least its first: their two smallest
+            auto merge = [least](float p1, float p2, float q1, float q2, float &r1, float &r2) {
+                r2 = __builtin_amdgcn_fmed3f(p1, q1, least(p2, q2));
+                r1 = least(p1, q1);
             };
-            merge32(m1[0], m2[0], m1[1], m2[1]);
-            merge32(m1[2], m2[2], m1[3], m2[3]);
-            const auto r1 = __builtin_amdgcn_permlane16_swap(m1[0], m1[2], false, false), r2 = __builtin_amdgcn_permlane16_swap(m2[0], m2[2], false, false);
-            const uint32_t k1 = min((uint32_t)r1[0], (uint32_t)r1[1]);
-            const uint32_t k2 = min(min((uint32_t)r2[0], (uint32_t)r2[1]), max((uint32_t)r1[0], (uint32_t)r1[1]));
-            // Roundings: at most DS + 3 of the expanded form and DS + 2 of eq. (1), each 2^-24 of at most 2 S (one more
-            // for the roundings of S itself), for two values; the dropped bits: 2^-19 of a value.  (Sums near the
-            // smallest normal numbers round otherwise: S > 1e-30.)
+            auto swap32 = [](float &p, float &q) {
+                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+                p = __uint_as_float(r[0]);
+                q = __uint_as_float(r[1]);
+            };
+            auto swap16 = [](float &p, float &q) {
+                const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+                p = __uint_as_float(r[0]);
+                q = __uint_as_float(r[1]);
+            };
+#pragma unroll
+            for (int u = 0; u < 4; u += 2) {
+                swap32(m1[u], m1[u + 1]);
+                swap32(m2[u], m2[u + 1]);
+                swap32(xx[u], xx[u + 1]);
+                merge(m1[u], m2[u], m1[u + 1], m2[u + 1], m1[u], m2[u]);
+                xx[u] += xx[u + 1];
+            }
+            swap16(m1[0], m1[2]);
+            swap16(m2[0], m2[2]);
+            swap16(xx[0], xx[2]);
+            float s1, s2;
+            merge(m1[0], m2[0], m1[2], m2[2], s1, s2);
+            // S bounds |2 x.c| and half of any distance in this lane's sub-space.  Roundings: at most DS + 3 of the expanded
+            // form and DS + 2 of eq. (1), each 2^-24 of at most 2 S (one more for the roundings of S itself), for two
+            // values; the dropped bits: 2^-19 of a value.  (Sums near the smallest normal numbers round otherwise, and
+            // near the largest they overflow: S within [1e-30, 1e38], which infinities and NaN are not.)
             constexpr float ROUND = (2 * DS + 6) * 4 / 16777216.0f;
-            const float f1 = __uint_as_float(k1 & ~15u), f2 = __uint_as_float(k2 & ~15u);
-            const bool clear = Sb > 1e-30f && f2 - f1 > __fmaf_rn(f2, 1.0f / 262144.0f, Sb * ROUND);
+            const float Sb = (xx[0] + xx[2]) + __uint_as_float(S.nmax[4 * q + sub]);
+            const uint32_t k1 = __float_as_uint(s1);
+            const float f1 = __uint_as_float(k1 & ~15u), f2 = __uint_as_float(__float_as_uint(s2) & ~15u);
+            const bool clear = Sb > 1e-30f && Sb < 1e38f && f2 - f1 > __fmaf_rn(fabsf(f1) + fabsf(f2), 1.0f / 262144.0f, Sb * ROUND);
             int besti = (int)(k1 & 15u);
             if (__ballot(!clear) != 0) {
                 if (!clear) {
                     float best = INFINITY;
-                    enc_nearest<DS>(&xs[v][(4 * q + sub) * DS], &S.cb[(4 * q + sub) * 16 * DS], 16, best, besti);
+                    enc_nearest<DS>(&xs[v][(4 * q + sub) * DS], &S.cb[(4 * q + sub) * Lds::CB], 16, best, besti);
                 }
             }
             word[q >> 1] |= (uint32_t)besti << (16 * (q & 1) + 4 * sub);
@@ -448,9 +473,11 @@ k_encode_mx(const float *__restrict__ cb, const float *__restrict__ x, int64_t n
 }
 
 // The matrix form takes 16 or 32 sub-quantizers of 4 bits over equal sub-spaces; vectors and shifts are read in
-// 16-byte pieces.  At every size and on both kinds of data it was the
-// faster one, us, expanded form on the vector units / here: 16 x 4 bits, d = 96: 1000 vectors 10.8 / 9.5, 2 * 10^6 250 / 212; d = 128:
-// 287 / 233; 32 x 4 bits, d = 96: 365 / 297, integer-valued data 364 / 341 (near ties); d = 128: 368 / 318.
+// 16-byte pieces.  At every size and on every kind of data timed it was the faster one, us for 10^6 vectors, expanded form on the vector
+// units / here: 16 x 4 bits, d = 64 98 / 73, d = 96 129 / 96, d = 128 150 / 102; 32 x 4 bits, d = 96 193 / 145, d = 128 191 / 141;
+// integer-valued data (near ties) 129 / 93, 144 / 96 and 189 / 152; variance falling as i^-1.5 to i^-4 or one sub-space a hundred
+// times as large 130 to 137 / 97 to 99 (d = 96); one dimension a hundred or a thousand standard deviations off the origin, which makes
+// near ties of one sub-space in sixteen, 139 and 142 / 114 and 124; 1000 vectors 10.8 / 9.5.
 static int enc_mx_width(const pq_index *idx, bool vec, bool nib) {
     const DevLayout &h = idx->h;
     if (!vec || !nib || h.ds_uniform == 0 || h.d != h.m * h.ds_uniform) return 0;

@@ -192,11 +192,12 @@ def test_encode_forms_and_second_tiles(qb, d, nbits, n, shift):
 
 
 @pytest.mark.parametrize("d,m", [(64, 16), (96, 16), (128, 16), (96, 32), (128, 32)])
-@pytest.mark.parametrize("kind", ["skewed", "integer", "unbounded"])
+@pytest.mark.parametrize("kind", ["skewed", "integer", "unbounded", "largest"])
 def test_encode_matrix_form(qb, d, m, kind):
     """The products on the matrix cores: counts around a wave's tile of 16 vectors and around its second tile
     (3072 waves), sub-spaces of very different size (what decides is small beside the vector's norm), many equal
-    distances, and vectors with infinities and NaN in one sub-space, which must not touch the others."""
+    distances, vectors with infinities and NaN in one sub-space, which must not touch the others, and norms around
+    the largest that the expanded form may take (sums of products overflow above them)."""
     lay = synth.make_layout(d, [4] * m, 16)
     rng = np.random.default_rng(d + m)
     ds = d // m
@@ -207,6 +208,9 @@ def test_encode_matrix_form(qb, d, m, kind):
         cb, x = cb * s[:, None, :], x * s[None]
     elif kind == "integer":
         cb, x = np.round(2 * cb), np.round(2 * x)
+    elif kind == "largest":
+        s = np.float32(10.0) ** rng.uniform(18.0, 19.3, (m, 1))
+        cb, x = cb * s[:, None, :], x * s[None]
     else:
         x[::3, 1, 0] = np.inf
         x[1::3, m - 1, ds - 1] = -np.inf
@@ -219,3 +223,32 @@ def test_encode_matrix_form(qb, d, m, kind):
         pick = torch.arange(n, device=dev()) % 700
         assert torch.equal(qb.pq_encode(idx, torch.from_numpy(x).to(dev())[pick].contiguous()), want[pick]), n
     idx.close()
+
+
+@pytest.mark.parametrize("d,m", [(96, 16), (128, 32)])
+def test_encode_matrix_form_decides_uneven_sub_spaces_itself(qb, d, m):
+    """Near ties are told by the sub-space's own size: vectors whose first dimensions, or one sub-space, carry nearly all
+    of the norm take about as long as even ones.  (With the whole vector's norm every other sub-space counted as a near tie
+    and was encoded twice: 1.5 to 2 times as long.)"""
+    lay = synth.make_layout(d, [4] * m, 16)
+    ds, g = d // m, torch.Generator(device=dev()).manual_seed(5)
+    scales = {"even": torch.ones(d), "falling": 1.0 / torch.arange(1.0, d + 1.0) ** 2, "one large": torch.ones(d)}
+    scales["one large"][ds:2 * ds] = 1000.0
+    calls = {}
+    for name, sc in scales.items():
+        x = torch.randn((500_000, d), generator=g, device=dev()) * sc.to(dev())
+        cb = x[:16].view(16, m, ds).transpose(0, 1).contiguous().view(-1)
+        calls[name] = (qb.PqIndex(lay.d, lay.nbits, lay.dsub, cb, 8), x, [])
+    for rep in range(12):
+        for idx, x, t in calls.values():
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                qb.pq_encode(idx, x)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+    med = {name: sorted(t)[6] for name, (_, _, t) in calls.items()}
+    for idx, _, _ in calls.values():
+        idx.close()
+    assert max(med.values()) < 1.35 * med["even"], med
