@@ -236,6 +236,10 @@ k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char 
             }
         }
     };
+    // Rows held: a tile's, which every query tile multiplies; with one query tile and many steps only the next eight, as the
+    // others' registers would leave a SIMD one wave ({6,6,4} x 8, 2 * 10^7 codes, 32 queries, us a call: 382, with all of a tile's 430).
+    constexpr int H = NCOL == 1 && S > 16 ? 8 : S;
+    static_assert(4 * S % H == 0, "a block of codes starts with the first of the rows held");
     for (int ch = blockIdx.x * 4 + wave; ch < nchunks; ch += gridDim.x * 4) {
         const int64_t first = (int64_t)ch * nblk * 128 + 4 * c;
         MxCodes<KIND> cur, nxt;
@@ -249,14 +253,14 @@ k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char 
         }
         int inb = 0, gi = 0;
         cur.arrange(h);
-        uint4 row[S];
+        uint4 row[H];
 #pragma unroll
-        for (int s = 0; s < S; ++s) row[s] = row_of(cur, 0, s);
+        for (int s = 0; s < H; ++s) row[s] = row_of(cur, 0, s);
         for (int blk = 0; blk < nblk; ++blk) {
             nxt.request(codes, first + (int64_t)(blk + 1 < nblk ? blk + 1 : blk) * 128, h);
             // Units (tile, query tile) in turn on two accumulators: between the products of one, the minima of the
             // one before (sums are >= 0: their bit patterns order as integers) and, in a tile's last unit, the
-            // rows of the next tile.  Products and vector instructions overlap on this chip where they alternate in
+            // rows H steps on: those of the next tile.  Products and vector instructions overlap on this chip where they alternate in
             // a wave's stream (four products 131 clocks, 32 minima 140, alternating 175, one after the other 271).
             mx_v16f acc[2];
             auto minima = [&](const mx_v16f &a, uint32_t &m, int p) {
@@ -268,14 +272,18 @@ k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char 
                 if (t == 3 && ct == NCOL - 1) nxt.arrange(h);
 #pragma unroll
                 for (int s = 0; s < S; ++s) {
-                    const mx_v8i a = {(int)row[s].x, (int)row[s].y, (int)row[s].z, (int)row[s].w, 0, 0, 0, 0};
+                    uint4 &r = row[(t * S + s) % H];
+                    const mx_v8i a = {(int)r.x, (int)r.y, (int)r.z, (int)r.w, 0, 0, 0, 0};
                     const uint32_t *bs = b[ct][s];
                     const mx_v8i bv = {(int)bs[0], (int)bs[1], (int)bs[2], (int)bs[3], (int)bs[4], (int)bs[5], 0, 0};
                     const mx_v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                     // formats: 4 = 4 bits (one-hot rows), 2 = 6 bits e2m3 (tables)
                     acc[u & 1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, bv, s == 0 ? zero : acc[u & 1], 4, 2, 0, 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (ct == NCOL - 1) row[s] = t < 3 ? row_of(cur, t + 1, s) : row_of(nxt, 0, s);
+                    if (ct == NCOL - 1) {
+                        if (s + H < S) r = row_of(cur, t, s + H);
+                        else r = t < 3 ? row_of(cur, t + 1, s + H - S) : row_of(nxt, 0, s + H - S);
+                    }
                     if (u > 0 && s > 0) {  // (the last product of the unit before needs a step or two to finish)
 #pragma unroll
                         for (int p = 8 * (s - 1) / (S - 1); p < 8 * s / (S - 1); ++p) minima(acc[(u + 1) & 1], mn[before], p);
