@@ -538,6 +538,11 @@ extern "C" int pq_encode(const pq_index_t *idx, const float *vectors, int64_t n,
         return PQ_EINVAL;
     }
     const DevLayout &h = idx->h;
+    const int64_t blocks = n / ENC_VB + (n % ENC_VB != 0);
+    if (blocks > 0x7fffffffLL) {
+        qadc_set_error("pq_encode: n=%lld too large for one call", (long long)n);
+        return PQ_EINVAL;
+    }
     const int vec = h.d % 4 == 0 && (((uintptr_t)vectors | (uintptr_t)shift_rows) & 15u) == 0;
     const int nib = (h.kind == SCAN_NIB8 || h.kind == SCAN_NIB16) && ((uintptr_t)codes & 3u) == 0;
     if (const int ds = enc_mx_width(idx, vec != 0, nib != 0)) {
@@ -562,11 +567,6 @@ extern "C" int pq_encode(const pq_index_t *idx, const float *vectors, int64_t n,
     // small codebooks are read through the scalar cache instead (faster than LDS reads)
     if (cbf * sizeof(float) <= 16 * 1024) cbf = 0;
     size_t lds = base_lds + cbf * sizeof(float);
-    const int64_t blocks = (n + ENC_VB - 1) / ENC_VB;
-    if (blocks > 0x7fffffffLL) {
-        qadc_set_error("pq_encode: n=%lld too large for one call", (long long)n);
-        return PQ_EINVAL;
-    }
     size_t nrm_words = (size_t)((h.T + 3) & ~3) + (size_t)((h.m + 3) & ~3);
     const EncForm f = enc_form(h, blocks, lds, nrm_words * sizeof(float), vec != 0);
     if (!f.fast) nrm_words = 0;

@@ -225,6 +225,19 @@ def test_encode_matrix_form(qb, d, m, kind):
     idx.close()
 
 
+@pytest.mark.parametrize("d,m", [(96, 16), (128, 32), (100, 5)])
+@pytest.mark.parametrize("n", [64 * 0x7FFFFFFF + 1, 1 << 62, (1 << 63) - 1])
+def test_encode_refuses_more_vectors_than_a_call_can_take(qb, d, m, n):
+    """Every form refuses the same n (before anything is launched)."""
+    lay = synth.make_layout(d, [4] * m, 16)
+    cb = torch.zeros(sum(16 * s for s in lay.dsub), device=dev())
+    idx = qb.PqIndex(lay.d, lay.nbits, lay.dsub, cb, 8)
+    x, codes = torch.zeros((64, d), device=dev()), torch.zeros((64, 16), dtype=torch.uint8, device=dev())
+    assert qb.load().pq_encode(idx.handle, x.data_ptr(), n, None, None, codes.data_ptr(), None) == qb.PQ_EINVAL
+    assert b"too large" in qb.load().pq_last_error()
+    idx.close()
+
+
 @pytest.mark.parametrize("d,m", [(96, 16), (128, 32)])
 def test_encode_matrix_form_decides_uneven_sub_spaces_itself(qb, d, m):
     """Near ties are told by the sub-space's own size: vectors whose first dimensions, or one sub-space, carry nearly all
