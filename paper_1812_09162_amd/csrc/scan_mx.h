@@ -140,8 +140,12 @@ struct MxCodes {
 // [h][gpc] bytes.  S product steps of 64 table entries; a lane half holds 32 of them.
 // PAT: the kinds of the steps (of each 64-bit word) at compile time, 100 N6 + 10 N5 + N4: N6 steps of
 // 6-bit fields, then N5 of 5-bit ones, then N4 of nibbles; 0: read from the descriptors.
+// Three query tiles of 16 x 4-bit codes: minima are stored four at a time, not sixteen, whose nine registers
+// would leave a SIMD two waves instead of three (2 * 10^7 codes, us a call: 96 queries 191, held 194; 192 342 and 349.
+// One, two and four tiles keep their waves either way, and are up to 3 % slower with more stores).
+constexpr bool mx_each(int kind, int ncol) { return kind == SCAN_NIB8 && ncol == 3; }
 template <int KIND, int S, int NCOL, int PAT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KIND == SCAN_W128 ? 1 : 2)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KIND == SCAN_W128 ? 1 : (mx_each(KIND, NCOL) ? 3 : 2))))
 k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char *__restrict__ ws,
           size_t per_query, size_t btab_off, size_t min_off, int nq, MxDesc md) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / QADC_WAVE), l = threadIdx.x % QADC_WAVE;
@@ -236,6 +240,9 @@ k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char 
             }
         }
     };
+    auto minima_of = [&](int ct, int ch) {  // this lane's part of a chunk: gpc bytes of query column ct * 32 + c
+        return ws + (size_t)(q0 + ct * 32 + c) * per_query + min_off + (size_t)ch * (2 * gpc) + h * gpc;
+    };
     // Rows held: a tile's, which every query tile multiplies; with one query tile and many steps only the next eight, as the
     // others' registers would leave a SIMD one wave ({6,6,4} x 8, 2 * 10^7 codes, 32 queries, us a call: 382, with all of a tile's 430).
     constexpr int H = NCOL == 1 && S > 16 ? 8 : S;
@@ -301,7 +308,13 @@ k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char 
                     pk[ct][3] = (pk[ct][3] >> 8) | (u << 24);
                     mn[ct] = 0x7f7fffffu;
                 }
-                if ((++gi & 3) == 0 && gi < gpc) {
+                if constexpr (mx_each(KIND, NCOL)) {
+                    if ((++gi & 3) == 0) {
+#pragma unroll
+                        for (int ct = 0; ct < NCOL; ++ct)
+                            if (q0 + ct * 32 + c < nq) *(uint32_t *)(minima_of(ct, ch) + gi - 4) = pk[ct][3];
+                    }
+                } else if ((++gi & 3) == 0 && gi < gpc) {
 #pragma unroll
                     for (int ct = 0; ct < NCOL; ++ct) {
                         pk[ct][0] = pk[ct][1];
@@ -312,16 +325,15 @@ k_scan_mx(const uint8_t *__restrict__ codes, int nchunks, int gpc, int nb, char 
             }
             cur = nxt;
         }
+        if constexpr (!mx_each(KIND, NCOL)) {
 #pragma unroll
-        for (int ct = 0; ct < NCOL; ++ct) {
-            const int q = q0 + ct * 32 + c;
-            if (q < nq) {
-                char *dst = ws + (size_t)q * per_query + min_off + (size_t)ch * (2 * gpc) + h * gpc;
-                if (gpc == 16)
-                    *(uint4 *)dst = make_uint4(pk[ct][0], pk[ct][1], pk[ct][2], pk[ct][3]);
-                else
-                    *(uint32_t *)dst = pk[ct][3];
-            }
+            for (int ct = 0; ct < NCOL; ++ct)
+                if (q0 + ct * 32 + c < nq) {
+                    if (gpc == 16)
+                        *(uint4 *)minima_of(ct, ch) = make_uint4(pk[ct][0], pk[ct][1], pk[ct][2], pk[ct][3]);
+                    else
+                        *(uint32_t *)minima_of(ct, ch) = pk[ct][3];
+                }
         }
     }
 }

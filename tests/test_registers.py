@@ -33,6 +33,7 @@ def kernels():
     ("k_scan_mxILi5ELi16ELi1ELi440E", 2),
     ("k_scan_mxILi1ELi4ELi1ELi0E", 5),     # 16 x 4 bits, one to four query tiles
     ("k_scan_mxILi1ELi4ELi2ELi0E", 4),
+    ("k_scan_mxILi1ELi4ELi3ELi0E", 3),
     ("k_scan_mxILi1ELi4ELi4ELi0E", 2),
     ("k_ivf_scan_mxILi6E", 7),
     ("k_encode_mxILi16ELi6E", 3),
