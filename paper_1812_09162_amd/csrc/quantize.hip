@@ -4,6 +4,7 @@
 
 
 #include "quotient.h"
+#include "rules.h"
 #include "scan_device.h"
 
 // P blocks per query (grid = nq * P, block q*P + p).  Every block of a query computes
@@ -478,14 +479,6 @@ static size_t quantize_lds(const DevLayout &h, int t_eff, size_t esz) {
            (size_t)h.gtab_len * esz;
 }
 
-// Wide blocks where one block does a query's whole work (batches for the matrix cores, calls without scratch memory) or
-// the calibration is long, and at most two of them share a CU.  k_quantize, 256 / 1024 threads: 32 x 4 bits, 2 * 10^7
-// codes, R = 1000 (4000 calibration codes) 29 / 18.8 us, with twice the pilot; {6,6,4} x 4, 32 queries 22 / 15.2 us.  A single
-// query with a short calibration spreads its pilot over 128 blocks, and wide ones wait for whole CUs to become free beside
-// the scans of other streams: 16 x 4 bits, 10^7 codes, alone 34.9 / 32.6 us a call, on four streams 12.7 / 15.3 a query;
-// {6,5,5,6,5,5,4,4} 40.5 / 36.0 and 13.2 / 15.0.
-static bool quantize_wide(int64_t blocks, int P, int t_eff) { return blocks <= 512 && (P == 1 || t_eff > 1024); }
-
 template <int KIND, typename QT>
 static int launch_quantize(const pq_index *idx, const float *queries, const float *tables_in,
                            float *tables_out, int nq, const uint8_t *codes, int t_eff, int k,
@@ -507,7 +500,7 @@ static int launch_quantize(const pq_index *idx, const float *queries, const floa
                            idx->edesc, idx->codebooks, queries, tables_in, tables_out, codes, t_eff, k, pp.pilot, \
                            pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, btab_rel, hdr_out, bound_rec); \
     } while (0)
-    if (quantize_wide((int64_t)nq * pp.P, pp.P, t_eff)) QADC_QUANT_GO(QUANT_WIDE); else QADC_QUANT_GO(QUANT_THREADS);
+    if (quantize_wide((int64_t)nq * pp.P, pp.P, t_eff, KIND == SCAN_NIB8)) QADC_QUANT_GO(QUANT_WIDE); else QADC_QUANT_GO(QUANT_THREADS);
 #undef QADC_QUANT_GO
     QADC_LAUNCH_CHECK("k_quantize");
     return PQ_OK;

@@ -1,0 +1,21 @@
+#pragma once
+// Size rules of the quantizer and the inverted-list calibration.  Plain C++, so that the lines can be checked without a GPU.
+#include <stdint.h>
+
+// Whether k_quantize runs blocks of 1024 threads: a block's time is a chain of dependent steps, each shorter with more
+// threads, but a wide block waits for half of a CU to become free, beside other streams' scans and beside other
+// blocks of its own.  us a call, 256 / 1024 threads, one stream and per call on four (8 x 8: m x 8 bits):
+//   one block does a query's whole work (batches for the matrix cores, no scratch memory), 2 * 10^6 codes, R = 100: 16 x 4 bits, 192
+//     queries 62.7 / 62.0 and 48.5 / 49.8; 320: 101 / 105 and 81 / 84; {6,6,4} x 4, 256: 139 / 134 and
+//     117 / 118; 320: 184 / 189 and 147 / 153 (k_quantize itself, 32 queries: 22 / 15.2): up to one block per CU
+//   one query over 128 blocks, R = 100: 16 x 4 bits, 10^7 codes 34.9 / 32.6 and 12.7 / 15.3: not with short calibrations
+//   ... more than 1024 calibration codes: one query, 10^6 codes, R = 257: 16 x 4 bits 30.2 / 27.1 and 16.8 / 15.7, 40-bit codes 41.2 / 32.3
+//     and 21.9 / 17.7; two: 37.8 / 35.3 and 23.2 / 24.1, 52.2 / 43.3 and 30.9 / 30.6, 8 x 8 55.8 / 48.5 and 33.7 / 35.5; four: 43.0 / 47.5
+//     and 27.6 / 34.4, 57.2 / 60.9 and 34.0 / 44.2: up to one block per CU
+//   ... R = 1000, four queries (two blocks per CU), 10^6 codes: 40-bit 87.2 / 77.3 and 61.0 / 60.3, 32 x 4 68.0 / 66.3 and 54.0 / 50.1; 16 x 4
+//     55.4 / 55.8 and 36.9 / 41.5; R = 2000: 128.7 / 105.7 and 106 / 84, 95.3 / 88.8 and 72.4 / 66.5, 74.4 / 72.4 and 54.2 / 53.0: long
+//     calibrations, whose chain outweighs it (later where look-ups are cheap)
+inline bool quantize_wide(int64_t blocks, int blocks_per_query, int calibration, bool cheap_lookups) {
+    if (blocks_per_query == 1) return blocks <= 256;
+    return calibration > 1024 && blocks <= (calibration > (cheap_lookups ? 4096 : 2048) ? 512 : 256);
+}

@@ -1,0 +1,14 @@
+// One line per call on stdin (rule and its arguments): the rule's answer.
+#include <stdio.h>
+#include <string.h>
+#include "rules.h"
+
+int main() {
+    char rule[32];
+    long long a, b, c, d;
+    while (scanf("%31s %lld %lld %lld %lld", rule, &a, &b, &c, &d) == 5) {
+        if (!strcmp(rule, "quantize_wide")) printf("%d\n", (int)quantize_wide(a, (int)b, (int)c, d != 0));
+        else return 1;
+    }
+    return 0;
+}

@@ -1,0 +1,29 @@
+"""Lines of the size rules in rules.h, without a GPU."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rules") / "rules")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_1812_09162_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "rules_driver.cpp"), "-o", exe])
+
+    def ask(name, *args):
+        line = " ".join(map(str, (name, *args, *[0] * (4 - len(args)))))
+        return int(subprocess.check_output([exe], input=line.encode()))
+    return ask
+
+
+@pytest.mark.parametrize("nq,per_query,calibration,cheap,wide", [
+    (1, 1, 400, 1, 1), (256, 1, 400, 0, 1), (257, 1, 400, 1, 0), (512, 1, 4000, 0, 0),   # one block a query: up to one a CU
+    (1, 128, 400, 1, 0), (1, 128, 1024, 0, 0),                                           # short calibrations beside scans
+    (1, 128, 1028, 1, 1), (2, 128, 2048, 0, 1), (3, 128, 1028, 0, 0), (4, 128, 2048, 0, 0), (4, 128, 4000, 1, 0),
+    (4, 128, 2052, 0, 1), (4, 128, 8000, 1, 1), (5, 128, 8000, 0, 0),                    # two a CU: long ones only
+])
+def test_width_of_the_quantizers_blocks(rule, nq, per_query, calibration, cheap, wide):
+    assert rule("quantize_wide", nq * per_query, per_query, calibration, cheap) == wide
