@@ -16,6 +16,7 @@
 //                R-th, rank the few up to it; exact multi-pass selection over
 //                all probed codes if a slot list overflowed.
 #include "ivf_mx.h"
+#include "rules.h"
 
 struct IvfLds {
     float *zres;   // [d]
@@ -202,11 +203,6 @@ __device__ __forceinline__ uint32_t dist_bin(float dist, float lo, float scale) 
 
 // ------------------------------------------------------------ k_ivf_calib ---
 #define CALIB_PC 64      // probes whose cell and list bounds the block keeps in LDS
-// Queries up to which the calibration runs blocks of 1024 threads (its time is then a block's chain of steps, in which
-// the pilot's look-ups and the selections take a third as long); a call's us, blocks of 256 / 1024, 32 probes: 16 x 4 bits,
-// 1 query 41.2 / 36.5, 256 98.6 / 93.3, 400 117.7 / 113.0, 1024 186 / 201; {6,5,5} x 4: 1 99 / 69, 400 295 / 292, 1024 607 / 620;
-// 8 x 8: 1 167 / 118, 400 591 / 590, 512 703 / 731.
-#define CALIB_WIDE_QUERIES 384
 #define CALIB_EARLY1 2   // codes per thread requested before the set-up, calibration pass
 #define CALIB_EARLY2 4   // the same, pilot pass
 
@@ -1396,7 +1392,7 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
     } while (0)
 #define QADC_IVF_CALIB(NIBV, DSV)                                                                    \
     do {                                                                                             \
-        if (nq <= CALIB_WIDE_QUERIES) QADC_IVF_CALIB1(NIBV, DSV, 1024);                              \
+        if (calib_wide(nq)) QADC_IVF_CALIB1(NIBV, DSV, 1024);                              \
         else QADC_IVF_CALIB1(NIBV, DSV, 256);                                                        \
     } while (0)
     // (the fixed 16 x 4-bit shape has a set-up of its own)

@@ -19,3 +19,10 @@ inline bool quantize_wide(int64_t blocks, int blocks_per_query, int calibration,
     if (blocks_per_query == 1) return blocks <= 256;
     return calibration > 1024 && blocks <= (calibration > (cheap_lookups ? 4096 : 2048) ? 512 : 256);
 }
+
+// Whether k_ivf_calib runs blocks of 1024 threads, one query each (the pilot's look-ups and the selections take a third as
+// long): up to one block per CU.  us a call, 256 / 1024 threads, one stream and per call on four; 2 * 10^6 codes in 4096 lists, 32 probes, R = 100:
+//   16 x 4 bits, 1 query 46.7 / 42.1 and 24.0 / 21.9, 256 83.8 / 80.4 and 46.4 / 47.2, 320 85.9 / 85.2 and 47.8 / 54.0
+//   {6,5,5} x 4, 1 134 / 100 and 67 / 50, 256 234 / 201 and 150 / 148, 320 258 / 269 and 174 / 186
+//   8 x 8 bits, 1 249 / 186 and 125 / 93, 256 485 / 423 and 330 / 322, 320 538 / 560 and 383 / 405
+inline bool calib_wide(int nq) { return nq <= 256; }

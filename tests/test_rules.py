@@ -27,3 +27,8 @@ def rule(tmp_path_factory):
 ])
 def test_width_of_the_quantizers_blocks(rule, nq, per_query, calibration, cheap, wide):
     assert rule("quantize_wide", nq * per_query, per_query, calibration, cheap) == wide
+
+
+@pytest.mark.parametrize("nq,wide", [(1, 1), (256, 1), (257, 0), (384, 0)])
+def test_width_of_the_calibrations_blocks(rule, nq, wide):
+    assert rule("calib_wide", nq) == wide
