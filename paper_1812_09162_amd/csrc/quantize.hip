@@ -425,10 +425,6 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
 // Codes one pilot block counts per batch (eight per thread) and at most in total.
 #define PILOT_BATCH (8 * QUANT_THREADS)
 #define PILOT_BLOCK_MAX 65536
-// Pilot codes per result of long lists: 32 x 4 bits, 2 * 10^7 codes, R = 1000, whole call: 512 100.6 us, 1024 96.3, 2048 95.2, 4096 102.8
-// (fewer candidates to gather against more codes to count).
-#define PILOT_PER_RESULT 1024
-
 int qadc_pilot_blocks_max(int nq) {
     const int64_t cap = qadc_option(PQ_OPT_PILOT_BLOCKS);
     int pmax = 2048 / (nq > 0 ? nq : 1);  // (blocks of 256 threads: a few thousand fill the chip)
@@ -456,7 +452,7 @@ PilotPlan qadc_pilot_plan(int nq, int64_t n, int t_eff, int R, bool have_scratch
     if (multi > 262144 && multi > per_block * pmax) multi = per_block * pmax > 262144 ? per_block * pmax : 262144;
     int64_t want = pmax > 1 ? multi : single;
     // the candidates the scan keeps grow with R / pilot: long result lists get a longer pilot
-    if (pmax > 1 && want < PILOT_PER_RESULT * (int64_t)R) want = PILOT_PER_RESULT * (int64_t)R;
+    if (pmax > 1 && want < pilot_for_results(n, R)) want = pilot_for_results(n, R);
     if (want > (int64_t)pmax * PILOT_BLOCK_MAX) want = (int64_t)pmax * PILOT_BLOCK_MAX;
     if (want < 64 * (int64_t)R) want = 64 * (int64_t)R;
     if (want < t_eff) want = t_eff;

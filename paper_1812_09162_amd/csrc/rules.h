@@ -26,3 +26,14 @@ inline bool quantize_wide(int64_t blocks, int blocks_per_query, int calibration,
 //   {6,5,5} x 4, 1 134 / 100 and 67 / 50, 256 234 / 201 and 150 / 148, 320 258 / 269 and 174 / 186
 //   8 x 8 bits, 1 249 / 186 and 125 / 93, 256 485 / 423 and 330 / 322, 320 538 / 560 and 383 / 405
 inline bool calib_wide(int nq) { return nq <= 256; }
+
+// Pilot codes that a search with long results counts at least, over all blocks of a query: the scan keeps about R / pilot of its
+// codes for the selection, so fewer candidates stand against more codes to count.  1024 per result, but beyond 512 no more than a quarter of
+// the list.  us a call of one query, gamma data, d = 128, 512 / 1024 per result: R = 1000, 10^7 codes 16 x 4 bits 50.9 / 46.5, 32 x 4
+// 65.9 / 60.8, 40-bit 55.9 / 51.9, 8 x 8 69.5 / 64.5, {6,6,4} x 8 98.5 / 98.6; 10^6 codes 30.5 / 31.4, 35.0 / 37.4, 39.5 / 40.8, 47.5 / 49.5,
+// 67.7 / 73.5; R = 2000, 10^7 65.9 / 62.8, 89.9 / 88.1, 78.0 / 76.3, 91.4 / 88.6, 144 / 151; 3 * 10^6 49.3 / 51.2, 60.9 / 65.0, 63.4 / 66.3,
+// 72.8 / 76.4, 121 / 131; 5 * 10^6 between (a quarter: 53.4, 1024: 54.5; 69.3, 71.7; 68.9, 70.6; 76.8, 81.5; 133, 139).
+inline int64_t pilot_for_results(int64_t n, int R) {
+    const int64_t least = 512 * (int64_t)R, most = 1024 * (int64_t)R;
+    return n / 4 <= least ? least : (n / 4 < most ? n / 4 : most);
+}

@@ -32,3 +32,9 @@ def test_width_of_the_quantizers_blocks(rule, nq, per_query, calibration, cheap,
 @pytest.mark.parametrize("nq,wide", [(1, 1), (256, 1), (257, 0), (384, 0)])
 def test_width_of_the_calibrations_blocks(rule, nq, wide):
     assert rule("calib_wide", nq) == wide
+
+
+@pytest.mark.parametrize("n,R,codes", [(10_000_000, 1000, 1_024_000), (4_096_000, 1000, 1_024_000), (3_000_000, 1000, 750_000),
+                                       (2_048_000, 1000, 512_000), (1_000_000, 1000, 512_000), (1, 2048, 1_048_576)])
+def test_pilot_for_long_results(rule, n, R, codes):
+    assert rule("pilot_for_results", n, R) == codes  # at most a quarter of the list above 512 codes a result
