@@ -1519,14 +1519,6 @@ static size_t ivf_group_bytes(int nq, int nprobe, int K) {
     return ((3 * ((size_t)K + 2) + 2048 + pairs) * sizeof(uint32_t) + 16 +
             (pairs / IVF_COLS + (size_t)K + 1) * sizeof(IvfGroup) + (size_t)nq * sizeof(float2) + 255) & ~(size_t)255;
 }
-// When one pass over a list for the pairs that probe it (k_ivf_scan_mx) beats a block per pair: from one and a half
-// pairs per cell on, and not below a thousand pairs, where the four extra launches of the exact sort show.  16 x 4 bits,
-// d = 96, R = 100, us a call, block per pair / shared: 2 * 10^7 codes in 16384 lists, 64 probes: 1 pair per cell 129 / 140,
-// 1.5 151 / 155, 2 173 / 163, 4 265 / 198; in 4096 lists: 0.25 (1024 pairs) 154 / 122, 1.5 171 / 144; 2 * 10^6 in 4096:
-// 2 85 / 89, 4 103 / 99; 500,000 codes in 100 lists, 20 probes: 4 (400 pairs) 73 / 85.
-#define IVF_SHARED_MIN_HALF_PAIRS_PER_CELL 3
-#define IVF_SHARED_MIN_PAIRS 1024
-
 extern "C" size_t ivf_sorted_workspace_bytes(const pq_index_t *idx, int nq, int nprobe, int R, int K) {
     if (!idx || nq < 0 || nprobe < 1 || R < 1 || K < 1) return 0;
     const size_t base = (qadc_ivf_plan(idx, nq, nprobe, R).total + 255) & ~(size_t)255;
@@ -1580,12 +1572,11 @@ static int ivf_search(const char *name, bool tighten, const pq_index_t *idx, con
     if (!tighten && (int64_t)nq * nprobe * 4 >= (int64_t)K &&
         workspace_bytes >= base_bytes + ivf_sort_bytes(nq, nprobe, K))
         sortws = (uint32_t *)(ws + base_bytes);
-    // many pairs per cell (or the option says always): one pass over a list serves up to sixteen pairs
+    // enough pairs (or the option says always): one pass over a list serves up to sixteen pairs
     const int64_t shared_opt = qadc_option(PQ_OPT_IVF_SHARED_LISTS);
     const bool shared_lists = !tighten && shared_opt != 0 && ivf_fixed_shape(idx) != 0 && K < (1 << 20) &&
                               workspace_bytes >= base_bytes + ivf_group_bytes(nq, nprobe, K) &&
-                              (shared_opt == 2 || ((int64_t)nq * nprobe >= IVF_SHARED_MIN_PAIRS &&
-                                                   2 * (int64_t)nq * nprobe >= (int64_t)IVF_SHARED_MIN_HALF_PAIRS_PER_CELL * K));
+                              (shared_opt == 2 || ivf_shared_pays((int64_t)nq * nprobe, K));
     if (shared_lists) sortws = (uint32_t *)(ws + base_bytes);
     const bool u8 = idx->h.acc_bits == 8;
 #define QADC_GO(KIND, QT)                                                                          \

@@ -37,3 +37,18 @@ inline int64_t pilot_for_results(int64_t n, int R) {
     const int64_t least = 512 * (int64_t)R, most = 1024 * (int64_t)R;
     return n / 4 <= least ? least : (n / 4 < most ? n / 4 : most);
 }
+
+// When one pass over an inverted list for the (query, probe) pairs of its cell (k_ivf_scan_mx) is taken rather than a block per
+// pair.  How long the lists are decides it, which the host does not know (their offsets are on the device): long lists gain from
+// a quarter of a pair per cell on, short ones lose the four launches of the exact sort and blocks that wait for few
+// codes up to about 6000 pairs.  The lines are a compromise, and PQ_OPT_IVF_SHARED_LISTS = 0 or 2 is for the caller who knows.  us a call,
+// block per pair / shared, 16 x 4 bits, R = 100, codes per list first:
+//   122, 16384 lists: 1.5 pairs per cell 155 / 166, 2 162 / 168, 4 226 / 204     200, 4096: 1.5 87 / 92, 3 102 / 101, 8 146 / 125
+//   500, 512: 4 57 / 66, 16 76 / 78, 32 103 / 93     1000, 1024: 1.5 52 / 58, 4 65 / 64, 8 73 / 74     1200, 4096: 1.5 81 / 79, 4 109 / 95
+//   1220, 16384: 0.5 102 / 109, 1.5 146 / 150, 2 171 / 161     2000, 256: 8 61 / 66, 32 91 / 88     2000, 512: 4 65 / 68, 32 126 / 100
+//   4900, 4096: 0.25 148 / 115, 1.5 165 / 138     5000, 1024: 1 120 / 93, 2 121 / 96, 8 151 / 144     8000, 256: 1.5 100 / 91, 4 120 / 105
+// Below 1024 pairs only lists of 5000 codes and more gain (by up to a tenth), shorter ones lose as much; and with fewer groups than about
+// one per CU (a cell's pairs are taken sixteen at a time) even those lose: 5000, 100: 4 65 / 78, 12 81 / 91, 20 83 / 93; 2000, 64: 32 54 / 65.
+inline bool ivf_shared_pays(int64_t pairs, int64_t cells) {
+    return pairs >= 1024 && 2 * pairs >= 3 * cells && cells + pairs / 16 >= 320;
+}

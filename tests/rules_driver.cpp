@@ -10,6 +10,7 @@ int main() {
         if (!strcmp(rule, "quantize_wide")) printf("%d\n", (int)quantize_wide(a, (int)b, (int)c, d != 0));
         else if (!strcmp(rule, "calib_wide")) printf("%d\n", (int)calib_wide((int)a));
         else if (!strcmp(rule, "pilot_for_results")) printf("%lld\n", (long long)pilot_for_results(a, (int)b));
+        else if (!strcmp(rule, "ivf_shared_pays")) printf("%d\n", (int)ivf_shared_pays(a, b));
         else return 1;
     }
     return 0;

@@ -426,7 +426,7 @@ def check_ivf(qb, ip, R, t=T_CAL, probe=None):
                         device=dev())
     gi2, gd2 = qb.ivf_adc_scan_topk(*args, workspace=small)   # minimal workspace: blocks in grid order
     ti, td = qb.ivf_adc_scan_topk_tightening(*args)           # the bound tightened list by list
-    qb.pq_set_option(qb.PQ_OPT_IVF_SHARED_LISTS, 2)           # one pass per list for four pairs, always
+    qb.pq_set_option(qb.PQ_OPT_IVF_SHARED_LISTS, 2)           # one pass per list for up to sixteen pairs, always
     try:
         gi3, gd3 = qb.ivf_adc_scan_topk(*args)
         torch.cuda.synchronize()

@@ -38,3 +38,17 @@ def test_width_of_the_calibrations_blocks(rule, nq, wide):
                                        (2_048_000, 1000, 512_000), (1_000_000, 1000, 512_000), (1, 2048, 1_048_576)])
 def test_pilot_for_long_results(rule, n, R, codes):
     assert rule("pilot_for_results", n, R) == codes  # at most a quarter of the list above 512 codes a result
+
+
+@pytest.mark.parametrize("pairs,cells,shared", [
+    (1023, 256, 0), (1024, 256, 1), (1536, 1024, 1), (1535, 1024, 0), (640_000, 65_536, 1), (64_000, 65_536, 0),
+    (1200, 100, 0), (2000, 100, 0), (3520, 100, 1), (2048, 64, 0), (4096, 64, 1),  # too few groups for the CUs
+])
+def test_when_pairs_share_a_pass_over_a_list(rule, pairs, cells, shared):
+    assert rule("ivf_shared_pays", pairs, cells) == shared
+
+
+def test_header_states_the_lines_of_the_shared_pass():
+    text = " ".join(open(os.path.join(ROOT, "include", "qadc.h")).read().replace("*", " ").split())
+    assert text.count("1.5 pairs per cell, 1024 pairs and K + pairs / 16 >= 320") == 1
+    assert text.count("1.5 (query, probe) pairs per cell, 1024 pairs and K + pairs / 16 >= 320") == 1
