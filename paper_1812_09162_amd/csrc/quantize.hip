@@ -116,7 +116,6 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     if (KIND == SCAN_NIB8 && hi > lo) {
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
-            if (lo + u * NT >= hi) break;
             int id = lo + u * NT + (int)threadIdx.x;
             id = id < hi ? id : hi - 1;
             pc[u] = *(const uint2 *)(codes + (size_t)id * 8);
@@ -318,7 +317,6 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
                 if (base != lo) {
 #pragma unroll
                     for (int u = 0; u < PPT; ++u) {
-                        if (base + u * NT >= hi) break;
                         int id = base + u * NT + (int)threadIdx.x;
                         id = id < hi ? id : hi - 1;
                         pc[u] = *(const uint2 *)(codes + (size_t)id * 8);
@@ -341,7 +339,6 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
                     uint2 w[PPT];
 #pragma unroll
                     for (int u = 0; u < PPT; ++u) {
-                        if (base + u * NT >= hi) break;
                         int id = base + u * NT + (int)threadIdx.x;
                         id = id < hi ? id : hi - 1;
                         w[u] = *(const uint2 *)(codes + (size_t)id * 8);
@@ -425,8 +422,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     }
 }
 
-// Pilot codes of a block at least, when several share them (one batch of a block of 256 threads, eight per thread, half of one of a
-// wide block, which requests and counts no round beyond its slice), and at most.
+// Codes one pilot block counts per batch (eight per thread) and at most in total.
 #define PILOT_BATCH (8 * QUANT_THREADS)
 #define PILOT_BLOCK_MAX 65536
 int qadc_pilot_blocks_max(int nq) {
