@@ -422,7 +422,9 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     }
 }
 
-// Codes one pilot block counts per batch (eight per thread) and at most in total.
+// Pilot codes of a block at least, when several share them (one batch of a block of 256 threads, eight per thread, half of one of a
+// wide block), and at most.  A batch's requests beyond the slice ask for its last code again: ending them there cost more
+// (16 x 4 bits, 1000 queries, 88 us a call, 93 with an end in the loop).
 #define PILOT_BATCH (8 * QUANT_THREADS)
 #define PILOT_BLOCK_MAX 65536
 int qadc_pilot_blocks_max(int nq) {
@@ -496,7 +498,7 @@ static int launch_quantize(const pq_index *idx, const float *queries, const floa
                            idx->edesc, idx->codebooks, queries, tables_in, tables_out, codes, t_eff, k, pp.pilot, \
                            pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, btab_rel, hdr_out, bound_rec); \
     } while (0)
-    if (quantize_wide((int64_t)nq * pp.P, pp.P, t_eff, KIND == SCAN_NIB8)) QADC_QUANT_GO(QUANT_WIDE); else QADC_QUANT_GO(QUANT_THREADS);
+    if (quantize_wide((int64_t)nq * pp.P, pp.P, t_eff, pp.pilot, KIND == SCAN_NIB8)) QADC_QUANT_GO(QUANT_WIDE); else QADC_QUANT_GO(QUANT_THREADS);
 #undef QADC_QUANT_GO
     QADC_LAUNCH_CHECK("k_quantize");
     return PQ_OK;

@@ -8,6 +8,8 @@
 //   one block does a query's whole work (batches for the matrix cores, no scratch memory), 2 * 10^6 codes, R = 100: 16 x 4 bits, 192
 //     queries 62.7 / 62.0 and 48.5 / 49.8; 320: 101 / 105 and 81 / 84; {6,6,4} x 4, 256: 139 / 134 and
 //     117 / 118; 320: 184 / 189 and 147 / 153 (k_quantize itself, 32 queries: 22 / 15.2): up to one block per CU
+//   ... and counts a pilot too (tables quantized for inspection), 10^6 codes: 300 queries 16 x 4 59 / 52, 40-bit 117 / 77, 8 x 8 145 / 98, {6,6,4} x 8
+//     279 / 209; 256: 53 / 28, 112 / 40, 139 / 51, 240 / 107: up to two
 //   one query over 128 blocks, R = 100: 16 x 4 bits, 10^7 codes 34.9 / 32.6 and 12.7 / 15.3: not with short calibrations
 //   ... more than 1024 calibration codes: one query, 10^6 codes, R = 257: 16 x 4 bits 30.2 / 27.1 and 16.8 / 15.7, 40-bit codes 41.2 / 32.3
 //     and 21.9 / 17.7; two: 37.8 / 35.3 and 23.2 / 24.1, 52.2 / 43.3 and 30.9 / 30.6, 8 x 8 55.8 / 48.5 and 33.7 / 35.5; four: 43.0 / 47.5
@@ -15,8 +17,8 @@
 //   ... R = 1000, four queries (two blocks per CU), 10^6 codes: 40-bit 87.2 / 77.3 and 61.0 / 60.3, 32 x 4 68.0 / 66.3 and 54.0 / 50.1; 16 x 4
 //     55.4 / 55.8 and 36.9 / 41.5; R = 2000: 128.7 / 105.7 and 106 / 84, 95.3 / 88.8 and 72.4 / 66.5, 74.4 / 72.4 and 54.2 / 53.0: long
 //     calibrations, whose chain outweighs it (later where look-ups are cheap)
-inline bool quantize_wide(int64_t blocks, int blocks_per_query, int calibration, bool cheap_lookups) {
-    if (blocks_per_query == 1) return blocks <= 256;
+inline bool quantize_wide(int64_t blocks, int blocks_per_query, int calibration, int pilot, bool cheap_lookups) {
+    if (blocks_per_query == 1) return blocks <= (pilot > 0 ? 512 : 256);
     return calibration > 1024 && blocks <= (calibration > (cheap_lookups ? 4096 : 2048) ? 512 : 256);
 }
 

@@ -14,19 +14,20 @@ def rule(tmp_path_factory):
                            os.path.join(ROOT, "tests", "rules_driver.cpp"), "-o", exe])
 
     def ask(name, *args):
-        line = " ".join(map(str, (name, *args, *[0] * (4 - len(args)))))
+        line = " ".join(map(str, (name, *args, *[0] * (5 - len(args)))))
         return int(subprocess.check_output([exe], input=line.encode()))
     return ask
 
 
-@pytest.mark.parametrize("nq,per_query,calibration,cheap,wide", [
-    (1, 1, 400, 1, 1), (256, 1, 400, 0, 1), (257, 1, 400, 1, 0), (512, 1, 4000, 0, 0),   # one block a query: up to one a CU
-    (1, 128, 400, 1, 0), (1, 128, 1024, 0, 0),                                           # short calibrations beside scans
-    (1, 128, 1028, 1, 1), (2, 128, 2048, 0, 1), (3, 128, 1028, 0, 0), (4, 128, 2048, 0, 0), (4, 128, 4000, 1, 0),
-    (4, 128, 2052, 0, 1), (4, 128, 8000, 1, 1), (5, 128, 8000, 0, 0),                    # two a CU: long ones only
+@pytest.mark.parametrize("nq,per_query,calibration,pilot,cheap,wide", [
+    (1, 1, 400, 0, 1, 1), (256, 1, 400, 0, 0, 1), (257, 1, 400, 0, 1, 0), (512, 1, 4000, 0, 0, 0),  # one block a query: up to one a CU
+    (257, 1, 400, 4096, 1, 1), (512, 1, 400, 6400, 0, 1), (513, 1, 400, 6400, 0, 0),                # ... with a pilot two
+    (1, 128, 400, 65536, 1, 0), (1, 128, 1024, 65536, 0, 0),                                        # short calibrations beside scans
+    (1, 128, 1028, 65536, 1, 1), (2, 128, 2048, 65536, 0, 1), (3, 128, 1028, 65536, 0, 0), (4, 128, 2048, 65536, 0, 0),
+    (4, 128, 4000, 65536, 1, 0), (4, 128, 2052, 65536, 0, 1), (4, 128, 8000, 65536, 1, 1), (5, 128, 8000, 65536, 0, 0),
 ])
-def test_width_of_the_quantizers_blocks(rule, nq, per_query, calibration, cheap, wide):
-    assert rule("quantize_wide", nq * per_query, per_query, calibration, cheap) == wide
+def test_width_of_the_quantizers_blocks(rule, nq, per_query, calibration, pilot, cheap, wide):
+    assert rule("quantize_wide", nq * per_query, per_query, calibration, pilot, cheap) == wide
 
 
 @pytest.mark.parametrize("nq,wide", [(1, 1), (256, 1), (257, 0), (384, 0)])
