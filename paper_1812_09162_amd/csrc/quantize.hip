@@ -454,7 +454,7 @@ PilotPlan qadc_pilot_plan(int nq, int64_t n, int t_eff, int R, bool have_scratch
     if (multi > 262144 && multi > per_block * pmax) multi = per_block * pmax > 262144 ? per_block * pmax : 262144;
     int64_t want = pmax > 1 ? multi : single;
     // the candidates the scan keeps grow with R / pilot: long result lists get a longer pilot
-    if (pmax > 1 && want < pilot_for_results(n, R)) want = pilot_for_results(n, R);
+    if (pmax > 1 && want < pilot_for_results(n, R, nq)) want = pilot_for_results(n, R, nq);
     if (want > (int64_t)pmax * PILOT_BLOCK_MAX) want = (int64_t)pmax * PILOT_BLOCK_MAX;
     if (want < 64 * (int64_t)R) want = 64 * (int64_t)R;
     if (want < t_eff) want = t_eff;

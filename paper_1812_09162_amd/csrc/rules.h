@@ -35,9 +35,11 @@ inline bool calib_wide(int nq) { return nq <= 256; }
 // 65.9 / 60.8, 40-bit 55.9 / 51.9, 8 x 8 69.5 / 64.5, {6,6,4} x 8 98.5 / 98.6; 10^6 codes 30.5 / 31.4, 35.0 / 37.4, 39.5 / 40.8, 47.5 / 49.5,
 // 67.7 / 73.5; R = 2000, 10^7 65.9 / 62.8, 89.9 / 88.1, 78.0 / 76.3, 91.4 / 88.6, 144 / 151; 3 * 10^6 49.3 / 51.2, 60.9 / 65.0, 63.4 / 66.3,
 // 72.8 / 76.4, 121 / 131; 5 * 10^6 between (a quarter: 53.4, 1024: 54.5; 69.3, 71.7; 68.9, 70.6; 76.8, 81.5; 133, 139).
-inline int64_t pilot_for_results(int64_t n, int R) {
+// With more than four queries the blocks fill the chip and every code counted costs time: 512 (100 queries over 5 * 10^6 codes, R = 2000, 512 / 1024:
+// 40-bit 734 / 774, {6,6,4} x 4 1117 / 1212, 8 x 8 1002 / 1098, 16 x 8 1829 / 2022).
+inline int64_t pilot_for_results(int64_t n, int R, int nq) {
     const int64_t least = 512 * (int64_t)R, most = 1024 * (int64_t)R;
-    return n / 4 <= least ? least : (n / 4 < most ? n / 4 : most);
+    return nq > 4 || n / 4 <= least ? least : (n / 4 < most ? n / 4 : most);
 }
 
 // When one pass over an inverted list for the (query, probe) pairs of its cell (k_ivf_scan_mx) is taken rather than a block per

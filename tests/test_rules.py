@@ -35,10 +35,11 @@ def test_width_of_the_calibrations_blocks(rule, nq, wide):
     assert rule("calib_wide", nq) == wide
 
 
-@pytest.mark.parametrize("n,R,codes", [(10_000_000, 1000, 1_024_000), (4_096_000, 1000, 1_024_000), (3_000_000, 1000, 750_000),
-                                       (2_048_000, 1000, 512_000), (1_000_000, 1000, 512_000), (1, 2048, 1_048_576)])
-def test_pilot_for_long_results(rule, n, R, codes):
-    assert rule("pilot_for_results", n, R) == codes  # at most a quarter of the list above 512 codes a result
+@pytest.mark.parametrize("n,R,nq,codes", [
+    (10_000_000, 1000, 1, 1_024_000), (4_096_000, 1000, 4, 1_024_000), (3_000_000, 1000, 1, 750_000), (2_048_000, 1000, 1, 512_000),
+    (1_000_000, 1000, 2, 512_000), (1, 2048, 1, 1_048_576), (10_000_000, 1000, 5, 512_000), (10_000_000, 2048, 512, 1_048_576)])
+def test_pilot_for_long_results(rule, n, R, nq, codes):
+    assert rule("pilot_for_results", n, R, nq) == codes  # few queries: up to 1024 a result, a quarter of the list; else 512
 
 
 @pytest.mark.parametrize("pairs,cells,shared", [
