@@ -37,6 +37,8 @@ def kernels():
     ("k_scan_mxILi1ELi4ELi4ELi0E", 2),
     ("k_ivf_scan_mxILi6E", 7),
     ("k_encode_mxILi16ELi6E", 3),
+    ("k_quantizeILi1EhLi256E", 7),
+    ("k_quantizeILi1EtLi256E", 7),
 ])
 def test_wavefronts_a_simd_holds(name, waves):
     found = [v for k, v in kernels().items() if name in k]
