@@ -1392,7 +1392,8 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
     } while (0)
 #define QADC_IVF_CALIB(NIBV, DSV)                                                                    \
     do {                                                                                             \
-        if (calib_wide(nq)) QADC_IVF_CALIB1(NIBV, DSV, 1024);                              \
+        if (calib_threads(nq) == 1024) QADC_IVF_CALIB1(NIBV, DSV, 1024);                             \
+        else if (calib_threads(nq) == 512) QADC_IVF_CALIB1(NIBV, DSV, 512);                          \
         else QADC_IVF_CALIB1(NIBV, DSV, 256);                                                        \
     } while (0)
     // (the fixed 16 x 4-bit shape has a set-up of its own)

@@ -22,12 +22,14 @@ inline bool quantize_wide(int64_t blocks, int blocks_per_query, int calibration,
     return calibration > 1024 && blocks <= (calibration > (cheap_lookups ? 4096 : 2048) ? 512 : 256);
 }
 
-// Whether k_ivf_calib runs blocks of 1024 threads, one query each (the pilot's look-ups and the selections take a third as
-// long): up to one block per CU.  us a call, 256 / 1024 threads, one stream and per call on four; 2 * 10^6 codes in 4096 lists, 32 probes, R = 100:
-//   16 x 4 bits, 1 query 46.7 / 42.1 and 24.0 / 21.9, 256 83.8 / 80.4 and 46.4 / 47.2, 320 85.9 / 85.2 and 47.8 / 54.0
-//   {6,5,5} x 4, 1 134 / 100 and 67 / 50, 256 234 / 201 and 150 / 148, 320 258 / 269 and 174 / 186
-//   8 x 8 bits, 1 249 / 186 and 125 / 93, 256 485 / 423 and 330 / 322, 320 538 / 560 and 383 / 405
-inline bool calib_wide(int nq) { return nq <= 256; }
+// Threads of k_ivf_calib's blocks, one query each (the pilot's look-ups and the selections shorten with them): 1024 up to one block per CU,
+// 512 up to two, else 256.  us a call with 256 / 512 / 1024 threads (- : not taken), one stream; per call on four:
+//   2 * 10^6 codes, 4096 lists, 32 probes, R = 100, 16 x 4 bits: 1 query 46.7 / - / 42.1; 24.0 / - / 21.9; 256 83.8 / - / 80.4; 46.4 / - / 47.2;
+//     340 86.9 / 83.4 / 85.8; 50.1 / 48.5 / 55.7; 512 93.1 / 90.8 / 92.5; 55.9 / 56.0 / 67.2
+//   {6,5,5} x 4: 1 134 / - / 100; 67 / - / 50; 256 234 / - / 201; 150 / - / 148; 340 263 / 232 / 273; 179 / 161 / 192; 512 310 / 278 / 352; 234 / 221 / 279
+//   8 x 8 bits, 1.3 * 10^7 codes, 43 probes, R = 200: 256 699 / - / 627; 511 / - / 478; 340 899 / 816 / 838; 658 / 618 / 631; 512 1112 / 1028 / 1046
+//   32 x 4 bits, 5 * 10^6 codes, 26 probes: 256 265 / - / 201; 144 / - / 129; 288 266 / 218 / 248; 148 / 126 / 150; 512 290 / 239 / 307; 194 / 170 / 230
+inline int calib_threads(int nq) { return nq <= 256 ? 1024 : (nq <= 512 ? 512 : 256); }
 
 // Pilot codes that a search with long results counts at least, over all blocks of a query: the scan keeps about R / pilot of its
 // codes for the selection, so fewer candidates stand against more codes to count.  1024 per result, but beyond 512 no more than a quarter of

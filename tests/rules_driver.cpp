@@ -8,7 +8,7 @@ int main() {
     long long a, b, c, d, e;
     while (scanf("%31s %lld %lld %lld %lld %lld", rule, &a, &b, &c, &d, &e) == 6) {
         if (!strcmp(rule, "quantize_wide")) printf("%d\n", (int)quantize_wide(a, (int)b, (int)c, (int)d, e != 0));
-        else if (!strcmp(rule, "calib_wide")) printf("%d\n", (int)calib_wide((int)a));
+        else if (!strcmp(rule, "calib_threads")) printf("%d\n", calib_threads((int)a));
         else if (!strcmp(rule, "pilot_for_results")) printf("%lld\n", (long long)pilot_for_results(a, (int)b, (int)c));
         else if (!strcmp(rule, "ivf_shared_pays")) printf("%d\n", (int)ivf_shared_pays(a, b));
         else return 1;

@@ -1,4 +1,4 @@
-"""The inverted-list calibration runs wide blocks for few queries and narrow ones for many: both give the same
+"""The inverted-list calibration runs blocks of 1024, 512 or 256 threads by the number of queries: all give the same
 results (defined bit for bit), for every code layout the kernel tells apart."""
 import numpy as np
 import pytest
@@ -16,7 +16,7 @@ def test_wide_and_narrow_calibration_agree(nbits, d, acc, R):
     from paper_1812_09162_amd import binding as qb
     rng = np.random.default_rng(R + d)
     lens = [0, 1, 255, 256, 257, 1023, 1025, 90, 3000, 4500]
-    K, n, nq, nprobe = len(lens), sum(lens), 400, 7
+    K, n, nq, nprobe = len(lens), sum(lens), 513, 7
     dsub = [d // len(nbits)] * len(nbits)
     dsub[0] += d - sum(dsub)
     cb = rng.standard_normal(sum((1 << b) * s for b, s in zip(nbits, dsub))).astype(np.float32)
@@ -31,10 +31,11 @@ def test_wide_and_narrow_calibration_agree(nbits, d, acc, R):
     lists = [torch.from_numpy(x).to(dev) for x in (coarse, off, codes, ids)]
     for search in (qb.ivf_adc_scan_topk, qb.ivf_adc_scan_topk_tightening):
         many = search(idx, *lists, torch.from_numpy(q).to(dev), torch.from_numpy(probe).to(dev), 400, R)
-        few = search(idx, *lists, torch.from_numpy(q[:9]).to(dev), torch.from_numpy(probe[:9]).to(dev), 400, R)
-        torch.cuda.synchronize()
-        for a, b in zip(many, few):
-            assert torch.equal(a[:9], b)
+        for k in (9, 300):
+            few = search(idx, *lists, torch.from_numpy(q[:k]).to(dev), torch.from_numpy(probe[:k]).to(dev), 400, R)
+            torch.cuda.synchronize()
+            for a, b in zip(many, few):
+                assert torch.equal(a[:k], b)
     few = qb.ivf_adc_scan_topk(idx, *lists, torch.from_numpy(q[:2]).to(dev), torch.from_numpy(probe[:2]).to(dev), 400, R)
     for i in range(2):
         oi, od, _ = oracle.search_ivf(d, nbits, dsub, acc, cb, coarse, off, codes, ids, q[i], probe[i], 400, R)

@@ -30,9 +30,9 @@ def test_width_of_the_quantizers_blocks(rule, nq, per_query, calibration, pilot,
     assert rule("quantize_wide", nq * per_query, per_query, calibration, pilot, cheap) == wide
 
 
-@pytest.mark.parametrize("nq,wide", [(1, 1), (256, 1), (257, 0), (384, 0)])
-def test_width_of_the_calibrations_blocks(rule, nq, wide):
-    assert rule("calib_wide", nq) == wide
+@pytest.mark.parametrize("nq,threads", [(1, 1024), (256, 1024), (257, 512), (512, 512), (513, 256)])
+def test_width_of_the_calibrations_blocks(rule, nq, threads):
+    assert rule("calib_threads", nq) == threads
 
 
 @pytest.mark.parametrize("n,R,nq,codes", [
