@@ -347,7 +347,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
                     }
 #pragma unroll
                     for (int u = 0; u < PPT; ++u) {
-                        if (NT > QUANT_THREADS && base + u * NT >= hi) break;  // (in narrow blocks it costs more than it saves)
+                        if (base + u * NT >= hi) break;
                         const int id = base + u * NT + (int)threadIdx.x;
                         const uint32_t sm = sum_groups_rt(gd, gtab, w[u].x, w[u].y);
                         count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu);
