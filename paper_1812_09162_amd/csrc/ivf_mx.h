@@ -55,9 +55,10 @@ struct IvfMxLds {
 //      their exact distance, go to the pair's slot list.  So the lists hold what k_ivf_scan's would.
 // What bounds it: vector instructions and, behind them, the chain of loads that starts a block (three deep).  10^8 codes in
 // 65,536 lists, 10,000 queries x 64 probes (640,000 pairs in 75,000 groups, 8.7 million tiles of 16 x 16, 6 million
-// results within the bounds): 780 us, of which 370 make tables, 250 form rows and compare, 150 sum queued codes
-// again; 1544 us as a pass per four pairs with byte-pair tables in LDS (2048 entries of eight bytes to build per group, and
-// 1.3 random 8-byte reads per code and pair).  Seven waves per SIMD: with six 840 us, with five 920.
+// results within the bounds): the call 1609 us, 1682 with every quotient in fp64 (1240 and 1410 vector instructions a wave), when the
+// kernel took 780: 370 to make tables, 250 to form rows and compare, 150 to sum queued codes again; 1544 as a pass per four pairs
+// with byte-pair tables in LDS (2048 entries of eight bytes to build per group, and 1.3 random 8-byte reads per code and
+// pair).  Seven waves per SIMD: with six 840, with five 920.
 template <int DS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DS < 8 ? 7 : 6)))
 k_ivf_scan_mx(const float *__restrict__ cb, const float *__restrict__ coarse,

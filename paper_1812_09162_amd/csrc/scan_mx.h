@@ -18,13 +18,13 @@
 //              be within it lies in a group whose minimum is within it.  Those codes' exact keys are
 //              computed from the group tables, and the R smallest (key, id) are written.
 //
-// What bounds it: the matrix cores (busy 74 % of the time at 256 queries, at the 2.0 GHz the chip holds under
-// them), and beside them the vector units (minima, row addresses), which overlap them in part where both alternate
-// in a wave's stream.  16 x 4 bits, K = 256: four products of 64 (32 clocks each) and eight
-// three-operand minima per 32 x 32 results.  10^7 codes, 256 queries: 205 us = 12.5 T (code, query)
-// pairs/s, 940 us as look-ups in LDS (k_scan_mq); 32 queries: 40 and 165 us; {6,6,4} x 4, 32 queries:
-// 67 and 230 us (81 with the minima behind all products of a tile; 110 with the one-hot rows shifted together
-// on the vector units).  k_pick: 16 us for
+// What bounds it: the matrix cores, and beside them the vector units (minima, row addresses), which overlap them in part
+// where both alternate in a wave's stream.  16 x 4 bits, K = 256: four products of 64 (32 clocks each) and eight
+// three-operand minima per 32 x 32 results.  10^7 codes, 256 queries, by counters: matrix cores busy 312,400 of the 423,800 cycles in which a CU has
+// waves (74 %), vector instructions (37.8 million besides the products) 148,000.  Kernel times from a trace of 12 calls: 236 us, of which the uneven
+// end of 2442 blocks, two to a CU, is a tenth (940 us as look-ups in LDS, k_scan_mq); back to back the whole call takes 235.  32 queries:
+// 41 and 165 us; {6,6,4} x 4, 32 queries: 69 and 230 us (81 with the minima behind all products of a tile; 110 with the one-hot
+// rows shifted together on the vector units).  k_pick: 16 us for
 // 32 queries, 24 for 256 (it replaces the quantizer's pilot and k_final: 95 + 16 us at 256 queries).
 #include <string.h>
 
