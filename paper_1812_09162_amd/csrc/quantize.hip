@@ -424,6 +424,143 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     }
 }
 
+// The pilot of four queries by one block, for batches whose queries have one block each: the same bound as k_quantize's
+// own pilot (the largest key of the bin of the k-th smallest key among the first `pilot` codes), from the quantized tables
+// that it left.  A code is loaded and split once for the four, whose entries of a group are one 8-byte word of an
+// interleaved table; and once a few thousand codes are counted, the bin of the k-th among them bounds the final one from
+// above, and only keys up to it are counted from there on.
+// What bounds it: the 8-byte LDS reads, eight a code of 64 bits (random entries, about seven clocks a wave).  16 x 4 bits, 65,536 codes, 1000
+// queries: 42 us beside 8 of the quantizer that counts nothing; 95 with a block per query counting its own.
+#define PILOT4_THREADS 1024
+template <int KIND, typename QT>
+__global__ void __launch_bounds__(PILOT4_THREADS)
+k_pilot4(const DevLayout *__restrict__ L, const uint8_t *__restrict__ codes, int k, int pilot,
+         const void *__restrict__ qtables, int T, int gtab_len, int nq, GroupDesc gd, pq_qparams_t *__restrict__ qparams) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int NT = PILOT4_THREADS, PC = KIND == SCAN_NIB16 ? 2 : 4 /* codes per thread and round (128 registers) */, shift = sizeof(QT) == 1 ? 0 : 8;
+    constexpr bool WIDE = KIND == SCAN_NIB16 || KIND == SCAN_W128;
+    uint2 *tab = (uint2 *)smem;  // [gtab_len]
+    uint2 *ent = tab + gtab_len;  // [T] quantized entries of the four queries
+    uint32_t *hist = (uint32_t *)(ent + T);  // [MQ][256]
+    uint32_t *sel = hist + MQ * 256;         // [MQ][2]
+    const int q0 = blockIdx.x * MQ, wave = threadIdx.x / QADC_WAVE;
+    uint4 c[PC];  // a round's codes
+    auto request = [&](int base) {  // codes past the end: the last one again
+#pragma unroll
+        for (int u = 0; u < PC; ++u) {
+            int id = base + u * NT + (int)threadIdx.x;
+            id = id < pilot ? id : pilot - 1;
+            if (WIDE) {
+                c[u] = *(const uint4 *)(codes + (size_t)id * 16);
+            } else if (KIND == SCAN_C5) {
+                const size_t at = (size_t)id * 5;
+                if (id + 1 < pilot) {  // the two aligned dwords that hold the code
+                    const uint32_t *p = (const uint32_t *)(codes + (at & ~(size_t)3));
+                    const uint64_t w = (((uint64_t)p[1] << 32) | p[0]) >> (8 * ((uint32_t)at & 3u));
+                    c[u] = make_uint4((uint32_t)w, (uint32_t)(w >> 32) & 0xffu, 0u, 0u);
+                } else {  // (there may be no memory behind the last code)
+                    const uint8_t *p = codes + at;
+                    c[u] = make_uint4((uint32_t)p[0] | (uint32_t)p[1] << 8 | (uint32_t)p[2] << 16 | (uint32_t)p[3] << 24, p[4], 0u, 0u);
+                }
+            } else {
+                const uint2 w = *(const uint2 *)(codes + (size_t)id * 8);
+                c[u] = make_uint4(w.x, w.y, 0u, 0u);
+            }
+        }
+    };
+    request(0);
+    for (int e = threadIdx.x; e < T; e += NT) {
+        uint32_t v[MQ];
+#pragma unroll
+        for (int j = 0; j < MQ; ++j) v[j] = ((const QT *)qtables)[(size_t)(q0 + j < nq ? q0 + j : q0) * T + e];
+        ent[e] = make_uint2(v[0] | (v[1] << 16), v[2] | (v[3] << 16));
+    }
+    for (int i = threadIdx.x; i < MQ * 256; i += NT) hist[i] = 0;
+    __syncthreads();
+    // Group entries as sums of four at a time.  8-bit tables: not saturated (at most 64 addends of 255 stay below 2^16;
+    // the key is the smaller of the sum and q_max all the same).
+    if constexpr (KIND == SCAN_NIB8 || KIND == SCAN_NIB16) {
+        for (int e = threadIdx.x; e < gtab_len; e += NT) {  // group = code byte
+            const uint2 *s = ent + 32 * (e >> 8);
+            MqAcc<QT> a;
+            a.zero();
+            a.add(s[e & 15]);
+            a.add(s[16 + ((e >> 4) & 15)]);
+            tab[e] = make_uint2(a.a, a.b);
+        }
+    } else {
+        const int ng = L->ng;
+        for (int g = 0; g < ng; ++g) {
+            const int entries = 1 << L->gw[g], first = L->gfirst[g], cnt = L->gcount[g], base = L->gbase[g];
+            for (int e = threadIdx.x; e < entries; e += NT) {
+                uint32_t rem = (uint32_t)e;
+                MqAcc<QT> a;
+                a.zero();
+                for (int i = 0; i < cnt; ++i) {
+                    const int b = L->nbits[first + i];
+                    a.add(ent[L->toff[first + i] + (rem & ((1u << b) - 1u))]);
+                    rem >>= b;
+                }
+                tab[base + e] = make_uint2(a.a, a.b);
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t lim[MQ];  // keys in bins below it are counted (never the last: the selection's answer where there are too few)
+#pragma unroll
+    for (int j = 0; j < MQ; ++j) lim[j] = 255u << shift;
+    const uint32_t three = 3;
+    for (int base = 0; base < pilot; base += PC * NT) {
+        uint4 w[PC];
+#pragma unroll
+        for (int u = 0; u < PC; ++u) w[u] = c[u];
+        if (base + PC * NT < pilot) request(base + PC * NT);
+        MqAcc<QT> acc[PC];
+#pragma unroll
+        for (int u = 0; u < PC; ++u) {
+            acc[u].zero();
+            if constexpr (KIND == SCAN_NIB8 || KIND == SCAN_NIB16) {
+                const uint32_t d[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+#pragma unroll
+                for (int g = 0; g < (KIND == SCAN_NIB8 ? 8 : 16); g += 4) {
+                    acc[u].add(mq_entry<0>(g, d[g >> 2], three));
+                    acc[u].add(mq_entry<1>(g + 1, d[g >> 2], three));
+                    acc[u].add(mq_entry<2>(g + 2, d[g >> 2], three));
+                    acc[u].add(mq_entry<3>(g + 3, d[g >> 2], three));
+                }
+            } else {
+#pragma unroll
+                for (int g = 0; g < QADC_MAXG_FAST; ++g)
+                    if (g < gd.ng) {
+                        const uint32_t off = (uint32_t)(gd.off[g] & 31), wd = (uint32_t)gd.w[g];
+                        acc[u].add(tab[gd.base[g] + __builtin_amdgcn_ubfe(gd.off[g] >= 32 ? w[u].y : w[u].x, off, wd)]);
+                        if (WIDE) acc[u].add(tab[gd.base2[g] + __builtin_amdgcn_ubfe(gd.off[g] >= 32 ? w[u].w : w[u].z, off, wd)]);
+                    }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PC; ++u) {
+            const bool in = base + u * NT + (int)threadIdx.x < pilot;
+#pragma unroll
+            for (int j = 0; j < MQ; ++j) {
+                const uint32_t s = acc[u].sum(j);
+                if (in && s < lim[j]) atomicAdd(&hist[j * 256 + (s >> shift)], 1u);
+            }
+        }
+        // after 4,096 and 16,384 codes, and at the end: the bin of the k-th so far
+        const int done = base + PC * NT;
+        if (done == 4096 || done == 16384 || done >= pilot) {
+            __syncthreads();
+            if (wave < MQ) qadc_wave_select_bin(hist + wave * 256, (uint32_t)k, 0u, sel + 2 * wave);
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < MQ; ++j) lim[j] = min(sel[2 * j] + 1u, 255u) << shift;
+        }
+    }
+    if (threadIdx.x < MQ && q0 + (int)threadIdx.x < nq)
+        qparams[q0 + threadIdx.x].key_bound = sizeof(QT) == 1 ? sel[2 * threadIdx.x] : (sel[2 * threadIdx.x] << 8) | 255u;
+}
+
 // Pilot codes of a block at least, when several share them (one batch of a block of 256 threads, eight per thread, half of one of a
 // wide block), and at most.  A batch's requests beyond the slice ask for its last code again: ending them there cost more
 // (16 x 4 bits, 1000 queries, 88 us a call, 93 with an end in the loop).
@@ -479,11 +616,31 @@ static size_t quantize_lds(const DevLayout &h, int t_eff, size_t esz) {
            (size_t)h.gtab_len * esz;
 }
 
+#define PILOT4_LEAST 16384  // codes
+static size_t pilot4_lds(const DevLayout &h) { return ((size_t)h.gtab_len + (size_t)h.T) * sizeof(uint2) + MQ * 256 * 4 + MQ * 8; }
+
+// Whether a batch's pilots are counted four queries to a block (k_pilot4) behind a quantizer that counts none.  Stage calls of
+// gamma or Gaussian data, d = 128, R = 100, 200,001 codes, us a call, own pilots / four to a block: 16 x 4 bits 256 queries 89 / 105, 257 115 / 105, 512 144 / 134,
+// 1000 244 / 202; 32 x 4 257 178 / 159, 1000 422 / 312; {6,6,4} x 4 256 164 / 170, 257 209 / 169, 1000 417 / 315; 40-bit codes 111 / 125,
+// 149 / 126, 295 / 227; 8 x 8 134 / 142, 182 / 144, 363 / 263; {6,6,4} x 8 64 queries 229 / 206, 257 499 / 379, 1000 1078 / 792: where a CU would have
+// more than one query's pilot.  Short ones lose the second launch: {6,5,5} x 4, 301 codes, 1030 queries 80 / 87; 40-bit, 5000 codes, 1100 114 / 117;
+// 16,384 codes, 300 queries: 16 x 4 47.8 / 45.1, 40-bit 67 / 59.
+template <int KIND>
+static bool pilot4_pays(const DevLayout &h, int nq, const PilotPlan &pp) {
+    if (KIND == SCAN_GENERIC || pp.P != 1 || pp.pilot < PILOT4_LEAST) return false;
+    if ((KIND == SCAN_W64 || KIND == SCAN_C5) && (h.g32ok == 0 || h.ng > QADC_MAXG_FAST)) return false;
+    if (KIND == SCAN_W128 && h.ng / 2 > QADC_MAXG_FAST) return false;
+    return nq > 256 && pilot4_lds(h) <= 128 * 1024;
+}
+
 template <int KIND, typename QT>
 static int launch_quantize(const pq_index *idx, const float *queries, const float *tables_in,
                            float *tables_out, int nq, const uint8_t *codes, int t_eff, int k,
-                           const PilotPlan &pp, void *qtables, pq_qparams_t *qparams, char *gtab_out,
+                           const PilotPlan &plan, void *qtables, pq_qparams_t *qparams, char *gtab_out,
                            size_t gtab_stride, size_t btab_rel, char *hdr_out, uint16_t *bound_rec, hipStream_t s) {
+    const bool pilot4 = pilot4_pays<KIND>(idx->h, nq, plan);
+    PilotPlan pp = plan;
+    if (pilot4) pp.pilot = 0;
     const size_t lds = quantize_lds(idx->h, t_eff, sizeof(QT));
     int ubits = idx->h.nbits[0], uds = idx->h.dsub[0];
     for (int j = 1; j < idx->h.m; ++j) {
@@ -503,6 +660,26 @@ static int launch_quantize(const pq_index *idx, const float *queries, const floa
     if (quantize_wide((int64_t)nq * pp.P, pp.P, t_eff, pp.pilot, KIND == SCAN_NIB8)) QADC_QUANT_GO(QUANT_WIDE); else QADC_QUANT_GO(QUANT_THREADS);
 #undef QADC_QUANT_GO
     QADC_LAUNCH_CHECK("k_quantize");
+    if constexpr (KIND != SCAN_GENERIC)
+        if (pilot4) {
+            GroupDesc gd = group_desc_args(idx->h);
+            if (KIND == SCAN_W128) gd.ng = idx->h.ng / 2;
+            const size_t lds4 = pilot4_lds(idx->h);
+            // (mq_entry reads its table from LDS address 0: the kernel must have no static LDS)
+            static const bool at_zero = [] {
+                hipFuncAttributes a;
+                return hipFuncGetAttributes(&a, (const void *)k_pilot4<KIND, QT>) == hipSuccess && a.sharedSizeBytes == 0;
+            }();
+            if (!at_zero) {
+                qadc_set_error("k_pilot4: static LDS (its tables must start at LDS address 0)");
+                return PQ_EHIP;
+            }
+            if (lds4 > 48 * 1024)
+                QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_pilot4<KIND, QT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds4));
+            hipLaunchKernelGGL((k_pilot4<KIND, QT>), dim3((unsigned)(nq + MQ - 1) / MQ), dim3(PILOT4_THREADS), lds4, s, idx->dev, codes, k,
+                               plan.pilot, qtables, idx->h.T, idx->h.gtab_len, nq, gd, qparams);
+            QADC_LAUNCH_CHECK("k_pilot4");
+        }
     return PQ_OK;
 }
 

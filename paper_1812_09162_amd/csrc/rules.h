@@ -8,7 +8,8 @@
 //   one block does a query's whole work (batches for the matrix cores, no scratch memory), 2 * 10^6 codes, R = 100: 16 x 4 bits, 192
 //     queries 62.7 / 62.0 and 48.5 / 49.8; 320: 101 / 105 and 81 / 84; {6,6,4} x 4, 256: 139 / 134 and
 //     117 / 118; 320: 184 / 189 and 147 / 153 (k_quantize itself, 32 queries: 22 / 15.2): up to one block per CU
-//   ... and counts a pilot too (tables quantized for inspection), 10^6 codes: 300 queries 16 x 4 59 / 52, 40-bit 117 / 77, 8 x 8 145 / 98, {6,6,4} x 8
+//   ... and counts a pilot too (tables quantized for inspection; since then k_pilot4 has taken over above 256 queries what its kinds of codes and
+//     16,384 codes of pilot allow), 10^6 codes: 300 queries 16 x 4 59 / 52, 40-bit 117 / 77, 8 x 8 145 / 98, {6,6,4} x 8
 //     279 / 209; 256: 53 / 28, 112 / 40, 139 / 51, 240 / 107: up to two
 //   one query over 128 blocks, R = 100: 16 x 4 bits, 10^7 codes 34.9 / 32.6 and 12.7 / 15.3: not with short calibrations
 //   ... more than 1024 calibration codes: one query, 10^6 codes, R = 257: 16 x 4 bits 30.2 / 27.1 and 16.8 / 15.7, 40-bit codes 41.2 / 32.3

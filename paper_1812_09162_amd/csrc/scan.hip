@@ -362,7 +362,6 @@ k_scan(const DevLayout *__restrict__ L, const void *__restrict__ qtables,
 // 32-bit adds accumulate them (eight or sixteen addends of at most 255 cannot carry out
 // of a 16-bit field).  Code bytes are loaded and split into indices once for all four.
 // NG = groups per code (8: 64-bit codes, 16: 128-bit codes).
-#define MQ 4
 #define MQ_STAGE_BYTES ((SCAN_THREADS / QADC_WAVE) * MQ * QADC_WSTAGE * 8)
 template <int NG>
 __global__ void __launch_bounds__(SCAN_THREADS)
@@ -498,45 +497,6 @@ k_scan_mq(const pq_qparams_t *__restrict__ qparams, int nq, const uint8_t *__res
 // The same for the irregular layouts (5-, 8- and 16-byte codes with group descriptors, 8- or
 // 16-bit tables): entry e of the interleaved table holds the four queries' values of group
 // table entry e as {u16 q0, u16 q1, u16 q2, u16 q3}; a code's four sums live in two packed words.
-typedef unsigned short mq_u16x2 __attribute__((ext_vector_type(2)));
-// a += b on both 16-bit halves, saturating at 65535 (one packed instruction)
-__device__ __forceinline__ uint32_t mq_add_sat16(uint32_t a, uint32_t b) {
-    const mq_u16x2 r = __builtin_elementwise_add_sat(__builtin_bit_cast(mq_u16x2, a), __builtin_bit_cast(mq_u16x2, b));
-    return __builtin_bit_cast(uint32_t, r);
-}
-
-// Sums of four queries as two packed words: a = q0 | q1 << 16, b = q2 | q3 << 16.  8-bit tables:
-// plain adds (at most 16 groups of at most 255 cannot carry).  16-bit tables: saturating packed
-// adds, which is the saturating accumulation of Section 3.4 itself (q_max = 65535).
-template <typename QT>
-struct MqAcc {
-    uint32_t a, b;
-    __device__ __forceinline__ void zero() { a = b = 0; }
-    __device__ __forceinline__ void add(const uint2 e) {
-        if (sizeof(QT) == 1) {
-            a += e.x;
-            b += e.y;
-        } else {
-            a = mq_add_sat16(a, e.x);
-            b = mq_add_sat16(b, e.y);
-        }
-    }
-    __device__ __forceinline__ uint32_t sum(int j) const {
-        return j == 0 ? (a & 0xffffu) : j == 1 ? (a >> 16) : j == 2 ? (b & 0xffffu) : (b >> 16);
-    }
-};
-
-template <int NG, int NLO, typename QT>
-__device__ __forceinline__ void mq_add_groups(const GroupDesc &d, const uint2 *tab, uint32_t lo,
-                                              uint32_t hi, bool upper, MqAcc<QT> &acc) {
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        const uint32_t x = NLO >= 0 ? (g < NLO ? lo : hi) : (d.off[g] >= 32 ? hi : lo);
-        const int base = upper ? d.base2[g] : d.base[g];
-        acc.add(tab[base + __builtin_amdgcn_ubfe(x, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])]);
-    }
-}
-
 template <int KIND, typename QT, int NG, int MODE>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_mqg(const pq_qparams_t *__restrict__ qparams, int nq, const uint8_t *__restrict__ codes,

@@ -376,6 +376,47 @@ __device__ __forceinline__ uint2 mq_entry(int g, uint32_t w, uint32_t three) {
     return make_uint2((uint32_t)e, (uint32_t)(e >> 32));
 }
 
+// Four queries per pass over the codes.
+#define MQ 4
+typedef unsigned short mq_u16x2 __attribute__((ext_vector_type(2)));
+// a += b on both 16-bit halves, saturating at 65535 (one packed instruction)
+__device__ __forceinline__ uint32_t mq_add_sat16(uint32_t a, uint32_t b) {
+    const mq_u16x2 r = __builtin_elementwise_add_sat(__builtin_bit_cast(mq_u16x2, a), __builtin_bit_cast(mq_u16x2, b));
+    return __builtin_bit_cast(uint32_t, r);
+}
+
+// Sums of four queries as two packed words: a = q0 | q1 << 16, b = q2 | q3 << 16.  8-bit tables:
+// plain adds (at most 16 groups of at most 255 cannot carry).  16-bit tables: saturating packed
+// adds, which is the saturating accumulation of Section 3.4 itself (q_max = 65535).
+template <typename QT>
+struct MqAcc {
+    uint32_t a, b;
+    __device__ __forceinline__ void zero() { a = b = 0; }
+    __device__ __forceinline__ void add(const uint2 e) {
+        if (sizeof(QT) == 1) {
+            a += e.x;
+            b += e.y;
+        } else {
+            a = mq_add_sat16(a, e.x);
+            b = mq_add_sat16(b, e.y);
+        }
+    }
+    __device__ __forceinline__ uint32_t sum(int j) const {
+        return j == 0 ? (a & 0xffffu) : j == 1 ? (a >> 16) : j == 2 ? (b & 0xffffu) : (b >> 16);
+    }
+};
+
+template <int NG, int NLO, typename QT>
+__device__ __forceinline__ void mq_add_groups(const GroupDesc &d, const uint2 *tab, uint32_t lo,
+                                              uint32_t hi, bool upper, MqAcc<QT> &acc) {
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const uint32_t x = NLO >= 0 ? (g < NLO ? lo : hi) : (d.off[g] >= 32 ? hi : lo);
+        const int base = upper ? d.base2[g] : d.base[g];
+        acc.add(tab[base + __builtin_amdgcn_ubfe(x, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])]);
+    }
+}
+
 // ------------------------------------------------------------ slot lists ---
 #define MAX_G 4096                 // slot lists per query a final kernel can gather
 #define FINAL_LPT (MAX_G / 1024)   // slot lists per thread of a 1024-thread final kernel
