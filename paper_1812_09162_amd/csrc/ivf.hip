@@ -1139,6 +1139,8 @@ __device__ inline uint64_t tight_keep_small(uint64_t *A, int na, int R, int nsor
     return ((uint64_t)sh[3] << 32) | sh[2];
 }
 
+#include "ivf_tight.h"
+
 template <int KIND, typename QT, int CAP, int DS = 0>
 __global__ void __launch_bounds__(256)
 k_ivf_tight(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
@@ -1404,6 +1406,19 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
 #undef QADC_IVF_CALIB1
 #undef QADC_IVF_CALIB
     QADC_LAUNCH_CHECK("k_ivf_calib");
+    if (tighten && dsf != 0 && R <= 256 && KIND == SCAN_NIB8 && sizeof(QT) == 1) {
+#define QADC_IVF_TIGHT_FIX(DSV, NRV)                                                                 \
+    hipLaunchKernelGGL((k_ivf_tight_fix<DSV, NRV>), dim3(nq), dim3(TIGHTF_THREADS), 0, s, idx->codebooks, coarse, \
+                       list_offsets, list_codes, list_ids, queries, probe_ids, nprobe, K, R, (const char *)ws, p.per_query, out_ids, out_dist)
+        if (R <= 128) {
+            if (dsf == 4) QADC_IVF_TIGHT_FIX(4, 2); else if (dsf == 6) QADC_IVF_TIGHT_FIX(6, 2); else QADC_IVF_TIGHT_FIX(8, 2);
+        } else {
+            if (dsf == 4) QADC_IVF_TIGHT_FIX(4, 4); else if (dsf == 6) QADC_IVF_TIGHT_FIX(6, 4); else QADC_IVF_TIGHT_FIX(8, 4);
+        }
+#undef QADC_IVF_TIGHT_FIX
+        QADC_LAUNCH_CHECK("k_ivf_tight_fix");
+        return PQ_OK;
+    }
     if (tighten) {
         static_assert(PQ_MAX_R + TIGHT_U * 256 <= TIGHT_CAP, "room for one batch above R candidates");
         const bool small_cap = R + TIGHT_U * 256 <= TIGHT_CAP_SMALL;

@@ -7,6 +7,14 @@
 
 #define QADC_WAVE 64
 
+// A copy in a register of its own.  In a loop whose next loads go to the registers that this round's values came in, the compiler otherwise keeps
+// the values there, loads to others and copies those back at the loop's end, which waits for the loads.
+__device__ __forceinline__ uint32_t qadc_move(uint32_t x) {
+    uint32_t r;
+    asm volatile("v_mov_b32 %0, %1" : "=&v"(r) : "v"(x));
+    return r;
+}
+
 // Sub-code extraction from a little-endian bit stream (Section 3.3): `b` bits
 // starting at bit `off`; b <= 8, so at most two bytes are touched and the
 // second one is only read when the field really reaches into it.
@@ -131,14 +139,15 @@ __device__ inline void qadc_wave_select_bin(const uint32_t *hist, uint32_t kk, u
     }
 }
 
-// k-th smallest (k >= 1, k <= cnt) of cnt > 0 uint32 values in LDS, by radix selection over
+// k-th smallest (k >= 1, k <= cnt) of cnt > 0 uint32 values vals[0..cnt) in LDS, by radix selection over
 // the bits in which the values differ at all: the bits above the highest differing one are
 // common to all values (ordered floats of similar size share their upper bytes, and counting
 // those would send every value to one histogram bin), the rest is taken eight bits at a time
 // from the top.  All threads of the block call it; `hist` is 256 words of LDS, `sel` two
 // words.  Returns the value to every thread.  (`nbytes` is kept for callers: the values'
 // width in bytes.)
-__device__ inline uint32_t qadc_block_kth_u32(const uint32_t *vals, int cnt, int k, int nbytes,
+template <class Vals>
+__device__ inline uint32_t qadc_block_kth_u32(const Vals &vals, int cnt, int k, int nbytes,
                                               uint32_t *hist, uint32_t *sel) {
     (void)nbytes;
     uint32_t mn = 0xffffffffu, mxn = 0xffffffffu;  // minimum, and minimum of the complements
@@ -206,7 +215,8 @@ __device__ inline uint32_t qadc_block_kth_u32(const uint32_t *vals, int cnt, int
 // is 256 words of LDS, `sel` eight, `mem` QADC_KTH_MEM.  Returns the value to every thread.
 // mn, mx: the smallest and largest value; `hist` is clear, and a barrier lies behind both.
 #define QADC_KTH_MEM 256
-__device__ inline uint32_t qadc_block_kth_f32(const uint32_t *vals, int cnt, int k, uint32_t *hist,
+template <class Vals>
+__device__ inline uint32_t qadc_block_kth_f32(const Vals &vals, int cnt, int k, uint32_t *hist,
                                               uint32_t *sel, uint32_t *mem, uint32_t mn, uint32_t mx) {
     if (threadIdx.x == 0) sel[2] = 0u;  // members gathered
     if (mn == mx) return mn;
@@ -252,7 +262,8 @@ __device__ inline uint32_t qadc_block_kth_f32(const uint32_t *vals, int cnt, int
 }
 
 // The same when the range has to be found first.
-__device__ inline uint32_t qadc_block_kth_f32(const uint32_t *vals, int cnt, int k, uint32_t *hist,
+template <class Vals>
+__device__ inline uint32_t qadc_block_kth_f32(const Vals &vals, int cnt, int k, uint32_t *hist,
                                               uint32_t *sel, uint32_t *mem) {
     uint32_t mn = 0xffffffffu, mx = 0u;
     for (int i = threadIdx.x; i < cnt; i += blockDim.x) {

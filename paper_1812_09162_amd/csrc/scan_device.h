@@ -123,6 +123,20 @@ __device__ __forceinline__ uint32_t sum8(const QT *t, uint32_t lo, uint32_t hi) 
            (uint32_t)t[1536 + ((hi >> 16) & 255u)] + (uint32_t)t[1792 + (hi >> 24)];
 }
 
+// The same of two codes with all sixteen reads in flight (where registers are few the compiler waits for every other one).
+__device__ __forceinline__ void sum8_two(const uint8_t *t, const uint2 &a, const uint2 &b, uint32_t sum[2]) {
+    uint32_t r[16];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+        r[g] = t[256 * g + (((g < 4 ? a.x : a.y) >> (8 * (g & 3))) & 255u)];
+        r[8 + g] = t[256 * g + (((g < 4 ? b.x : b.y) >> (8 * (g & 3))) & 255u)];
+    }
+    asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]),
+                      "+v"(r[8]), "+v"(r[9]), "+v"(r[10]), "+v"(r[11]), "+v"(r[12]), "+v"(r[13]), "+v"(r[14]), "+v"(r[15]));
+    sum[0] = r[0] + r[1] + r[2] + r[3] + r[4] + r[5] + r[6] + r[7];
+    sum[1] = r[8] + r[9] + r[10] + r[11] + r[12] + r[13] + r[14] + r[15];
+}
+
 template <typename QT>
 __device__ __forceinline__ uint32_t key_generic(const DevLayout *L, const QT *gtab,
                                                 const uint8_t *code) {
