@@ -122,6 +122,19 @@ int qadc_scan_mx(const pq_index *idx, const pq_qparams_t *qparams, int nq, const
                  int32_t *out_ids, uint16_t *out_keys, float *out_dist, char *ws, const ScanPlan &sp, const MxPlan &p,
                  hipStream_t s);
 
+// Short lists: the quantizer's blocks scan the whole list (k_quantize_short), P blocks of `slice` codes per query, `cap` entries in a block's list.
+#define SHORT_SLICE_BITS 12
+#define SHORT_CAP_MAX 208     // thirteen entries for each of the sixteen threads that read a list
+#define SHORT_BLOCKS 512      // of a call, where slices need not be longer for it; at most
+#define SHORT_MAX_BLOCKS 2048
+struct ShortPlan {
+    bool use;
+    int P, slice, cap;
+};
+ShortPlan qadc_short_plan(const pq_index *idx, int nq, int64_t n, int R, int t, const ScanPlan &sp);
+int qadc_quantize_short(const pq_index *idx, const float *queries, int nq, const uint8_t *codes, int64_t n, int t, int R, const ShortPlan &sh,
+                        void *qtables, pq_qparams_t *qparams, const ScanPlan &sp, char *ws, hipStream_t s);
+
 // btab_rel: if not 0, the operand tables of the batched matrix-core scan are written btab_rel bytes
 // behind the group tables, and no pilot is counted (that scan needs no bound).
 // gtab_out: if non-null, query q's group tables are also written to gtab_out + q*gtab_stride bytes.

@@ -67,17 +67,18 @@ __device__ __forceinline__ float quant_entry(const float *z, const float *__rest
     }
     return acc;
 }
-// (64-bit codes of nibbles: narrow blocks hold 80 registers without the bound, six to a CU, and calls of some 1600 to 1800 blocks have a second
-// filling: 16 x 4 bits, 85,000 codes, 41 queries 34.9 us a call, 32.9 with seven)
-template <int KIND, typename QT, int NT>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == QUANT_THREADS && KIND == SCAN_NIB8 ? 7 : 1)))
-k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryDesc *__restrict__ edesc,
-           const float *__restrict__ cb,
-           const float *__restrict__ queries, const float *__restrict__ tables_in,
-           float *__restrict__ tables_out, const uint8_t *__restrict__ codes, int t_eff, int k,
-           int pilot, int slice, int P, void *__restrict__ qtables,
-           pq_qparams_t *__restrict__ qparams, char *__restrict__ gtab_out, size_t gtab_stride, size_t btab_rel,
-           char *__restrict__ hdr_out, uint16_t *__restrict__ bound_rec) {
+#define QUANT_PARAMS                                                                                                             \
+    const DevLayout *__restrict__ L, const QuantShape shape, const EntryDesc *__restrict__ edesc, const float *__restrict__ cb, \
+    const float *__restrict__ queries, const float *__restrict__ tables_in, float *__restrict__ tables_out,                      \
+    const uint8_t *__restrict__ codes, int t_eff, int k, int pilot, int slice, int P, void *__restrict__ qtables,                \
+    pq_qparams_t *__restrict__ qparams, char *__restrict__ gtab_out, size_t gtab_stride, size_t btab_rel,                        \
+    char *__restrict__ hdr_out, uint16_t *__restrict__ bound_rec
+#define QUANT_ARGS                                                                                                                \
+    L, shape, edesc, cb, queries, tables_in, tables_out, codes, t_eff, k, pilot, slice, P, qtables, qparams, gtab_out, gtab_stride, \
+    btab_rel, hdr_out, bound_rec
+// SHORT: the pilot is the whole list, and instead of a record a block leaves the codes that can be results (k_quantize_short).
+template <int KIND, typename QT, int NT, bool SHORT>
+__device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, int short_cap) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int T = shape.T, m = shape.m, cs = shape.cs, qmax = shape.qmax, d = shape.d;
     float *tab = (float *)smem;
@@ -88,6 +89,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
     uint8_t *esub = (uint8_t *)(qt + T);
     QT *gtab = (QT *)(smem + (((size_t)T * 4 + (size_t)nord * 4 + PQ_MAX_M * 4 + (size_t)T * 3 + 15) &
                               ~(size_t)15));
+    uint16_t *skey = SHORT ? (uint16_t *)(gtab + ((L->gtab_len + 7) & ~7)) : nullptr;  // [slice] keys of the block's codes
     __shared__ __align__(16) uint32_t hist[256];
     __shared__ uint32_t sel[8];
     __shared__ uint32_t kmem[QADC_KTH_MEM];
@@ -301,14 +303,15 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
             }
         }
     }
-    if (hdr_out && first) scan_hdr_clear((ScanHdr *)(hdr_out + q * gtab_stride));  // empty candidate lists
+    if (!SHORT && hdr_out && first) scan_hdr_clear((ScanHdr *)(hdr_out + q * gtab_stride));  // empty candidate lists
     if (pilot > 0) {
         const int shift = sizeof(QT) == 1 ? 0 : 8;
         for (int i = threadIdx.x; i < 256; i += NT) hist[i] = 0;
         __syncthreads();
         // count one key (0xffffffff = none); the top bin collects every saturated key and
         // is counted once per wave
-        auto count_key = [&](uint32_t key) {
+        auto count_key = [&](uint32_t key, int id) {
+            if (SHORT && key != 0xffffffffu) skey[id - lo] = (uint16_t)key;
             const uint32_t bin = key == 0xffffffffu ? 0xffffffffu : key >> shift;
             const uint64_t top = __ballot(bin == 255u);
             if (top != 0 && __lane_id() == 0) atomicAdd(&hist[255], (uint32_t)__popcll(top));
@@ -329,7 +332,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
                     if (NT > QUANT_THREADS && base + u * NT >= hi) break;  // (in narrow blocks it costs more than it saves)
                     const int id = base + u * NT + (int)threadIdx.x;
                     const uint32_t sm = sum8(gtab, pc[u].x, pc[u].y);
-                    count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu);
+                    count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu, id);
                 }
             }
         } else if ((KIND == SCAN_W64 || KIND == SCAN_C5) && L->g32ok != 0 && L->ng <= QADC_MAXG_FAST) {
@@ -350,7 +353,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
                         if (base + u * NT >= hi) break;
                         const int id = base + u * NT + (int)threadIdx.x;
                         const uint32_t sm = sum_groups_rt(gd, gtab, w[u].x, w[u].y);
-                        count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu);
+                        count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu, id);
                     }
                 } else {
                     uint32_t c5[PPT / 4][5];
@@ -384,7 +387,7 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
                         }
                         // (count_key holds wave-wide operations: every lane calls it)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) count_key(k4[v]);
+                        for (int v = 0; v < 4; ++v) count_key(k4[v], id + v);
                     }
                 }
             }
@@ -394,11 +397,42 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
                 keys_batch<KIND, QT, PPT>(L, gtab, codes, (int64_t)base + threadIdx.x, NT,
                                         (int64_t)hi, key);
 #pragma unroll
-                for (int u = 0; u < PPT; ++u) count_key(key[u]);
+                for (int u = 0; u < PPT; ++u) count_key(key[u], base + u * NT + (int)threadIdx.x);
             }
         }
         __syncthreads();
-        if (P > 1) {
+        if constexpr (SHORT) {
+            // The codes of as many whole bins from the lowest on as the block's list holds, and how many bins these are: no code outside them
+            // is in a lower bin than one inside, so if the R-th of all is within every block's bins, it was found among these.
+            if (threadIdx.x < QADC_WAVE) {
+                const uint4 h4 = *(const uint4 *)&hist[4 * threadIdx.x];
+                const uint32_t c4 = h4.x + h4.y + h4.z + h4.w, room = (uint32_t)short_cap;
+                uint32_t run = qadc_wave_incl_scan(c4) - c4;
+                uint32_t whole = 0;
+                whole += (run += h4.x) <= room ? 1u : 0u;
+                whole += (run += h4.y) <= room ? 1u : 0u;
+                whole += (run += h4.z) <= room ? 1u : 0u;
+                whole += (run += h4.w) <= room ? 1u : 0u;
+                whole = (uint32_t)__builtin_amdgcn_readlane((int)qadc_wave_incl_scan(whole), QADC_WAVE - 1);
+                if (threadIdx.x == 0) {
+                    sel[0] = whole;
+                    sel[1] = 0u;
+                }
+            }
+            __syncthreads();
+            const uint32_t whole = sel[0];
+            ScanHdr *hd = (ScanHdr *)(hdr_out + q * gtab_stride);
+            uint32_t *cand = (uint32_t *)(hdr_out + q * gtab_stride + cand_rel) + (size_t)p * short_cap;
+            for (int i = threadIdx.x; i < hi - lo; i += NT) {
+                const uint32_t key = skey[i];
+                if ((key >> shift) < whole) cand[atomicAdd(&sel[1], 1u)] = (key << SHORT_SLICE_BITS) | (uint32_t)i;
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                hd->count[p][0] = sel[1];
+                hd->count[p][1] = whole;
+            }
+        } else if (P > 1) {
             // this block's record: cumulative counts over 64 coarse bins, one lane per bin
             if (threadIdx.x < QADC_WAVE) {
                 const uint4 h4 = *(const uint4 *)&hist[4 * threadIdx.x];
@@ -422,6 +456,24 @@ k_quantize(const DevLayout *__restrict__ L, const QuantShape shape, const EntryD
         prm.key_bound = bound;
         qparams[q] = prm;
     }
+}
+
+// (64-bit codes of nibbles: narrow blocks hold 80 registers without the bound, six to a CU, and calls of some 1600 to 1800 blocks have a second
+// filling: 16 x 4 bits, 85,000 codes, 41 queries 34.9 us a call, 32.9 with seven)
+template <int KIND, typename QT, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == QUANT_THREADS && KIND == SCAN_NIB8 ? 7 : 1)))
+k_quantize(QUANT_PARAMS) {
+    quantize_block<KIND, QT, NT, false>(QUANT_ARGS, 0, 0);
+}
+
+// Short lists, a few queries: the blocks that would count a pilot count every code of the list, so the scan's work is done when
+// they have, and they leave the codes that can be results, a list per block of (key, place in the slice), for k_short_final.
+// (512 threads: 16 x 4 bits, one query over 250,000 codes 17.6 us a call, 20.3 with 256, 17.0 with 1024; 32 queries over 65,537 26.9, 24.6, 45.2.)
+#define SHORT_THREADS 512
+template <int KIND, typename QT>
+__global__ void __launch_bounds__(SHORT_THREADS)
+k_quantize_short(QUANT_PARAMS, size_t cand_rel, int short_cap) {
+    quantize_block<KIND, QT, SHORT_THREADS, true>(QUANT_ARGS, cand_rel, short_cap);
 }
 
 // The pilot of four queries by one block, for batches whose queries have one block each: the same bound as k_quantize's
@@ -610,6 +662,16 @@ PilotPlan qadc_pilot_plan(int nq, int64_t n, int t_eff, int R, bool have_scratch
     return pp;
 }
 
+// bits and dimensions of every sub-quantizer if they are all alike, else 0
+static void quantize_alike(const DevLayout &h, int &ubits, int &uds) {
+    ubits = h.nbits[0];
+    uds = h.dsub[0];
+    for (int j = 1; j < h.m; ++j) {
+        if (h.nbits[j] != ubits) ubits = 0;
+        if (h.dsub[j] != uds) uds = 0;
+    }
+}
+
 static size_t quantize_lds(const DevLayout &h, int t_eff, size_t esz) {
     const size_t nord = (size_t)((t_eff > h.d ? t_eff : h.d) > 0 ? (t_eff > h.d ? t_eff : h.d) : 1);
     return (((size_t)h.T * 4 + nord * 4 + PQ_MAX_M * 4 + (size_t)h.T * 3 + 15) & ~(size_t)15) +
@@ -633,6 +695,70 @@ static bool pilot4_pays(const DevLayout &h, int nq, const PilotPlan &pp) {
     return nq > 256 && pilot4_lds(h) <= 128 * 1024;
 }
 
+// The whole of a short list's scan by the quantizer's blocks, if it is one: blocks per query, codes per block and entries of a block's list.
+// Where the pilot would be the whole list anyway, the slices are at most 4096 codes (64 lists a query: 262,144 codes) and a block's list holds the
+// results and a quarter more.  us a call of one query, R = 100, pilot and scan / this: 16 x 4 bits 1000 codes 20.2 / 15.2, 50,000 19.2 / 15.3,
+// 250,000 19.3 / 17.6; {6,6,4} x 4 33.6 / 21.5, 33.0 / 21.7, 33.2 / 26.0; 32 queries over 65,537: 33.5 / 22.9, 52.0 / 33.5.  None of
+// 110 sizes over six layouts was slower.
+ShortPlan qadc_short_plan(const pq_index *idx, int nq, int64_t n, int R, int t, const ScanPlan &sp) {
+    ShortPlan p = {};
+    if (n < 1 || nq < 1) return p;
+    const int64_t want = t > 4 * (int64_t)R ? t : 4 * (int64_t)R;
+    const PilotPlan pp = qadc_pilot_plan(nq, n, (int)(n < want ? n : want), R, true, idx->h.kind == SCAN_NIB8 || idx->h.kind == SCAN_NIB16);
+    if (pp.pilot < n) return p;
+    const int64_t least = R + R / 4 + 16, room = (int64_t)QADC_NSUB * sp.cap * 2;
+    if (least > SHORT_CAP_MAX || room < least) return p;
+    int64_t P = room / least < QADC_NSUB ? room / least : QADC_NSUB;
+    // (about two blocks per CU, with more queries longer slices: every block makes its query's tables.  130,001 codes, 16 queries, us a call, up to 1024 / 512
+    // blocks: 16 x 4 bits 25.1 / 20.4, {6,6,4} x 4 40.3 / 29.7, 40-bit codes 34.7 / 26.0; 65,537 codes, 32 queries 22.0 / 22.9, 32.2 / 33.5, 28.2 / 28.9)
+    const int64_t few = SHORT_BLOCKS / nq, longest = (n + (1 << SHORT_SLICE_BITS) - 1) >> SHORT_SLICE_BITS;
+    if (P > few) P = few > longest ? few : (longest < P ? longest : P);
+    const int64_t slice = ((n + P - 1) / P + 1023) / 1024 * 1024;
+    if (slice > (1 << SHORT_SLICE_BITS)) return p;
+    P = (n + slice - 1) / slice;
+    if (P * nq > SHORT_MAX_BLOCKS) return p;
+    p.use = true;
+    p.P = (int)P;
+    p.slice = (int)slice;
+    p.cap = (int)(room / P < SHORT_CAP_MAX ? room / P : SHORT_CAP_MAX);
+    return p;
+}
+
+template <int KIND, typename QT>
+static int launch_short(const pq_index *idx, const float *queries, int nq, const uint8_t *codes, int n, int t_eff, int k, const ShortPlan &sh,
+                        void *qtables, pq_qparams_t *qparams, const ScanPlan &sp, char *ws, hipStream_t s) {
+    const size_t lds = ((quantize_lds(idx->h, t_eff, sizeof(QT)) + 15) & ~(size_t)15) + 16 * sizeof(QT) + (size_t)sh.slice * 2;
+    int ubits, uds;
+    quantize_alike(idx->h, ubits, uds);
+    if (lds > 48 * 1024)
+        QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_quantize_short<KIND, QT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL((k_quantize_short<KIND, QT>), dim3((unsigned)nq * (unsigned)sh.P), dim3(SHORT_THREADS), lds, s, idx->dev,
+                       QuantShape{idx->h.T, idx->h.m, idx->h.cs, idx->h.qmax, idx->h.d, ubits, uds}, idx->edesc, idx->codebooks, queries,
+                       (const float *)nullptr, (float *)nullptr, codes, t_eff, k, n, sh.slice, sh.P, qtables, qparams, ws + sp.gtab_off,
+                       sp.per_query, (size_t)0, ws, (uint16_t *)nullptr, sp.cand_off, sh.cap);
+    QADC_LAUNCH_CHECK("k_quantize_short");
+    return PQ_OK;
+}
+
+int qadc_quantize_short(const pq_index *idx, const float *queries, int nq, const uint8_t *codes, int64_t n, int t, int R, const ShortPlan &sh,
+                        void *qtables, pq_qparams_t *qparams, const ScanPlan &sp, char *ws, hipStream_t s) {
+    const int64_t want = t > 4 * (int64_t)R ? t : 4 * (int64_t)R;
+    const int t_eff = (int)(n < want ? n : want), k = R < t_eff ? R : t_eff;
+    const bool u8 = idx->h.acc_bits == 8;
+#define QADC_GO(KIND)                                                                                                        \
+    return u8 ? launch_short<KIND, uint8_t>(idx, queries, nq, codes, (int)n, t_eff, k, sh, qtables, qparams, sp, ws, s)  \
+              : launch_short<KIND, uint16_t>(idx, queries, nq, codes, (int)n, t_eff, k, sh, qtables, qparams, sp, ws, s)
+    switch (idx->h.kind) {
+        case SCAN_NIB8: QADC_GO(SCAN_NIB8);
+        case SCAN_NIB16: QADC_GO(SCAN_NIB16);
+        case SCAN_W64: QADC_GO(SCAN_W64);
+        case SCAN_C5: QADC_GO(SCAN_C5);
+        case SCAN_W128: QADC_GO(SCAN_W128);
+        default: QADC_GO(SCAN_GENERIC);
+    }
+#undef QADC_GO
+}
+
 template <int KIND, typename QT>
 static int launch_quantize(const pq_index *idx, const float *queries, const float *tables_in,
                            float *tables_out, int nq, const uint8_t *codes, int t_eff, int k,
@@ -642,11 +768,8 @@ static int launch_quantize(const pq_index *idx, const float *queries, const floa
     PilotPlan pp = plan;
     if (pilot4) pp.pilot = 0;
     const size_t lds = quantize_lds(idx->h, t_eff, sizeof(QT));
-    int ubits = idx->h.nbits[0], uds = idx->h.dsub[0];
-    for (int j = 1; j < idx->h.m; ++j) {
-        if (idx->h.nbits[j] != ubits) ubits = 0;
-        if (idx->h.dsub[j] != uds) uds = 0;
-    }
+    int ubits, uds;
+    quantize_alike(idx->h, ubits, uds);
 #define QADC_QUANT_GO(NT)                                                                                         \
     do {                                                                                                          \
         if (lds > 48 * 1024)                                                                                      \

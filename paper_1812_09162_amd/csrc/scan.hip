@@ -645,6 +645,114 @@ k_final(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparam
                                             (const QT *)nullptr, gtab_room);
 }
 
+// ---------------------------------------------------------- k_short_final ---
+// The selection behind k_quantize_short: the lists of its P blocks, sixteen threads each, are read once (their lengths and entries in one
+// round trip), the bin of the R-th smallest key is found, and the candidates up to it are ranked.  Where that bin is not among the
+// whole bins of every block (a crowd of equal keys), the exact selection from the codes decides.
+#define SHORT_FINAL_THREADS (16 * QADC_NSUB)
+template <int KIND, typename QT>
+__global__ void __launch_bounds__(SHORT_FINAL_THREADS)
+k_short_final(const DevLayout *__restrict__ L, const pq_qparams_t *__restrict__ qparams, const uint8_t *__restrict__ codes,
+              int64_t n, int R, const char *__restrict__ ws, size_t per_query, size_t cand_off, size_t gtab_off, int P, int slice,
+              int cap, int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_keys, float *__restrict__ out_dist) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int NT = SHORT_FINAL_THREADS, ACAP = FINAL_SMALL_CAP, REG = SHORT_CAP_MAX / 16, shift = sizeof(QT) == 1 ? 0 : 8;
+    typedef SelectLds<NT, ACAP> Lds;
+    Lds &S = *(Lds *)smem;
+    const size_t q = blockIdx.x;
+    const char *wq = ws + q * per_query;
+    const ScanHdr *h = (const ScanHdr *)wq;
+    const int l = threadIdx.x / 16, sub = threadIdx.x % 16, wave = threadIdx.x / QADC_WAVE, lane = threadIdx.x % QADC_WAVE;
+    uint32_t c[REG], cnt = 0, whole = 256;
+#pragma unroll
+    for (int u = 0; u < REG; ++u) c[u] = 0;
+    if (l < P) {
+        const uint32_t *mine = (const uint32_t *)(wq + cand_off) + (size_t)l * cap;
+        cnt = h->count[l][0];
+        whole = h->count[l][1];
+#pragma unroll
+        for (int u = 0; u < REG; ++u)
+            if (u * 16 + sub < cap) c[u] = mine[u * 16 + sub];  // (beyond the length: read and ignored)
+    }
+    const pq_qparams_t prm = qparams[q];
+    for (int i = threadIdx.x; i < (NT / 64) * 256; i += NT) (&S.whist[0][0])[i] = 0;
+    if (threadIdx.x < 8) S.sh[threadIdx.x] = threadIdx.x == 3 ? 256u : 0u;  // 0: kept, 1: too many, 2: all, 3: least whole bins, 4: bin of the R-th
+    __syncthreads();
+    if (sub == 0) {
+        atomicAdd(&S.sh[2], cnt);
+        atomicMin(&S.sh[3], whole);
+    }
+#pragma unroll
+    for (int u = 0; u < REG; ++u)
+        if ((uint32_t)(u * 16 + sub) < cnt) atomicAdd(&S.whist[wave][c[u] >> (SHORT_SLICE_BITS + shift)], 1u);
+    __syncthreads();
+    const uint32_t E = S.sh[2];
+    if (threadIdx.x < QADC_WAVE) {
+        uint32_t hb[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) {
+            const uint4 x = *(const uint4 *)&S.whist[w][4 * lane];
+            hb[0] += x.x; hb[1] += x.y; hb[2] += x.z; hb[3] += x.w;
+        }
+        const uint32_t kk = E < (uint32_t)R ? E : (uint32_t)R;
+        const uint32_t s4 = hb[0] + hb[1] + hb[2] + hb[3];
+        uint32_t run = qadc_wave_incl_scan(s4) - s4;
+        uint32_t my = 0xffffffffu;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (my == 0xffffffffu && (run + hb[i] >= kk || 4 * lane + i == 255)) my = (uint32_t)(4 * lane + i);
+            run += hb[i];
+        }
+        const uint32_t best = qadc_wave_min(my);
+        if (lane == 0) S.sh[4] = best;
+    }
+    __syncthreads();
+    const uint32_t kbin = S.sh[4], least = S.sh[3];
+    int na = -1;
+    if (least == 256u || (E >= (uint32_t)R && kbin < least)) {
+#pragma unroll
+        for (int u = 0; u < REG; ++u) {
+            const uint32_t key = c[u] >> SHORT_SLICE_BITS;
+            if ((uint32_t)(u * 16 + sub) < cnt && (key >> shift) <= kbin) {
+                const uint32_t pos = atomicAdd(&S.sh[0], 1u);
+                if (pos < (uint32_t)ACAP) S.A[pos] = ((uint64_t)key << 32) | ((uint32_t)(l * slice) + (c[u] & ((1u << SHORT_SLICE_BITS) - 1u)));
+                else S.sh[1] = 1u;
+            }
+        }
+        __syncthreads();
+        na = S.sh[1] != 0 ? -1 : (int)S.sh[0];
+        __syncthreads();
+    }
+    FinalOut o;
+    o.ids = out_ids + q * R;
+    o.keys = out_keys + q * R;
+    o.dist = out_dist + q * R;
+    if (na < 0) {
+        QT *gtab = (QT *)(smem + sizeof(Lds));
+        const int n16 = (L->gtab_len * (int)sizeof(QT) + 15) >> 4;
+        for (int i = threadIdx.x; i < n16; i += NT) ((uint4 *)gtab)[i] = ((const uint4 *)(wq + gtab_off))[i];
+        __syncthreads();
+        exact_select<KIND, QT>(L, gtab, codes, n, R, S.A, S.hist, S.sh);
+        __syncthreads();
+        na = (int)S.sh[2];
+        __syncthreads();
+    }
+    rank_and_write<NT, ACAP>(S, na, R, prm, (uint32_t)L->qmax, o, shift);
+}
+
+template <int KIND, typename QT>
+static int launch_short_final(const pq_index *idx, const pq_qparams_t *qparams, int nq, const uint8_t *codes, int64_t n, int R,
+                              int32_t *out_ids, uint16_t *out_keys, float *out_dist, const char *ws, const ScanPlan &p, const ShortPlan &sh,
+                              hipStream_t s) {
+    const size_t lds = sizeof(SelectLds<SHORT_FINAL_THREADS, FINAL_SMALL_CAP>) + (((size_t)idx->h.gtab_len * sizeof(QT) + 15) & ~(size_t)15);
+    if (lds > 48 * 1024)
+        QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_short_final<KIND, QT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL((k_short_final<KIND, QT>), dim3(nq), dim3(SHORT_FINAL_THREADS), lds, s, idx->dev, qparams, codes, n, R, ws, p.per_query,
+                       p.cand_off, p.gtab_off, sh.P, sh.slice, sh.cap, out_ids, out_keys, out_dist);
+    QADC_LAUNCH_CHECK("k_short_final");
+    return PQ_OK;
+}
+
 // ------------------------------------------------------------------ host ---
 // what: 4 = prepare the group tables, 1 = scan kernel, 2 = selection kernel
 // mp: the matrix-core scan, if the call takes it (scan and selection asked for together).  The plan is
@@ -978,6 +1086,24 @@ extern "C" int pq_search_topk(const pq_index_t *idx, const float *queries, int n
     char *scratch = ws + up256(p.total);
     PilotPlan pp;
     const MxPlan mp = qadc_mx_plan(idx, nq, n, R, p, false);
+    const ShortPlan sh = mp.use ? ShortPlan{} : qadc_short_plan(idx, nq, n, R, t, p);
+    if (sh.use) {
+        rc = qadc_quantize_short(idx, queries, nq, codes, n, t, R, sh, qtables, qparams, p, ws, s);
+        if (rc != PQ_OK) return rc;
+        const bool u8 = idx->h.acc_bits == 8;
+#define QADC_GO(KIND)                                                                                                              \
+    return u8 ? launch_short_final<KIND, uint8_t>(idx, qparams, nq, codes, n, R, out_ids, out_keys, out_dist, ws, p, sh, s)  \
+              : launch_short_final<KIND, uint16_t>(idx, qparams, nq, codes, n, R, out_ids, out_keys, out_dist, ws, p, sh, s)
+        switch (idx->h.kind) {
+            case SCAN_NIB8: QADC_GO(SCAN_NIB8);
+            case SCAN_NIB16: QADC_GO(SCAN_NIB16);
+            case SCAN_W64: QADC_GO(SCAN_W64);
+            case SCAN_C5: QADC_GO(SCAN_C5);
+            case SCAN_W128: QADC_GO(SCAN_W128);
+            default: QADC_GO(SCAN_GENERIC);
+        }
+#undef QADC_GO
+    }
     rc = qadc_quantize_launch(idx, queries, nullptr, nullptr, nq, codes, n, t, R, qtables, qparams, ws + p.gtab_off,
                               p.per_query, mp.use ? mp.btab_off - p.gtab_off : (size_t)0, ws, scratch, &pp, s);
     if (rc != PQ_OK) return rc;

@@ -1039,17 +1039,21 @@ __device__ inline void rank_and_write(SelectLds<NT, ACAP> &S, int na, int R, con
     if (na <= 512) {
         // few candidates (the usual case): every candidate counts the smaller ones; all lanes
         // read the same four entries at a time (the list is filled up with largest ones)
+        // (one, two or four adjacent lanes share a candidate's count, as many as there are threads for)
         if (threadIdx.x < 4) S.A[na + threadIdx.x] = ~0ull;
         __syncthreads();
-        for (int i = threadIdx.x; i < na; i += NT) {
+        const int lp = 4 * na <= NT ? 2 : (2 * na <= NT ? 1 : 0), part = (int)threadIdx.x & ((1 << lp) - 1);
+        for (int i = (int)threadIdx.x >> lp; i < na; i += NT >> lp) {
             const uint64_t mine = A[i];
             int r = 0;
 #pragma unroll 4
-            for (int j = 0; j < na; j += 4) {
+            for (int j = 4 * part; j < na; j += 4 << lp) {
                 const ulonglong2 a = *(const ulonglong2 *)&A[j], b = *(const ulonglong2 *)&A[j + 2];
                 r += (a.x < mine ? 1 : 0) + (a.y < mine ? 1 : 0) + (b.x < mine ? 1 : 0) + (b.y < mine ? 1 : 0);
             }
-            if (r < R) {
+            if (lp > 0) r += (int)QADC_DPP_STEP(0u, r, 0xB1, 0xf);  // quad_perm [1,0,3,2]
+            if (lp > 1) r += (int)QADC_DPP_STEP(0u, r, 0x4E, 0xf);  // quad_perm [2,3,0,1]
+            if (part == 0 && r < R) {
                 const uint32_t key = (uint32_t)(mine >> 32);
                 o.ids[r] = (int32_t)(uint32_t)mine;
                 o.keys[r] = (uint16_t)key;
