@@ -33,9 +33,12 @@
 #define QUANT_WIDE 1024
 // The few layout numbers the kernel needs before anything else, as kernel arguments (reading
 // them through the layout pointer would be a memory round trip ahead of every other load).
+#define QUANT_MAX_GROUPS 16
 struct QuantShape {
     int T, m, cs, qmax, d;
     int ubits, uds;  // bits and dimensions of every sub-quantizer if they are all alike, else 0
+    int groups;      // groups described in grp (none: more of them, or of more than three sub-quantizers)
+    uint32_t grp[QUANT_MAX_GROUPS][2];  // first group-table entry | bits << 16 | sub-quantizers << 24; bits of the first two of them | the first one's table entry << 16
 };
 // Pilot codes of a thread per batch (a wide block's batch is 4096 codes, the longest slice that is usual)
 #define PILOT_PER_THREAD 8
@@ -67,6 +70,24 @@ __device__ __forceinline__ float quant_entry(const float *z, const float *__rest
     }
     return acc;
 }
+// The same with sub-spaces of different widths in a wave (those of 128 dimensions have up to 20): 24 values at a time, in one round trip.
+// ({6,6,4} x 4, 846,539 codes, one query: 33.0 us a call with eight at a time, 31.6; with loads past the end instead of none 32.2)
+__device__ __forceinline__ float quant_entry_ragged(const float *z, const float *__restrict__ c, int ds) {
+    constexpr int B = 24;
+    float acc = 0.0f;
+    for (int l = 0; l < ds; l += B) {
+        float cv[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) cv[u] = l + u < ds ? c[l + u] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (l + u < ds) {
+                const float diff = __fsub_rn(z[l + u], cv[u]);
+                acc = __fadd_rn(acc, __fmul_rn(diff, diff));
+            }
+    }
+    return acc;
+}
 #define QUANT_PARAMS                                                                                                             \
     const DevLayout *__restrict__ L, const QuantShape shape, const EntryDesc *__restrict__ edesc, const float *__restrict__ cb, \
     const float *__restrict__ queries, const float *__restrict__ tables_in, float *__restrict__ tables_out,                      \
@@ -76,6 +97,17 @@ __device__ __forceinline__ float quant_entry(const float *z, const float *__rest
 #define QUANT_ARGS                                                                                                                \
     L, shape, edesc, cb, queries, tables_in, tables_out, codes, t_eff, k, pilot, slice, P, qtables, qparams, gtab_out, gtab_stride, \
     btab_rel, hdr_out, bound_rec
+// fp32 sum in ascending order of the sixteen entries that the nibbles of two dwords select, all reads in flight
+__device__ __forceinline__ float adc_sum16(const float *tab, uint32_t lo, uint32_t hi, float s) {
+    float r[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) r[j] = tab[16 * j + (((j < 8 ? lo : hi) >> (4 * (j & 7))) & 15u)];
+    asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]),
+                      "+v"(r[8]), "+v"(r[9]), "+v"(r[10]), "+v"(r[11]), "+v"(r[12]), "+v"(r[13]), "+v"(r[14]), "+v"(r[15]));
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s = __fadd_rn(s, r[j]);
+    return s;
+}
 // SHORT: the pilot is the whole list, and instead of a record a block leaves the codes that can be results (k_quantize_short).
 template <int KIND, typename QT, int NT, bool SHORT>
 __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, int short_cap) {
@@ -95,8 +127,9 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
     __shared__ uint32_t kmem[QADC_KTH_MEM];
     __shared__ double s_dmin;
     __shared__ uint32_t s_range[2];  // smallest and largest calibration sum, as ordered words
-    __shared__ uint32_t sdesc[PQ_MAX_M];  // table offset | bit offset << 12 | bits << 24 of each sub-quantizer
+    __shared__ __align__(16) uint32_t sdesc[PQ_MAX_M];  // table offset | bit offset << 12 | bits << 24 of each sub-quantizer; beyond: 0
     __shared__ uint32_t pmin_ord[PQ_MAX_M];  // table minima as ordered words (qadc_f2ord), by LDS atomic min
+    if ((int)threadIdx.x >= m && threadIdx.x < PQ_MAX_M) sdesc[threadIdx.x] = 0u;
     if ((int)threadIdx.x < m) {  // (read after the barriers of the table set-up)
         sdesc[threadIdx.x] = (uint32_t)L->toff[threadIdx.x] | ((uint32_t)L->bitoff[threadIdx.x] << 12) |
                              ((uint32_t)L->nbits[threadIdx.x] << 24);
@@ -184,7 +217,7 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
         __syncthreads();
         for (int e = threadIdx.x; e < T; e += NT) {
             const EntryDesc ed = e == (int)threadIdx.x ? ed0 : edesc[e];
-            const float acc = quant_entry(zs + ed.dim_off, cb + ed.cb_off, ed.ds);
+            const float acc = KIND == SCAN_NIB8 || KIND == SCAN_NIB16 ? quant_entry(zs + ed.dim_off, cb + ed.cb_off, ed.ds) : quant_entry_ragged(zs + ed.dim_off, cb + ed.cb_off, ed.ds);
             tab[e] = acc;
             esub[e] = (uint8_t)ed.j;
             atomicMin(&pmin_ord[ed.j], qadc_f2ord(acc));
@@ -211,15 +244,10 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
         const uint32_t *cwr = cw[r & 1];  // (r < 2 whenever cal_pre)
         if (KIND == SCAN_NIB8) {  // sub-code j is nibble j of the 8-byte code
             const uint2 v = cal_pre ? make_uint2(cwr[0], cwr[1]) : *(const uint2 *)code;
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                s = __fadd_rn(s, tab[16 * j + (((j < 8 ? v.x : v.y) >> (4 * (j & 7))) & 15u)]);
+            s = adc_sum16(tab, v.x, v.y, s);
         } else if (KIND == SCAN_NIB16) {  // ... of the 16-byte code
             const uint4 v = cal_pre ? make_uint4(cwr[0], cwr[1], cwr[2], cwr[3]) : *(const uint4 *)code;
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int j = 0; j < 32; ++j)
-                s = __fadd_rn(s, tab[16 * j + ((w[j >> 3] >> (4 * (j & 7))) & 15u)]);
+            s = adc_sum16(tab + 256, v.z, v.w, adc_sum16(tab, v.x, v.y, s));
         } else if (cs <= 16) {  // the code in registers, the sub-quantizers' fields from LDS
             uint32_t w[4];
             if (cal_pre) {
@@ -227,9 +255,16 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
             } else {
                 qadc_load_code16(code, cs, w);
             }
-            for (int j = 0; j < m; ++j) {
-                const uint32_t ds = sdesc[j];
-                s = __fadd_rn(s, tab[(ds & 0xfffu) + qadc_extract_sub16(w, (ds >> 12) & 0xfffu, ds >> 24)]);
+            // (four sub-quantizers' descriptors, then their entries, in flight together; behind the last it is entry 0, not added)
+            for (int j = 0; j < m; j += 4) {
+                const uint4 dq = *(const uint4 *)&sdesc[j];
+                const uint32_t ds[4] = {dq.x, dq.y, dq.z, dq.w};
+                float r[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) r[i] = tab[(ds[i] & 0xfffu) + qadc_extract_sub16(w, (ds[i] >> 12) & 0xfffu, ds[i] >> 24)];
+                asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s = j + i < m ? __fadd_rn(s, r[i]) : s;
             }
         } else {
             for (int j = 0; j < m; ++j)
@@ -293,7 +328,25 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
     __syncthreads();
     uint32_t bound = (uint32_t)qmax;
     if (pilot > 0 || gtab_out) {
-        build_gtab<KIND, QT>(L, qt, gtab);
+        if ((KIND != SCAN_NIB8 && KIND != SCAN_NIB16) && shape.groups > 0) {
+            // build_gtab with the groups' descriptors at hand: read from the layout, they are two memory round trips a group
+#pragma unroll
+            for (int g = 0; g < QUANT_MAX_GROUPS; ++g)
+                if (g < shape.groups) {
+                    const uint32_t a = shape.grp[g][0], b = shape.grp[g][1];
+                    const int cnt = (int)(a >> 24), entries = 1 << ((a >> 16) & 255u), b0 = (int)(b & 15u), b1 = (int)((b >> 4) & 15u);
+                    const uint16_t *t0 = qt + (b >> 16), *t1 = t0 + (1 << b0), *t2 = t1 + (1 << b1);
+                    for (int e = threadIdx.x; e < entries; e += NT) {
+                        uint32_t s = t0[e & ((1 << b0) - 1)];
+                        if (cnt > 1) s += t1[(e >> b0) & ((1 << b1) - 1)];
+                        if (cnt > 2) s += t2[e >> (b0 + b1)];
+                        gtab[(a & 0xffffu) + e] = (QT)(s > (uint32_t)qmax ? (uint32_t)qmax : s);
+                    }
+                }
+            __syncthreads();
+        } else {
+            build_gtab<KIND, QT>(L, qt, gtab);
+        }
         if (gtab_out && first) {  // hand the prepared group tables to the scan kernel
             QT *dst = (QT *)(gtab_out + q * gtab_stride);
             for (int e = threadIdx.x; e < L->gtab_len; e += NT) dst[e] = gtab[e];
@@ -304,17 +357,17 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
         }
     }
     if (!SHORT && hdr_out && first) scan_hdr_clear((ScanHdr *)(hdr_out + q * gtab_stride));  // empty candidate lists
+    // (A block's time is a chain of LDS round trips: the entries of a code are read in flight together, and saturated keys, three in four,
+    // are not counted by a vote and an atomic of their own.  10^7 codes, one query, us a call: 16 x 4 bits 33.7 / 32.6; {6,6,4} x 4 34.1 / 31.1 of 846,539.)
     if (pilot > 0) {
         const int shift = sizeof(QT) == 1 ? 0 : 8;
         for (int i = threadIdx.x; i < 256; i += NT) hist[i] = 0;
         __syncthreads();
-        // count one key (0xffffffff = none); the top bin collects every saturated key and
-        // is counted once per wave
+        // count one key (0xffffffff = none); not those of the last bin, every saturated key among them: where the others are fewer
+        // than k it is the answer all the same
         auto count_key = [&](uint32_t key, int id) {
             if (SHORT && key != 0xffffffffu) skey[id - lo] = (uint16_t)key;
-            const uint32_t bin = key == 0xffffffffu ? 0xffffffffu : key >> shift;
-            const uint64_t top = __ballot(bin == 255u);
-            if (top != 0 && __lane_id() == 0) atomicAdd(&hist[255], (uint32_t)__popcll(top));
+            const uint32_t bin = key >> shift;
             if (bin < 255u) atomicAdd(&hist[bin], 1u);
         };
         if (KIND == SCAN_NIB8) {
@@ -328,11 +381,15 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
                     }
                 }
 #pragma unroll
-                for (int u = 0; u < PPT; ++u) {
+                for (int u = 0; u < PPT; u += 2) {
                     if (NT > QUANT_THREADS && base + u * NT >= hi) break;  // (in narrow blocks it costs more than it saves)
-                    const int id = base + u * NT + (int)threadIdx.x;
-                    const uint32_t sm = sum8(gtab, pc[u].x, pc[u].y);
-                    count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu, id);
+                    uint32_t sm[2];
+                    sum8_two(gtab, pc[u], pc[u + 1], sm);
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) {
+                        const int id = base + (u + v) * NT + (int)threadIdx.x;
+                        count_key(id < hi ? (sm[v] > (uint32_t)qmax ? (uint32_t)qmax : sm[v]) : 0xffffffffu, id);
+                    }
                 }
             }
         } else if ((KIND == SCAN_W64 || KIND == SCAN_C5) && L->g32ok != 0 && L->ng <= QADC_MAXG_FAST) {
@@ -352,7 +409,7 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
                     for (int u = 0; u < PPT; ++u) {
                         if (base + u * NT >= hi) break;
                         const int id = base + u * NT + (int)threadIdx.x;
-                        const uint32_t sm = sum_groups_rt(gd, gtab, w[u].x, w[u].y);
+                        const uint32_t sm = sum_groups_flight(gd, gtab, w[u].x, w[u].y);
                         count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu, id);
                     }
                 } else {
@@ -377,7 +434,7 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
                                                     (c5[u][3] >> 16) & 0xffu, c5[u][4] >> 24};
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
-                                const uint32_t sm = sum_groups_rt(gd, gtab, l4[v], h4[v]);
+                                const uint32_t sm = sum_groups_flight(gd, gtab, l4[v], h4[v]);
                                 k4[v] = sm > (uint32_t)qmax ? (uint32_t)qmax : sm;
                             }
                         } else {
@@ -385,7 +442,6 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
                             for (int v = 0; v < 4; ++v)
                                 k4[v] = id + v < hi ? key_at<KIND, QT>(L, gtab, codes, id + v) : 0xffffffffu;
                         }
-                        // (count_key holds wave-wide operations: every lane calls it)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) count_key(k4[v], id + v);
                     }
@@ -405,9 +461,10 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
             // The codes of as many whole bins from the lowest on as the block's list holds, and how many bins these are: no code outside them
             // is in a lower bin than one inside, so if the R-th of all is within every block's bins, it was found among these.
             if (threadIdx.x < QADC_WAVE) {
-                const uint4 h4 = *(const uint4 *)&hist[4 * threadIdx.x];
-                const uint32_t c4 = h4.x + h4.y + h4.z + h4.w, room = (uint32_t)short_cap;
-                uint32_t run = qadc_wave_incl_scan(c4) - c4;
+                uint4 h4 = *(const uint4 *)&hist[4 * threadIdx.x];
+                const uint32_t c4 = h4.x + h4.y + h4.z + h4.w, room = (uint32_t)short_cap, upto = qadc_wave_incl_scan(c4);
+                if (threadIdx.x == QADC_WAVE - 1) h4.w = (uint32_t)(hi - lo) - upto;  // (the last bin was not counted)
+                uint32_t run = upto - c4;
                 uint32_t whole = 0;
                 whole += (run += h4.x) <= room ? 1u : 0u;
                 whole += (run += h4.y) <= room ? 1u : 0u;
@@ -672,6 +729,22 @@ static void quantize_alike(const DevLayout &h, int &ubits, int &uds) {
     }
 }
 
+static QuantShape quantize_shape(const DevLayout &h) {
+    QuantShape s = {h.T, h.m, h.cs, h.qmax, h.d, 0, 0, 0, {}};
+    quantize_alike(h, s.ubits, s.uds);
+    bool ok = h.ng <= QUANT_MAX_GROUPS && h.gtab_len <= 65536;
+    for (int g = 0; g < h.ng && ok; ++g) ok = h.gcount[g] >= 1 && h.gcount[g] <= 3;
+    if (ok) {
+        s.groups = h.ng;
+        for (int g = 0; g < h.ng; ++g) {
+            const int f = h.gfirst[g], c = h.gcount[g];
+            s.grp[g][0] = (uint32_t)h.gbase[g] | ((uint32_t)h.gw[g] << 16) | ((uint32_t)c << 24);
+            s.grp[g][1] = (uint32_t)h.nbits[f] | (uint32_t)(c > 1 ? h.nbits[f + 1] : 0) << 4 | ((uint32_t)h.toff[f] << 16);
+        }
+    }
+    return s;
+}
+
 static size_t quantize_lds(const DevLayout &h, int t_eff, size_t esz) {
     const size_t nord = (size_t)((t_eff > h.d ? t_eff : h.d) > 0 ? (t_eff > h.d ? t_eff : h.d) : 1);
     return (((size_t)h.T * 4 + nord * 4 + PQ_MAX_M * 4 + (size_t)h.T * 3 + 15) & ~(size_t)15) +
@@ -728,12 +801,11 @@ template <int KIND, typename QT>
 static int launch_short(const pq_index *idx, const float *queries, int nq, const uint8_t *codes, int n, int t_eff, int k, const ShortPlan &sh,
                         void *qtables, pq_qparams_t *qparams, const ScanPlan &sp, char *ws, hipStream_t s) {
     const size_t lds = ((quantize_lds(idx->h, t_eff, sizeof(QT)) + 15) & ~(size_t)15) + 16 * sizeof(QT) + (size_t)sh.slice * 2;
-    int ubits, uds;
-    quantize_alike(idx->h, ubits, uds);
+    const QuantShape shape = quantize_shape(idx->h);
     if (lds > 48 * 1024)
         QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_quantize_short<KIND, QT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL((k_quantize_short<KIND, QT>), dim3((unsigned)nq * (unsigned)sh.P), dim3(SHORT_THREADS), lds, s, idx->dev,
-                       QuantShape{idx->h.T, idx->h.m, idx->h.cs, idx->h.qmax, idx->h.d, ubits, uds}, idx->edesc, idx->codebooks, queries,
+                       shape, idx->edesc, idx->codebooks, queries,
                        (const float *)nullptr, (float *)nullptr, codes, t_eff, k, n, sh.slice, sh.P, qtables, qparams, ws + sp.gtab_off,
                        sp.per_query, (size_t)0, ws, (uint16_t *)nullptr, sp.cand_off, sh.cap);
     QADC_LAUNCH_CHECK("k_quantize_short");
@@ -768,15 +840,14 @@ static int launch_quantize(const pq_index *idx, const float *queries, const floa
     PilotPlan pp = plan;
     if (pilot4) pp.pilot = 0;
     const size_t lds = quantize_lds(idx->h, t_eff, sizeof(QT));
-    int ubits, uds;
-    quantize_alike(idx->h, ubits, uds);
+    const QuantShape shape = quantize_shape(idx->h);
 #define QADC_QUANT_GO(NT)                                                                                         \
     do {                                                                                                          \
         if (lds > 48 * 1024)                                                                                      \
             QADC_HIP_TRY(hipFuncSetAttribute((const void *)k_quantize<KIND, QT, NT>,                              \
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));              \
         hipLaunchKernelGGL((k_quantize<KIND, QT, NT>), dim3((unsigned)nq * (unsigned)pp.P), dim3(NT), lds, s,     \
-                           idx->dev, QuantShape{idx->h.T, idx->h.m, idx->h.cs, idx->h.qmax, idx->h.d, ubits, uds}, \
+                           idx->dev, shape, \
                            idx->edesc, idx->codebooks, queries, tables_in, tables_out, codes, t_eff, k, pp.pilot, \
                            pp.slice, pp.P, qtables, qparams, gtab_out, gtab_stride, btab_rel, hdr_out, bound_rec); \
     } while (0)

@@ -124,7 +124,8 @@ __device__ __forceinline__ uint32_t sum8(const QT *t, uint32_t lo, uint32_t hi) 
 }
 
 // The same of two codes with all sixteen reads in flight (where registers are few the compiler waits for every other one).
-__device__ __forceinline__ void sum8_two(const uint8_t *t, const uint2 &a, const uint2 &b, uint32_t sum[2]) {
+template <typename QT>
+__device__ __forceinline__ void sum8_two(const QT *t, const uint2 &a, const uint2 &b, uint32_t sum[2]) {
     uint32_t r[16];
 #pragma unroll
     for (int g = 0; g < 8; ++g) {
@@ -203,6 +204,19 @@ __device__ __forceinline__ uint32_t sum_groups_rt(const GroupDesc &d, const QT *
             const uint32_t x = d.off[g] >= 32 ? hi : lo;
             s += gtab[d.base[g] + __builtin_amdgcn_ubfe(x, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])];
         }
+    return s;
+}
+// the same with the reads of all groups in flight (a branch per group has each waited for before the next); absent groups read entry 0
+template <typename QT>
+__device__ __forceinline__ uint32_t sum_groups_flight(const GroupDesc &d, const QT *gtab, uint32_t lo, uint32_t hi) {
+    static_assert(QADC_MAXG_FAST == 8, "eight operands below");
+    uint32_t r[QADC_MAXG_FAST], s = 0;
+#pragma unroll
+    for (int g = 0; g < QADC_MAXG_FAST; ++g)
+        r[g] = gtab[d.base[g] + __builtin_amdgcn_ubfe(d.off[g] >= 32 ? hi : lo, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])];
+    asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
+#pragma unroll
+    for (int g = 0; g < QADC_MAXG_FAST; ++g) s += g < d.ng ? r[g] : 0u;
     return s;
 }
 // ... of the upper half of a 128-bit code
