@@ -13,8 +13,10 @@
 //                <= thr0 go to the block's slot list as
 //                (ordered float distance << 32 | stored id).
 //   k_ivf_final  one block per query: gather the candidates, find the bin of the
-//                R-th, rank the few up to it; exact multi-pass selection over
+//                R-th, rank the few up to it; exact selection over
 //                all probed codes if a slot list overflowed.
+#include <type_traits>
+
 #include "ivf_mx.h"
 #include "rules.h"
 
@@ -510,6 +512,37 @@ k_pair_fill(const int32_t *__restrict__ probe_ids, const int64_t *__restrict__ l
     order[start[b] + atomicAdd(&fill[b], 1u)] = (uint32_t)p;
 }
 
+// The entries of slot[0..n) up to the R-th smallest distance (ordered word, upper half), R <= n, moved to the front; their number goes to
+// *count, the distance is returned.  The entries were written by this block.
+__device__ inline uint32_t ivf_cut_slots(uint64_t *slot, int n, int R, uint32_t *hist, uint32_t *sel, uint32_t *count) {
+    uint32_t prefix = 0, mask = 0, kk = (uint32_t)R;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
+        __syncthreads();
+        for (int i = threadIdx.x; i < n; i += blockDim.x) {
+            const uint32_t o = (uint32_t)(slot[i] >> 32);
+            if ((o & mask) == prefix) atomicAdd(&hist[(o >> shift) & 255u], 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x < QADC_WAVE) qadc_wave_select_bin(hist, kk, 0u, sel);
+        __syncthreads();
+        prefix |= sel[0] << shift;
+        mask |= 255u << shift;
+        kk -= sel[1];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *count = 0;
+    for (int i0 = 0; i0 < n; i0 += blockDim.x) {  // (what is written lies within what has been read)
+        const int i = i0 + (int)threadIdx.x;
+        const uint64_t e = i < n ? slot[i] : ~0ull;
+        __syncthreads();
+        if (i < n && (uint32_t)(e >> 32) <= prefix) slot[atomicAdd(count, 1u)] = e;
+    }
+    __threadfence_block();
+    __syncthreads();
+    return prefix;
+}
+
 // ------------------------------------------------------------- k_ivf_scan ---
 // One block per (query, probed cell).  A block is short (a few thousand codes behind a chain
 // of small dependent steps) and the kernel as a whole streams lists that are not cached, so
@@ -517,6 +550,9 @@ k_pair_fill(const int32_t *__restrict__ probe_ids, const int64_t *__restrict__ l
 //   A  probe id, query state, query, entry descriptors      (independent loads)
 //   B  list bounds, centroid, codebook values of the entries (need A)
 //   C  the first codes of the list                           (need B; used after the set-up)
+// A long list cuts its slots back to the codes up to the R-th distance and takes that distance as its bound from there on: no pair
+// needs more than its R best, and the bound of the pilot, the first few thousand probed codes, lets a list of 40,000 codes and more overflow its
+// slots.  (Where many codes share the R-th distance, or one in eight is within the bound, they still can: k_ivf_final then goes over the codes.)
 // NE = table entries per thread (1, 2 or 4; 0 = the general set-up routine, no early loads).
 // DS > 0 fixes the shape at compile time: 16 sub-quantizers of 16 centroids over DS dimensions
 // each (T = 256, d = 16 DS) and blocks of 256 / NE threads, so that table entry e = thread +
@@ -533,9 +569,10 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
            const int32_t *__restrict__ list_ids, const float *__restrict__ queries,
            const int32_t *__restrict__ probe_ids, int nprobe, int K, int R, char *__restrict__ ws,
            size_t per_query, size_t counts_off, size_t slots_off, int cap_b,
-           const uint32_t *__restrict__ order) {
+           const uint32_t *__restrict__ order, GroupDesc gd) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_count;
+    __shared__ uint32_t s_hist[256], s_sel[2];
     IvfLds l;
     ivf_carve(L, smem, sizeof(QT), l);
     // block -> (query, probe): in grid order, or in the order of the probed cells
@@ -701,28 +738,54 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
     const QT *gtab = (const QT *)l.gtab;
     const float fdelta = (float)l.sc[1], fdmin = (float)l.sc[0];
     uint64_t *slot = (uint64_t *)(wq + slots_off) + (size_t)a * cap_b;
+    // Long lists, behind every sixteenth batch (of four codes per thread): half full is cut back.  (Behind every batch it cost lists of some
+    // thousand codes up to 17 %, so shorter ones have a loop without; lists of some 10,000 codes that would not have overflowed lose 2 to 7 %.  us a
+    // call, before, with overflowing slots / here: 16 x 4 bits, one query, 37 lists of 220,000 codes in all 9380 / 210; {6,6,4} x 8, 28 queries over 1.5 * 10^7
+    // codes 43,900 / 1125; 8 x 8, 309 queries 31,000 / 880.)
+    int batch = 0;
+    auto make_room = [&](float &thr) {
+        if ((++batch & 15) != 0) return;
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane((int)s_count);
+        if (n > cap_b / 2 && n <= cap_b) {  // (hence n > R)
+            __threadfence_block();
+            __syncthreads();
+            thr = qadc_ord2f(ivf_cut_slots(slot, n, R, s_hist, s_sel, &s_count));
+        } else {
+            __syncthreads();  // (the count has been read)
+        }
+    };
+    auto scan_list = [&](auto is_long) {
+    constexpr bool LONG = decltype(is_long)::value;
+    float thr = thr0;
     if (NE > 0 && KIND == SCAN_NIB8) {
-        for (int64_t pb = 0; pb < npair; pb += (int64_t)PF * bd) {
-            if (pb != 0) {
+        auto request = [&](int64_t pb) {
 #pragma unroll
-                for (int u = 0; u < PF; ++u) {
-                    int64_t pi = pb + (int64_t)u * bd + threadIdx.x;
-                    pi = pi < npair ? pi : npair - 1;
-                    pp[u] = pairs[pi];
-                }
+            for (int u = 0; u < PF; ++u) {
+                int64_t pi = pb + (int64_t)u * bd + threadIdx.x;
+                pi = pi < npair ? pi : npair - 1;
+                pp[u] = pairs[pi];
             }
+        };
+        for (int64_t pb = 0; pb < npair; pb += (int64_t)PF * bd) {
+            if (!LONG && pb != 0) request(pb);
+            uint4 w[PF];
+#pragma unroll
+            for (int u = 0; u < PF; ++u)
+                w[u] = LONG ? make_uint4(qadc_move(pp[u].x), qadc_move(pp[u].y), qadc_move(pp[u].z), qadc_move(pp[u].w)) : pp[u];
+            if (LONG && pb + (int64_t)PF * bd < npair) request(pb + (int64_t)PF * bd);  // (a long list has the block, its loads' latency counts)
             uint32_t ord[2 * PF], id[2 * PF];
             bool pass[2 * PF], any = false;
 #pragma unroll
             for (int u = 0; u < PF; ++u) {
                 const int64_t pi = pb + (int64_t)u * bd + threadIdx.x;
-                const uint32_t k0 = sum8(gtab, pp[u].x, pp[u].y), k1 = sum8(gtab, pp[u].z, pp[u].w);
+                const uint32_t k0 = sum8(gtab, w[u].x, w[u].y), k1 = sum8(gtab, w[u].z, w[u].w);
                 const float d0 = fmaf((float)(k0 > (uint32_t)qmax ? (uint32_t)qmax : k0), fdelta, fdmin);
                 const float d1 = fmaf((float)(k1 > (uint32_t)qmax ? (uint32_t)qmax : k1), fdelta, fdmin);
                 ord[2 * u] = qadc_f2ord(d0);
                 ord[2 * u + 1] = qadc_f2ord(d1);
-                pass[2 * u] = pi < npair && d0 <= thr0;
-                pass[2 * u + 1] = pi < npair && d1 <= thr0;
+                pass[2 * u] = pi < npair && d0 <= thr;
+                pass[2 * u + 1] = pi < npair && d1 <= thr;
                 any = any || pass[2 * u] || pass[2 * u + 1];
             }
             if (__ballot(any) != 0) {
@@ -733,6 +796,7 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
                 }
                 slot_append_multi<2 * PF>(pass, ord, id, slot, (uint32_t)cap_b, &s_count);
             }
+            if constexpr (LONG) make_room(thr);
         }
         // the codes outside the pairs: position lo if it is odd, position hi-1 if one is left over
         if (threadIdx.x < QADC_WAVE) {
@@ -745,7 +809,7 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
                 const uint32_t key = key_at<KIND, QT>(L, gtab, list_codes, pos);
                 const float dist = fmaf((float)key, fdelta, fdmin);
                 o = qadc_f2ord(dist);
-                ps = dist <= thr0;
+                ps = dist <= thr;
                 idv = ps ? (uint32_t)list_ids[pos] : 0u;
             }
             slot_append(ps, o, idv, slot, (uint32_t)cap_b, &s_count);
@@ -754,12 +818,14 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
         for (int64_t base = lo; base < hi; base += 4 * bd) {
             uint32_t key[4], ord[4], id[4];
             bool pass[4], any = false;
-            keys_batch<KIND, QT, 4>(L, gtab, list_codes, base + threadIdx.x, bd, hi, key);
+            // (fields of 8-byte and shorter codes read in flight gain a single query up to 7 % and cost batches as much)
+            if constexpr (KIND == SCAN_W128) keys_batch_w128<QT, 4>(gd, gtab, list_codes, base + threadIdx.x, bd, hi, key);
+            else keys_batch<KIND, QT, 4>(L, gtab, list_codes, base + threadIdx.x, bd, hi, key);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const float dist = fmaf((float)(key[u] == 0xffffffffu ? 0u : key[u]), fdelta, fdmin);
                 ord[u] = qadc_f2ord(dist);
-                pass[u] = key[u] != 0xffffffffu && dist <= thr0;
+                pass[u] = key[u] != 0xffffffffu && dist <= thr;
                 any = any || pass[u];
             }
             if (__ballot(any) != 0) {
@@ -770,8 +836,11 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
                 }
                 slot_append_multi<4>(pass, ord, id, slot, (uint32_t)cap_b, &s_count);
             }
+            if constexpr (LONG) make_room(thr);
         }
     }
+    };
+    if (hi - lo > 16 * 4 * (int64_t)bd) scan_list(std::true_type{}); else scan_list(std::false_type{});
     __syncthreads();
     if (threadIdx.x == 0) counts[a] = s_count;  // uncapped: > cap_b tells k_ivf_final about the overflow
 }
@@ -889,137 +958,6 @@ __device__ inline void ivf_rank_and_write(const uint64_t *A, int na, int R, int3
     }
 }
 
-// Exact selection by one block over every code of the probed, unskipped lists:
-// byte-wise radix selection of the R-th smallest 64-bit (distance, id) word,
-// regenerating the stream once per byte, then one collecting pass.
-template <int KIND, typename QT>
-__device__ inline int ivf_exact_select(const DevLayout *L, const EntryDesc *edesc, const float *cb,
-                                       const float *coarse,
-                                       const int64_t *list_offsets, const uint8_t *list_codes,
-                                       const int32_t *list_ids, const float *z,
-                                       const int32_t *probes, int nprobe, int K, float dmax, int R,
-                                       const IvfLds &l, uint64_t *A, uint32_t *hist, uint32_t *sh) {
-    uint64_t prefix = 0, mask = 0;
-    uint32_t kk = 0;
-    // pass 8 counts the stream, passes 7..0 select a byte each, pass -1 collects
-    for (int pass = 8; pass >= -1; --pass) {
-        for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;
-        if (threadIdx.x == 0) sh[2] = 0;
-        __syncthreads();
-        for (int a = 0; a < nprobe; ++a) {
-            const int c = probes[a];
-            if (c < 0 || c >= K) continue;
-            const int64_t lo = list_offsets[c], hi = list_offsets[c + 1];
-            if (hi == lo) continue;
-            if (!ivf_setup<KIND, QT>(L, edesc, cb, z, coarse + (size_t)c * L->d, dmax, true, true, l)) continue;
-            const QT *gtab = (const QT *)l.gtab;
-            const float fdelta = (float)l.sc[1], fdmin = (float)l.sc[0];
-            for (int64_t p = lo + threadIdx.x; p < hi; p += blockDim.x) {
-                const uint32_t key = key_at<KIND, QT>(L, gtab, list_codes, p);
-                const uint64_t item = ((uint64_t)qadc_f2ord(fmaf((float)key, fdelta, fdmin)) << 32) |
-                                      (uint64_t)(uint32_t)list_ids[p];
-                if (pass == 8) {
-                    atomicAdd(&hist[0], 1u);
-                } else if (pass >= 0) {
-                    if ((item & mask) == prefix) atomicAdd(&hist[(item >> (8 * pass)) & 255u], 1u);
-                } else if (item <= prefix) {
-                    uint32_t pos = atomicAdd(&sh[2], 1u);
-                    if (pos < (uint32_t)R) A[pos] = item;
-                }
-            }
-            __syncthreads();
-        }
-        __syncthreads();
-        if (pass == 8) {
-            const uint32_t total = hist[0];
-            kk = total < (uint32_t)R ? total : (uint32_t)R;
-            if (kk == 0) return 0;
-        } else if (pass >= 0) {
-            if (threadIdx.x == 0) {
-                uint32_t run = 0;
-                int b = 0;
-                for (; b < 255; ++b) {
-                    if (run + hist[b] >= kk) break;
-                    run += hist[b];
-                }
-                sh[0] = (uint32_t)b;
-                sh[1] = kk - run;
-            }
-            __syncthreads();
-            prefix |= (uint64_t)sh[0] << (8 * pass);
-            mask |= (uint64_t)255u << (8 * pass);
-            kk = sh[1];
-        }
-        __syncthreads();
-    }
-    const uint32_t got = sh[2];
-    return (int)(got < (uint32_t)R ? got : (uint32_t)R);
-}
-
-// SMALL: blocks of 256 threads that can rank IVF_SMALL_CAP candidates (short result lists):
-// a quarter of the LDS and of the wave slots, so that several queries share a CU.
-#define IVF_SMALL_CAP 2048
-template <int KIND, typename QT, bool SMALL>
-__global__ void __launch_bounds__(SMALL ? 256 : 1024)
-k_ivf_final(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
-            const float *__restrict__ cb,
-            const float *__restrict__ coarse, const int64_t *__restrict__ list_offsets,
-            const uint8_t *__restrict__ list_codes, const int32_t *__restrict__ list_ids,
-            const float *__restrict__ queries, const int32_t *__restrict__ probe_ids, int nprobe,
-            int K, int R, char *__restrict__ ws, size_t per_query, size_t counts_off, size_t slots_off,
-            int cap_b, int32_t *__restrict__ out_ids, float *__restrict__ out_dist) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int CAP = SMALL ? IVF_SMALL_CAP : FINAL_CAP;
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t whist[SMALL ? 4 : 16][256];  // one histogram per wave
-    __shared__ uint32_t sh[32];
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t off[1024 + 1];  // one slot list per probed cell, nprobe <= 1024
-    uint64_t *A = (uint64_t *)smem;  // CAP entries
-    const size_t q = blockIdx.x;
-    char *wq = ws + q * per_query;
-    IvfState *st = (IvfState *)wq;
-    const uint32_t *counts = (const uint32_t *)(wq + counts_off);
-    const uint64_t *slots = (const uint64_t *)(wq + slots_off);
-    const float blo = st->lo, bscale = st->scale;
-    FinalShared S;
-    S.hist = hist;
-    S.whist = whist;
-    S.sh = sh;
-    S.wsum = wsum;
-    S.off = off;
-    int na = 0;
-    const bool slow = gather_select(
-        counts, slots, nprobe, cap_b, R,
-        [blo, bscale](uint64_t c) { return dist_bin(qadc_ord2f((uint32_t)(c >> 32)), blo, bscale); }, A,
-        CAP, S, na);
-    if (slow) {
-        IvfLds l;
-        ivf_carve(L, smem + CAP * 8, sizeof(QT), l);
-        na = ivf_exact_select<KIND, QT>(L, edesc, cb, coarse, list_offsets, list_codes, list_ids,
-                                        queries + q * L->d, probe_ids + q * nprobe, nprobe, K,
-                                        st->dmax, R, l, A, hist, sh);
-        __syncthreads();
-    }
-    ivf_rank_and_write(A, na, R, out_ids + q * R, out_dist + q * R);
-}
-
-// ------------------------------------------------------------ k_ivf_tight ---
-// The search with a bound that tightens from list to list (Section 3.5: a scanned vector is
-// kept when it is closer than the worst of the R candidates held; Section 3.4: that worst
-// distance is the largest the quantizer has to represent).  One block per query walks the
-// probed lists in probe order; list l is quantized against
-//     cur = min(d_max, R-th smallest distance among the candidates of the lists before l),
-// a list whose d_min is not below cur is skipped, and a code whose sum saturates is no
-// candidate.  The block holds the candidates as (ordered float distance << 32 | stored id) in
-// LDS; whenever the buffer runs full, and at the end of every list that added to it, the R
-// smallest are kept and the rest dropped: a dropped word is above R held ones, so it can
-// neither be a result nor move a later R-th smallest.
-#define TIGHT_CAP 4096       // words of the candidate buffer ...
-#define TIGHT_CAP_SMALL 2048 // ... and for R <= TIGHT_CAP_SMALL - TIGHT_U * 256: half the LDS, more blocks per CU
-#define TIGHT_U 4  // codes per thread between two looks at the fill level
-#define TIGHT_PC 64  // probes whose cells and list bounds are fetched together
-
 // k-th smallest (k = 1..na) of the different 64-bit words A[0..na), byte by byte from the top.
 __device__ inline uint64_t tight_kth(const uint64_t *A, int na, int k, uint32_t *hist, uint32_t *sh) {
     uint64_t prefix = 0, mask = 0;
@@ -1060,6 +998,147 @@ __device__ inline uint64_t tight_kth(const uint64_t *A, int na, int k, uint32_t 
     }
     return prefix;
 }
+
+// The R smallest of A[0..na), na > R, exactly R of them (equal words, which repeated ids give, among them); returns the R-th.
+template <int CAP, int NT>
+__device__ inline uint64_t ivf_keep(uint64_t *A, int na, int R, uint32_t *hist, uint32_t *sh, uint32_t *count) {
+    constexpr int PER = (CAP + NT - 1) / NT;
+    const uint64_t rth = tight_kth(A, na, R, hist, sh);
+    uint64_t mine[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = (int)threadIdx.x + u * NT;
+        mine[u] = i < na ? A[i] : ~0ull;
+    }
+    if (threadIdx.x == 0) *count = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (mine[u] < rth) A[atomicAdd(count, 1u)] = mine[u];  // (fewer than R)
+    __syncthreads();
+    for (int i = (int)*count + (int)threadIdx.x; i < R; i += NT) A[i] = rth;
+    __syncthreads();
+    if (threadIdx.x == 0) *count = (uint32_t)R;
+    __syncthreads();
+    return rth;
+}
+
+// Exact selection by one block over every code of the probed, unskipped lists, where a slot list overflowed: one pass, in which
+// the words (distance, id) within the bound are gathered in A and cut back to the R smallest when the next batch might not fit; the
+// R-th of them is the bound from there on.  (Ten passes, one to count and one per byte of the R-th word before: 220,000 codes
+// in 37 lists of 16 x 4 bits, one query, 9.4 ms a call.)
+template <int KIND, typename QT, int CAP, int NT>
+__device__ inline int ivf_exact_select(const DevLayout *L, const EntryDesc *edesc, const float *cb,
+                                       const float *coarse,
+                                       const int64_t *list_offsets, const uint8_t *list_codes,
+                                       const int32_t *list_ids, const float *z,
+                                       const int32_t *probes, int nprobe, int K, float dmax, float thr0, int R,
+                                       const IvfLds &l, uint64_t *A, uint32_t *hist, uint32_t *sh) {
+    constexpr int U = 2;
+    static_assert((CAP == FINAL_CAP ? PQ_MAX_R : FINAL_SMALL_R) + U * NT <= CAP, "a batch fits behind the R smallest");
+    uint32_t *count = sh + 8;
+    uint64_t most = ((uint64_t)qadc_f2ord(thr0) << 32) | 0xffffffffu;
+    int na = 0;
+    if (threadIdx.x == 0) *count = 0;
+    __syncthreads();
+    for (int a = 0; a < nprobe; ++a) {
+        const int c = probes[a];
+        if (c < 0 || c >= K) continue;
+        const int64_t lo = list_offsets[c], hi = list_offsets[c + 1];
+        if (hi == lo) continue;
+        if (!ivf_setup<KIND, QT>(L, edesc, cb, z, coarse + (size_t)c * L->d, dmax, true, true, l)) continue;
+        const QT *gtab = (const QT *)l.gtab;
+        const float fdelta = (float)l.sc[1], fdmin = (float)l.sc[0];
+        for (int64_t base = lo; base < hi; base += U * NT) {
+            if (na + U * NT > CAP) {
+                most = ivf_keep<CAP, NT>(A, na, R, hist, sh, count);
+                na = R;
+            }
+            uint32_t key[U];
+            keys_batch<KIND, QT, U>(L, gtab, list_codes, base + threadIdx.x, NT, hi, key);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (key[u] == 0xffffffffu) continue;
+                const uint32_t o = qadc_f2ord(fmaf((float)key[u], fdelta, fdmin));
+                if (o > (uint32_t)(most >> 32)) continue;
+                const uint64_t item = ((uint64_t)o << 32) | (uint64_t)(uint32_t)list_ids[base + u * NT + threadIdx.x];
+                if (item <= most) A[atomicAdd(count, 1u)] = item;
+            }
+            __syncthreads();
+            na = (int)*count;
+            __syncthreads();
+        }
+    }
+    if (na > R) {
+        ivf_keep<CAP, NT>(A, na, R, hist, sh, count);
+        na = R;
+    }
+    return na;
+}
+
+// SMALL: blocks of 256 threads that can rank IVF_SMALL_CAP candidates (short result lists):
+// a quarter of the LDS and of the wave slots, so that several queries share a CU.
+#define IVF_SMALL_CAP 2048
+template <int KIND, typename QT, bool SMALL>
+__global__ void __launch_bounds__(SMALL ? 256 : 1024)
+k_ivf_final(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
+            const float *__restrict__ cb,
+            const float *__restrict__ coarse, const int64_t *__restrict__ list_offsets,
+            const uint8_t *__restrict__ list_codes, const int32_t *__restrict__ list_ids,
+            const float *__restrict__ queries, const int32_t *__restrict__ probe_ids, int nprobe,
+            int K, int R, char *__restrict__ ws, size_t per_query, size_t counts_off, size_t slots_off,
+            int cap_b, int32_t *__restrict__ out_ids, float *__restrict__ out_dist) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int CAP = SMALL ? IVF_SMALL_CAP : FINAL_CAP;
+    __shared__ __align__(16) uint32_t hist[256];
+    __shared__ uint32_t whist[SMALL ? 4 : 16][256];  // one histogram per wave
+    __shared__ uint32_t sh[32];
+    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t off[1024 + 1];  // one slot list per probed cell, nprobe <= 1024
+    uint64_t *A = (uint64_t *)smem;  // CAP entries
+    const size_t q = blockIdx.x;
+    char *wq = ws + q * per_query;
+    IvfState *st = (IvfState *)wq;
+    const uint32_t *counts = (const uint32_t *)(wq + counts_off);
+    const uint64_t *slots = (const uint64_t *)(wq + slots_off);
+    const float blo = st->lo, bscale = st->scale;
+    FinalShared S;
+    S.hist = hist;
+    S.whist = whist;
+    S.sh = sh;
+    S.wsum = wsum;
+    S.off = off;
+    int na = 0;
+    const bool slow = gather_select(
+        counts, slots, nprobe, cap_b, R,
+        [blo, bscale](uint64_t c) { return dist_bin(qadc_ord2f((uint32_t)(c >> 32)), blo, bscale); }, A,
+        CAP, S, na);
+    if (slow) {
+        IvfLds l;
+        ivf_carve(L, smem + CAP * 8, sizeof(QT), l);
+        na = ivf_exact_select<KIND, QT, CAP, SMALL ? 256 : 1024>(L, edesc, cb, coarse, list_offsets, list_codes, list_ids,
+                                                                 queries + q * L->d, probe_ids + q * nprobe, nprobe, K,
+                                                                 st->dmax, st->thr0, R, l, A, hist, sh);
+        __syncthreads();
+    }
+    ivf_rank_and_write(A, na, R, out_ids + q * R, out_dist + q * R);
+}
+
+// ------------------------------------------------------------ k_ivf_tight ---
+// The search with a bound that tightens from list to list (Section 3.5: a scanned vector is
+// kept when it is closer than the worst of the R candidates held; Section 3.4: that worst
+// distance is the largest the quantizer has to represent).  One block per query walks the
+// probed lists in probe order; list l is quantized against
+//     cur = min(d_max, R-th smallest distance among the candidates of the lists before l),
+// a list whose d_min is not below cur is skipped, and a code whose sum saturates is no
+// candidate.  The block holds the candidates as (ordered float distance << 32 | stored id) in
+// LDS; whenever the buffer runs full, and at the end of every list that added to it, the R
+// smallest are kept and the rest dropped: a dropped word is above R held ones, so it can
+// neither be a result nor move a later R-th smallest.
+#define TIGHT_CAP 4096       // words of the candidate buffer ...
+#define TIGHT_CAP_SMALL 2048 // ... and for R <= TIGHT_CAP_SMALL - TIGHT_U * 256: half the LDS, more blocks per CU
+#define TIGHT_U 4  // codes per thread between two looks at the fill level
+#define TIGHT_PC 64  // probes whose cells and list bounds are fetched together
 
 // Keep the R smallest of A[0..na), na > R; returns the R-th smallest.  *count becomes R.
 template <int CAP>
@@ -1487,13 +1566,15 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
         QADC_LAUNCH_CHECK("k_ivf_scan_mx");
     } else {
     const int scan_threads = (int)qadc_option(PQ_OPT_IVF_THREADS);
+    GroupDesc gd = group_desc_args(idx->h);
+    if (KIND == SCAN_W128) gd.ng = idx->h.ng / 2;
     // table entries per thread: the low-latency set-up holds up to four in registers
     const int ne = idx->h.T <= scan_threads ? 1 : (idx->h.T <= 2 * scan_threads ? 2 : (idx->h.T <= 4 * scan_threads ? 4 : 0));
 #define QADC_IVF_SCAN(NEV)                                                                          \
     hipLaunchKernelGGL((k_ivf_scan<KIND, QT, NEV>), dim3(nprobe, nq), dim3(scan_threads), lds_scan, s, \
                        idx->dev, idx->edesc, idx->codebooks, coarse, list_offsets, list_codes,     \
                        list_ids, queries, probe_ids, nprobe, K, R, ws, p.per_query, p.counts_off,  \
-                       p.slots_off, p.cap_b, order)
+                       p.slots_off, p.cap_b, order, gd)
     // 16 x 4 bits over equal sub-spaces with 8-bit tables, at the default block size: the
     // fixed-shape set-up
     const int dsfix = scan_threads == 128 ? dsf : 0;
@@ -1501,7 +1582,7 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
     hipLaunchKernelGGL((k_ivf_scan<SCAN_NIB8, uint8_t, 2, DSV>), dim3(nprobe, nq), dim3(128), lds_scan, s, \
                        idx->dev, idx->edesc, idx->codebooks, coarse, list_offsets, list_codes,     \
                        list_ids, queries, probe_ids, nprobe, K, R, ws, p.per_query, p.counts_off,  \
-                       p.slots_off, p.cap_b, order)
+                       p.slots_off, p.cap_b, order, gd)
     if (dsfix != 0) {
         if (KIND == SCAN_NIB8 && sizeof(QT) == 1) {  // (the macro names the types itself)
             if (dsfix == 4) QADC_IVF_SCAN_FIX(4); else if (dsfix == 6) QADC_IVF_SCAN_FIX(6); else QADC_IVF_SCAN_FIX(8);

@@ -55,29 +55,6 @@ struct TightHi {  // the distances of the words, as the selection wants them
     __device__ __forceinline__ uint32_t operator[](int i) const { return (uint32_t)(A[i] >> 32); }
 };
 
-// The R smallest of A[0..na), na > R, exactly R of them (equal words, which repeated ids give, among them); returns the R-th.
-__device__ inline uint64_t tightf_keep(uint64_t *A, int na, int R, uint32_t *hist, uint32_t *sel, uint32_t *count) {
-    constexpr int NT = TIGHTF_THREADS, PER = TIGHTF_CAP / NT;
-    const uint64_t rth = tight_kth(A, na, R, hist, sel);
-    uint64_t mine[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int i = (int)threadIdx.x + u * NT;
-        mine[u] = i < na ? A[i] : ~0ull;
-    }
-    if (threadIdx.x == 0) *count = 0;
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < PER; ++u)
-        if (mine[u] < rth) A[atomicAdd(count, 1u)] = mine[u];  // (fewer than R)
-    __syncthreads();
-    for (int i = (int)*count + (int)threadIdx.x; i < R; i += NT) A[i] = rth;
-    __syncthreads();
-    if (threadIdx.x == 0) *count = (uint32_t)R;
-    __syncthreads();
-    return rth;
-}
-
 template <int DS, int NR>
 __global__ void __launch_bounds__(TIGHTF_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
 k_ivf_tight_fix(const float *__restrict__ cb, const float *__restrict__ coarse, const int64_t *__restrict__ list_offsets,
@@ -319,7 +296,7 @@ k_ivf_tight_fix(const float *__restrict__ cb, const float *__restrict__ coarse, 
                     __syncthreads();
                     for (int base = over ? s0 : s1; base < s1; base += NT) {  // in batches that surely fit
                         if (na + NT > CAP) {  // na > R here
-                            most = tightf_keep(S.A, na, R, S.hist, S.sel, &S.na);
+                            most = ivf_keep<CAP, NT>(S.A, na, R, S.hist, S.sel, &S.na);
                             na = R;
                         }
                         const int i = base + tid;
@@ -337,7 +314,7 @@ k_ivf_tight_fix(const float *__restrict__ cb, const float *__restrict__ coarse, 
                         if (base > 0x7fffffff - NT) break;
                     }
                     if (na > R) {
-                        most = tightf_keep(S.A, na, R, S.hist, S.sel, &S.na);
+                        most = ivf_keep<CAP, NT>(S.A, na, R, S.hist, S.sel, &S.na);
                         na = R;
                     }
                     known = na;

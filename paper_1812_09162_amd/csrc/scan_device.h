@@ -208,28 +208,15 @@ __device__ __forceinline__ uint32_t sum_groups_rt(const GroupDesc &d, const QT *
 }
 // the same with the reads of all groups in flight (a branch per group has each waited for before the next); absent groups read entry 0
 template <typename QT>
-__device__ __forceinline__ uint32_t sum_groups_flight(const GroupDesc &d, const QT *gtab, uint32_t lo, uint32_t hi) {
+__device__ __forceinline__ uint32_t sum_groups_flight(const GroupDesc &d, const QT *gtab, uint32_t lo, uint32_t hi, bool upper = false) {
     static_assert(QADC_MAXG_FAST == 8, "eight operands below");
     uint32_t r[QADC_MAXG_FAST], s = 0;
 #pragma unroll
     for (int g = 0; g < QADC_MAXG_FAST; ++g)
-        r[g] = gtab[d.base[g] + __builtin_amdgcn_ubfe(d.off[g] >= 32 ? hi : lo, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])];
+        r[g] = gtab[(upper ? d.base2[g] : d.base[g]) + __builtin_amdgcn_ubfe(d.off[g] >= 32 ? hi : lo, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])];
     asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
 #pragma unroll
     for (int g = 0; g < QADC_MAXG_FAST; ++g) s += g < d.ng ? r[g] : 0u;
-    return s;
-}
-// ... of the upper half of a 128-bit code
-template <typename QT>
-__device__ __forceinline__ uint32_t sum_groups_rt_upper(const GroupDesc &d, const QT *gtab, uint32_t lo,
-                                                        uint32_t hi) {
-    uint32_t s = 0;
-#pragma unroll
-    for (int g = 0; g < QADC_MAXG_FAST; ++g)
-        if (g < d.ng) {
-            const uint32_t x = d.off[g] >= 32 ? hi : lo;
-            s += gtab[d.base2[g] + __builtin_amdgcn_ubfe(x, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])];
-        }
     return s;
 }
 // the descriptors as a kernel argument (host); 128-bit codes: of the groups of one half
@@ -375,6 +362,24 @@ __device__ __forceinline__ void keys_batch(const DevLayout *L, const QT *gtab,
             const int64_t id = base + u * stride;
             key[u] = id < n ? key_at<KIND, QT>(L, gtab, codes, id) : 0xffffffffu;
         }
+    }
+}
+
+// The same for 16-byte codes with their groups at hand (gd: of one 64-bit half): all entries of a half are read in flight.
+template <typename QT, int U>
+__device__ __forceinline__ void keys_batch_w128(const GroupDesc &gd, const QT *gtab, const uint8_t *__restrict__ codes,
+                                                int64_t base, int64_t stride, int64_t n, uint32_t *key) {
+    constexpr uint32_t qmax = sizeof(QT) == 1 ? 255u : 65535u;
+    uint4 w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t id = base + u * stride;
+        w[u] = *(const uint4 *)(codes + (id < n ? id : n - 1) * 16);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t s = sum_groups_flight(gd, gtab, w[u].x, w[u].y) + sum_groups_flight(gd, gtab, w[u].z, w[u].w, true);
+        key[u] = base + u * stride < n ? (s > qmax ? qmax : s) : 0xffffffffu;
     }
 }
 

@@ -357,17 +357,17 @@ __device__ __forceinline__ uint32_t pick_key(const DevLayout *L, const GroupDesc
             uint32_t s;
             if constexpr (KIND == SCAN_W64) {
                 const uint2 w = *(const uint2 *)(codes + id * 8);
-                s = sum_groups_rt(gd, gtab, w.x, w.y);
+                s = sum_groups_flight(gd, gtab, w.x, w.y);
             } else if constexpr (KIND == SCAN_C5) {
                 // the two aligned dwords that hold the code (the last code of the array: byte by byte)
                 if (id + 1 >= n) return key_at<KIND, QT>(L, gtab, codes, id);
                 const int64_t at = id * 5;
                 const uint32_t *p = (const uint32_t *)(codes + (at & ~(int64_t)3));
                 const uint64_t w = (((uint64_t)p[1] << 32) | p[0]) >> (8 * ((uint32_t)at & 3u));
-                s = sum_groups_rt(gd, gtab, (uint32_t)w, (uint32_t)(w >> 32) & 0xffu);
+                s = sum_groups_flight(gd, gtab, (uint32_t)w, (uint32_t)(w >> 32) & 0xffu);
             } else {
                 const uint4 w = *(const uint4 *)(codes + id * 16);
-                s = sum_groups_rt(gd, gtab, w.x, w.y) + sum_groups_rt_upper(gd, gtab, w.z, w.w);
+                s = sum_groups_flight(gd, gtab, w.x, w.y) + sum_groups_flight(gd, gtab, w.z, w.w, true);
             }
             return s > qmax ? qmax : s;
         }
