@@ -18,6 +18,7 @@
 // coarse search and calibration included 610 -> 510; a block's time (stamps, average of all) 353 -> 288 us, of which scans 204 -> 111, tables and
 // quantizers 96 -> 90, candidates 53 -> 58, waiting 0 -> 41; one query, 128 probes, 2.9 * 10^6 codes 2333 -> 1486 (1677 where the compiler
 // waits for every other read of a code).
+#include "fill_level.h"
 #include "quotient.h"
 #include "scan_device.h"
 
@@ -277,8 +278,7 @@ k_ivf_tight_fix(const float *__restrict__ cb, const float *__restrict__ coarse, 
                             }
                         if (base > 0x7fffffff - U * NT) break;
                     }
-                    __syncthreads();
-                    int total = (int)S.na;
+                    int total = (int)fill_level([&] { return S.na; }, s1 < len, [] { __syncthreads(); });
                     const bool over = total > CAP;
                     if (!over && (s1 == len || total <= CAP / 2)) {
                         na = total;

@@ -58,3 +58,18 @@ def test_candidate_buffer_runs_full(qb, R, kind):  # noqa: F811
     p["probe"][0] = [1, 0, 2, 3, 4]
     p["probe"][1] = [0, 1, 3, 2, 4]
     run(qb, p, R)
+
+
+@pytest.mark.parametrize("R", [1, 100, 256])
+def test_late_segments_overflow(qb, R):  # noqa: F811
+    # a list of many segments, the first query's far codes first: the fill level left by the ones before is what an overflow goes back to
+    p = problem(6, [700, 41_000, 12_289, 8192, 300], 3, 5, 31 + R)
+    for c in range(p["K"]):
+        lo, hi = p["off"][c], p["off"][c + 1]
+        z = (p["q"][0] - p["coarse"][c]).reshape(16, 1, 6)
+        tab = ((z - p["cb"].reshape(16, 16, 6)) ** 2).sum(2)
+        codes = p["codes"][lo:hi]
+        nib = np.stack([codes & 15, codes >> 4], axis=2).reshape(-1, 16)
+        p["codes"][lo:hi] = codes[np.argsort(-tab[np.arange(16), nib].sum(1), kind="stable")]
+    p["probe"][:] = [0, 1, 2, 3, 4]
+    run(qb, p, R)
