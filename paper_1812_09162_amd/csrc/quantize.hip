@@ -357,8 +357,10 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
         }
     }
     if (!SHORT && hdr_out && first) scan_hdr_clear((ScanHdr *)(hdr_out + q * gtab_stride));  // empty candidate lists
-    // (A block's time is a chain of LDS round trips: the entries of a code are read in flight together, and saturated keys, three in four,
-    // are not counted by a vote and an atomic of their own.  10^7 codes, one query, us a call: 16 x 4 bits 33.7 / 32.6; {6,6,4} x 4 34.1 / 31.1 of 846,539.)
+    // (A block's time is a chain of LDS round trips: the entries of an irregular code are read in flight together, and saturated keys, three in four,
+    // are not counted by a vote and an atomic of their own.  10^7 codes of 16 x 4 bits, one query, us a call 34.0 / 32.6, two streams 20.2 / 19.6, three
+    // 16.1 / 15.6; on four, where scans of three queries share the memory system, 12.6 / 12.6 (12.5 with the vote, and as much with a pause of its length.
+    // Entries of two codes of 16 x 4 bits in flight together: one stream the same, four 12.7.)  {6,6,4} x 4, 846,539 codes 34.1 / 31.1.)
     if (pilot > 0) {
         const int shift = sizeof(QT) == 1 ? 0 : 8;
         for (int i = threadIdx.x; i < 256; i += NT) hist[i] = 0;
@@ -381,15 +383,11 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
                     }
                 }
 #pragma unroll
-                for (int u = 0; u < PPT; u += 2) {
+                for (int u = 0; u < PPT; ++u) {
                     if (NT > QUANT_THREADS && base + u * NT >= hi) break;  // (in narrow blocks it costs more than it saves)
-                    uint32_t sm[2];
-                    sum8_two(gtab, pc[u], pc[u + 1], sm);
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) {
-                        const int id = base + (u + v) * NT + (int)threadIdx.x;
-                        count_key(id < hi ? (sm[v] > (uint32_t)qmax ? (uint32_t)qmax : sm[v]) : 0xffffffffu, id);
-                    }
+                    const int id = base + u * NT + (int)threadIdx.x;
+                    const uint32_t sm = sum8(gtab, pc[u].x, pc[u].y);
+                    count_key(id < hi ? (sm > (uint32_t)qmax ? (uint32_t)qmax : sm) : 0xffffffffu, id);
                 }
             }
         } else if ((KIND == SCAN_W64 || KIND == SCAN_C5) && L->g32ok != 0 && L->ng <= QADC_MAXG_FAST) {
