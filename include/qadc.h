@@ -311,7 +311,8 @@ const char *pq_last_error(void);
  * (pq_last_error says which); pq_get_option returns -1 for an unknown option.
  */
 enum {
-    PQ_OPT_SCAN_BLOCKS = 0,        /* scan blocks per query for one or a few queries: 1..4096 (2048) */
+    PQ_OPT_SCAN_BLOCKS = 0,        /* scan blocks per query for one or a few queries, at most: 1..4096 (2048,
+                                      which stands for half as many where these are faster) */
     PQ_OPT_PILOT_CODES = 1,        /* codes the fused search samples for its pruning bound when
                                       several blocks share them: 0..2^24 (524288) */
     PQ_OPT_PILOT_CODES_SINGLE = 2, /* ... when one block per query counts them: 0..2^24 (65536) */

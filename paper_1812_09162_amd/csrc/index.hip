@@ -6,6 +6,7 @@
 
 #include <vector>
 
+#include "rules.h"
 #include "scan_device.h"
 
 static thread_local char g_err[512] = "";
@@ -23,7 +24,7 @@ extern "C" const char *pq_last_error(void) { return g_err; }
 // Process-wide, set through pq_set_option; none changes a result.
 #include <atomic>
 static std::atomic<int64_t> g_opt[PQ_OPT_COUNT] = {
-    {2048},    // PQ_OPT_SCAN_BLOCKS
+    {SCAN_BLOCKS_DEFAULT},  // PQ_OPT_SCAN_BLOCKS
     {524288},  // PQ_OPT_PILOT_CODES
     {65536},   // PQ_OPT_PILOT_CODES_SINGLE
     {128},     // PQ_OPT_PILOT_BLOCKS
@@ -313,10 +314,9 @@ ScanPlan qadc_scan_plan(const pq_index *idx, int nq, int64_t n, int R) {
     ScanPlan p;
     const int64_t tile_codes = 1024;
     int64_t tiles = (n + tile_codes - 1) / tile_codes;
-    // A single query gets several times more blocks than fit on the chip at once: blocks
-    // start cheaply (their tables are prepared beforehand) and the hardware hands the
-    // next block to whichever compute unit finishes first, which evens out the tail.
-    const int64_t g1 = qadc_option(PQ_OPT_SCAN_BLOCKS);
+    // (blocks start cheaply, their tables are prepared beforehand)
+    int64_t g1 = qadc_option(PQ_OPT_SCAN_BLOCKS);
+    if (g1 == SCAN_BLOCKS_DEFAULT) g1 = scan_blocks_most(nq, n, idx->h.kind == SCAN_NIB8 || idx->h.kind == SCAN_NIB16);
     int64_t gmax = 32768 / (nq > 0 ? nq : 1);
     if (gmax < 64) gmax = 64;
     if (gmax > g1) gmax = g1;

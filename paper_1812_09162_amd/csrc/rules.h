@@ -1,5 +1,5 @@
 #pragma once
-// Size rules of the quantizer and the inverted-list calibration.  Plain C++, so that the lines can be checked without a GPU.
+// Size rules of the quantizer, the scan and the inverted-list search.  Plain C++, so that the lines can be checked without a GPU.
 #include <stdint.h>
 
 // Whether k_quantize runs blocks of 1024 threads: a block's time is a chain of dependent steps, each shorter with more
@@ -58,4 +58,19 @@ inline int64_t pilot_for_results(int64_t n, int R, int nq) {
 // one per CU (a cell's pairs are taken sixteen at a time) even those lose: 5000, 100: 4 65 / 78, 12 81 / 91, 20 83 / 93; 2000, 64: 32 54 / 65.
 inline bool ivf_shared_pays(int64_t pairs, int64_t cells) {
     return pairs >= 1024 && 2 * pairs >= 3 * cells && cells + pairs / 16 >= 320;
+}
+
+// Blocks of the look-up scan per query at most, where the caller has not set a number (PQ_OPT_SCAN_BLOCKS at its default).  2048 are eight per
+// CU, all that fit: one query's scan ends soonest with them, but they leave no room for the next query's kernels, and a block stages its tables,
+// adds up its records and counts itself in for few codes.  us a call, 2048 / 1024, one stream and per call on four:
+//   2 to 16 queries (300 sizes of eight layouts, 1.2 to 30 million codes, R = 10 to 1000): 1.02 to 1.25 and 0.99 to 1.30 times faster; 16 x 4 bits, 10^7, two
+//     queries 52.0 / 46.3 and 28.9 / 22.5; four (on four) 34.2 / 26.8; 12 x {6,6,4}, 5 million, eight 104 / 80 and 74 / 53
+//   one query, irregular layouts, 10^7: 40-bit 39.3 / 39.3 and 13.4 / 12.5, {6,6,4} x 4 48.7 / 47.1 and 18.6 / 16.6, {6,5,5} x 4 47.0 / 45.7 and 18.3 / 15.9,
+//     {6,6,4} x 8 74.1 / 73.4 and 31.9 / 30.3, 8 x 8 45.8 / 45.2 and 17.7 / 17.0, 16 x 8 73.0 / 73.9 and 34.5 / 32.8; longer lists, whose loops outweigh
+//     the rest: 30 million of 40 bits, R = 1000 77.4 / 78.2 and 34.0 / 36.0, {6,6,4} x 4 95.6 / 92.1 and 48.2 / 49.3: up to 2^24 codes
+//   one query, nibbles: 16 x 4 bits, 10^7 32.4 / 32.8 and 12.6 / 12.6, R = 300 38.1 / 37.9 and 18.0 / 19.1, 2 * 10^7 46.7 / 46.5 and 22.9 / 25.6; 32 x 4
+//     2 * 10^7 R = 100 75.5 / 75.8 and 46.8 / 46.1, R = 1000 96.2 / 95.0 and 53.9 / 54.6: not
+#define SCAN_BLOCKS_DEFAULT 2048
+inline int scan_blocks_most(int nq, int64_t n, bool nibbles) {
+    return nq > 1 || (!nibbles && n <= ((int64_t)1 << 24)) ? SCAN_BLOCKS_DEFAULT / 2 : SCAN_BLOCKS_DEFAULT;
 }

@@ -11,6 +11,7 @@ int main() {
         else if (!strcmp(rule, "calib_threads")) printf("%d\n", calib_threads((int)a));
         else if (!strcmp(rule, "pilot_for_results")) printf("%lld\n", (long long)pilot_for_results(a, (int)b, (int)c));
         else if (!strcmp(rule, "ivf_shared_pays")) printf("%d\n", (int)ivf_shared_pays(a, b));
+        else if (!strcmp(rule, "scan_blocks_most")) printf("%d\n", scan_blocks_most((int)a, b, c != 0));
         else return 1;
     }
     return 0;

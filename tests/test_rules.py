@@ -50,6 +50,12 @@ def test_when_pairs_share_a_pass_over_a_list(rule, pairs, cells, shared):
     assert rule("ivf_shared_pays", pairs, cells) == shared
 
 
+@pytest.mark.parametrize("nq,n,nibbles,blocks", [
+    (1, 10_000_000, 1, 2048), (2, 10_000_000, 1, 1024), (16, 100_000_000, 1, 1024), (1, 1 << 24, 0, 1024), (1, (1 << 24) + 1, 0, 2048)])
+def test_blocks_of_the_look_up_scan(rule, nq, n, nibbles, blocks):
+    assert rule("scan_blocks_most", nq, n, nibbles) == blocks
+
+
 def test_header_states_the_lines_of_the_shared_pass():
     text = " ".join(open(os.path.join(ROOT, "include", "qadc.h")).read().replace("*", " ").split())
     assert text.count("1.5 pairs per cell, 1024 pairs and K + pairs / 16 >= 320") == 1
