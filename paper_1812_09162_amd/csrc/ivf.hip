@@ -39,6 +39,11 @@ static size_t ivf_lds_bytes(const DevLayout &L, size_t esz) {
            (((size_t)L.gtab_len * esz + 15) & ~(size_t)15) + 32;
 }
 
+// Whether the words of k_ivf_scan's slot cutting fit in the room of residual, float tables and minima.  (Words of its own cost blocks per CU: {6,5,5} x 4
+// bits, 12,377,132 codes, 802 queries 2210 us a call, 2325 with them.)
+#define IVF_CUT_BYTES (258 * 4)
+__host__ __device__ inline bool ivf_cut_fits(const DevLayout &L) { return ((size_t)L.d + L.T + PQ_MAX_M) * 4 >= IVF_CUT_BYTES; }
+
 // carve the per-list LDS arrays out of `base` (16-byte aligned)
 __device__ inline unsigned char *ivf_carve(const DevLayout *L, unsigned char *base, size_t esz,
                                            IvfLds &l) {
@@ -572,7 +577,6 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
            const uint32_t *__restrict__ order, GroupDesc gd) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_count;
-    __shared__ uint32_t s_hist[256], s_sel[2];
     IvfLds l;
     ivf_carve(L, smem, sizeof(QT), l);
     // block -> (query, probe): in grid order, or in the order of the probed cells
@@ -738,6 +742,8 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
     const QT *gtab = (const QT *)l.gtab;
     const float fdelta = (float)l.sc[1], fdmin = (float)l.sc[0];
     uint64_t *slot = (uint64_t *)(wq + slots_off) + (size_t)a * cap_b;
+    // (256 + 2 words: where the residual, float tables and minima were, or behind the rest)
+    uint32_t *cut_hist = ivf_cut_fits(*L) ? (uint32_t *)l.zres : (uint32_t *)(smem + ivf_lds_bytes_dev(L, sizeof(QT)));
     // Long lists, behind every sixteenth batch (of four codes per thread): half full is cut back.  (Behind every batch it cost lists of some
     // thousand codes up to 17 %, so shorter ones have a loop without; lists of some 10,000 codes that would not have overflowed lose 2 to 7 %.  us a
     // call, before, with overflowing slots / here: 16 x 4 bits, one query, 37 lists of 220,000 codes in all 9380 / 210; {6,6,4} x 8, 28 queries over 1.5 * 10^7
@@ -750,7 +756,7 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
         if (n > cap_b / 2 && n <= cap_b) {  // (hence n > R)
             __threadfence_block();
             __syncthreads();
-            thr = qadc_ord2f(ivf_cut_slots(slot, n, R, s_hist, s_sel, &s_count));
+            thr = qadc_ord2f(ivf_cut_slots(slot, n, R, cut_hist, cut_hist + 256, &s_count));
         } else {
             __syncthreads();  // (the count has been read)
         }
@@ -1448,10 +1454,10 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
     if ((size_t)pilot_want > (lds_room - lds_tabs) / 4) pilot_want = (int)((lds_room - lds_tabs) / 4);
     if (pilot_want < want) pilot_want = want;
     const size_t lds_calib = lds_tabs + (size_t)pilot_want * 4;
-    const size_t lds_scan = ivf_lds_bytes(idx->h, sizeof(QT));
+    const size_t lds_list = ivf_lds_bytes(idx->h, sizeof(QT)), lds_scan = lds_list + (ivf_cut_fits(idx->h) ? 0 : IVF_CUT_BYTES);
     // short result lists: the small selection kernel (four lists per thread: nprobe <= 1024)
     const bool small_final = R <= IVF_SMALL_CAP / 8;
-    const size_t lds_final = (small_final ? IVF_SMALL_CAP : FINAL_CAP) * 8 + lds_scan;
+    const size_t lds_final = (small_final ? IVF_SMALL_CAP : FINAL_CAP) * 8 + lds_list;
     int rc;
     constexpr bool NIB = KIND == SCAN_NIB8;
     if ((rc = allow_lds(k_ivf_scan<KIND, QT, 0>, lds_scan)) != PQ_OK) return rc;
@@ -1501,7 +1507,7 @@ static int launch_ivf(const pq_index *idx, const float *coarse, const int64_t *l
     if (tighten) {
         static_assert(PQ_MAX_R + TIGHT_U * 256 <= TIGHT_CAP, "room for one batch above R candidates");
         const bool small_cap = R + TIGHT_U * 256 <= TIGHT_CAP_SMALL;
-        const size_t lds_tight = (size_t)(small_cap ? TIGHT_CAP_SMALL : TIGHT_CAP) * 8 + lds_scan;
+        const size_t lds_tight = (size_t)(small_cap ? TIGHT_CAP_SMALL : TIGHT_CAP) * 8 + lds_list;
 #define QADC_IVF_TIGHT1(...)                                                                         \
     do {                                                                                             \
         if ((rc = allow_lds(k_ivf_tight<__VA_ARGS__>, lds_tight)) != PQ_OK) return rc;               \
