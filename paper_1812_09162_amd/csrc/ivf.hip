@@ -40,7 +40,7 @@ static size_t ivf_lds_bytes(const DevLayout &L, size_t esz) {
 }
 
 // Whether the words of k_ivf_scan's slot cutting fit in the room of residual, float tables and minima.  (Words of its own cost blocks per CU: {6,5,5} x 4
-// bits, 12,377,132 codes, 802 queries 2210 us a call, 2325 with them.)
+// bits, 12,377,132 codes, 802 queries 2130 us a call, 2330 with them.)
 #define IVF_CUT_BYTES (258 * 4)
 __host__ __device__ inline bool ivf_cut_fits(const DevLayout &L) { return ((size_t)L.d + L.T + PQ_MAX_M) * 4 >= IVF_CUT_BYTES; }
 
@@ -557,7 +557,8 @@ __device__ inline uint32_t ivf_cut_slots(uint64_t *slot, int n, int R, uint32_t 
 //   C  the first codes of the list                           (need B; used after the set-up)
 // A long list cuts its slots back to the codes up to the R-th distance and takes that distance as its bound from there on: no pair
 // needs more than its R best, and the bound of the pilot, the first few thousand probed codes, lets a list of 40,000 codes and more overflow its
-// slots.  (Where many codes share the R-th distance, or one in eight is within the bound, they still can: k_ivf_final then goes over the codes.)
+// slots.  (Where many codes share the R-th distance, or sixteen batches hold more codes within the bound than half the slots, they still can: with 128
+// threads one code in sixteen up to R = 128, one in four beyond.  k_ivf_final then goes over the codes.)
 // NE = table entries per thread (1, 2 or 4; 0 = the general set-up routine, no early loads).
 // DS > 0 fixes the shape at compile time: 16 sub-quantizers of 16 centroids over DS dimensions
 // each (T = 256, d = 16 DS) and blocks of 256 / NE threads, so that table entry e = thread +
@@ -576,7 +577,7 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
            size_t per_query, size_t counts_off, size_t slots_off, int cap_b,
            const uint32_t *__restrict__ order, GroupDesc gd) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ uint32_t s_count;
+    __shared__ uint32_t s_count, s_more;
     IvfLds l;
     ivf_carve(L, smem, sizeof(QT), l);
     // block -> (query, probe): in grid order, or in the order of the probed cells
@@ -621,7 +622,7 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
         if (threadIdx.x == 0) counts[a] = 0;
         return;
     }
-    if (threadIdx.x == 0) s_count = 0;
+    if (threadIdx.x == 0) s_count = 0, s_more = 0;
     bool ok;
     // 64-bit m x 4 codes are read two at a time: the list from its first even position
     constexpr int PF = QADC_IVF_PF;  // 16-byte loads per lane in flight
@@ -744,27 +745,28 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
     uint64_t *slot = (uint64_t *)(wq + slots_off) + (size_t)a * cap_b;
     // (256 + 2 words: where the residual, float tables and minima were, or behind the rest)
     uint32_t *cut_hist = ivf_cut_fits(*L) ? (uint32_t *)l.zres : (uint32_t *)(smem + ivf_lds_bytes_dev(L, sizeof(QT)));
-    // Long lists, behind every sixteenth batch (of four codes per thread): half full is cut back.  (Behind every batch it cost lists of some
-    // thousand codes up to 17 %, so shorter ones have a loop without; lists of some 10,000 codes that would not have overflowed lose 2 to 7 %.  us a
-    // call, before, with overflowing slots / here: 16 x 4 bits, one query, 37 lists of 220,000 codes in all 9380 / 210; {6,6,4} x 8, 28 queries over 1.5 * 10^7
-    // codes 43,900 / 1125; 8 x 8, 309 queries 31,000 / 880.)
-    int batch = 0;
-    auto make_room = [&](float &thr) {
-        if ((++batch & 15) != 0) return;
-        __syncthreads();
-        const int n = __builtin_amdgcn_readfirstlane((int)s_count);
-        if (n > cap_b / 2 && n <= cap_b) {  // (hence n > R)
-            __threadfence_block();
-            __syncthreads();
-            thr = qadc_ord2f(ivf_cut_slots(slot, n, R, cut_hist, cut_hist + 256, &s_count));
-        } else {
-            __syncthreads();  // (the count has been read)
-        }
+    // Behind every sixteenth batch (of four codes per thread) a wave looks whether the slots are half full; if so it waits, and when all waves wait or
+    // are done with the list, the slots are cut back.  (A look with a barrier cost lists that would not overflow up to 7 %, and behind every batch
+    // up to 17 %.  us a call, without cutting / with barriers / so: 32 x 4 bits, 6 * 10^6 codes in 512 lists, 40 queries, 16 probes, R = 50 252 / 269 / 246; 1.8 * 10^7 codes, six
+    // queries 14,015 / 482 / 430; 40-bit codes, 10^7, one query 246 / 253 / 205; 16 x 4 5888 / 121 / 122; {6,6,4} x 8, 28 queries over 1.5 * 10^7 codes 43,900 / 1125.)
+    auto half_full = [&] {
+        if (__builtin_amdgcn_readfirstlane((int)s_count) <= cap_b / 2) return false;
+        s_more = 1u;
+        return true;
     };
-    auto scan_list = [&](auto is_long) {
-    constexpr bool LONG = decltype(is_long)::value;
+    auto make_room = [&](float &thr) {  // true: codes are left
+        __syncthreads();
+        if (s_more == 0u) return false;  // nobody waits
+        const int n = __builtin_amdgcn_readfirstlane((int)s_count);  // (more than R)
+        __threadfence_block();
+        __syncthreads();
+        if (n > cap_b) return false;  // left to k_ivf_final
+        if (threadIdx.x == 0) s_more = 0u;
+        thr = qadc_ord2f(ivf_cut_slots(slot, n, R, cut_hist, cut_hist + 256, &s_count));
+        return true;
+    };
     float thr = thr0;
-    if (NE > 0 && KIND == SCAN_NIB8) {
+    if constexpr (NE > 0 && KIND == SCAN_NIB8) {
         auto request = [&](int64_t pb) {
 #pragma unroll
             for (int u = 0; u < PF; ++u) {
@@ -773,36 +775,50 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
                 pp[u] = pairs[pi];
             }
         };
-        for (int64_t pb = 0; pb < npair; pb += (int64_t)PF * bd) {
-            if (!LONG && pb != 0) request(pb);
-            uint4 w[PF];
+        auto scan_pairs = [&](int64_t &pb, int64_t stop, auto is_long) {
+            constexpr bool LONG = decltype(is_long)::value;
+            for (; pb < stop; pb += (int64_t)PF * bd) {
+                if (!LONG && pb != 0) request(pb);
+                uint4 w[PF];
 #pragma unroll
-            for (int u = 0; u < PF; ++u)
-                w[u] = LONG ? make_uint4(qadc_move(pp[u].x), qadc_move(pp[u].y), qadc_move(pp[u].z), qadc_move(pp[u].w)) : pp[u];
-            if (LONG && pb + (int64_t)PF * bd < npair) request(pb + (int64_t)PF * bd);  // (a long list has the block, its loads' latency counts)
-            uint32_t ord[2 * PF], id[2 * PF];
-            bool pass[2 * PF], any = false;
+                for (int u = 0; u < PF; ++u)
+                    w[u] = LONG ? make_uint4(qadc_move(pp[u].x), qadc_move(pp[u].y), qadc_move(pp[u].z), qadc_move(pp[u].w)) : pp[u];
+                if (LONG && pb + (int64_t)PF * bd < npair) request(pb + (int64_t)PF * bd);  // (a long list has the block, its loads' latency counts)
+                uint32_t ord[2 * PF], id[2 * PF];
+                bool pass[2 * PF], any = false;
 #pragma unroll
-            for (int u = 0; u < PF; ++u) {
-                const int64_t pi = pb + (int64_t)u * bd + threadIdx.x;
-                const uint32_t k0 = sum8(gtab, w[u].x, w[u].y), k1 = sum8(gtab, w[u].z, w[u].w);
-                const float d0 = fmaf((float)(k0 > (uint32_t)qmax ? (uint32_t)qmax : k0), fdelta, fdmin);
-                const float d1 = fmaf((float)(k1 > (uint32_t)qmax ? (uint32_t)qmax : k1), fdelta, fdmin);
-                ord[2 * u] = qadc_f2ord(d0);
-                ord[2 * u + 1] = qadc_f2ord(d1);
-                pass[2 * u] = pi < npair && d0 <= thr;
-                pass[2 * u + 1] = pi < npair && d1 <= thr;
-                any = any || pass[2 * u] || pass[2 * u + 1];
-            }
-            if (__ballot(any) != 0) {
-#pragma unroll
-                for (int u = 0; u < 2 * PF; ++u) {
-                    const int64_t pos = lo2 + 2 * (pb + (int64_t)(u >> 1) * bd + threadIdx.x) + (u & 1);
-                    id[u] = pass[u] ? (uint32_t)list_ids[pos] : 0u;
+                for (int u = 0; u < PF; ++u) {
+                    const int64_t pi = pb + (int64_t)u * bd + threadIdx.x;
+                    const uint32_t k0 = sum8(gtab, w[u].x, w[u].y), k1 = sum8(gtab, w[u].z, w[u].w);
+                    const float d0 = fmaf((float)(k0 > (uint32_t)qmax ? (uint32_t)qmax : k0), fdelta, fdmin);
+                    const float d1 = fmaf((float)(k1 > (uint32_t)qmax ? (uint32_t)qmax : k1), fdelta, fdmin);
+                    ord[2 * u] = qadc_f2ord(d0);
+                    ord[2 * u + 1] = qadc_f2ord(d1);
+                    pass[2 * u] = pi < npair && d0 <= thr;
+                    pass[2 * u + 1] = pi < npair && d1 <= thr;
+                    any = any || pass[2 * u] || pass[2 * u + 1];
                 }
-                slot_append_multi<2 * PF>(pass, ord, id, slot, (uint32_t)cap_b, &s_count);
+                if (__ballot(any) != 0) {
+#pragma unroll
+                    for (int u = 0; u < 2 * PF; ++u) {
+                        const int64_t pos = lo2 + 2 * (pb + (int64_t)(u >> 1) * bd + threadIdx.x) + (u & 1);
+                        id[u] = pass[u] ? (uint32_t)list_ids[pos] : 0u;
+                    }
+                    slot_append_multi<2 * PF>(pass, ord, id, slot, (uint32_t)cap_b, &s_count);
+                }
             }
-            if constexpr (LONG) make_room(thr);
+        };
+        int64_t pb = 0;
+        if (hi - lo > 16 * 4 * (int64_t)bd) {
+            do {
+                while (pb < npair) {
+                    const int64_t some = pb + 16 * (int64_t)PF * bd;
+                    scan_pairs(pb, some < npair ? some : npair, std::true_type{});
+                    if (pb < npair && half_full()) break;
+                }
+            } while (make_room(thr));
+        } else {
+            scan_pairs(pb, npair, std::false_type{});
         }
         // the codes outside the pairs: position lo if it is odd, position hi-1 if one is left over
         if (threadIdx.x < QADC_WAVE) {
@@ -821,32 +837,34 @@ k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
             slot_append(ps, o, idv, slot, (uint32_t)cap_b, &s_count);
         }
     } else {
-        for (int64_t base = lo; base < hi; base += 4 * bd) {
-            uint32_t key[4], ord[4], id[4];
-            bool pass[4], any = false;
-            // (fields of 8-byte and shorter codes read in flight gain a single query up to 7 % and cost batches as much)
-            if constexpr (KIND == SCAN_W128) keys_batch_w128<QT, 4>(gd, gtab, list_codes, base + threadIdx.x, bd, hi, key);
-            else keys_batch<KIND, QT, 4>(L, gtab, list_codes, base + threadIdx.x, bd, hi, key);
+        int64_t base = lo;
+        do {
+            while (base < hi) {
+                const int64_t some = base + 16 * 4 * (int64_t)bd, stop = some < hi ? some : hi;
+                for (; base < stop; base += 4 * bd) {
+                    uint32_t key[4], ord[4], id[4];
+                    bool pass[4], any = false;
+                    keys_batch_flight<KIND, QT, 4>(L, gd, gtab, list_codes, base + threadIdx.x, bd, hi, key);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float dist = fmaf((float)(key[u] == 0xffffffffu ? 0u : key[u]), fdelta, fdmin);
-                ord[u] = qadc_f2ord(dist);
-                pass[u] = key[u] != 0xffffffffu && dist <= thr;
-                any = any || pass[u];
-            }
-            if (__ballot(any) != 0) {
+                    for (int u = 0; u < 4; ++u) {
+                        const float dist = fmaf((float)(key[u] == 0xffffffffu ? 0u : key[u]), fdelta, fdmin);
+                        ord[u] = qadc_f2ord(dist);
+                        pass[u] = key[u] != 0xffffffffu && dist <= thr;
+                        any = any || pass[u];
+                    }
+                    if (__ballot(any) != 0) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t p = base + u * bd + threadIdx.x;
-                    id[u] = pass[u] ? (uint32_t)list_ids[p] : 0u;
+                        for (int u = 0; u < 4; ++u) {
+                            const int64_t p = base + u * bd + threadIdx.x;
+                            id[u] = pass[u] ? (uint32_t)list_ids[p] : 0u;
+                        }
+                        slot_append_multi<4>(pass, ord, id, slot, (uint32_t)cap_b, &s_count);
+                    }
                 }
-                slot_append_multi<4>(pass, ord, id, slot, (uint32_t)cap_b, &s_count);
+                if (base < hi && half_full()) break;
             }
-            if constexpr (LONG) make_room(thr);
-        }
+        } while (make_room(thr));
     }
-    };
-    if (hi - lo > 16 * 4 * (int64_t)bd) scan_list(std::true_type{}); else scan_list(std::false_type{});
     __syncthreads();
     if (threadIdx.x == 0) counts[a] = s_count;  // uncapped: > cap_b tells k_ivf_final about the overflow
 }

@@ -268,7 +268,7 @@ k_ivf_tight_fix(const float *__restrict__ cb, const float *__restrict__ coarse, 
                         for (int u = 0; u < U; u += 2)
                             if (base + u * NT + wave * QADC_WAVE < len) {
                                 uint32_t sum[2];
-                                sum8_two(gtab, w[u], w[u + 1], sum);
+                                sum8_pair(gtab, gtab, w[u], w[u + 1], sum);
                                 const int i = base + u * NT + tid;
                                 const bool one = i < len && sum[0] < lim, two = i < len - NT && sum[1] < lim;
                                 if (__ballot(one || two) != 0) {

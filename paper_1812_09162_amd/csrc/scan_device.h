@@ -123,14 +123,14 @@ __device__ __forceinline__ uint32_t sum8(const QT *t, uint32_t lo, uint32_t hi) 
            (uint32_t)t[1536 + ((hi >> 16) & 255u)] + (uint32_t)t[1792 + (hi >> 24)];
 }
 
-// The same of two codes with all sixteen reads in flight (where registers are few the compiler waits for every other one).
+// The same of two codes, each with its tables, all sixteen reads in flight (where registers are few the compiler waits for every other one).
 template <typename QT>
-__device__ __forceinline__ void sum8_two(const QT *t, const uint2 &a, const uint2 &b, uint32_t sum[2]) {
+__device__ __forceinline__ void sum8_pair(const QT *ta, const QT *tb, const uint2 &a, const uint2 &b, uint32_t sum[2]) {
     uint32_t r[16];
 #pragma unroll
     for (int g = 0; g < 8; ++g) {
-        r[g] = t[256 * g + (((g < 4 ? a.x : a.y) >> (8 * (g & 3))) & 255u)];
-        r[8 + g] = t[256 * g + (((g < 4 ? b.x : b.y) >> (8 * (g & 3))) & 255u)];
+        r[g] = ta[256 * g + (((g < 4 ? a.x : a.y) >> (8 * (g & 3))) & 255u)];
+        r[8 + g] = tb[256 * g + (((g < 4 ? b.x : b.y) >> (8 * (g & 3))) & 255u)];
     }
     asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]),
                       "+v"(r[8]), "+v"(r[9]), "+v"(r[10]), "+v"(r[11]), "+v"(r[12]), "+v"(r[13]), "+v"(r[14]), "+v"(r[15]));
@@ -365,21 +365,80 @@ __device__ __forceinline__ void keys_batch(const DevLayout *L, const QT *gtab,
     }
 }
 
-// The same for 16-byte codes with their groups at hand (gd: of one 64-bit half): all entries of a half are read in flight.
-template <typename QT, int U>
-__device__ __forceinline__ void keys_batch_w128(const GroupDesc &gd, const QT *gtab, const uint8_t *__restrict__ codes,
-                                                int64_t base, int64_t stride, int64_t n, uint32_t *key) {
-    constexpr uint32_t qmax = sizeof(QT) == 1 ? 255u : 65535u;
-    uint4 w[U];
+// Sum of the group entries of a 64-bit word, descriptors from the layout, eight groups' reads in flight; behind the last group (all zero) it is entry 0.
+template <typename QT>
+__device__ __forceinline__ uint32_t sum_groups64_flight(const DevLayout *L, const QT *gtab, uint64_t v) {
+    const int ng = L->ng;
+    uint32_t s = 0;
+    auto eight = [&](int g0, uint32_t (&r)[8]) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int64_t id = base + u * stride;
-        w[u] = *(const uint4 *)(codes + (id < n ? id : n - 1) * 16);
+        for (int g = 0; g < 8; ++g) r[g] = gtab[L->gbase[g0 + g] + __builtin_amdgcn_ubfe((uint32_t)(v >> L->goff[g0 + g]), 0u, (uint32_t)L->gw[g0 + g])];
+        asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
+    };
+    uint32_t r[8];
+    int g0 = 0;
+    for (; g0 + 8 <= ng; g0 += 8) {
+        eight(g0, r);
+        s += r[0] + r[1] + r[2] + r[3] + r[4] + r[5] + r[6] + r[7];
     }
+    if (g0 < ng) {
+        eight(g0, r);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint32_t s = sum_groups_flight(gd, gtab, w[u].x, w[u].y) + sum_groups_flight(gd, gtab, w[u].z, w[u].w, true);
-        key[u] = base + u * stride < n ? (s > qmax ? qmax : s) : 0xffffffffu;
+        for (int g = 0; g < 7; ++g) s += g0 + g < ng ? r[g] : 0u;
+    }
+    return s;
+}
+
+// keys_batch with a code's look-ups in flight together, whatever the compiler makes of the kernel around it (where it counts on many waves it waits
+// for every other one).  gd: 128-bit codes, the groups of one half.
+template <int KIND, typename QT, int U>
+__device__ __forceinline__ void keys_batch_flight(const DevLayout *L, const GroupDesc &gd, const QT *gtab, const uint8_t *__restrict__ codes,
+                                                  int64_t base, int64_t stride, int64_t n, uint32_t *key) {
+    constexpr uint32_t qmax = sizeof(QT) == 1 ? 255u : 65535u;
+    if constexpr (KIND == SCAN_NIB16 || KIND == SCAN_W128) {
+        uint4 w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t id = base + u * stride;
+            w[u] = *(const uint4 *)(codes + (id < n ? id : n - 1) * 16);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint32_t s;
+            if constexpr (KIND == SCAN_NIB16) {
+                uint32_t h[2];
+                sum8_pair(gtab, gtab + 2048, make_uint2(w[u].x, w[u].y), make_uint2(w[u].z, w[u].w), h);
+                s = h[0] + h[1];
+            } else {
+                s = sum_groups_flight(gd, gtab, w[u].x, w[u].y) + sum_groups_flight(gd, gtab, w[u].z, w[u].w, true);
+            }
+            key[u] = base + u * stride < n ? (s > qmax ? qmax : s) : 0xffffffffu;
+        }
+    } else if constexpr (KIND == SCAN_W64) {
+        uint2 w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t id = base + u * stride;
+            w[u] = *(const uint2 *)(codes + (id < n ? id : n - 1) * 8);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t s = sum_groups64_flight(L, gtab, ((uint64_t)w[u].y << 32) | w[u].x);
+            key[u] = base + u * stride < n ? (s > qmax ? qmax : s) : 0xffffffffu;
+        }
+    } else if constexpr (KIND == SCAN_C5) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t id = base + u * stride;
+            key[u] = 0xffffffffu;
+            if (id < n) {
+                const uint8_t *c = codes + id * 5;
+                const uint32_t s = sum_groups64_flight(L, gtab, (uint64_t)c[0] | ((uint64_t)c[1] << 8) | ((uint64_t)c[2] << 16) | ((uint64_t)c[3] << 24) | ((uint64_t)c[4] << 32));
+                key[u] = s > qmax ? qmax : s;
+            }
+        }
+    } else {
+        keys_batch<KIND, QT, U>(L, gtab, codes, base, stride, n, key);
     }
 }
 
