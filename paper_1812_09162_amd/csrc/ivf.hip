@@ -559,6 +559,8 @@ __device__ inline uint32_t ivf_cut_slots(uint64_t *slot, int n, int R, uint32_t 
 // needs more than its R best, and the bound of the pilot, the first few thousand probed codes, lets a list of 40,000 codes and more overflow its
 // slots.  (Where many codes share the R-th distance, or sixteen batches hold more codes within the bound than half the slots, they still can: with 128
 // threads one code in sixteen up to R = 128, one in four beyond.  k_ivf_final then goes over the codes.)
+// Registers: eight waves per SIMD, but six for 16-byte irregular codes, whose groups' descriptors are many scalars (with eight 20 bytes a lane
+// went to scratch memory: 16 x 8 bits, 1.2 * 10^7 codes, 1 / 12 / 100 queries of 16 probes 234 / 344 / 501 us a call, with six 227 / 351 / 491).
 // NE = table entries per thread (1, 2 or 4; 0 = the general set-up routine, no early loads).
 // DS > 0 fixes the shape at compile time: 16 sub-quantizers of 16 centroids over DS dimensions
 // each (T = 256, d = 16 DS) and blocks of 256 / NE threads, so that table entry e = thread +
@@ -568,7 +570,7 @@ __device__ inline uint32_t ivf_cut_slots(uint64_t *slot, int n, int R, uint32_t 
 #define QADC_IVF_PF 2
 #endif
 template <int KIND, typename QT, int NE, int DS = 0>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KIND == SCAN_W128 ? 6 : 8, 8)))
 k_ivf_scan(const DevLayout *__restrict__ L, const EntryDesc *__restrict__ edesc,
            const float *__restrict__ cb, const float *__restrict__ coarse,
            const int64_t *__restrict__ list_offsets, const uint8_t *__restrict__ list_codes,

@@ -36,11 +36,13 @@ def kernels():
     ("k_scan_mxILi1ELi4ELi3ELi0E", 3),
     ("k_scan_mxILi1ELi4ELi4ELi0E", 2),
     ("k_ivf_scan_mxILi6E", 7),
-    ("k_ivf_scanILi1EhLi2ELi6E", 8),       # the inverted-list scan
+    ("k_ivf_scanILi1EhLi2ELi6E", 8),       # the inverted-list scan: the fixed shape, 8- and 16-byte codes
     ("k_ivf_scanILi1EhLi2ELi0E", 8),
     ("k_ivf_scanILi2EhLi4ELi0E", 8),
     ("k_ivf_scanILi3EtLi4ELi0E", 8),
     ("k_ivf_scanILi4EtLi2ELi0E", 8),
+    ("k_ivf_scanILi5EtLi4ELi0E", 6),
+    ("k_ivf_scanILi5EtLi0ELi0E", 6),
     ("k_encode_mxILi16ELi6E", 3),
     ("k_quantizeILi1EhLi256E", 7),
     ("k_quantizeILi1EtLi256E", 7),
