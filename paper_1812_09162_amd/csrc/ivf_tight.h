@@ -122,6 +122,7 @@ k_ivf_tight_fix(const float *__restrict__ cb, const float *__restrict__ coarse, 
     for (int a0 = 0; a0 < nprobe; a0 += TIGHTF_PC) {
         __syncthreads();  // the previous chunk's entries have been used
         if (wave == 0) {  // the lists that hold codes, in probe order
+            TIGHTF_THREAD;
             const int a = a0 + lane, c = a < nprobe ? probes[a] : -1;
             const bool valid = c >= 0 && c < K;
             const int64_t lo = valid ? list_offsets[c] : 0, hi = valid ? list_offsets[c + 1] : 0;

@@ -15,6 +15,13 @@ __device__ __forceinline__ uint32_t qadc_move(uint32_t x) {
     return r;
 }
 
+// All ones, made where they are wanted: constants of a rare path inside a loop are otherwise held, or put in scratch memory, across the loop.
+__device__ __forceinline__ uint32_t qadc_ones() {
+    uint32_t r;
+    asm volatile("v_mov_b32 %0, -1" : "=v"(r));
+    return r;
+}
+
 // Sub-code extraction from a little-endian bit stream (Section 3.3): `b` bits
 // starting at bit `off`; b <= 8, so at most two bytes are touched and the
 // second one is only read when the field really reaches into it.
@@ -158,10 +165,7 @@ __device__ inline uint32_t qadc_block_kth_u32(const Vals &vals, int cnt, int k, 
     }
     mn = qadc_wave_min(mn);
     mxn = qadc_wave_min(mxn);
-    if (threadIdx.x == 0) {
-        sel[0] = 0xffffffffu;
-        sel[1] = 0xffffffffu;
-    }
+    if (threadIdx.x == 0) sel[0] = sel[1] = qadc_ones();
     __syncthreads();
     if (threadIdx.x % QADC_WAVE == 0) {
         atomicMin(&sel[0], mn);
@@ -274,7 +278,7 @@ __device__ inline uint32_t qadc_block_kth_f32(const Vals &vals, int cnt, int k, 
     mn = qadc_wave_min(mn);
     mx = qadc_wave_max(mx);
     if (threadIdx.x == 0) {
-        sel[0] = 0xffffffffu;
+        sel[0] = qadc_ones();
         sel[1] = 0u;
     }
     for (int i = threadIdx.x; i < 256; i += blockDim.x) hist[i] = 0;

@@ -43,6 +43,7 @@ def kernels():
     ("k_ivf_scanILi4EtLi2ELi0E", 8),
     ("k_ivf_scanILi5EtLi4ELi0E", 6),
     ("k_ivf_scanILi5EtLi0ELi0E", 6),
+    *((f"k_ivf_tight_fixILi{ds}ELi{nr}E", 8) for ds in (4, 6, 8) for nr in (2, 4)),
     ("k_encode_mxILi16ELi6E", 3),
     ("k_quantizeILi1EhLi256E", 7),
     ("k_quantizeILi1EtLi256E", 7),
