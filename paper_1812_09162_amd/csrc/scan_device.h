@@ -194,17 +194,18 @@ __device__ __forceinline__ GroupDesc load_group_desc(const DevLayout *L) {
     return d;
 }
 // sum of the group entries of a code of at most 64 bits as two dwords, no group crossing the dword boundary, all reads in flight (a branch
-// per group has each waited for before the next); absent groups read entry 0
-template <typename QT>
+// per group has each waited for before the next); absent groups read entry 0.  N: five or eight, groups at most
+template <int N = QADC_MAXG_FAST, typename QT>
 __device__ __forceinline__ uint32_t sum_groups_flight(const GroupDesc &d, const QT *gtab, uint32_t lo, uint32_t hi, bool upper = false) {
-    static_assert(QADC_MAXG_FAST == 8, "eight operands below");
-    uint32_t r[QADC_MAXG_FAST], s = 0;
+    static_assert(QADC_MAXG_FAST == 8 && (N == 5 || N == 8), "operands below");
+    uint32_t r[N], s = 0;
 #pragma unroll
-    for (int g = 0; g < QADC_MAXG_FAST; ++g)
+    for (int g = 0; g < N; ++g)
         r[g] = gtab[(upper ? d.base2[g] : d.base[g]) + __builtin_amdgcn_ubfe(d.off[g] >= 32 ? hi : lo, (uint32_t)(d.off[g] & 31), (uint32_t)d.w[g])];
-    asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
+    if constexpr (N == 5) asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]));
+    else asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
 #pragma unroll
-    for (int g = 0; g < QADC_MAXG_FAST; ++g) s += g < d.ng ? r[g] : 0u;
+    for (int g = 0; g < N; ++g) s += g < d.ng ? r[g] : 0u;
     return s;
 }
 // the descriptors as a kernel argument (host); 128-bit codes: of the groups of one half

@@ -364,7 +364,9 @@ __device__ __forceinline__ uint32_t pick_key(const DevLayout *L, const GroupDesc
                 const int64_t at = id * 5;
                 const uint32_t *p = (const uint32_t *)(codes + (at & ~(int64_t)3));
                 const uint64_t w = (((uint64_t)p[1] << 32) | p[0]) >> (8 * ((uint32_t)at & 3u));
-                s = sum_groups_flight(gd, gtab, (uint32_t)w, (uint32_t)(w >> 32) & 0xffu);
+                // (five groups as eight cost more than they gained: 2 * 10^6 codes, 20 queries 47.2 us a call with a branch per group, 48.7 as eight, 44.9)
+                const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32) & 0xffu;
+                s = gd.ng <= 5 ? sum_groups_flight<5>(gd, gtab, lo, hi) : sum_groups_flight(gd, gtab, lo, hi);
             } else {
                 const uint4 w = *(const uint4 *)(codes + id * 16);
                 s = sum_groups_flight(gd, gtab, w.x, w.y) + sum_groups_flight(gd, gtab, w.z, w.w, true);

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 LAYOUTS = {
     "16x4": ([4] * 16, 8), "16x4u16": ([4] * 16, 16), "32x4": ([4] * 32, 8),
-    "c3": ([6, 5, 5, 6, 5, 5, 4, 4], 16), "c3u8": ([6, 5, 5, 6, 5, 5, 4, 4], 8), "5x8": ([5] * 8, 16),
+    "c3": ([6, 5, 5, 6, 5, 5, 4, 4], 16), "c3u8": ([6, 5, 5, 6, 5, 5, 4, 4], 8), "5x8": ([5] * 8, 16), "40six": ([6, 5, 6, 5, 6, 4, 4, 4], 16),
     "664": ([6, 6, 4] * 4, 16), "655": ([6, 5, 5] * 4, 16), "664u8": ([6, 6, 4] * 4, 8),
     "6to4": ([6] * 8 + [4] * 4, 16),  # as many steps of each kind as {6,6,4} x 4, fields elsewhere
     "odd64": ([4, 5, 6, 5, 4, 6, 6, 5, 5, 4, 6, 5], 16),
@@ -76,7 +76,8 @@ def test_batch_equals_single(name, n, nq, R):
 # other fields have the narrowest range)
 MATRIX_SIZES = {
     "16x4": (262_144, 97, 32), "16x4u16": (262_144, 97, 32), "32x4": (131_583, 225, 1), "c3": (1_600_001, 17, 100),
-    "c3u8": (1_607_680, 16, 100), "5x8": (1_600_513, 18, 100), "664": (300_033, 84, 33), "655": (262_144, 97, 32),
+    "c3u8": (1_607_680, 16, 100), "5x8": (1_600_513, 18, 100), "40six": (1_600_513, 18, 100),
+    "664": (300_033, 84, 33), "655": (262_144, 97, 32),
     "664u8": (300_033, 84, 33), "6to4": (800_001, 33, 33), "odd64": (800_513, 61, 50), "664x2": (131_583, 225, 1),
     "655x2": (300_033, 84, 33), "mixed128": (800_100, 40, 33),
 }
