@@ -250,8 +250,8 @@ int ivf_adc_scan_topk(const pq_index_t *idx, const float *coarse_centroids, int 
  * below their bounds.  Later lists are quantized more finely than with the fixed
  * bound; the result depends on the probe order by construction.
  * Arguments, workspace size (ivf_workspace_bytes), limits and errors as for
- * ivf_adc_scan_topk.  One block of 256 threads serves a query: the call needs a
- * few hundred queries to fill the chip.
+ * ivf_adc_scan_topk.  One block of 256 or 512 threads serves a query: the call
+ * needs a few hundred queries to fill the chip.
  */
 int ivf_adc_scan_topk_tightening(const pq_index_t *idx, const float *coarse_centroids, int K,
                                  const int64_t *list_offsets, const uint8_t *list_codes,

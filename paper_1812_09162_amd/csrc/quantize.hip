@@ -343,7 +343,7 @@ __device__ __forceinline__ void quantize_block(QUANT_PARAMS, size_t cand_rel, in
     // (A block's time is a chain of LDS round trips: the entries of an irregular code are read in flight together, and saturated keys, three in four,
     // are not counted by a vote and an atomic of their own.  10^7 codes of 16 x 4 bits, one query, us a call 34.0 / 32.6, two streams 20.2 / 19.6, three
     // 16.1 / 15.6; on four, where scans of three queries share the memory system, 12.6 / 12.6 (12.5 with the vote, and as much with a pause of its length.
-    // Entries of two codes of 16 x 4 bits in flight together: one stream the same, four 12.7.)  {6,6,4} x 4, 846,539 codes 34.1 / 31.1.)
+    // Entries of two codes of 16 x 4 bits in flight together: one stream the same, four 12.7.)  {6,6,4} x 4, 621,640 codes 32.0 / 27.9.)
     if (pilot > 0) {
         const int shift = sizeof(QT) == 1 ? 0 : 8;
         for (int i = threadIdx.x; i < 256; i += NT) hist[i] = 0;
